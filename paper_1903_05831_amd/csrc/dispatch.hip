@@ -43,10 +43,8 @@ static const TunedEntry kTuned[] = {
 
 // The table was measured at the batch sizes of the detector workloads.  A layer with the same
 // geometry and a batch within a factor of two of a measured one (half or twice the rows: the same
-// tile shapes still fill the chip about as well) takes that entry too, the exact batch first;
-// *scale_splits is then the factor by which the pixel count, and with it the number of pixel
-// ranges of a weight gradient, differs from the measured one.
-static const TunedEntry* tuned_lookup(const Geom& g, int pass, double* scale_splits = nullptr)
+// tile shapes still fill the chip about as well) takes that entry too, the exact batch first.
+static const TunedEntry* tuned_lookup(const Geom& g, int pass)
 {
     if (hook("SDCONV_NO_TUNED_TABLE", 0)) return nullptr;
     const TunedEntry* near = nullptr;
@@ -58,7 +56,6 @@ static const TunedEntry* tuned_lookup(const Geom& g, int pass, double* scale_spl
         if (e->N == g.N) { near = e; break; }
         if (!near && 2 * g.N >= e->N && g.N <= 2 * e->N) near = e;
     }
-    if (near && scale_splits) *scale_splits = (double)g.N / near->N;
     return near;
 }
 
@@ -251,48 +248,122 @@ Plan plan_dgrad(const Geom& g)
     return Plan{ROUTE_IGEMM, v, 1, ws, igemm_name(v, true)};
 }
 
-// Pixel-range count for the weight gradient: enough workgroups to fill the chip a few times
-// over, but at least four 64-pixel steps per range.
 static const WgradVariant& wgrad_variant(int v)
 {
     return v >= 100 ? kWgradDmaVariants[v - 100] : kWgradVariants[v];
 }
 
-static int pick_wgrad_variant(const Geom& g)
+// Time of a weight gradient as a function of the tile variant and the number of pixel ranges, from
+// which both are chosen.  A workgroup takes `step` us per 64-pixel step while it has a compute
+// unit to itself, and `shared` times their number when several live on one; launch, set-up, first
+// loads and drain are `fixed`; the kernel cannot be faster than the operands once at `hbm` MB/us, and
+// the partial sums leave at `store` MB/us.  The constants are least-squares fits to 5400
+// kernel-trace timings of 170 layers of random size (0.5 us to 200 us, 8 to 2048 channels, 1x1 and
+// 3x3, strides 1 and 2, 200 to 170 000 pixels); the fit's scatter is 7-12 %, and the choice made
+// with it is 3 % slower than the fastest (variant, ranges) pair of every layer on average (10 % at the 90th
+// percentile).  Fixed rules by channel counts, with one range count for all, lost 48 %: the time has
+// a narrow minimum between too few workgroups and the traffic of too many partial sums.
+struct WgradCost { float fixed, step, shared, store, hbm; };
+struct WgradModel { int variant, per_cu; WgradCost linear, gather; };   // per_cu: workgroups a compute unit holds
+static const WgradModel kWgradModels[] = {
+    {107, 3, {3.37f, 0.292f, 0.246f, 2.86f, 7.63f}, {4.52f, 0.408f, 0.265f, 3.44f, 5.00f}},
+    {118, 3, {3.49f, 0.294f, 0.244f, 2.95f, 7.98f}, {4.96f, 0.390f, 0.245f, 3.78f, 5.00f}},
+    {108, 2, {3.97f, 0.425f, 0.332f, 2.62f, 8.30f}, {5.29f, 0.568f, 0.383f, 3.45f, 5.00f}},
+    {100, 2, {5.78f, 0.588f, 0.450f, 3.67f, 7.16f}, {7.29f, 0.772f, 0.467f, 4.39f, 7.37f}},
+    {119, 2, {5.80f, 0.597f, 0.449f, 4.04f, 7.14f}, {8.19f, 0.732f, 0.456f, 5.55f, 6.77f}},
+    {112, 1, {4.54f, 0.550f, 0.423f, 2.71f, 7.06f}, {6.05f, 0.600f, 0.435f, 3.31f, 5.26f}},
+    {116, 1, {4.73f, 0.524f, 0.068f, 2.80f, 6.95f}, {6.60f, 0.567f, 0.622f, 3.57f, 5.00f}},
+    {117, 1, {6.56f, 0.895f, 0.552f, 4.01f, 5.73f}, {8.80f, 0.904f, 0.604f, 4.79f, 7.04f}},
+    {114, 1, {7.97f, 1.620f, 1.523f, 6.55f, 5.42f}, {12.7f, 1.560f, 0.592f, 12.2f, 9.50f}},
+};
+constexpr float kReduceFixed = 5.1f, kReduceRate = 9.6f;    // us with the gap between the kernels, MB/us
+
+// More partial sums than this are not considered (the fixed scratch of conv2d_wgrad_static_scratch).
+constexpr size_t kPartialBytes = (size_t)64 << 20;
+
+static long wgrad_steps(const Geom& g) { return ((long)g.N * g.Ho * g.Wo + 63) / 64; }
+static long wgrad_tiles(const Geom& g, const WgradVariant& v)
 {
-    if (!byte_offsets_fit_31_bits(g)) return g.K <= 64 ? 1 : 0;
-    int fv = forced_wgrad_variant();
-    if ((fv >= 0 && fv < kNumWgradVariants) || (fv >= 100 && fv < 100 + kNumWgradDmaVariants)) return fv;
-    if (const TunedEntry* e = tuned_lookup(g, SDCONV_WGRAD)) return e->variant;
-    // No table entry: rules read off the tuned layers of the detector workloads (tile = filters x
-    // channels of one tap): narrow tiles for narrow layers, the 256x256 tile when both are wide
-    // and the pixel axis is long enough to feed it, else 128x128.
-    const long pixels = (long)g.N * g.Ho * g.Wo;
-    if (g.K <= 64 && g.C <= 64) return 100 + 7;
-    if (g.K <= 64) return 100 + 20;
-    if (g.C <= 64) return 100 + 8;
-    if (g.K >= 512 && g.C >= 512 && pixels >= 20000) return 100 + 14;
-    return 100 + 12;
+    return (long)((g.K + v.bm - 1) / v.bm) * ((g.C + v.bn - 1) / v.bn) * g.R * g.S;
 }
 
-static void wgrad_split(const Geom& g, int variant, int* splits, int* steps_per_split)
+struct WgradChoice { int variant, splits; float us; };
+
+static float wgrad_us(const Geom& g, const WgradModel& m, long tiles, long total_steps, long splits)
 {
-    const WgradVariant& v = wgrad_variant(variant);
-    long tiles = (long)((g.K + v.bm - 1) / v.bm) * ((g.C + v.bn - 1) / v.bn) * g.R * g.S;
-    long P = (long)g.N * g.Ho * g.Wo;
-    long total_steps = (P + 63) / 64;
-    long want = (384 + tiles - 1) / tiles;
-    double scale = 1.0;
-    if (const TunedEntry* e = tuned_lookup(g, SDCONV_WGRAD, &scale)) want = (long)(e->splits * scale + 0.5);
-    int fs = forced_wgrad_splits();
-    if (fs > 0) want = fs;
-    long cap = total_steps / 4;
-    if (cap < 1) cap = 1;
-    if (want > cap) want = cap;
-    if (want < 1) want = 1;
-    long sps = (total_steps + want - 1) / want;
-    *steps_per_split = (int)sps;
-    *splits = (int)((total_steps + sps - 1) / sps);
+    const WgradCost& c = (g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0) ? m.linear : m.gather;
+    const long steps = (total_steps + splits - 1) / splits, n = tiles * splits, per_round = 256 * m.per_cu;
+    const float alone = c.step, full = m.per_cu * c.shared;
+    float t = (float)(n / per_round) * steps * (full > alone ? full : alone);
+    if (const long rest = n % per_round) {
+        const float crowd = (float)((rest + 255) / 256) * c.shared;
+        t += steps * (crowd > alone ? crowd : alone);
+    }
+    const float dw = 4e-6f * g.K * g.R * g.S * g.C;         // MB
+    const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 ? g.sh * g.sw : 1);
+    const float operands = (x + 2e-6f * g.N * g.Ho * g.Wo * g.K + dw) / c.hbm;
+    if (t < operands) t = operands;
+    t += c.fixed;
+    if (splits > 1) t += splits * dw * (1.f / c.store + 1.f / kReduceRate) + kReduceFixed;
+    return t;
+}
+
+// The fastest number of pixel ranges for one variant: those that make the workgroups a little fewer
+// than a multiple of the compute units, and the smallest.
+static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial_limit, WgradChoice* best)
+{
+    const long tiles = wgrad_tiles(g, wgrad_variant(m.variant)), total = wgrad_steps(g);
+    const size_t dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
+    // a gradient of more than half the limit is split in two where conv2d_wgrad always needed more
+    // than the limit for it: long pixel axis, wide layer
+    const bool large = dw_bytes <= kPartialBytes && wgrad_steps(g) >= 313 && g.K >= 512 && g.C >= 512;
+    static const int candidates[] = {1, 2, 3, -40, -64, -96, -128, -192, -256, -320, -384, -512, -768, -1024};
+    long last = 0;
+    for (int cand : candidates) {                           // ranges, or minus the workgroups to make
+        long s = cand > 0 ? cand : -cand / tiles;
+        if (s > total / 2) s = total / 2;
+        if (s < 1) s = 1;
+        const long steps = (total + s - 1) / s;
+        s = (total + steps - 1) / steps;                    // ranges that are not empty
+        if (s <= last) continue;
+        last = s;
+        if (s > 1 && s * dw_bytes > partial_limit && !(s == 2 && large)) break;
+        const float us = wgrad_us(g, m, tiles, total, s);
+        if (best->variant < 0 || us < best->us) *best = WgradChoice{m.variant, (int)s, us};
+    }
+}
+
+// Tile variant and pixel ranges.  A geometry of the measured table keeps its tile variant at every
+// batch size near the measured one; the ranges chosen for that one are scaled with the batch.
+static WgradChoice choose_wgrad(const Geom& g, size_t partial_limit)
+{
+    const int fv = forced_wgrad_variant();
+    const bool forced = (fv >= 0 && fv < kNumWgradVariants) || (fv >= 100 && fv < 100 + kNumWgradDmaVariants);
+    int only = forced ? fv : -1;
+    Geom measured = g;
+    if (!byte_offsets_fit_31_bits(g)) only = g.K <= 64 ? 1 : 0;
+    else if (!forced)
+        if (const TunedEntry* e = tuned_lookup(g, SDCONV_WGRAD)) { only = e->variant; measured.N = e->N; }
+    WgradChoice c{-1, 1, 0.f};
+    for (const WgradModel& m : kWgradModels)
+        if (only < 0 || m.variant == only) wgrad_best_splits(measured, m, partial_limit, &c);
+    if (g.N != measured.N) {
+        c.splits = (2 * c.splits * g.N + measured.N) / (2 * measured.N);
+        const size_t dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
+        if (c.splits * dw_bytes > partial_limit) c.splits = (int)(partial_limit / dw_bytes);
+        if (c.splits < 1) c.splits = 1;
+    }
+    if (c.variant < 0) {    // a variant without a model: enough workgroups to fill the chip
+        const long tiles = wgrad_tiles(g, wgrad_variant(only)), cap = wgrad_steps(g) / 4;
+        long want = (384 + tiles - 1) / tiles;
+        if (want > cap) want = cap;
+        c = WgradChoice{only, (int)(want < 1 ? 1 : want), 0.f};
+    }
+    if (const int fs = forced_wgrad_splits(); fs > 0) {
+        const long cap = wgrad_steps(g) / 2;
+        c.splits = fs < cap ? fs : (cap < 1 ? 1 : (int)cap);
+    }
+    return c;
 }
 
 Plan plan_wgrad(const Geom& g)
@@ -305,12 +376,13 @@ Plan plan_wgrad(const Geom& g)
     }
     if (thin_ok(g)) return Plan{ROUTE_THIN, 0, 1, align256(thin_wgrad_partial_bytes(g)), "thin_wgrad"};
     if (!igemm_ok(g)) return Plan{ROUTE_DIRECT, 0, 1, 0, "direct_wgrad"};
-    int v = pick_wgrad_variant(g);
-    int splits, sps;
-    wgrad_split(g, v, &splits, &sps);
+    const WgradChoice c = choose_wgrad(g, kPartialBytes);
+    const int v = c.variant;
+    const long total_steps = wgrad_steps(g), sps = (total_steps + c.splits - 1) / c.splits;
+    const int splits = (int)((total_steps + sps - 1) / sps);
     size_t ws = splits > 1 ? align256((size_t)splits * g.K * g.R * g.S * g.C * sizeof(float)) : 0;
     Plan p{ROUTE_IGEMM, v, splits, ws, wgrad_variant(v).name};
-    p.steps_per_split = sps;
+    p.steps_per_split = (int)sps;
     return p;
 }
 

@@ -295,7 +295,7 @@ def main() -> int:
     # or a reduction beside their main kernel)
     def single_kernel(name, g):
         if g["pass"] == "fwd":
-            return not name.startswith(("thin", "padk"))
+            return not name.startswith(("thin", "padk", "narrow"))
         return g["pass"] == "dgrad" and ("_ws_" in name or "patch" in name) and not name.startswith("padk")
     try:
         with open(args.traffic_file) as f:

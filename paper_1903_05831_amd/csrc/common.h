@@ -53,7 +53,7 @@ __device__ __forceinline__ float epilogue_apply(const Epilogue& E, float v, int 
 }
 
 // What the dispatcher decided for one (geometry, pass).
-enum Route { ROUTE_DIRECT = 0, ROUTE_IGEMM = 1, ROUTE_THIN = 2, ROUTE_PADK = 3 };
+enum Route { ROUTE_DIRECT = 0, ROUTE_IGEMM = 1, ROUTE_THIN = 2, ROUTE_PADK = 3, ROUTE_NARROW = 4 };
 struct Plan {
     Route route;
     int variant;             // tile variant index within the route

@@ -9,7 +9,7 @@ import pytest
 
 import paper_1903_05831_amd as sd
 
-from gpu_harness import check_all_passes, say
+from gpu_harness import check_all_passes, check_fused, say
 
 pytestmark = pytest.mark.gpu
 
@@ -139,3 +139,48 @@ def test_wgrad_kernel_variants(variant):
             d, x, w, g = _rand_case(*case, seed=variant * 13 + splits)
             with forced(SDCONV_WGRAD_VARIANT=variant, SDCONV_WGRAD_SPLITS=splits, SDCONV_NO_TUNED_TABLE=1):
                 check_all_passes(d, x, w, g, f"wgrad{variant}s{splits}{case}")
+
+
+# pointwise layers with few filters: pixel counts around the 16 of a wave, the 64 of a workgroup and
+# the weight gradient's 256 of a pixel range; channels below, at and past one 256-channel load and one
+# 128-channel tile; filters around each multiple of 16, odd and in fours; the longest filter accepted
+NARROW_SHAPES = [
+    # N  H   W   C     K
+    (1, 1, 1, 8, 1),
+    (1, 3, 5, 32, 3),
+    (1, 4, 4, 40, 4),
+    (2, 8, 16, 256, 12),
+    (1, 16, 16, 128, 15),
+    (1, 1, 257, 136, 17),
+    (2, 13, 21, 264, 28),
+    (1, 7, 9, 512, 33),
+    (1, 31, 33, 96, 47),
+    (1, 25, 42, 512, 60),
+    (1, 9, 7, 576, 63),
+    (3, 50, 84, 256, 3),
+]
+
+
+@pytest.mark.parametrize("shape", NARROW_SHAPES)
+def test_narrow_pointwise_kernels(shape):
+    N, H, W, C, K = shape
+    say(f"narrow pointwise {shape}")
+    d, x, w, g = _rand_case(N, H, W, C, K, 1, 1, (1, 1), (0, 0), (1, 1), seed=C * 64 + K)
+    assert [sd.kernel_name(d, p) for p in (sd.FWD, sd.DGRAD, sd.WGRAD)] == ["narrow_fwd", "narrow_dgrad", "narrow_wgrad"]
+    check_all_passes(d, x, w, g, f"narrow{shape}")
+    check_fused(d, x, w, g, f"narrow_fused{shape}")
+
+
+def test_narrow_pointwise_route_borders():
+    def names(*geom):
+        d = sd.make_desc(*geom)
+        return {sd.kernel_name(d, p).startswith("narrow") for p in (sd.FWD, sd.DGRAD, sd.WGRAD)}
+    one, zero = (1, 1), (0, 0)
+    assert names(1, 9, 7, 576, 63, 1, 1, one, zero, one) == {True}
+    for geom in [(1, 9, 7, 584, 63, 1, 1, one, zero, one),      # the filter does not fit in LDS
+                 (1, 9, 7, 64, 65, 1, 1, one, zero, one),       # too many filters
+                 (1, 9, 7, 64, 16, 1, 1, one, zero, one),       # a multiple of 8
+                 (1, 9, 7, 60, 12, 1, 1, one, zero, one),       # channels not in eights
+                 (1, 9, 7, 64, 12, 1, 1, (2, 2), zero, one), (1, 9, 7, 64, 12, 1, 1, one, one, one),
+                 (1, 9, 7, 64, 12, 3, 3, one, one, one)]:
+        assert names(*geom) == {False}, geom

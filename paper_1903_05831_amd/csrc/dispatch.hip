@@ -143,6 +143,81 @@ static int ws_variant_for(const Geom& g, bool dgrad, int v)
     return v;
 }
 
+// Time of a forward or data-gradient pass under each tile variant, for geometries outside the
+// measured table.  A workgroup takes `step` us per 64 contraction channels of a tap (where two share a
+// compute unit `shared` us times two, if that is more), and `tile` us per tile besides; launch and first loads are
+// `fixed`; the operands move at no more than `hbm` MB/us.  A variant's time is that of the fullest
+// compute unit, so what decides is how its tiles divide by 256.  Three sets of constants: pointwise
+// layers, layers that gather, and strided data gradients (parity classes, with the mean steps of
+// their tiles).  Least-squares fits to 25 000 kernel-trace timings of 240 layers of random size (20 to
+// 170 000 pixels, 8 to 2048 channels; scatter 5-9 %, strided 13 %).  Over those layers the choice is
+// 3.4 % slower than the fastest variant on average (10 % at the 90th percentile); rules by row
+// counts alone, read off the table, were 17.7 % slower (53 %).
+struct RowCost { float fixed, step, shared, tile, hbm; };
+struct RowModel { int variant, per_cu; RowCost pointwise, gather, strided; };   // step 0: not taken
+static const RowModel kRowModels[] = {
+    {300, 1, {1.41f, 0.533f, 0.f, 3.62f, 3.83f}, {1.00f, 0.547f, 0.f, 3.73f, 5.00f}, {6.51f, 0.842f, 0.f, 1.49f, 5.00f}},
+    {303, 1, {1.00f, 0.760f, 0.f, 4.98f, 4.08f}, {1.00f, 0.763f, 0.f, 5.12f, 4.96f}, {8.23f, 1.260f, 0.f, 0.94f, 5.03f}},
+    {310, 1, {1.00f, 1.100f, 0.f, 5.75f, 4.03f}, {1.00f, 1.110f, 0.f, 5.67f, 3.31f}, {11.5f, 1.740f, 0.f, 2.46f, 8.12f}},
+    {311, 1, {1.00f, 1.190f, 0.f, 6.14f, 4.04f}, {1.00f, 1.200f, 0.f, 5.95f, 3.19f}, {12.0f, 1.910f, 0.f, 3.27f, 5.66f}},
+    {316, 1, {1.00f, 0.778f, 0.f, 4.33f, 3.86f}, {1.00f, 0.776f, 0.f, 4.52f, 4.96f}, {8.31f, 1.270f, 0.f, 0.50f, 5.11f}},
+    {318, 1, {1.74f, 0.392f, 0.f, 2.77f, 5.00f}, {1.38f, 0.408f, 0.f, 2.77f, 5.00f}, {4.70f, 0.585f, 0.f, 1.58f, 5.00f}},
+    {319, 2, {2.38f, 0.340f, 0.219f, 2.25f, 4.35f}, {2.63f, 0.353f, 0.214f, 2.07f, 5.00f}, {4.40f, 0.539f, 0.095f, 1.43f, 5.00f}},
+    {321, 1, {1.43f, 0.571f, 0.f, 3.54f, 4.62f}, {1.00f, 0.580f, 0.f, 3.75f, 5.00f}, {6.82f, 0.852f, 0.f, 1.36f, 5.00f}},
+    {322, 1, {1.24f, 0.979f, 0.f, 4.96f, 3.63f}, {1.00f, 1.010f, 0.f, 4.25f, 4.94f}, {12.0f, 1.560f, 0.f, 0.43f, 5.05f}},
+    {324, 1, {1.00f, 0.764f, 0.f, 5.02f, 3.03f}, {1.00f, 0.768f, 0.f, 5.58f, 3.31f}, {}},
+    {417, 1, {}, {1.00f, 0.425f, 0.f, 4.06f, 5.00f}, {}},
+    {433, 2, {}, {1.98f, 0.504f, 0.328f, 2.03f, 5.00f}, {}},
+    {435, 1, {}, {1.55f, 0.311f, 0.f, 3.28f, 5.00f}, {}},
+};
+
+// Tiles of a variant, and the 64-channel steps of one of them (their mean, where classes differ).
+static long row_model_tiles(const Geom& g, bool dgrad, int variant, float* steps)
+{
+    const int cs = dgrad ? g.K : g.C, cd = dgrad ? g.C : g.K;
+    const int Hd = dgrad ? g.H : g.Ho, Wd = dgrad ? g.W : g.Wo;
+    const int slabs = (cs + 63) / 64;
+    *steps = (float)g.R * g.S * slabs;
+    if (variant >= 400) {
+        const PatchVariant& v = kPatchVariants[variant - 400];
+        return (long)g.N * ((Hd + v.th - 1) / v.th) * ((Wd + v.tw - 1) / v.tw) * ((cd + v.bn - 1) / v.bn);
+    }
+    const IgemmVariant& v = igemm_variant(variant);
+    const long columns = (cd + v.bn - 1) / v.bn;
+    int starts[kMaxClasses + 1], nc;
+    const long rows = row_tiles(g, dgrad, v.bm, starts, &nc);
+    if (nc > 1 && rows > 0) {
+        double sum = 0.;
+        for (int q = 0; q < nc; ++q) {
+            const int a = q / g.sw, b = q % g.sw;
+            int taps_h = 0, taps_w = 0;
+            for (int r = 0; r < g.R; ++r) taps_h += (a + g.ph - r * g.dh) % g.sh == 0;
+            for (int t = 0; t < g.S; ++t) taps_w += (b + g.pw - t * g.dw) % g.sw == 0;
+            sum += (double)(starts[q + 1] - starts[q]) * taps_h * taps_w * slabs;
+        }
+        *steps = (float)(sum / rows);
+    }
+    return rows * columns;
+}
+
+static float row_us(const Geom& g, bool dgrad, const RowModel& m)
+{
+    const bool pointwise = g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
+    const RowCost& c = pointwise ? m.pointwise : (dgrad && g.sh * g.sw > 1 ? m.strided : m.gather);
+    if (c.step == 0.f) return -1.f;
+    float steps;
+    const long n = row_model_tiles(g, dgrad, m.variant, &steps), per_round = 256 * m.per_cu;
+    const float full = m.per_cu * c.shared > c.step ? m.per_cu * c.shared : c.step;
+    float t = (float)(n / per_round) * (steps * full + c.tile);
+    if (const long rest = n % per_round) {
+        const float crowd = (float)((rest + 255) / 256);
+        t += steps * (crowd * c.shared > c.step ? crowd * c.shared : c.step) + c.tile * crowd / m.per_cu;
+    }
+    const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 && !dgrad ? g.sh * g.sw : 1);    // MB
+    const float move = (x + 2e-6f * g.N * g.Ho * g.Wo * g.K + 2e-6f * g.K * g.R * g.S * g.C) / c.hbm;
+    return c.fixed + (t > move ? t : move);
+}
+
 static int pick_variant(const Geom& g, bool dgrad)
 {
     if (!byte_offsets_fit_31_bits(g)) return (dgrad ? g.C : g.K) <= 64 ? 3 : 0;
@@ -154,34 +229,14 @@ static int pick_variant(const Geom& g, bool dgrad)
     if (fv >= 300 && fv < 300 + kNumIgemmWsVariants) return ws_variant_for(g, dgrad, fv);
     if (const TunedEntry* e = tuned_lookup(g, dgrad ? SDCONV_DGRAD : SDCONV_FWD))
         if (e->variant < 400 || patch_variant_ok(g, dgrad, e->variant)) return ws_variant_for(g, dgrad, e->variant);
-    // No table entry: rules read off the tuned layers of the detector workloads.
-    const int nout = dgrad ? g.C : g.K;
-    const int kgemm = g.R * g.S * (dgrad ? g.K : g.C);
-    const long rows = dgrad ? (long)g.N * g.H * g.W : (long)g.N * g.Ho * g.Wo;
-    int starts[kMaxClasses + 1], nc;
-    // stride-1 3x3-class layers: the patch-resident kernel (wide blocks when there is enough work),
-    // unless its 10x14 pixel blocks would be mostly empty (the 7x7 maps of an RoI head)
-    const int Hd = dgrad ? g.H : g.Ho, Wd = dgrad ? g.W : g.Wo;
-    const long covered = (long)((Hd + 9) / 10) * 10 * ((Wd + 13) / 14) * 14;
-    const bool blocks_fill = covered * 2 <= (long)Hd * Wd * 3;      // at most 1.5x the pixels
-    if (blocks_fill && nout >= 128 && rows >= 20000 && patch_variant_ok(g, dgrad, 415)) return 415;
-    if (blocks_fill && (dgrad ? g.K : g.C) == 64 && patch_variant_ok(g, dgrad, 433)) return 433;
-    if (blocks_fill && patch_variant_ok(g, dgrad, 429)) return 429;
-    // narrow outputs: 64-wide tiles
-    if (nout <= 64) return 100 + 7;
-    // enough rows to fill the chip with 224-row tiles: the big tile for long contractions and wide
-    // outputs (half the LDS traffic per flop), else the 128-wide one; small layers: 128x128
-    const int t224 = row_tiles(g, dgrad, 224, starts, &nc);
-    if (kgemm >= 512 && nout >= 256 && (long)t224 * ((nout + 255) / 256) >= 200) return 300 + 10;
-    if ((long)t224 * ((nout + 127) / 128) >= 200) return 300 + 16;
-    // few pixels (a 25x42 map, a fully connected head): small tiles, so that every compute unit
-    // still gets a workgroup
-    const long t128 = (long)row_tiles(g, dgrad, 128, starts, &nc) * ((nout + 127) / 128);
-    if (t128 < 160) {
-        const long t64x128 = (long)row_tiles(g, dgrad, 64, starts, &nc) * ((nout + 127) / 128);
-        return t64x128 >= 200 ? 300 + 20 : 300 + 19;
+    int best = -1;
+    float best_us = 0.f;
+    for (const RowModel& m : kRowModels) {
+        if (m.variant >= 400 && !patch_variant_ok(g, dgrad, m.variant)) continue;
+        const float us = row_us(g, dgrad, m);
+        if (us >= 0.f && (best < 0 || us < best_us)) { best = m.variant; best_us = us; }
     }
-    return 300 + 0;
+    return ws_variant_for(g, dgrad, best);
 }
 
 static bool thin_ok(const Geom& g) { return !force_direct() && g.C <= 4 && thin_supported(g); }

@@ -74,6 +74,7 @@ hipError_t run_wgrad(const Geom& g, const Plan& p, const __half* x, const __half
 // Single-precision companion path (conv_f32.hip): matrix kernels for channel and filter counts in
 // multiples of 4 (f32_supported), the direct kernels for everything else.
 bool f32_supported(const Geom& g);
+int forced_f32_tile();      // tuning hook: index into the tile list of conv_f32.hip, or -1
 size_t f32_workspace_bytes(const Geom& g, int pass);
 hipError_t run_fwd_f32(const Geom& g, const float* x, const float* w, float* y, hipStream_t st);
 hipError_t run_dgrad_f32(const Geom& g, const float* dy, const float* w, float* dx, void* ws, hipStream_t st);

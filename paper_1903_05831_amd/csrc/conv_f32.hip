@@ -3,11 +3,13 @@
 // that the FP32 -> FP16 speedup of section 2.2 / Figure 1(b) of the paper can be measured on this
 // hardware with both sides on the matrix cores.
 //
-// The fp32 matrix rate is 1/16 of the fp16 one (157.3 against 2516.6 TFLOP/s), so these
-// kernels are bound by the matrix pipe with a wide margin: a 128x128 tile needs 16 KB of
-// operands per 2048 cycles of MFMA.  They therefore keep the plain structure of igemm.hip /
-// wgrad.hip (global -> registers -> LDS double buffer, one barrier per step) and spend no
-// effort on the memory side.
+// The fp32 matrix rate is 1/16 of the fp16 one (157.3 against 2516.6 TFLOP/s), so the
+// kernels are bound by the matrix pipe: a 128x128 tile needs 32 KB of operands per 4096 cycles of
+// MFMA.  They therefore keep the plain structure of igemm.hip / wgrad.hip (global -> registers -> LDS
+// double buffer, one barrier per step).  What costs time on the small layers is that few tiles divide badly
+// by 256 compute units, and that a lone workgroup waits for its loads and its barrier; hence
+// tiles down to 32x32.  3x3 stride 2, 256 -> 256 channels, 100x168 pixels in: forward 119 us with
+// 132 tiles of 128x64, 84 us with 1056 of 32x32; 1x1, 512 -> 256: 64 us with 128x64, 53 us with 96x64.
 //
 // Forward / data gradient: implicit GEMM, rows = pixels, 32 floats of contraction per step (a
 // 128-byte row, 16-byte chunks XOR-swizzled with the row number).  An MFMA takes one float per
@@ -43,14 +45,25 @@ struct F32Params {
 constexpr int kF32BK = 32;              // contraction floats per step
 constexpr int kF32RowBytes = kF32BK * 4;
 
-template <int MODE, int BM, int BN, int WGM, int WGN>
+template <int BM, int BN, int WGK>
+constexpr size_t f32_lds_bytes()
+{
+    const size_t loop = 2 * (BM + BN) * kF32RowBytes + (3 * kMaxTaps + 4) * sizeof(int);
+    const size_t sums = (size_t)(WGK - 1) * BM * BN * sizeof(float);    // over the same memory after the loop
+    return loop > sums ? loop : sums;
+}
+
+// WGK > 1: the waves divide the 32 contraction floats of a step among WGK groups, and the groups' sums
+// meet in LDS after the loop.  That is what makes tiles possible whose sides four waves cannot
+// divide into 32x32 blocks.
+template <int MODE, int BM, int BN, int WGM, int WGN, int WGK>
 __global__ __launch_bounds__(256) void igemm_f32_kernel(F32Params P)
 {
-    static_assert(WGM * WGN == 4, "four waves per workgroup");
+    static_assert(WGM * WGN * WGK == 4, "four waves per workgroup");
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int FM = WM / 32, FN = WN / 32;
     constexpr int PA = BM / 32, PB = BN / 32;       // staging passes (32 rows per pass)
-    static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile is a multiple of the MFMA block");
+    static_assert(WM % 32 == 0 && WN % 32 == 0 && WM * WGM == BM && WN * WGN == BN, "wave tile is a multiple of the MFMA block");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char* ldsA = smem;                                 // [2][BM rows][128 B]
@@ -63,7 +76,8 @@ __global__ __launch_bounds__(256) void igemm_f32_kernel(F32Params P)
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
+    const int wk = wave / (WGM * WGN), wmn = wave % (WGM * WGN);
+    const int wm = wmn / WGN, wn = wmn % WGN;
 
     const int tile = blockIdx.x;
     const int tn = tile % P.tiles_n;
@@ -177,8 +191,8 @@ __global__ __launch_bounds__(256) void igemm_f32_kernel(F32Params P)
         const unsigned char* sa = ldsA + buf * BM * kF32RowBytes;
         const unsigned char* sb = ldsB + buf * BN * kF32RowBytes;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int chunk = 2 * j + lhi;          // contraction floats 4*chunk .. 4*chunk+3 of the step
+        for (int j = 0; j < 4 / WGK; ++j) {
+            const int chunk = 2 * (j + wk * (4 / WGK)) + lhi;   // contraction floats 4*chunk .. 4*chunk+3 of the step
             f32x4 fa[FM], fb[FN];
 #pragma unroll
             for (int b = 0; b < FM; ++b) {
@@ -211,6 +225,32 @@ __global__ __launch_bounds__(256) void igemm_f32_kernel(F32Params P)
             if (more) stage((it + 1) & 1);
             __syncthreads();
         }
+    }
+
+    if constexpr (WGK > 1) {        // add the groups' sums, in the order of the groups
+        float* sums = reinterpret_cast<float*>(smem);
+        auto slot = [&](int group, int a, int b, int e) {
+            return ((((group - 1) * WGM * WGN + wmn) * FN + a) * FM + b) * 1024 + e * 64 + lane;
+        };
+        __syncthreads();            // the last step's reads, and those of the tap count where there was no step
+        if (wk > 0) {
+#pragma unroll
+            for (int a = 0; a < FN; ++a)
+#pragma unroll
+                for (int b = 0; b < FM; ++b)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) sums[slot(wk, a, b, e)] = acc[a][b][e];
+        }
+        __syncthreads();
+        if (wk > 0) return;
+#pragma unroll
+        for (int group = 1; group < WGK; ++group)
+#pragma unroll
+            for (int a = 0; a < FN; ++a)
+#pragma unroll
+                for (int b = 0; b < FM; ++b)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[a][b][e] += sums[slot(group, a, b, e)];
     }
 
     // ---- epilogue: a lane holds 4 consecutive destination channels of one pixel per group ----
@@ -446,19 +486,84 @@ size_t f32_workspace_bytes(const Geom& g, int pass)
     return 0;
 }
 
-template <int MODE, int BM, int BN, int WGM, int WGN>
+template <int MODE, int BM, int BN, int WGM, int WGN, int WGK>
 static hipError_t launch_f32_variant(const F32Params& P, hipStream_t st)
 {
-    constexpr size_t lds = 2 * (BM + BN) * kF32RowBytes + (3 * kMaxTaps + 4) * sizeof(int);
+    constexpr size_t lds = f32_lds_bytes<BM, BN, WGK>();
     static std::atomic<bool> configured{false};   // set once the attribute call has succeeded; a second thread may repeat it, harmlessly
     if (!configured.load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_f32_kernel<MODE, BM, BN, WGM, WGN>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_f32_kernel<MODE, BM, BN, WGM, WGN, WGK>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((igemm_f32_kernel<MODE, BM, BN, WGM, WGN>), dim3(P.total_tiles), dim3(256), lds, st, P);
+    hipLaunchKernelGGL((igemm_f32_kernel<MODE, BM, BN, WGM, WGN, WGK>), dim3(P.total_tiles), dim3(256), lds, st, P);
     return hipGetLastError();
+}
+
+// Tiles, and the time each takes: us per step and tile where a tile has a compute unit to itself (`step`) or
+// several share one (`shared` each, at most `per_cu` at a time), us per tile besides, launch
+// and first loads.  Fits to 148 passes (74 layers of res2-res5, 40x60 to 200x336 pixels, both passes),
+// scatter 5-6 %.  A 128x128 tile reaches 77 % of the fp32 matrix peak beside another and 32x32 only 48 %
+// (more LDS reads and loads per product), but small layers have too few large tiles for 256 compute
+// units: the choice is 0.9 % slower than the fastest tile on average (4 % at the 90th percentile),
+// where the evenest spread of 128x128, 128x64 and 64x64 tiles was 19 % slower.
+struct F32Tile {
+    int bm, bn, per_cu;
+    float step, shared, tile, fixed;
+    hipError_t (*launch[2])(const F32Params&, hipStream_t);     // forward, data gradient
+};
+#define F32_TILE(BM, BN, WGM, WGN, WGK) {launch_f32_variant<0, BM, BN, WGM, WGN, WGK>, launch_f32_variant<1, BM, BN, WGM, WGN, WGK>}
+static const F32Tile kF32Tiles[] = {
+    {128, 128, 2, 2.468f, 2.209f, 5.06f, 0.88f, F32_TILE(128, 128, 2, 2, 1)},
+    {128, 64, 3, 1.485f, 1.229f, 3.44f, 1.83f, F32_TILE(128, 64, 2, 2, 1)},
+    {96, 64, 3, 1.207f, 0.967f, 3.30f, 2.13f, F32_TILE(96, 64, 1, 2, 2)},
+    {64, 64, 4, 0.903f, 0.673f, 1.31f, 3.69f, F32_TILE(64, 64, 2, 2, 1)},
+    {32, 64, 6, 0.518f, 0.366f, 1.73f, 3.30f, F32_TILE(32, 64, 1, 2, 2)},
+    {32, 32, 5, 0.373f, 0.220f, 1.46f, 3.49f, F32_TILE(32, 32, 1, 1, 4)},
+};
+#undef F32_TILE
+
+// Row tiles of height bm (all parity classes of a strided data gradient), with P into its tables, and
+// those among them that have taps, with their taps summed.
+struct F32Rows { long all, busy; double taps; };
+static F32Rows f32_row_tiles(const Geom& g, bool dgrad, int bm, F32Params* P)
+{
+    const int nc = dgrad ? g.sh * g.sw : 1;
+    F32Rows out{0, 0, 0.};
+    if (P) P->nclasses = nc;
+    for (int q = 0; q < nc; ++q) {
+        long rows = (long)g.N * g.Ho * g.Wo;
+        int taps = g.R * g.S;
+        if (dgrad) {
+            const int a = q / g.sw, b = q % g.sw;
+            const long Hi = (g.H - a + g.sh - 1) / g.sh, Wj = (g.W - b + g.sw - 1) / g.sw;
+            int th = 0, tw = 0;
+            for (int r = 0; r < g.R; ++r) th += (a + g.ph - r * g.dh) % g.sh == 0;
+            for (int t = 0; t < g.S; ++t) tw += (b + g.pw - t * g.dw) % g.sw == 0;
+            rows = Hi > 0 && Wj > 0 ? g.N * Hi * Wj : 0;
+            taps = th * tw;
+        }
+        const long tiles = (rows + bm - 1) / bm;
+        if (P) P->class_tile_start[q] = (int)out.all;
+        out.all += tiles;
+        if (taps) out.busy += tiles;
+        out.taps += (double)tiles * taps;
+    }
+    if (P) P->class_tile_start[nc] = (int)out.all;
+    return out;
+}
+
+static double f32_us(const Geom& g, bool dgrad, const F32Tile& t)
+{
+    const int cs = dgrad ? g.K : g.C, cd = dgrad ? g.C : g.K;
+    const F32Rows rows = f32_row_tiles(g, dgrad, t.bm, nullptr);
+    if (rows.busy == 0) return t.fixed;
+    const double steps = rows.taps / rows.busy * ((cs + kF32BK - 1) / kF32BK);
+    const long fullest = (rows.busy * ((cd + t.bn - 1) / t.bn) + 255) / 256;    // tiles of one compute unit
+    auto round = [&](long n) { return steps * (n * t.shared > t.step ? n * t.shared : t.step) + t.tile; };
+    const long rest = fullest % t.per_cu;
+    return t.fixed + fullest / t.per_cu * round(t.per_cu) + (rest ? round(rest) : 0.);
 }
 
 static hipError_t run_f32_igemm(const Geom& g, bool dgrad, const float* A, const float* B, float* D, hipStream_t st)
@@ -472,48 +577,19 @@ static hipError_t run_f32_igemm(const Geom& g, bool dgrad, const float* A, const
     P.sh = g.sh; P.sw = g.sw; P.ph = g.ph; P.pw = g.pw; P.dh = g.dh; P.dw = g.dw;
     P.sw_cls = dgrad ? g.sw : 1;
     P.b_row_pitch = g.R * g.S * P.Cs;
-    // Tile: 128x128, 128x64 or 64x64, chosen below (these kernels are matrix-bound, so an idle or
-    // overloaded compute unit costs its full share).
-    auto count_tiles = [&](int bm, int bn, bool fill) {
-        int acc = 0;
-        if (!dgrad) {
-            if (fill) { P.nclasses = 1; P.class_tile_start[0] = 0; }
-            acc = (int)(((long)g.N * g.Ho * g.Wo + bm - 1) / bm);
-            if (fill) P.class_tile_start[1] = acc;
-        } else {
-            const int nc = g.sh * g.sw;
-            if (fill) P.nclasses = nc;
-            for (int q = 0; q < nc; ++q) {
-                int a = q / g.sw, b = q % g.sw;
-                long Hi = (g.H - a + g.sh - 1) / g.sh, Wj = (g.W - b + g.sw - 1) / g.sw;
-                if (Hi < 0) Hi = 0;
-                if (Wj < 0) Wj = 0;
-                if (fill) P.class_tile_start[q] = acc;
-                acc += (int)((g.N * Hi * Wj + bm - 1) / bm);
-            }
-            if (fill) P.class_tile_start[nc] = acc;
-        }
-        return (long)acc * ((P.Cd + bn - 1) / bn);
-    };
-    // score = how evenly the tiles spread over the compute units (they are all resident at once and
-    // share the matrix pipes: the fullest unit sets the time) x a small preference for the larger tile
-    const int cus = 256;
-    const int cand[3][2] = {{128, 128}, {128, 64}, {64, 64}};
-    const double pref[3] = {1.0, 0.96, 0.90};
-    int bm = 64, bn = 64;
-    double best = -1.0;
-    for (int i = 0; i < 3; ++i) {
-        if (cand[i][1] == 128 && P.Cd <= 64) continue;
-        const long t = count_tiles(cand[i][0], cand[i][1], false);
-        const double fill = (double)t / (double)(((t + cus - 1) / cus) * cus);
-        if (fill * pref[i] > best) { best = fill * pref[i]; bm = cand[i][0]; bn = cand[i][1]; }
+    const F32Tile* tile = nullptr;
+    double best = 0.;
+    for (const F32Tile& t : kF32Tiles) {
+        const double us = f32_us(g, dgrad, t);
+        if (!tile || us < best) { best = us; tile = &t; }
     }
-    P.tiles_n = (P.Cd + bn - 1) / bn;
-    P.total_tiles = (int)count_tiles(bm, bn, true);
-    if (P.total_tiles <= 0) return hipErrorInvalidValue;
-    if (bm == 64) return dgrad ? launch_f32_variant<1, 64, 64, 2, 2>(P, st) : launch_f32_variant<0, 64, 64, 2, 2>(P, st);
-    if (bn == 64) return dgrad ? launch_f32_variant<1, 128, 64, 2, 2>(P, st) : launch_f32_variant<0, 128, 64, 2, 2>(P, st);
-    return dgrad ? launch_f32_variant<1, 128, 128, 2, 2>(P, st) : launch_f32_variant<0, 128, 128, 2, 2>(P, st);
+    const int forced = forced_f32_tile();
+    if (forced >= 0 && forced < (int)(sizeof(kF32Tiles) / sizeof(kF32Tiles[0]))) tile = &kF32Tiles[forced];
+    P.tiles_n = (P.Cd + tile->bn - 1) / tile->bn;
+    const long total = f32_row_tiles(g, dgrad, tile->bm, &P).all * P.tiles_n;
+    if (total <= 0 || total > 0x7fffffffL) return hipErrorInvalidValue;
+    P.total_tiles = (int)total;
+    return tile->launch[dgrad](P, st);
 }
 
 hipError_t run_fwd_f32(const Geom& g, const float* x, const float* w, float* y, hipStream_t st)

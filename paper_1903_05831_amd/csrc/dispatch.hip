@@ -30,6 +30,7 @@ static int hook(const char* name, int dflt) { return tuning() ? env_int(name, df
 static bool force_direct() { return hook("SDCONV_FORCE_DIRECT", 0) != 0; }
 static int forced_variant() { return hook("SDCONV_IGEMM_VARIANT", -1); }
 static int forced_wgrad_splits() { return hook("SDCONV_WGRAD_SPLITS", -1); }
+int forced_f32_tile() { return hook("SDCONV_F32_TILE", -1); }
 static int forced_wgrad_variant() { return hook("SDCONV_WGRAD_VARIANT", -1); }
 
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }

@@ -24,6 +24,7 @@ pytestmark = pytest.mark.gpu
 
 ELEM_TOL_F32 = 2e-4
 FRO_TOL_F32 = 2e-5
+F32_TILES = 6           # tiles of the forward / data-gradient kernel
 
 
 def _compare(got, ref, what, nterms, term_rms):
@@ -96,6 +97,24 @@ def test_f32_small_shapes_full_tensor(case):
     say(f"f32 case {case}")
     d, x, w, g = _rand32(*case, seed=sum(case[:7]))
     _check(d, x, w, g, f"f32{case}")
+
+
+# a tile's rows and columns with remainders, a contraction that ends inside a step, classes without taps
+TILE_SHAPES = [
+    (1, 13, 17, 36, 164, 3, 3, (1, 1), (1, 1), (1, 1)),
+    (2, 15, 14, 132, 68, 3, 3, (2, 2), (1, 1), (1, 1)),
+    (1, 20, 25, 64, 100, 1, 1, (2, 2), (0, 0), (1, 1)),
+    (1, 1, 2, 4, 4, 1, 1, (1, 1), (0, 0), (1, 1)),
+]
+
+
+@pytest.mark.parametrize("tile", range(F32_TILES))
+def test_f32_forward_and_data_gradient_tiles(tile, monkeypatch):
+    monkeypatch.setenv("SDCONV_F32_TILE", str(tile))
+    for case in TILE_SHAPES:
+        say(f"f32 tile {tile} case {case}")
+        d, x, w, g = _rand32(*case, seed=sum(case[:7]) + tile)
+        _check(d, x, w, g, f"f32tile{tile}{case}")
 
 
 def _distinct_backbone_and_head_shapes():

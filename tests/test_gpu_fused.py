@@ -6,9 +6,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_1903_05831_amd as sd
 
-from gpu_harness import GuardedOut, check_fused, say, to_dev, workspace_for
+from gpu_harness import GuardedOut, check_fused, oracle_desc, say, to_dev, workspace_for
 from test_gpu_variants import ONE_SLAB, PATCH_VARIANTS, THREE_TAP_STEP, WS_VARIANTS, _rand_case, forced
 
 pytestmark = pytest.mark.gpu
@@ -63,6 +64,39 @@ def test_empty_tail_is_the_plain_pass_bit_for_bit():
         sd.conv2d_dgrad_fused(d, gd, wd, b.view, workspace_for(d, sd.DGRAD), st)
         torch.cuda.synchronize()
         assert np.array_equal(a.numpy().view(np.uint16), b.numpy().view(np.uint16))
+
+
+@pytest.mark.parametrize("case,rounds_the_sum", [
+    ((2, 25, 42, 256, 12, 1, 1, (1, 1), (0, 0), (1, 1)), True),     # narrow pointwise kernel
+    ((1, 17, 23, 64, 47, 1, 1, (1, 1), (0, 0), (1, 1)), True),      # ... three filter tiles, K odd
+    ((2, 19, 21, 64, 20, 3, 3, (1, 1), (1, 1), (1, 1)), True),      # padded filter count
+    ((1, 31, 37, 128, 72, 1, 1, (1, 1), (0, 0), (1, 1)), False),    # filters in eights
+])
+def test_fused_forward_roundings(case, rounds_the_sum):
+    """The documented number of roundings, bit for bit: the tail works on the binary32 sum, or, for K not
+    a multiple of 8 with C that is, on the sum rounded to binary16.  Whole numbers, and factors that
+    are powers of two, make every operation but the roundings to binary16 exact."""
+    say(f"fused roundings case {case}")
+    d = sd.make_desc(*case)
+    rng = np.random.default_rng(11)
+    ho, wo = sd.conv2d_out_shape(d)
+    x = rng.integers(-30, 31, (d.N, d.H, d.W, d.C)).astype(np.float16)
+    w = rng.integers(-30, 31, (d.K, d.R, d.S, d.C)).astype(np.float16)
+    scale = (2.0 ** rng.integers(-1, 1, d.K) * rng.choice([-1.0, 1.0], d.K)).astype(np.float32)
+    bias = rng.integers(-999, 1000, d.K).astype(np.float32)
+    res = rng.integers(-999, 1000, (d.N, ho, wo, d.K)).astype(np.float16)
+    st = torch.cuda.current_stream().cuda_stream
+    out = GuardedOut((d.N, ho, wo, d.K), torch.float16)
+    sd.conv2d_fwd_fused(d, to_dev(x), to_dev(w), out.view, workspace_for(d, sd.FWD), st, scale=to_dev(scale),
+                        bias=to_dev(bias), residual=to_dev(res), relu=True)
+    torch.cuda.synchronize()
+    out.check_guards()
+    z = oracle.conv2d_fwd(oracle_desc(d), x, w).reshape(out.shape)
+    assert np.array_equal(z, np.rint(z)) and 2048 < np.abs(z).max() < 65504
+    if rounds_the_sum:
+        z = z.astype(np.float16).astype(np.float64)
+    want = np.maximum(z * scale + bias + res.astype(np.float64), 0.0).astype(np.float16)
+    assert np.array_equal(out.numpy(), want), int((out.numpy() != want).sum())
 
 
 FUSED_WS_SHAPES = [

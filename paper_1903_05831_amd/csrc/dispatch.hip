@@ -341,13 +341,29 @@ static const WgradModel kWgradModels[] = {
 };
 constexpr float kReduceFixed = 5.1f, kReduceRate = 9.6f;    // us with the gap between the kernels, MB/us
 
-// More partial sums than this are not considered (the fixed scratch of conv2d_wgrad_static_scratch).
-constexpr size_t kPartialBytes = (size_t)64 << 20;
-
 static long wgrad_steps(const Geom& g) { return ((long)g.N * g.Ho * g.Wo + 63) / 64; }
 static long wgrad_tiles(const Geom& g, const WgradVariant& v)
 {
     return (long)((g.K + v.bm - 1) / v.bm) * ((g.C + v.bn - 1) / v.bn) * g.R * g.S;
+}
+
+// Bytes that the partial sums of a layer may take beside `copies` bytes of padded operands in the
+// workspace.  conv2d_wgrad_static_scratch has SDCONV_STATIC_SCRATCH_BYTES for both and runs the same plan, so the
+// partial sums stay within what is left of it: every layer whose copies fit is served.  Layers that need
+// more for 384 workgroups of the plain tile may have that much: one range or two would leave most of the
+// chip idle for long (3x3 1024 -> 1024 on 8x56x56: 536 us with the 75 MB of two ranges, 447 with three).
+static size_t wgrad_partial_limit(const Geom& g, size_t copies)
+{
+    const long pixels = (long)g.N * g.Ho * g.Wo, steps = wgrad_steps(g);
+    const int side = g.K >= 512 && g.C >= 512 && pixels >= 20000 && byte_offsets_fit_31_bits(g) ? 256 : 128;
+    const int bm = g.K <= 64 ? 64 : side, bn = g.C <= 64 && byte_offsets_fit_31_bits(g) ? 64 : side;
+    const long tiles = (long)((g.K + bm - 1) / bm) * ((g.C + bn - 1) / bn) * g.R * g.S;
+    long ranges = (384 + tiles - 1) / tiles;
+    if (ranges > steps / 4) ranges = steps / 4;
+    const size_t demand = ranges > 1 ? ranges * (size_t)4 * g.K * g.R * g.S * g.C : 0;
+    const size_t scratch = SDCONV_STATIC_SCRATCH_BYTES, left = copies < scratch ? scratch - copies : 0;
+    if (left && tuned_lookup(g, SDCONV_WGRAD)) return left;     // measured with ranges that fit
+    return demand > left ? demand : left;
 }
 
 struct WgradChoice { int variant, splits; float us; };
@@ -377,9 +393,6 @@ static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial
 {
     const long tiles = wgrad_tiles(g, wgrad_variant(m.variant)), total = wgrad_steps(g);
     const size_t dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
-    // a gradient of more than half the limit is split in two where conv2d_wgrad always needed more
-    // than the limit for it: long pixel axis, wide layer
-    const bool large = dw_bytes <= kPartialBytes && wgrad_steps(g) >= 313 && g.K >= 512 && g.C >= 512;
     static const int candidates[] = {1, 2, 3, -40, -64, -96, -128, -192, -256, -320, -384, -512, -768, -1024};
     long last = 0;
     for (int cand : candidates) {                           // ranges, or minus the workgroups to make
@@ -390,7 +403,7 @@ static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial
         s = (total + steps - 1) / steps;                    // ranges that are not empty
         if (s <= last) continue;
         last = s;
-        if (s > 1 && s * dw_bytes > partial_limit && !(s == 2 && large)) break;
+        if (s > 1 && s * dw_bytes > partial_limit) break;
         const float us = wgrad_us(g, m, tiles, total, s);
         if (best->variant < 0 || us < best->us) *best = WgradChoice{m.variant, (int)s, us};
     }
@@ -429,19 +442,20 @@ static WgradChoice choose_wgrad(const Geom& g, size_t partial_limit)
     return c;
 }
 
-Plan plan_wgrad(const Geom& g)
+// `copies`: bytes of padded operands that the plan's workspace lies behind
+static Plan plan_wgrad_beside(const Geom& g, size_t copies)
 {
     if (narrow_ok(g))
         return Plan{ROUTE_NARROW, 0, narrow_wgrad_ranges(g), align256(narrow_wgrad_partial_bytes(g)), "narrow_wgrad"};
     if (padk_ok(g)) {
         const Geom gp = padded_k(g);
-        const Plan in = plan_wgrad(gp);
-        return Plan{ROUTE_PADK, in.variant, in.splits, padk_act_bytes(gp) + padk_dw_bytes(gp) + in.workspace_bytes,
-                    padk_name(in.name)};
+        const size_t padded = padk_act_bytes(gp) + padk_dw_bytes(gp);
+        const Plan in = plan_wgrad_beside(gp, padded);
+        return Plan{ROUTE_PADK, in.variant, in.splits, padded + in.workspace_bytes, padk_name(in.name)};
     }
     if (thin_ok(g)) return Plan{ROUTE_THIN, 0, 1, align256(thin_wgrad_partial_bytes(g)), "thin_wgrad"};
     if (!igemm_ok(g)) return Plan{ROUTE_DIRECT, 0, 1, 0, "direct_wgrad"};
-    const WgradChoice c = choose_wgrad(g, kPartialBytes);
+    const WgradChoice c = choose_wgrad(g, wgrad_partial_limit(g, copies));
     const int v = c.variant;
     const long total_steps = wgrad_steps(g), sps = (total_steps + c.splits - 1) / c.splits;
     const int splits = (int)((total_steps + sps - 1) / sps);
@@ -450,6 +464,8 @@ Plan plan_wgrad(const Geom& g)
     p.steps_per_split = (int)sps;
     return p;
 }
+
+Plan plan_wgrad(const Geom& g) { return plan_wgrad_beside(g, 0); }
 
 static hipError_t run_igemm(const Geom& g, const Plan& p, bool dgrad, const __half* A, const __half* B,
                             __half* D, hipStream_t st, const Epilogue& ep)
@@ -552,7 +568,7 @@ hipError_t run_wgrad(const Geom& g, const Plan& p, const __half* x, const __half
         void* inner_ws = base + padk_act_bytes(gp) + padk_dw_bytes(gp);
         hipError_t e = launch_pad_channels(dy, gpad, (long)g.N * g.Ho * g.Wo, g.K, gp.K, st);
         if (e != hipSuccess) return e;
-        e = run_wgrad(gp, plan_wgrad(gp), x, gpad, dwp, inner_ws, st);
+        e = run_wgrad(gp, plan_wgrad_beside(gp, padk_act_bytes(gp) + padk_dw_bytes(gp)), x, gpad, dwp, inner_ws, st);
         if (e != hipSuccess) return e;
         return launch_copy_f32(dwp, dw, (long)g.K * g.R * g.S * g.C, st);
     }

@@ -172,3 +172,56 @@ def test_neighbouring_batch_sizes_take_the_tuned_entries():
     l = next(l for l in workloads.CONFIGS[5] if l.name == "res4.1b")
     ws = [sd.conv2d_workspace_bytes(sd.desc_of(dataclasses.replace(l, N=n)), sd.WGRAD) for n in (1, 2, 4)]
     assert ws[0] < ws[1] < ws[2]
+
+
+def _weight_gradient_demand(d):
+    """Bytes of padded copies, and of partial sums in as many pixel ranges as make 384 workgroups."""
+    ho, wo = sd.conv2d_out_shape(d)
+    pixels, K, copies = d.N * ho * wo, d.K, 0
+    if K % 8:
+        K = -(-K // 8) * 8
+        copies = -(-pixels * K * 2 // 256) * 256 + -(-K * d.R * d.S * d.C * 4 // 256) * 256
+    wide = K >= 512 and d.C >= 512 and pixels >= 20000
+    bm, bn = (64 if n <= 64 else 256 if wide else 128 for n in (K, d.C))
+    tiles, steps = -(-K // bm) * -(-d.C // bn) * d.R * d.S, -(-pixels // 64)
+    ranges = min(-(-384 // tiles), steps // 4)
+    return copies, ranges * 4 * K * d.R * d.S * d.C if ranges > 1 else 0
+
+
+def test_static_scratch_serves_layers_whose_copies_and_partial_sums_fit():
+    """conv2d_wgrad_static_scratch returns SDCONV_EWORKSPACE where conv2d_wgrad needs more than the fixed
+    scratch: the need must count padded copies and partial sums together, and not grow past the
+    scratch for a layer that it can serve."""
+    import random
+    assert sd.conv2d_workspace_bytes(_desc(N=17, H=199, W=55, C=1456, K=86), sd.WGRAD) <= sd.STATIC_SCRATCH_BYTES
+    strided = _desc(N=9, H=190, W=155, C=576, K=568, R=7, S=7, stride_h=3, stride_w=3, pad_h=0, pad_w=0)
+    assert sd.conv2d_workspace_bytes(strided, sd.WGRAD) <= sd.STATIC_SCRATCH_BYTES
+    # layers of the measured table and, at other batch sizes and filter counts, beside it
+    for l in workloads.CONFIGS[5]:
+        d = sd.desc_of(l)
+        for n in (1, l.N, l.N * 3 // 2):
+            for k in (d.K, d.K - 1):
+                e = sd.make_desc(n, d.H, d.W, d.C, k, d.R, d.S, (d.stride_h, d.stride_w), (d.pad_h, d.pad_w))
+                if d.C % 8 == 0 and sum(_weight_gradient_demand(e)) <= sd.STATIC_SCRATCH_BYTES:
+                    assert sd.conv2d_workspace_bytes(e, sd.WGRAD) <= sd.STATIC_SCRATCH_BYTES, (l.name, n, k)
+    rng, padded, served = random.Random(8), 0, 0
+
+    def spread(lo, hi):
+        return int(lo * (hi / lo) ** rng.random())
+    for _ in range(6000):
+        d = _desc(N=rng.choice([1, 2, 5, 17, 64]), H=spread(8, 400), W=spread(8, 400), C=8 * spread(1, 400),
+                  K=rng.choice([8 * spread(1, 400), spread(1, 700)]))
+        d.R = d.S = rng.choice([1, 3, 7])
+        d.stride_h = d.stride_w = rng.choice([1, 2, 3])
+        try:
+            copies, partials = _weight_gradient_demand(d)
+        except sd.SdconvError:
+            continue
+        need = sd.conv2d_workspace_bytes(d, sd.WGRAD)
+        if copies + partials <= sd.STATIC_SCRATCH_BYTES:
+            assert need <= sd.STATIC_SCRATCH_BYTES, ([getattr(d, f) for f, _ in d._fields_], copies, partials, need)
+            served += 1
+            padded += copies > 0
+        else:
+            assert need <= max(copies + partials + 512, sd.STATIC_SCRATCH_BYTES)
+    assert served > 1000 and padded > 200, (served, padded)

@@ -4,6 +4,7 @@
 #include "wgrad.h"
 #include "thin.h"
 #include "narrow.h"
+#include <math.h>
 #include <stdlib.h>
 #include <map>
 #include <mutex>
@@ -145,78 +146,151 @@ static int ws_variant_for(const Geom& g, bool dgrad, int v)
 }
 
 // Time of a forward or data-gradient pass under each tile variant, for geometries outside the
-// measured table.  A workgroup takes `step` us per 64 contraction channels of a tap (where two share a
-// compute unit `shared` us times two, if that is more), and `tile` us per tile besides; launch and first loads are
-// `fixed`; the operands move at no more than `hbm` MB/us.  A variant's time is that of the fullest
-// compute unit, so what decides is how its tiles divide by 256.  Three sets of constants: pointwise
-// layers, layers that gather, and strided data gradients (parity classes, with the mean steps of
-// their tiles).  Least-squares fits to 25 000 kernel-trace timings of 240 layers of random size (20 to
-// 170 000 pixels, 8 to 2048 channels; scatter 5-9 %, strided 13 %).  Over those layers the choice is
-// 3.4 % slower than the fastest variant on average (10 % at the 90th percentile); rules by row
-// counts alone, read off the table, were 17.7 % slower (53 %).
+// measured table.  A workgroup takes `step` us per 64 contraction channels of a tap (where several share a
+// compute unit `shared` us times their number, if that is more), and `tile` us per tile besides; launch
+// and first loads are `fixed`; the operands move at `hbm` MB/us meanwhile.  What decides is mostly how the
+// tiles of a variant divide by 256 compute units.  Three sets of constants: pointwise layers, layers that
+// gather, and strided data gradients, whose parity classes have tiles of different length (a step is that of
+// gathering).  The constants are least-squares fits to the timings in profiles/layer_timings.jsonl.gz
+// (fit_models.py), bounded by the measured rates of matrix instructions alone (2.06 PFLOP/s) and of
+// streaming (6.1 TB/s; 3.5 at least).  On layers left out of the fit the choice is 1.4 % slower than the fastest of 23 measured
+// variants (4.2 % at the 90th percentile); on 1738 passes of detector layers on images of random size
+// 1.4 % (4.6 %).  The model of one round with its last tiles half as wide (324) at a rate of its own, and without the
+// variants below 300, was 2.7 % slower there (9.1 %), rules by row counts 17 % (57 %).
 struct RowCost { float fixed, step, shared, tile, hbm; };
 struct RowModel { int variant, per_cu; RowCost pointwise, gather, strided; };   // step 0: not taken
 static const RowModel kRowModels[] = {
-    {300, 1, {1.41f, 0.533f, 0.f, 3.62f, 3.83f}, {1.00f, 0.547f, 0.f, 3.73f, 5.00f}, {6.51f, 0.842f, 0.f, 1.49f, 5.00f}},
-    {303, 1, {1.00f, 0.760f, 0.f, 4.98f, 4.08f}, {1.00f, 0.763f, 0.f, 5.12f, 4.96f}, {8.23f, 1.260f, 0.f, 0.94f, 5.03f}},
-    {310, 1, {1.00f, 1.100f, 0.f, 5.75f, 4.03f}, {1.00f, 1.110f, 0.f, 5.67f, 3.31f}, {11.5f, 1.740f, 0.f, 2.46f, 8.12f}},
-    {311, 1, {1.00f, 1.190f, 0.f, 6.14f, 4.04f}, {1.00f, 1.200f, 0.f, 5.95f, 3.19f}, {12.0f, 1.910f, 0.f, 3.27f, 5.66f}},
-    {316, 1, {1.00f, 0.778f, 0.f, 4.33f, 3.86f}, {1.00f, 0.776f, 0.f, 4.52f, 4.96f}, {8.31f, 1.270f, 0.f, 0.50f, 5.11f}},
-    {318, 1, {1.74f, 0.392f, 0.f, 2.77f, 5.00f}, {1.38f, 0.408f, 0.f, 2.77f, 5.00f}, {4.70f, 0.585f, 0.f, 1.58f, 5.00f}},
-    {319, 2, {2.38f, 0.340f, 0.219f, 2.25f, 4.35f}, {2.63f, 0.353f, 0.214f, 2.07f, 5.00f}, {4.40f, 0.539f, 0.095f, 1.43f, 5.00f}},
-    {321, 1, {1.43f, 0.571f, 0.f, 3.54f, 4.62f}, {1.00f, 0.580f, 0.f, 3.75f, 5.00f}, {6.82f, 0.852f, 0.f, 1.36f, 5.00f}},
-    {322, 1, {1.24f, 0.979f, 0.f, 4.96f, 3.63f}, {1.00f, 1.010f, 0.f, 4.25f, 4.94f}, {12.0f, 1.560f, 0.f, 0.43f, 5.05f}},
-    {324, 1, {1.00f, 0.764f, 0.f, 5.02f, 3.03f}, {1.00f, 0.768f, 0.f, 5.58f, 3.31f}, {}},
-    {417, 1, {}, {1.00f, 0.425f, 0.f, 4.06f, 5.00f}, {}},
-    {433, 2, {}, {1.98f, 0.504f, 0.328f, 2.03f, 5.00f}, {}},
-    {435, 1, {}, {1.55f, 0.311f, 0.f, 3.28f, 5.00f}, {}},
+    {101, 3, {3.053f, 0.799f, 0.704f, 1.135f, 3.937f}, {2.826f, 0.803f, 0.628f, 1.527f, 3.500f}, {4.334f, 0.803f, 0.628f, 0.738f, 3.500f}},
+    {107, 3, {3.166f, 0.626f, 0.507f, 0.353f, 3.553f}, {2.669f, 0.648f, 0.463f, 1.127f, 3.500f}, {3.728f, 0.648f, 0.463f, 0.000f, 3.500f}},
+    {112, 5, {3.155f, 0.782f, 0.506f, 0.371f, 3.563f}, {3.714f, 0.782f, 0.475f, 0.000f, 3.500f}, {3.374f, 0.782f, 0.475f, 0.465f, 3.500f}},
+    {300, 1, {0.990f, 0.580f, 0.000f, 3.674f, 3.630f}, {0.500f, 0.552f, 0.000f, 3.922f, 3.743f}, {1.197f, 0.552f, 0.000f, 5.197f, 3.500f}},
+    {303, 1, {0.500f, 0.843f, 0.000f, 4.771f, 3.500f}, {0.500f, 0.800f, 0.000f, 4.702f, 3.500f}, {0.500f, 0.800f, 0.000f, 6.639f, 3.500f}},
+    {310, 1, {0.500f, 1.311f, 0.000f, 5.196f, 3.500f}, {0.500f, 1.194f, 0.000f, 5.062f, 3.500f}, {0.500f, 1.194f, 0.000f, 8.411f, 3.500f}},
+    {311, 1, {0.500f, 1.428f, 0.000f, 5.422f, 3.500f}, {0.500f, 1.283f, 0.000f, 5.287f, 3.500f}, {0.500f, 1.283f, 0.000f, 9.121f, 3.500f}},
+    {314, 1, {0.500f, 0.969f, 0.000f, 4.255f, 3.957f}, {0.500f, 0.916f, 0.000f, 4.115f, 3.500f}, {0.500f, 0.916f, 0.000f, 6.309f, 3.500f}},
+    {316, 1, {0.549f, 0.858f, 0.000f, 4.073f, 3.728f}, {0.500f, 0.818f, 0.000f, 4.034f, 3.500f}, {0.500f, 0.818f, 0.000f, 5.912f, 3.500f}},
+    {318, 1, {1.346f, 0.432f, 0.000f, 2.701f, 3.500f}, {0.894f, 0.412f, 0.000f, 2.941f, 5.713f}, {1.552f, 0.412f, 0.000f, 3.666f, 3.500f}},
+    {319, 2, {1.736f, 0.325f, 0.257f, 2.053f, 3.500f}, {1.404f, 0.348f, 0.234f, 2.173f, 4.536f}, {1.146f, 0.348f, 0.234f, 3.097f, 3.500f}},
+    {321, 1, {1.160f, 0.614f, 0.000f, 3.356f, 3.748f}, {0.500f, 0.592f, 0.000f, 3.776f, 4.345f}, {0.898f, 0.592f, 0.000f, 5.450f, 3.500f}},
+    {322, 1, {0.889f, 1.159f, 0.000f, 4.432f, 3.500f}, {0.500f, 1.053f, 0.000f, 4.358f, 3.500f}, {0.500f, 1.053f, 0.000f, 8.053f, 3.865f}},
+    {323, 1, {1.355f, 0.511f, 0.000f, 2.994f, 3.500f}, {1.034f, 0.509f, 0.000f, 3.116f, 4.398f}, {1.309f, 0.509f, 0.000f, 4.329f, 3.500f}},
+    {417, 1, {}, {1.353f, 0.445f, 0.000f, 2.979f, 3.500f}, {}},
+    {427, 2, {}, {2.882f, 0.213f, 0.299f, 0.669f, 3.500f}, {}},
+    {433, 2, {}, {3.540f, 0.303f, 0.368f, 0.325f, 3.500f}, {}},
+    {435, 1, {}, {1.407f, 0.320f, 0.000f, 3.047f, 3.500f}, {}},
 };
+constexpr float kEmptyTile = 0.6f;      // of `tile`: a tile of a class that no tap reaches only stores zeros
+constexpr float kFilterCopy = 3.2f;     // us: the data gradient of the variants below 300 transposes the filter first
 
-// Tiles of a variant, and the 64-channel steps of one of them (their mean, where classes differ).
-static long row_model_tiles(const Geom& g, bool dgrad, int variant, float* steps)
+// Two resources at work together: near the larger time, more where they are alike.
+static float both(float a, float b)
 {
-    const int cs = dgrad ? g.K : g.C, cd = dgrad ? g.C : g.K;
-    const int Hd = dgrad ? g.H : g.Ho, Wd = dgrad ? g.W : g.Wo;
-    const int slabs = (cs + 63) / 64;
-    *steps = (float)g.R * g.S * slabs;
-    if (variant >= 400) {
-        const PatchVariant& v = kPatchVariants[variant - 400];
-        return (long)g.N * ((Hd + v.th - 1) / v.th) * ((Wd + v.tw - 1) / v.tw) * ((cd + v.bn - 1) / v.bn);
-    }
-    const IgemmVariant& v = igemm_variant(variant);
-    const long columns = (cd + v.bn - 1) / v.bn;
-    int starts[kMaxClasses + 1], nc;
-    const long rows = row_tiles(g, dgrad, v.bm, starts, &nc);
-    if (nc > 1 && rows > 0) {
-        double sum = 0.;
-        for (int q = 0; q < nc; ++q) {
-            const int a = q / g.sw, b = q % g.sw;
-            int taps_h = 0, taps_w = 0;
-            for (int r = 0; r < g.R; ++r) taps_h += (a + g.ph - r * g.dh) % g.sh == 0;
-            for (int t = 0; t < g.S; ++t) taps_w += (b + g.pw - t * g.dw) % g.sw == 0;
-            sum += (double)(starts[q + 1] - starts[q]) * taps_h * taps_w * slabs;
-        }
-        *steps = (float)(sum / rows);
-    }
-    return rows * columns;
+    a *= a;
+    b *= b;
+    return sqrtf(sqrtf(a * a + b * b));
 }
 
-static float row_us(const Geom& g, bool dgrad, const RowModel& m)
+// Time until the last tile is done when `slots` workgroups take the tiles in order, class by class.
+struct TileClass { long tiles; float us; };
+static float makespan(const TileClass* classes, int n, long slots)
+{
+    struct { float at; long slots; } free[kMaxClasses + 2] = {{0.f, slots}};    // sorted; a class adds at most one group
+    int groups = 1;
+    for (int q = 0; q < n; ++q) {
+        long m = classes[q].tiles;
+        const float us = classes[q].us;
+        if (m > 4 * slots) {                // whole rounds move every slot alike
+            const long rounds = m / slots - 2;
+            for (int i = 0; i < groups; ++i) free[i].at += rounds * us;
+            m -= rounds * slots;
+        }
+        while (m > 0) {
+            const long take = free[0].slots < m ? free[0].slots : m;
+            const float done = free[0].at + us;
+            m -= take;
+            free[0].slots -= take;
+            if (free[0].slots == 0) {
+                --groups;
+                for (int i = 0; i < groups; ++i) free[i] = free[i + 1];
+            }
+            int i = groups;
+            while (i > 0 && free[i - 1].at > done) --i;
+            if (i > 0 && free[i - 1].at == done) {
+                free[i - 1].slots += take;
+                continue;
+            }
+            for (int j = groups; j > i; --j) free[j] = free[j - 1];
+            free[i] = {done, take};
+            ++groups;
+        }
+    }
+    return free[groups - 1].at;
+}
+
+// Tiles of one length: the fullest compute unit sets the time.
+static float rounds_us(long tiles, float steps, int per_cu, const RowCost& c)
+{
+    auto round = [&](long n) { return steps * (n * c.shared > c.step ? n * c.shared : c.step) + c.tile; };
+    const long fullest = (tiles + 255) / 256, rest = fullest % per_cu;
+    return (float)(fullest / per_cu) * round(per_cu) + (rest ? round(rest) : 0.f);
+}
+
+static const RowModel& row_model(int variant)
+{
+    const RowModel* m = kRowModels;
+    while (m->variant != variant) ++m;
+    return *m;
+}
+
+static float row_us(const Geom& g, bool dgrad, int variant)
 {
     const bool pointwise = g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
-    const RowCost& c = pointwise ? m.pointwise : (dgrad && g.sh * g.sw > 1 ? m.strided : m.gather);
-    if (c.step == 0.f) return -1.f;
-    float steps;
-    const long n = row_model_tiles(g, dgrad, m.variant, &steps), per_round = 256 * m.per_cu;
-    const float full = m.per_cu * c.shared > c.step ? m.per_cu * c.shared : c.step;
-    float t = (float)(n / per_round) * (steps * full + c.tile);
-    if (const long rest = n % per_round) {
-        const float crowd = (float)((rest + 255) / 256);
-        t += steps * (crowd * c.shared > c.step ? crowd * c.shared : c.step) + c.tile * crowd / m.per_cu;
+    const bool strided = dgrad && g.sh * g.sw > 1;
+    auto cost = [&](int v) -> const RowCost& {
+        const RowModel& m = row_model(v);
+        return pointwise ? m.pointwise : strided ? m.strided : m.gather;
+    };
+    const int cs = dgrad ? g.K : g.C, cd = dgrad ? g.C : g.K, bk = variant < 300 ? 32 : 64;
+    const float slabs = (float)((cs + bk - 1) / bk) * bk / 64, steps = g.R * g.S * slabs;
+    const RowCost& c = cost(variant == 324 ? 310 : variant);
+    if (c.step == 0.f || (variant == 324 && strided)) return -1.f;
+    float work;
+    if (variant >= 400) {
+        const PatchVariant& v = kPatchVariants[variant - 400];
+        const int Hd = dgrad ? g.H : g.Ho, Wd = dgrad ? g.W : g.Wo;
+        work = rounds_us((long)g.N * ((Hd + v.th - 1) / v.th) * ((Wd + v.tw - 1) / v.tw) * ((cd + v.bn - 1) / v.bn),
+                         steps, row_model(variant).per_cu, c);
+    } else {
+        const IgemmVariant& v = igemm_variant(variant);
+        const int columns = (cd + v.bn - 1) / v.bn;
+        int starts[kMaxClasses + 1], nc;
+        const long rows = row_tiles(g, dgrad, v.bm, starts, &nc);
+        if (variant == 324) {       // as its launcher divides the rows: 224x256 tiles, then 224x128 ones
+            const long wide = mixed_wide_rows(rows, columns);
+            work = rounds_us(wide * columns, steps, 1, c);
+            if (wide < rows) work += rounds_us((rows - wide) * ((cd + 127) / 128), steps, 1, cost(316));
+        } else if (nc == 1) {
+            work = rounds_us(rows * columns, steps, row_model(variant).per_cu, c);
+        } else {
+            const int per_cu = row_model(variant).per_cu;
+            const long fullest = (rows * columns + 255) / 256, crowd = fullest < per_cu ? fullest : per_cu;
+            const float step = crowd * c.shared > c.step ? crowd * c.shared : c.step;
+            TileClass classes[kMaxClasses];
+            for (int q = 0; q < nc; ++q) {
+                const int a = q / g.sw, b = q % g.sw;
+                int taps_h = 0, taps_w = 0;
+                for (int r = 0; r < g.R; ++r) taps_h += (a + g.ph - r * g.dh) % g.sh == 0;
+                for (int t = 0; t < g.S; ++t) taps_w += (b + g.pw - t * g.dw) % g.sw == 0;
+                const int taps = taps_h * taps_w;
+                classes[q] = {(long)(starts[q + 1] - starts[q]) * columns,
+                              taps * slabs * step + (taps ? c.tile : kEmptyTile * c.tile)};
+            }
+            work = makespan(classes, nc, 256L * per_cu);
+        }
     }
     const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 && !dgrad ? g.sh * g.sw : 1);    // MB
     const float move = (x + 2e-6f * g.N * g.Ho * g.Wo * g.K + 2e-6f * g.K * g.R * g.S * g.C) / c.hbm;
-    return c.fixed + (t > move ? t : move);
+    return c.fixed + (dgrad && variant < 300 ? kFilterCopy : 0.f) + both(work, move);
 }
 
 static int pick_variant(const Geom& g, bool dgrad)
@@ -232,11 +306,13 @@ static int pick_variant(const Geom& g, bool dgrad)
         if (e->variant < 400 || patch_variant_ok(g, dgrad, e->variant)) return ws_variant_for(g, dgrad, e->variant);
     int best = -1;
     float best_us = 0.f;
-    for (const RowModel& m : kRowModels) {
-        if (m.variant >= 400 && !patch_variant_ok(g, dgrad, m.variant)) continue;
-        const float us = row_us(g, dgrad, m);
-        if (us >= 0.f && (best < 0 || us < best_us)) { best = m.variant; best_us = us; }
-    }
+    auto consider = [&](int v) {
+        const float us = row_us(g, dgrad, v);
+        if (us >= 0.f && (best < 0 || us < best_us)) { best = v; best_us = us; }
+    };
+    for (const RowModel& m : kRowModels)
+        if (m.variant < 400 || patch_variant_ok(g, dgrad, m.variant)) consider(m.variant);
+    consider(324);
     return ws_variant_for(g, dgrad, best);
 }
 

@@ -39,6 +39,13 @@ extern const IgemmVariant kIgemmDmaVariants[kNumIgemmDmaVariants];
 hipError_t launch_igemm_dma(int variant, const IgemmParams& P, hipStream_t st);
 constexpr int kNumIgemmWsVariants = 25;
 extern const IgemmVariant kIgemmWsVariants[kNumIgemmWsVariants];
+// Row tiles that a launch with two tile widths takes at full width: whole rounds of 256 workgroups
+// (rounded down to whole row tiles), or all of them where the rest would make two rounds of half tiles.
+inline long mixed_wide_rows(long row_tiles, int tiles_n)
+{
+    const long total = row_tiles * tiles_n;
+    return 2 * (total % 256) > 256 + tiles_n ? row_tiles : total / 256 * 256 / tiles_n;
+}
 hipError_t launch_igemm_ws(int variant, const IgemmParams& P, hipStream_t st);
 struct PatchVariant { int th, tw, bn, tps, stages; const char* fwd_name; const char* dgrad_name; int one_slab = 0; };
 // tps: taps per pipeline step, must divide R*S, and R*S/tps must be at least stages-1;

@@ -381,12 +381,10 @@ static hipError_t launch_ws_mixed_impl(const IgemmParams& P0, hipStream_t st)
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
     }
-    // P0.tiles_n / P0.total_tiles describe the launch in BN-wide tiles.  Whole rounds of 256
-    // workgroups stay BN wide (rounded down to whole row tiles); the rest is cut in two.
+    // P0.tiles_n / P0.total_tiles describe the launch in BN-wide tiles.
     IgemmParams P = P0;
     const int row_tiles = P0.total_tiles / P0.tiles_n;
-    int big_rows = (P0.total_tiles / 256 * 256) / P0.tiles_n;
-    if (2 * (P0.total_tiles % 256) > 256 + P0.tiles_n) big_rows = row_tiles;     // the half tiles would need two rounds
+    const int big_rows = (int)mixed_wide_rows(row_tiles, P0.tiles_n);
     P.mix_big_tiles = big_rows * P0.tiles_n;
     P.mix_big_blocks = (P.mix_big_tiles + 63) / 64 * 64;
     P.mix_small_tm0 = big_rows;

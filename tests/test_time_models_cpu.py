@@ -1,0 +1,55 @@
+"""The time models of the dispatcher against the committed timings: the variant that the library picks
+must be about as fast as the fastest one measured."""
+import math
+import os
+
+import pytest
+
+import paper_1903_05831_amd as sd
+from paper_1903_05831_amd import fit_models
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+TIMINGS = os.path.join(ROOT, "profiles", "layer_timings.jsonl.gz")
+
+
+def _desc(k):
+    N, H, W, C, K, R, s, pad, dil = k
+    return sd.make_desc(N, H, W, C, K, R, R, (s, s), (pad, pad), (dil, dil))
+
+
+@pytest.fixture(scope="module")
+def variants():
+    """Variant of each kernel name (the overrides are honoured: conftest.py sets SDCONV_TUNE)."""
+    d, out = sd.make_desc(1, 28, 28, 64, 64, 3, 3, (1, 1), (1, 1)), {}
+    for name, known, passes in (("SDCONV_IGEMM_VARIANT", fit_models.ROW_VARIANTS, (sd.FWD, sd.DGRAD)),
+                                ("SDCONV_WGRAD_VARIANT", fit_models.WGRAD_VARIANTS, (sd.WGRAD,))):
+        for v in known:
+            os.environ[name] = str(v)
+            out.update({sd.kernel_name(d, p): v for p in passes})
+        del os.environ[name]
+    return out
+
+
+def _quality(loss):
+    loss = sorted(loss)
+    return math.exp(sum(map(math.log, loss)) / len(loss)) - 1, loss[int(0.99 * len(loss))] - 1
+
+
+def test_forward_and_data_gradient_tiles(variants):
+    loss = []
+    for x in fit_models.load([TIMINGS]):
+        if x["what"] == "rows":
+            times = dict(x["us"])
+            loss.append(times[variants[sd.kernel_name(_desc(x["k"]), x["p"])]] / min(times.values()))
+    mean, worst = _quality(loss)
+    assert len(loss) > 1000 and mean < 0.02 and worst < 0.22, (mean, worst)
+
+
+def test_two_tile_widths_cost_what_their_launch_makes():
+    """150 tiles of 224x256 all run at full width in the launch with two tile widths: it is the kernel of the
+    plain tiles there (59-60 us and 51 us for these layers) and must not be preferred as a cheaper one."""
+    for geom in [(2, 200, 336, 256, 256, 3, 3, (2, 2), (1, 1)), (2, 100, 168, 256, 256, 3, 3, (1, 1), (2, 2), (2, 2))]:
+        assert "tail128" not in sd.kernel_name(sd.make_desc(*geom), sd.FWD)
+    # 600 tiles: two rounds at full width, the third in halves
+    d = sd.make_desc(2, 200, 336, 512, 256, 1, 1, (1, 1), (0, 0))
+    assert "tail128" in sd.kernel_name(d, sd.FWD)

@@ -393,29 +393,28 @@ static const WgradVariant& wgrad_variant(int v)
 }
 
 // Time of a weight gradient as a function of the tile variant and the number of pixel ranges, from
-// which both are chosen.  A workgroup takes `step` us per 64-pixel step while it has a compute
-// unit to itself, and `shared` times their number when several live on one; launch, set-up, first
-// loads and drain are `fixed`; the kernel cannot be faster than the operands once at `hbm` MB/us, and
-// the partial sums leave at `store` MB/us.  The constants are least-squares fits to 5400
-// kernel-trace timings of 170 layers of random size (0.5 us to 200 us, 8 to 2048 channels, 1x1 and
-// 3x3, strides 1 and 2, 200 to 170 000 pixels); the fit's scatter is 7-12 %, and the choice made
-// with it is 3 % slower than the fastest (variant, ranges) pair of every layer on average (10 % at the 90th
-// percentile).  Fixed rules by channel counts, with one range count for all, lost 48 %: the time has
-// a narrow minimum between too few workgroups and the traffic of too many partial sums.
-struct WgradCost { float fixed, step, shared, store, hbm; };
+// which both are chosen.  A workgroup takes `step` us per 64-pixel step (where several share a compute unit
+// `shared` us times their number, if that is more), and `tile` us per tile besides; launch and first loads are
+// `fixed`; the operands move at `hbm` MB/us meanwhile, and the sums leave at `store` MB/us after the loop.
+// The constants are fits like those of kRowModels (fit_models.py, same bounds).  The time has a narrow
+// minimum between too few workgroups and the traffic of too many partial sums: rules by channel counts
+// with one number of ranges for all lost 48 % over layers of random size.  The choice is 1.7 % slower than
+// the fastest measured (variant, ranges) pair on layers left out of the fit (5.8 % at the 90th percentile), and 1.6 % (5.4 %)
+// on 543 detector layers on images of random size.
+struct WgradCost { float fixed, step, shared, tile, store, hbm; };
 struct WgradModel { int variant, per_cu; WgradCost linear, gather; };   // per_cu: workgroups a compute unit holds
 static const WgradModel kWgradModels[] = {
-    {107, 3, {3.37f, 0.292f, 0.246f, 2.86f, 7.63f}, {4.52f, 0.408f, 0.265f, 3.44f, 5.00f}},
-    {118, 3, {3.49f, 0.294f, 0.244f, 2.95f, 7.98f}, {4.96f, 0.390f, 0.245f, 3.78f, 5.00f}},
-    {108, 2, {3.97f, 0.425f, 0.332f, 2.62f, 8.30f}, {5.29f, 0.568f, 0.383f, 3.45f, 5.00f}},
-    {100, 2, {5.78f, 0.588f, 0.450f, 3.67f, 7.16f}, {7.29f, 0.772f, 0.467f, 4.39f, 7.37f}},
-    {119, 2, {5.80f, 0.597f, 0.449f, 4.04f, 7.14f}, {8.19f, 0.732f, 0.456f, 5.55f, 6.77f}},
-    {112, 1, {4.54f, 0.550f, 0.423f, 2.71f, 7.06f}, {6.05f, 0.600f, 0.435f, 3.31f, 5.26f}},
-    {116, 1, {4.73f, 0.524f, 0.068f, 2.80f, 6.95f}, {6.60f, 0.567f, 0.622f, 3.57f, 5.00f}},
-    {117, 1, {6.56f, 0.895f, 0.552f, 4.01f, 5.73f}, {8.80f, 0.904f, 0.604f, 4.79f, 7.04f}},
-    {114, 1, {7.97f, 1.620f, 1.523f, 6.55f, 5.42f}, {12.7f, 1.560f, 0.592f, 12.2f, 9.50f}},
+    {104, 2, {3.533f, 0.308f, 0.454f, 0.000f, 2.687f, 5.322f}, {3.884f, 0.635f, 0.407f, 0.000f, 2.898f, 2.848f}},
+    {107, 3, {2.567f, 0.353f, 0.315f, 0.000f, 2.477f, 4.303f}, {3.332f, 0.419f, 0.265f, 0.000f, 2.861f, 2.784f}},
+    {108, 2, {3.570f, 0.450f, 0.405f, 0.000f, 2.687f, 5.027f}, {3.265f, 0.565f, 0.367f, 0.727f, 2.949f, 2.964f}},
+    {112, 1, {3.033f, 0.552f, 0.000f, 1.396f, 2.601f, 5.398f}, {2.840f, 0.606f, 0.000f, 1.886f, 3.402f, 2.693f}},
+    {114, 1, {3.142f, 1.384f, 0.000f, 6.116f, 4.659f, 3.689f}, {4.125f, 1.480f, 0.000f, 4.575f, 5.874f, 2.764f}},
+    {116, 1, {3.225f, 0.543f, 0.000f, 1.198f, 2.585f, 5.313f}, {2.864f, 0.636f, 0.000f, 1.874f, 3.392f, 2.941f}},
+    {117, 1, {3.594f, 0.882f, 0.000f, 2.632f, 3.268f, 4.750f}, {3.552f, 0.937f, 0.000f, 2.688f, 4.472f, 2.999f}},
+    {118, 3, {2.596f, 0.356f, 0.314f, 0.000f, 2.388f, 4.328f}, {3.294f, 0.414f, 0.262f, 0.000f, 2.727f, 2.761f}},
+    {119, 2, {4.372f, 0.814f, 0.542f, 0.000f, 3.135f, 5.105f}, {4.200f, 0.797f, 0.476f, 1.083f, 3.738f, 3.066f}},
 };
-constexpr float kReduceFixed = 5.1f, kReduceRate = 9.6f;    // us with the gap between the kernels, MB/us
+constexpr float kReduceFixed = 2.5f, kReduceRate = 6.0f;    // us with the gap between the kernels, MB/us
 
 static long wgrad_steps(const Geom& g) { return ((long)g.N * g.Ho * g.Wo + 63) / 64; }
 static long wgrad_tiles(const Geom& g, const WgradVariant& v)
@@ -447,19 +446,14 @@ struct WgradChoice { int variant, splits; float us; };
 static float wgrad_us(const Geom& g, const WgradModel& m, long tiles, long total_steps, long splits)
 {
     const WgradCost& c = (g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0) ? m.linear : m.gather;
-    const long steps = (total_steps + splits - 1) / splits, n = tiles * splits, per_round = 256 * m.per_cu;
-    const float alone = c.step, full = m.per_cu * c.shared;
-    float t = (float)(n / per_round) * steps * (full > alone ? full : alone);
-    if (const long rest = n % per_round) {
-        const float crowd = (float)((rest + 255) / 256) * c.shared;
-        t += steps * (crowd > alone ? crowd : alone);
-    }
+    const float steps = (float)((total_steps + splits - 1) / splits);
+    auto round = [&](long n) { return steps * (n * c.shared > c.step ? n * c.shared : c.step) + c.tile; };
+    const long fullest = (tiles * splits + 255) / 256, rest = fullest % m.per_cu;
+    const float work = (float)(fullest / m.per_cu) * round(m.per_cu) + (rest ? round(rest) : 0.f);
     const float dw = 4e-6f * g.K * g.R * g.S * g.C;         // MB
     const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 ? g.sh * g.sw : 1);
-    const float operands = (x + 2e-6f * g.N * g.Ho * g.Wo * g.K + dw) / c.hbm;
-    if (t < operands) t = operands;
-    t += c.fixed;
-    if (splits > 1) t += splits * dw * (1.f / c.store + 1.f / kReduceRate) + kReduceFixed;
+    float t = c.fixed + both(work, (x + 2e-6f * g.N * g.Ho * g.Wo * g.K) / c.hbm) + splits * dw / c.store;
+    if (splits > 1) t += splits * dw / kReduceRate + kReduceFixed;
     return t;
 }
 
@@ -485,32 +479,34 @@ static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial
     }
 }
 
-// Tile variant and pixel ranges.  A geometry of the measured table keeps its tile variant at every
-// batch size near the measured one; the ranges chosen for that one are scaled with the batch.
+// Tile variant and pixel ranges.  A geometry of the measured table takes the variant from there, and the
+// ranges scaled with the batch: the entry's own or, where it has none, the model's at the measured batch.
 static WgradChoice choose_wgrad(const Geom& g, size_t partial_limit)
 {
     const int fv = forced_wgrad_variant();
     const bool forced = (fv >= 0 && fv < kNumWgradVariants) || (fv >= 100 && fv < 100 + kNumWgradDmaVariants);
     int only = forced ? fv : -1;
     Geom measured = g;
+    WgradChoice c{-1, 0, 0.f};
     if (!byte_offsets_fit_31_bits(g)) only = g.K <= 64 ? 1 : 0;
     else if (!forced)
-        if (const TunedEntry* e = tuned_lookup(g, SDCONV_WGRAD)) { only = e->variant; measured.N = e->N; }
-    WgradChoice c{-1, 1, 0.f};
-    for (const WgradModel& m : kWgradModels)
-        if (only < 0 || m.variant == only) wgrad_best_splits(measured, m, partial_limit, &c);
-    if (g.N != measured.N) {
-        c.splits = (2 * c.splits * g.N + measured.N) / (2 * measured.N);
-        const size_t dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
-        if (c.splits * dw_bytes > partial_limit) c.splits = (int)(partial_limit / dw_bytes);
-        if (c.splits < 1) c.splits = 1;
-    }
+        if (const TunedEntry* e = tuned_lookup(g, SDCONV_WGRAD)) {
+            only = e->variant;
+            measured.N = e->N;
+            if (e->splits > 0) c = WgradChoice{only, e->splits, 0.f};
+        }
+    if (c.variant < 0)
+        for (const WgradModel& m : kWgradModels)
+            if (only < 0 || m.variant == only) wgrad_best_splits(measured, m, partial_limit, &c);
     if (c.variant < 0) {    // a variant without a model: enough workgroups to fill the chip
-        const long tiles = wgrad_tiles(g, wgrad_variant(only)), cap = wgrad_steps(g) / 4;
-        long want = (384 + tiles - 1) / tiles;
-        if (want > cap) want = cap;
-        c = WgradChoice{only, (int)(want < 1 ? 1 : want), 0.f};
+        const long tiles = wgrad_tiles(g, wgrad_variant(only)), most = wgrad_steps(g) / 4;
+        const long want = (384 + tiles - 1) / tiles;
+        c = WgradChoice{only, (int)(want < most ? want : most), 0.f};
     }
+    if (g.N != measured.N) c.splits = (2 * c.splits * g.N + measured.N) / (2 * measured.N);
+    const size_t dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
+    if (c.splits > 1 && c.splits * dw_bytes > partial_limit) c.splits = (int)(partial_limit / dw_bytes);
+    if (c.splits < 1) c.splits = 1;
     if (const int fs = forced_wgrad_splits(); fs > 0) {
         const long cap = wgrad_steps(g) / 2;
         c.splits = fs < cap ? fs : (cap < 1 ? 1 : (int)cap);

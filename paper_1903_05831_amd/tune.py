@@ -5,7 +5,7 @@ GPU at hand and writes the winners to csrc/tuned_table.inc (rebuild the library 
 
 With SDCONV_TUNE=1 in the environment before the library's first call (set below) the dispatcher
 reads SDCONV_IGEMM_VARIANT / SDCONV_WGRAD_VARIANT / SDCONV_WGRAD_SPLITS on every call, which is
-how this script forces a variant.  Unlisted geometries keep using the built-in heuristics.
+how this script forces a variant.  Unlisted geometries use the time models of dispatch.hip (fit_models.py).
 
 In a training step every layer finds its inputs in HBM, not in the 256 MB Infinity Cache: the
 timed calls therefore rotate over enough copies of the layer's tensors (--cold-mib of
@@ -213,6 +213,7 @@ def main() -> int:
         lines = kept + lines
     with open(args.out, "w") as f:
         f.write("// Written by tune.py on %s: {N,H,W,C,K,R,S,sh,sw,ph,pw,dh,dw, pass, variant, splits}\n"
+                "// splits: pixel ranges of a weight gradient; 0 leaves them to the dispatcher's time model\n"
                 % torch.cuda.get_device_name(0))
         f.write("\n".join(lines) + "\n")
     print("wrote", args.out, len(lines), "entries")

@@ -53,3 +53,32 @@ def test_two_tile_widths_cost_what_their_launch_makes():
     # 600 tiles: two rounds at full width, the third in halves
     d = sd.make_desc(2, 200, 336, 512, 256, 1, 1, (1, 1), (0, 0))
     assert "tail128" in sd.kernel_name(d, sd.FWD)
+
+
+def test_weight_gradient_tiles_and_ranges(variants):
+    loss, unmeasured = [], 0
+    for x in fit_models.load([TIMINGS]):
+        if x["what"] != "wgrad":
+            continue
+        d, times = _desc(x["k"]), dict(x["us"])
+        dw_bytes = 4 * d.K * d.R * d.S * d.C
+        pair = variants[sd.kernel_name(d, sd.WGRAD)], max(1, sd.conv2d_workspace_bytes(d, sd.WGRAD) // dw_bytes)
+        if pair in times:
+            loss.append(times[pair] / min(times.values()))
+        else:
+            unmeasured += 1
+    mean, worst = _quality(loss)
+    assert len(loss) > 390 and unmeasured < 5 and mean < 0.025, (mean, worst, unmeasured)
+    assert worst < 0.16, worst
+
+
+def test_layers_of_the_measured_table_keep_the_measured_ranges():
+    """Entries with a number of pixel ranges: it was measured with that tile variant."""
+    for geom, name, ranges in [((512, 14, 14, 1024, 512, 1, 1, (1, 1), (0, 0)), "256x256x64_8w_s2_hf_m16", 32),
+                               ((512, 7, 7, 2048, 512, 1, 1, (1, 1), (0, 0)), "256x256x32_8w_s3_hf_m16", 12),
+                               ((2, 50, 84, 256, 256, 3, 3, (1, 1), (1, 1)), "128x128x64_4w_s2", 7)]:
+        for batch in (geom[0], geom[0] // 2):
+            d = sd.make_desc(batch, *geom[1:])
+            want = (2 * ranges * batch // geom[0] + 1) // 2
+            assert sd.kernel_name(d, sd.WGRAD) == "wgrad_dma_" + name
+            assert sd.conv2d_workspace_bytes(d, sd.WGRAD) == want * 4 * d.K * d.R * d.S * d.C

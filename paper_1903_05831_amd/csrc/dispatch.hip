@@ -329,10 +329,9 @@ static bool padk_ok(const Geom& g)
     const long kp = (g.K + 7) / 8 * 8, lim = 0x7fffffffL;
     return (long)g.N * g.Ho * g.Wo * kp <= lim && kp * g.R * g.S * g.C <= lim;
 }
-// Of these the pointwise layers with few filters have kernels that need no copies (narrow.hip):
-// wherever they apply they are the faster ones, from 2x13x21 pixels (forward 5.7 us instead of 10.3,
-// data gradient 4.6 / 11.4, weight gradient 9.3 / 10.2) to 2x200x336 (17.6 / 30.0, 17.0 / 35.6, 22.6 / 31.6).
-static bool narrow_ok(const Geom& g) { return padk_ok(g) && narrow_supported(g); }
+// Of these the pointwise layers with few filters have kernels that need no copies, where those are the
+// faster ones (narrow.hip).
+static bool narrow_ok(const Geom& g, int pass) { return padk_ok(g) && narrow_supported(g, pass); }
 static Geom padded_k(const Geom& g) { Geom p = g; p.K = (g.K + 7) / 8 * 8; return p; }
 static size_t padk_filter_bytes(const Geom& gp) { return align256((size_t)gp.K * gp.R * gp.S * gp.C * sizeof(__half)); }
 static size_t padk_act_bytes(const Geom& gp) { return align256((size_t)gp.N * gp.Ho * gp.Wo * gp.K * sizeof(__half)); }
@@ -351,7 +350,7 @@ static const char* padk_name(const char* inner)
 
 Plan plan_fwd(const Geom& g)
 {
-    if (narrow_ok(g)) return Plan{ROUTE_NARROW, 0, 1, 0, "narrow_fwd"};
+    if (narrow_ok(g, SDCONV_FWD)) return Plan{ROUTE_NARROW, 0, 1, 0, "narrow_fwd"};
     if (padk_ok(g)) {
         const Geom gp = padded_k(g);
         const Plan in = plan_fwd(gp);
@@ -366,7 +365,7 @@ Plan plan_fwd(const Geom& g)
 
 Plan plan_dgrad(const Geom& g)
 {
-    if (narrow_ok(g)) return Plan{ROUTE_NARROW, 0, 1, 0, "narrow_dgrad"};
+    if (narrow_ok(g, SDCONV_DGRAD)) return Plan{ROUTE_NARROW, 0, 1, 0, "narrow_dgrad"};
     if (padk_ok(g)) {
         const Geom gp = padded_k(g);
         const Plan in = plan_dgrad(gp);
@@ -517,7 +516,7 @@ static WgradChoice choose_wgrad(const Geom& g, size_t partial_limit)
 // `copies`: bytes of padded operands that the plan's workspace lies behind
 static Plan plan_wgrad_beside(const Geom& g, size_t copies)
 {
-    if (narrow_ok(g))
+    if (narrow_ok(g, SDCONV_WGRAD))
         return Plan{ROUTE_NARROW, 0, narrow_wgrad_ranges(g), align256(narrow_wgrad_partial_bytes(g)), "narrow_wgrad"};
     if (padk_ok(g)) {
         const Geom gp = padded_k(g);

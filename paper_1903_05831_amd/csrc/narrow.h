@@ -4,7 +4,7 @@
 
 namespace sdconv {
 
-bool narrow_supported(const Geom& g);
+bool narrow_supported(const Geom& g, int pass);
 int narrow_wgrad_ranges(const Geom& g);
 size_t narrow_wgrad_partial_bytes(const Geom& g);
 hipError_t launch_narrow_fwd(const Geom& g, const __half* x, const __half* w, __half* y, hipStream_t st, const Epilogue& ep);

@@ -18,17 +18,29 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 
 constexpr int kNarrowThreads = 256, kNarrowWaves = 4;
 constexpr int kNarrowMaxFilters = 64;
-constexpr size_t kNarrowLds = 80 * 1024;        // two workgroups a compute unit
-constexpr int kNarrowBlocks = 1024;             // persistent: four workgroups a compute unit
+constexpr int kNarrowBlocks = 1024;             // persistent: four workgroups a compute unit, at 33 KB of LDS each
 constexpr int kNarrowChunk = 128;               // weight gradient: channels of a wave
 
 static int filter_tiles(const Geom& g) { return (g.K + 15) / 16; }
+static long narrow_pixels(const Geom& g) { return (long)g.N * g.Ho * g.Wo; }
 
-// The filter lies in LDS: 32 bytes a channel and tile of 16 filters, and some padding.
-bool narrow_supported(const Geom& g)
+// Where these kernels are the faster ones, from timings of both routes with 3 to 63 filters, 32 to 1024 channels
+// and 64 to 134 400 pixels.  Forward and data gradient: each workgroup lays the filter out in LDS, 32
+// bytes a channel and tile of 16 filters.  Up to 1024 channels x tiles they take 0.61 and 0.50 of the
+// time on padded copies (380 sizes, 0.21-1.03 of it); above, 1.17 and 1.09 (60 filters, 512 channels, 4200
+// pixels: forward 13.5 us against 10.6, data gradient 11.8 against 9.7).  Weight gradient: dy is read in
+// 2-byte loads, for each 128 channels again.  One tile 0.79 (0.59-0.96), two tiles 0.93 up to 128 channels and
+// 1.01 above, more tiles 1.22 (60 filters, 512 channels: 15.5 us against 12.1); with two tiles a few
+// hundred pixels make two ranges and a reduction where the padded route has one (1.11-1.17).
+bool narrow_supported(const Geom& g, int pass)
 {
-    return g.R == 1 && g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0 && g.C % 8 == 0 &&
-           g.K <= kNarrowMaxFilters && (size_t)filter_tiles(g) * 32 * (g.C + 64) <= kNarrowLds;
+    const int tiles = filter_tiles(g);
+    if (g.R != 1 || g.S != 1 || g.sh != 1 || g.sw != 1 || g.ph != 0 || g.pw != 0 || g.C % 8 != 0 ||
+        g.K > kNarrowMaxFilters)
+        return false;
+    if (pass != SDCONV_WGRAD) return tiles * g.C <= 1024;
+    const long pixels = narrow_pixels(g);
+    return tiles == 1 || (tiles == 2 && g.C <= 128 && (pixels <= 256 || pixels >= 1024));
 }
 
 // Four values of one row of a [rows][K] tensor from column k on, zeros past its end.  Rows start at
@@ -302,7 +314,6 @@ __global__ __launch_bounds__(kNarrowThreads) void narrow_wgrad_kernel(
     }
 }
 
-static long narrow_pixels(const Geom& g) { return (long)g.N * g.Ho * g.Wo; }
 static int narrow_chunks(const Geom& g) { return (g.C + kNarrowChunk - 1) / kNarrowChunk; }
 
 // Steps of 32 pixels that each wave takes: as few as make at most 512 workgroups (two a compute unit,
@@ -335,33 +346,21 @@ static unsigned narrow_grid(const Geom& g)
     return (unsigned)(blocks < kNarrowBlocks ? blocks : kNarrowBlocks);
 }
 
-template <typename Kernel, typename... Args>
-static hipError_t launch_narrow(Kernel kernel, std::atomic<bool>& configured, const Geom& g, size_t lds, hipStream_t st, Args... args)
-{
-    if (!configured.load(std::memory_order_acquire)) {      // a second thread may repeat it, harmlessly
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kNarrowLds);
-        if (e != hipSuccess) return e;
-        configured.store(true, std::memory_order_release);
-    }
-    hipLaunchKernelGGL(kernel, dim3(narrow_grid(g)), dim3(kNarrowThreads), lds, st, args...);
-    return hipGetLastError();
-}
-
 template <int KT>
 static hipError_t fwd_tiles(const Geom& g, const _Float16* x, const _Float16* w, _Float16* y, hipStream_t st, const Epilogue& ep)
 {
-    static std::atomic<bool> configured{false};
-    return launch_narrow(narrow_fwd_kernel<KT>, configured, g, (size_t)KT * 32 * (g.C + 8), st, x, w, y,
-                         narrow_pixels(g), g.C, g.K, ep);
+    hipLaunchKernelGGL(narrow_fwd_kernel<KT>, dim3(narrow_grid(g)), dim3(kNarrowThreads), (size_t)KT * 32 * (g.C + 8), st,
+                       x, w, y, narrow_pixels(g), g.C, g.K, ep);
+    return hipGetLastError();
 }
 
 template <int KT>
 static hipError_t dgrad_tiles(const Geom& g, const _Float16* dy, const _Float16* w, _Float16* dx, hipStream_t st, const Epilogue& ep)
 {
-    static std::atomic<bool> configured[2] = {{false}, {false}};
     const size_t lds = (size_t)((g.C + 63) / 64) * 4 * KT * 64 * sizeof(half4v);
-    return ep.any() ? launch_narrow(narrow_dgrad_kernel<KT, true>, configured[1], g, lds, st, dy, w, dx, narrow_pixels(g), g.C, g.K, ep)
-                    : launch_narrow(narrow_dgrad_kernel<KT, false>, configured[0], g, lds, st, dy, w, dx, narrow_pixels(g), g.C, g.K, ep);
+    auto* kernel = ep.any() ? narrow_dgrad_kernel<KT, true> : narrow_dgrad_kernel<KT, false>;
+    hipLaunchKernelGGL(kernel, dim3(narrow_grid(g)), dim3(kNarrowThreads), lds, st, dy, w, dx, narrow_pixels(g), g.C, g.K, ep);
+    return hipGetLastError();
 }
 
 hipError_t launch_narrow_fwd(const Geom& g, const __half* x, const __half* w, __half* y, hipStream_t st, const Epilogue& ep)
@@ -399,8 +398,6 @@ hipError_t launch_narrow_wgrad(const Geom& g, const __half* x, const __half* dy,
     switch (filter_tiles(g)) {
         case 1: hipLaunchKernelGGL(narrow_wgrad_kernel<1>, grid, block, 0, st, xf, gf, out, P, g.C, g.K, chunks, steps); break;
         case 2: hipLaunchKernelGGL(narrow_wgrad_kernel<2>, grid, block, 0, st, xf, gf, out, P, g.C, g.K, chunks, steps); break;
-        case 3: hipLaunchKernelGGL(narrow_wgrad_kernel<3>, grid, block, 0, st, xf, gf, out, P, g.C, g.K, chunks, steps); break;
-        case 4: hipLaunchKernelGGL(narrow_wgrad_kernel<4>, grid, block, 0, st, xf, gf, out, P, g.C, g.K, chunks, steps); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

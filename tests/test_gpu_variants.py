@@ -141,9 +141,10 @@ def test_wgrad_kernel_variants(variant):
                 check_all_passes(d, x, w, g, f"wgrad{variant}s{splits}{case}")
 
 
-# pointwise layers with few filters: pixel counts around the 16 of a wave, the 64 of a workgroup and
-# the weight gradient's 256 of a pixel range; channels below, at and past one 256-channel load and one
-# 128-channel tile; filters around each multiple of 16, odd and in fours; the longest filter accepted
+# pointwise layers with few filters: pixel counts around the 16 of a wave, the 64 of a workgroup, the
+# weight gradient's 256 of a pixel range, and past the 65 536 that the persistent workgroups take in one
+# turn; channels below, at and past one 256-channel load and one 128-channel tile; filters around each
+# multiple of 16, odd and in fours; the longest filters accepted, and longer ones on padded copies
 NARROW_SHAPES = [
     # N  H   W   C     K
     (1, 1, 1, 8, 1),
@@ -158,7 +159,22 @@ NARROW_SHAPES = [
     (1, 25, 42, 512, 60),
     (1, 9, 7, 576, 63),
     (3, 50, 84, 256, 3),
+    (1, 9, 7, 256, 63),
+    (1, 5, 7, 1024, 12),
+    (1, 7, 9, 512, 30),
+    (1, 16, 16, 128, 31),
+    (1, 33, 32, 72, 20),
+    (1, 257, 259, 64, 15),
+    (1, 257, 259, 64, 28),
+    (1, 257, 259, 64, 47),
+    (1, 257, 259, 64, 60),
 ]
+
+
+def _narrow_passes(pixels, C, K):
+    tiles = -(-K // 16)
+    wgrad = tiles == 1 or (tiles == 2 and C <= 128 and not 256 < pixels < 1024)
+    return [tiles * C <= 1024, tiles * C <= 1024, wgrad]
 
 
 @pytest.mark.parametrize("shape", NARROW_SHAPES)
@@ -166,7 +182,8 @@ def test_narrow_pointwise_kernels(shape):
     N, H, W, C, K = shape
     say(f"narrow pointwise {shape}")
     d, x, w, g = _rand_case(N, H, W, C, K, 1, 1, (1, 1), (0, 0), (1, 1), seed=C * 64 + K)
-    assert [sd.kernel_name(d, p) for p in (sd.FWD, sd.DGRAD, sd.WGRAD)] == ["narrow_fwd", "narrow_dgrad", "narrow_wgrad"]
+    for p, name, narrow in zip((sd.FWD, sd.DGRAD, sd.WGRAD), ("fwd", "dgrad", "wgrad"), _narrow_passes(N * H * W, C, K)):
+        assert sd.kernel_name(d, p) == "narrow_" + name if narrow else sd.kernel_name(d, p).startswith("padk+")
     check_all_passes(d, x, w, g, f"narrow{shape}")
     check_fused(d, x, w, g, f"narrow_fused{shape}")
 
@@ -174,13 +191,19 @@ def test_narrow_pointwise_kernels(shape):
 def test_narrow_pointwise_route_borders():
     def names(*geom):
         d = sd.make_desc(*geom)
-        return {sd.kernel_name(d, p).startswith("narrow") for p in (sd.FWD, sd.DGRAD, sd.WGRAD)}
+        return [sd.kernel_name(d, p).startswith("narrow") for p in (sd.FWD, sd.DGRAD, sd.WGRAD)]
     one, zero = (1, 1), (0, 0)
-    assert names(1, 9, 7, 576, 63, 1, 1, one, zero, one) == {True}
-    for geom in [(1, 9, 7, 584, 63, 1, 1, one, zero, one),      # the filter does not fit in LDS
+    assert names(1, 9, 7, 256, 63, 1, 1, one, zero, one) == [True, True, False]
+    assert names(1, 9, 7, 1024, 15, 1, 1, one, zero, one) == [True, True, True]
+    assert names(1, 16, 16, 128, 31, 1, 1, one, zero, one) == [True, True, True]
+    assert names(1, 1, 257, 128, 31, 1, 1, one, zero, one) == [True, True, False]
+    assert names(1, 32, 32, 128, 31, 1, 1, one, zero, one) == [True, True, True]
+    assert names(1, 32, 32, 136, 31, 1, 1, one, zero, one) == [True, True, False]
+    assert names(1, 9, 7, 1032, 15, 1, 1, one, zero, one) == [False, False, True]
+    for geom in [(1, 9, 7, 264, 63, 1, 1, one, zero, one),      # faster on padded copies
                  (1, 9, 7, 64, 65, 1, 1, one, zero, one),       # too many filters
                  (1, 9, 7, 64, 16, 1, 1, one, zero, one),       # a multiple of 8
                  (1, 9, 7, 60, 12, 1, 1, one, zero, one),       # channels not in eights
                  (1, 9, 7, 64, 12, 1, 1, (2, 2), zero, one), (1, 9, 7, 64, 12, 1, 1, one, one, one),
                  (1, 9, 7, 64, 12, 3, 3, one, one, one)]:
-        assert names(*geom) == {False}, geom
+        assert names(*geom) == [False] * 3, geom

@@ -408,6 +408,7 @@ static const WgradModel kWgradModels[] = {
     {108, 2, {3.570f, 0.450f, 0.405f, 0.000f, 2.687f, 5.027f}, {3.265f, 0.565f, 0.367f, 0.727f, 2.949f, 2.964f}},
     {112, 1, {3.033f, 0.552f, 0.000f, 1.396f, 2.601f, 5.398f}, {2.840f, 0.606f, 0.000f, 1.886f, 3.402f, 2.693f}},
     {114, 1, {3.142f, 1.384f, 0.000f, 6.116f, 4.659f, 3.689f}, {4.125f, 1.480f, 0.000f, 4.575f, 5.874f, 2.764f}},
+    {115, 1, {3.475f, 1.417f, 0.000f, 5.879f, 5.044f, 3.987f}, {4.493f, 1.603f, 0.000f, 4.101f, 6.100f, 3.222f}},
     {116, 1, {3.225f, 0.543f, 0.000f, 1.198f, 2.585f, 5.313f}, {2.864f, 0.636f, 0.000f, 1.874f, 3.392f, 2.941f}},
     {117, 1, {3.594f, 0.882f, 0.000f, 2.632f, 3.268f, 4.750f}, {3.552f, 0.937f, 0.000f, 2.688f, 4.472f, 2.999f}},
     {118, 3, {2.596f, 0.356f, 0.314f, 0.000f, 2.388f, 4.328f}, {3.294f, 0.414f, 0.262f, 0.000f, 2.727f, 2.761f}},
@@ -425,7 +426,7 @@ static long wgrad_tiles(const Geom& g, const WgradVariant& v)
 // workspace.  conv2d_wgrad_static_scratch has SDCONV_STATIC_SCRATCH_BYTES for both and runs the same plan, so the
 // partial sums stay within what is left of it: every layer whose copies fit is served.  Layers that need
 // more for 384 workgroups of the plain tile may have that much: one range or two would leave most of the
-// chip idle for long (3x3 1024 -> 1024 on 8x56x56: 536 us with the 75 MB of two ranges, 447 with three).
+// chip idle for long (3x3 1024 -> 1024 on 8x56x56: 562 us with the 75 MB of two ranges, 465 with three).
 static size_t wgrad_partial_limit(const Geom& g, size_t copies)
 {
     const long pixels = (long)g.N * g.Ho * g.Wo, steps = wgrad_steps(g);
@@ -478,34 +479,34 @@ static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial
     }
 }
 
-// Tile variant and pixel ranges.  A geometry of the measured table takes the variant from there, and the
-// ranges scaled with the batch: the entry's own or, where it has none, the model's at the measured batch.
+// Tile variant and pixel ranges.  A geometry of the measured table takes the variant from there and, at the
+// measured batch, the entry's ranges if it has any; else the model's for that variant, or, for a
+// variant without a model, the entry's scaled with the batch.
 static WgradChoice choose_wgrad(const Geom& g, size_t partial_limit)
 {
     const int fv = forced_wgrad_variant();
     const bool forced = (fv >= 0 && fv < kNumWgradVariants) || (fv >= 100 && fv < 100 + kNumWgradDmaVariants);
     int only = forced ? fv : -1;
-    Geom measured = g;
-    WgradChoice c{-1, 0, 0.f};
+    const TunedEntry* e = nullptr;
     if (!byte_offsets_fit_31_bits(g)) only = g.K <= 64 ? 1 : 0;
-    else if (!forced)
-        if (const TunedEntry* e = tuned_lookup(g, SDCONV_WGRAD)) {
-            only = e->variant;
-            measured.N = e->N;
-            if (e->splits > 0) c = WgradChoice{only, e->splits, 0.f};
-        }
-    if (c.variant < 0)
+    else if (!forced && (e = tuned_lookup(g, SDCONV_WGRAD))) only = e->variant;
+    WgradChoice c{-1, 1, 0.f};
+    if (!(e && e->splits > 0 && e->N == g.N))
         for (const WgradModel& m : kWgradModels)
-            if (only < 0 || m.variant == only) wgrad_best_splits(measured, m, partial_limit, &c);
-    if (c.variant < 0) {    // a variant without a model: enough workgroups to fill the chip
-        const long tiles = wgrad_tiles(g, wgrad_variant(only)), most = wgrad_steps(g) / 4;
-        const long want = (384 + tiles - 1) / tiles;
-        c = WgradChoice{only, (int)(want < most ? want : most), 0.f};
+            if (only < 0 || m.variant == only) wgrad_best_splits(g, m, partial_limit, &c);
+    if (c.variant < 0) {
+        long want;
+        if (e) {
+            want = (2L * e->splits * g.N + e->N) / (2 * e->N);
+        } else {            // forced, or indexed by elements: enough workgroups to fill the chip
+            const long tiles = wgrad_tiles(g, wgrad_variant(only)), most = wgrad_steps(g) / 4;
+            want = (384 + tiles - 1) / tiles;
+            if (want > most) want = most;
+        }
+        const size_t dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
+        if (want > 1 && want * dw_bytes > partial_limit) want = (long)(partial_limit / dw_bytes);
+        c = WgradChoice{only, (int)(want < 1 ? 1 : want), 0.f};
     }
-    if (g.N != measured.N) c.splits = (2 * c.splits * g.N + measured.N) / (2 * measured.N);
-    const size_t dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
-    if (c.splits > 1 && c.splits * dw_bytes > partial_limit) c.splits = (int)(partial_limit / dw_bytes);
-    if (c.splits < 1) c.splits = 1;
     if (const int fs = forced_wgrad_splits(); fs > 0) {
         const long cap = wgrad_steps(g) / 2;
         c.splits = fs < cap ? fs : (cap < 1 ? 1 : (int)cap);

@@ -1,12 +1,12 @@
 """Timings of the kernel variants on layers of random size, and the constants of the time models in
-csrc/dispatch.hip fitted to them.
+csrc/dispatch.hip and csrc/conv_f32.hip fitted to them.
 
     python -m paper_1903_05831_amd.fit_models measure --what rows|wgrad|f32 --seed 1 --seconds 100 --out t.jsonl.gz
     python -m paper_1903_05831_amd.fit_models fit --timings profiles/layer_timings.jsonl.gz
 
 ``measure`` needs the GPU: every variant (and, for the weight gradient, every sensible number of
 pixel ranges) of each layer, as HIP graphs of many calls on tensors that do not fit the caches, the best
-of three runs, variants in turn.  ``fit`` runs anywhere.  It prints the constants of kRowModels and kWgradModels and,
+of three runs, variants in turn.  ``fit`` runs anywhere.  It prints the constants of kRowModels, kWgradModels and kF32Tiles and,
 by threefold cross-validation over the layers, how much slower than the fastest measured variant the model's
 choice is on layers that it was not fitted to.  Constants are bounded by what the hardware can do: a step
 takes no less than the matrix instructions alone (2.06 PFLOP/s measured over 256 compute units),
@@ -69,7 +69,7 @@ ROW_VARIANTS = [101, 105, 107, 112, 113, 300, 303, 310, 311, 314, 316, 317, 318,
                 417, 426, 427, 433, 435]
 # variants with a row in the models: the others add less than 0.1 % each
 ROW_MODELS = [101, 107, 112, 300, 303, 310, 311, 314, 316, 318, 319, 321, 322, 323, 417, 427, 433, 435]
-WGRAD_MODELS = [104, 107, 108, 112, 114, 116, 117, 118, 119]
+WGRAD_MODELS = [104, 107, 108, 112, 114, 115, 116, 117, 118, 119]
 ONE_SLAB = {426, 427, 433}          # one patch buffer: 64 contraction channels only
 WGRAD_VARIANTS = [100, 104, 107, 108, 109, 112, 113, 114, 115, 116, 117, 118, 119, 120]
 WORKGROUPS = (40, 64, 96, 128, 192, 256, 320, 384, 512, 768, 1024)
@@ -180,6 +180,7 @@ def measure(what: str, seed: int, seconds: float, path: str) -> None:
 
 # ---- the models, as in csrc/dispatch.hip -----------------------------------------------------------
 
+F32_MATRIX = 157.3e6                # flop/us, the fp32 matrix peak
 MATRIX, STREAM = 2.06e9, 6.1        # flop/us over the chip with matrix instructions alone; MB/us
 TILES = {101: (128, 128), 105: (256, 128), 107: (128, 64), 112: (128, 64), 113: (128, 64), 300: (128, 128),
          303: (256, 128), 310: (224, 256), 311: (256, 256), 314: (256, 128), 316: (224, 128), 317: (64, 64),
@@ -202,13 +203,13 @@ def kind(k, p):
 
 
 def tile_classes(k, p, v):
-    """[(tiles, 64-channel steps of each)] of the pass, in the order of their launch."""
+    """[(tiles, 64-channel steps of each)] of the pass, in the order of their launch ("f32": taps of each)."""
     N, H, W, C, K, R, s, pad, dil = k
     cs, cd = (K, C) if p else (C, K)
     hd, wd = (H, W) if p else out_hw(k)
-    bk = 32 if v < 300 else 64
-    slabs = -(-cs // bk) * bk / 64
-    if v >= 400:
+    bk = 32 if v == "f32" or v < 300 else 64
+    slabs = 1 if v == "f32" else -(-cs // bk) * bk / 64
+    if v in PATCHES:
         th, tw, bn = PATCHES[v]
         return [(N * -(-hd // th) * -(-wd // tw) * -(-cd // bn), R * R * slabs)]
     bm, bn = TILES[v]
@@ -309,6 +310,24 @@ def wgrad_us(models, k, v, ranges):
     return t + (ranges * dw / REDUCE_RATE + REDUCE_FIXED if ranges > 1 else 0.0)
 
 
+F32_TILES = [(128, 128, 2), (128, 64, 3), (96, 64, 3), (64, 64, 4), (32, 64, 6), (32, 32, 5)]     # and a unit's workgroups
+
+
+def f32_us(models, k, p, tile):
+    step, shared, per_tile, fixed = models[tile]
+    bm, bn, per_cu = F32_TILES[tile]
+    TILES["f32"] = bm, bn
+    chunks = -(-(k[4] if p else k[3]) // 32)        # 32 contraction floats a step
+    busy = [(n, steps) for n, steps in tile_classes(k, p, "f32") if steps]
+    tiles = sum(n for n, _ in busy)
+    if not tiles:
+        return fixed
+    steps = sum(n * taps for n, taps in busy) / tiles * chunks
+    full, rest = divmod(-(-tiles // 256), per_cu)
+    t = full * (steps * max(step, per_cu * shared) + per_tile)
+    return fixed + t + (steps * max(step, rest * shared) + per_tile if rest else 0.0)
+
+
 # ---- the fits --------------------------------------------------------------------------------------
 
 def least_squares_log(predict, samples, lo, hi, start):
@@ -368,6 +387,21 @@ def fit_wgrad(rows):
     return models
 
 
+def fit_f32(rows):
+    models = {}
+    for i, (bm, bn, per_cu) in enumerate(F32_TILES):
+        least = 2.0 * bm * bn * 32 * 256 / F32_MATRIX
+        samples = [(tuple(x["k"]), x["p"], dict(x["us"])[i]) for x in rows]
+        models[i] = least_squares_log(lambda th, s: f32_us({i: th}, s[0], s[1], i), samples,
+                                      [least, least, 0.0, 0.5], [6 * least, 6 * least, 10.0, 10.0],
+                                      [1.3 * least, 1.2 * least, 2.0, 2.0])
+    return models
+
+
+def f32_choice(models, x):
+    return min(range(len(F32_TILES)), key=lambda i: f32_us(models, x["k"], x["p"], i))
+
+
 def row_choice(models, x):
     times = dict(x["us"])
     return min((t, v) for v in times if (t := row_us(models, x["k"], x["p"], v)) is not None)[1]
@@ -413,10 +447,11 @@ def load(paths):
 
 def fit(paths, cross_validate):
     rows = load(paths)
-    parts = {what: [x for x in rows if x["what"] == what] for what in ("rows", "wgrad")}
+    parts = {what: [x for x in rows if x["what"] == what] for what in ("rows", "wgrad", "f32")}
     if cross_validate:
         report("rows", held_out(parts["rows"], fit_rows, row_choice))
         report("wgrad", held_out(parts["wgrad"], fit_wgrad, wgrad_choice))
+        report("f32", held_out(parts["f32"], fit_f32, f32_choice))
 
     def cost(c):
         return "{}" if c is None else "{" + ", ".join(f"{t:.3f}f" for t in c) + "}"
@@ -426,6 +461,11 @@ def fit(paths, cross_validate):
     models = fit_wgrad(parts["wgrad"])
     for v in WGRAD_MODELS:
         print(f"    {{{v}, {WGRAD_TILES[v][2]}, " + ", ".join(cost(models[v, c]) for c in range(2)) + "},")
+
+
+    models = fit_f32(parts["f32"])
+    for i, (bm, bn, per_cu) in enumerate(F32_TILES):
+        print(f"    {{{bm}, {bn}, {per_cu}, {cost(models[i])[1:-1]}, ...}},")
 
 
 def main() -> int:

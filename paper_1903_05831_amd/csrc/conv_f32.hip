@@ -503,11 +503,12 @@ static hipError_t launch_f32_variant(const F32Params& P, hipStream_t st)
 
 // Tiles, and the time each takes: us per step and tile where a tile has a compute unit to itself (`step`) or
 // several share one (`shared` each, at most `per_cu` at a time), us per tile besides, launch
-// and first loads.  Fits to 148 passes (74 layers of res2-res5, 40x60 to 200x336 pixels, both passes),
-// scatter 5-6 %.  A 128x128 tile reaches 77 % of the fp32 matrix peak beside another and 32x32 only 48 %
-// (more LDS reads and loads per product), but small layers have too few large tiles for 256 compute
-// units: the choice is 0.9 % slower than the fastest tile on average (4 % at the 90th percentile),
-// where the evenest spread of 128x128, 128x64 and 64x64 tiles was 19 % slower.
+// and first loads.  Fits to the fp32 timings in profiles/layer_timings.jsonl.gz (fit_models.py: 926 passes of
+// 463 layers of random size, 200 to 150 000 pixels, 8 to 2048 channels).  A 128x128 tile reaches 74 % of
+// the fp32 matrix peak beside another and 32x32 only 48 % (more LDS reads and loads per product), but
+// small layers have too few large tiles for 256 compute units: on layers left out of the fit the choice is
+// 0.8 % slower than the fastest tile (2.4 % at the 90th percentile), where the evenest spread of 128x128,
+// 128x64 and 64x64 tiles is 21 % slower (63 %).
 struct F32Tile {
     int bm, bn, per_cu;
     float step, shared, tile, fixed;
@@ -515,12 +516,12 @@ struct F32Tile {
 };
 #define F32_TILE(BM, BN, WGM, WGN, WGK) {launch_f32_variant<0, BM, BN, WGM, WGN, WGK>, launch_f32_variant<1, BM, BN, WGM, WGN, WGK>}
 static const F32Tile kF32Tiles[] = {
-    {128, 128, 2, 2.468f, 2.209f, 5.06f, 0.88f, F32_TILE(128, 128, 2, 2, 1)},
-    {128, 64, 3, 1.485f, 1.229f, 3.44f, 1.83f, F32_TILE(128, 64, 2, 2, 1)},
-    {96, 64, 3, 1.207f, 0.967f, 3.30f, 2.13f, F32_TILE(96, 64, 1, 2, 2)},
-    {64, 64, 4, 0.903f, 0.673f, 1.31f, 3.69f, F32_TILE(64, 64, 2, 2, 1)},
-    {32, 64, 6, 0.518f, 0.366f, 1.73f, 3.30f, F32_TILE(32, 64, 1, 2, 2)},
-    {32, 32, 5, 0.373f, 0.220f, 1.46f, 3.49f, F32_TILE(32, 32, 1, 1, 4)},
+    {128, 128, 2, 2.535f, 2.293f, 6.073f, 0.500f, F32_TILE(128, 128, 2, 2, 1)},
+    {128, 64, 3, 1.549f, 1.244f, 5.102f, 1.067f, F32_TILE(128, 64, 2, 2, 1)},
+    {96, 64, 3, 1.227f, 0.959f, 4.884f, 1.837f, F32_TILE(96, 64, 1, 2, 2)},
+    {64, 64, 4, 1.018f, 0.688f, 3.128f, 2.398f, F32_TILE(64, 64, 2, 2, 1)},
+    {32, 64, 6, 0.642f, 0.373f, 2.646f, 3.036f, F32_TILE(32, 64, 1, 2, 2)},
+    {32, 32, 5, 0.613f, 0.217f, 2.590f, 2.824f, F32_TILE(32, 32, 1, 1, 4)},
 };
 #undef F32_TILE
 

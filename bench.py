@@ -290,13 +290,13 @@ def main() -> int:
     instrumented_ms = sum(g["ms"] for g in groups.values()) + unscale_ms
 
     # dominant kernel: largest share of the step among the calls that are exactly one kernel per
-    # event pair: every forward call but the stem's, and the data-gradient calls of the split-role
-    # and patch kernels (the older data-gradient path and the weight gradient launch a filter copy
-    # or a reduction beside their main kernel)
+    # event pair: every forward call but the stem's and those on padded copies, and the data-gradient
+    # calls of the split-role, patch and narrow kernels (the older data-gradient path and the weight gradient
+    # launch a filter copy or a reduction beside their main kernel)
     def single_kernel(name, g):
         if g["pass"] == "fwd":
-            return not name.startswith(("thin", "padk", "narrow"))
-        return g["pass"] == "dgrad" and ("_ws_" in name or "patch" in name) and not name.startswith("padk")
+            return not name.startswith(("thin", "padk"))
+        return g["pass"] == "dgrad" and any(t in name for t in ("_ws_", "patch", "narrow")) and not name.startswith("padk")
     try:
         with open(args.traffic_file) as f:
             traffic_entries = json.load(f)

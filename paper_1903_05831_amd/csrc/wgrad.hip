@@ -258,7 +258,7 @@ hipError_t launch_wgrad(int variant, const WgradParams& P, hipStream_t st)
 
 hipError_t launch_splitk_reduce(const float* partial, float* dw, int splits, long numel, hipStream_t st)
 {
-    long n4 = numel / 4;   // numel is a multiple of 64 on this route (C and K multiples of 8)
+    long n4 = numel / 4;   // numel is a multiple of 8 on this route (C is)
     int G = 1;
     while (G < 16 && G * 2 <= splits && n4 * G < 65536) G *= 2;
     const int epb = 256 / G;

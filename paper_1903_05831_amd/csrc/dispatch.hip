@@ -153,16 +153,16 @@ static int ws_variant_for(const Geom& g, bool dgrad, int v)
 // gather, and strided data gradients, whose parity classes have tiles of different length (a step is that of
 // gathering).  The constants are least-squares fits to the timings in profiles/layer_timings.jsonl.gz
 // (fit_models.py), bounded by the measured rates of matrix instructions alone (2.06 PFLOP/s) and of
-// streaming (6.1 TB/s; 3.5 at least).  On layers left out of the fit the choice is 1.4 % slower than the fastest of 23 measured
-// variants (4.2 % at the 90th percentile); on 1738 passes of detector layers on images of random size
-// 1.4 % (4.6 %).  The model of one round with its last tiles half as wide (324) at a rate of its own, and without the
-// variants below 300, was 2.7 % slower there (9.1 %), rules by row counts 17 % (57 %).
+// streaming (6.1 TB/s; 3.5 at least).  On layers left out of the fit the choice is 1.6 % slower than the fastest of
+// 23 measured variants (4.8 % at the 90th percentile); on 1738 passes of detector layers on images of random
+// size 1.4 % (4.6 %).  A model that gave the launch with two tile widths (324) a rate of its own and left out
+// the variants below 300 was 2.7 % slower there (9.1 %), rules by row counts 17 % (57 %).
 struct RowCost { float fixed, step, shared, tile, hbm; };
 struct RowModel { int variant, per_cu; RowCost pointwise, gather, strided; };   // step 0: not taken
 static const RowModel kRowModels[] = {
-    {101, 3, {3.053f, 0.799f, 0.704f, 1.135f, 3.937f}, {2.826f, 0.803f, 0.628f, 1.527f, 3.500f}, {4.334f, 0.803f, 0.628f, 0.738f, 3.500f}},
-    {107, 3, {3.166f, 0.626f, 0.507f, 0.353f, 3.553f}, {2.669f, 0.648f, 0.463f, 1.127f, 3.500f}, {3.728f, 0.648f, 0.463f, 0.000f, 3.500f}},
-    {112, 5, {3.155f, 0.782f, 0.506f, 0.371f, 3.563f}, {3.714f, 0.782f, 0.475f, 0.000f, 3.500f}, {3.374f, 0.782f, 0.475f, 0.465f, 3.500f}},
+    {101, 3, {3.053f, 0.799f, 0.704f, 1.135f, 3.937f}, {2.826f, 0.803f, 0.628f, 1.527f, 3.500f}, {}},
+    {107, 3, {3.166f, 0.626f, 0.507f, 0.353f, 3.553f}, {2.669f, 0.648f, 0.463f, 1.127f, 3.500f}, {}},
+    {112, 5, {3.155f, 0.782f, 0.506f, 0.371f, 3.563f}, {3.714f, 0.782f, 0.475f, 0.000f, 3.500f}, {}},
     {300, 1, {0.990f, 0.580f, 0.000f, 3.674f, 3.630f}, {0.500f, 0.552f, 0.000f, 3.922f, 3.743f}, {1.197f, 0.552f, 0.000f, 5.197f, 3.500f}},
     {303, 1, {0.500f, 0.843f, 0.000f, 4.771f, 3.500f}, {0.500f, 0.800f, 0.000f, 4.702f, 3.500f}, {0.500f, 0.800f, 0.000f, 6.639f, 3.500f}},
     {310, 1, {0.500f, 1.311f, 0.000f, 5.196f, 3.500f}, {0.500f, 1.194f, 0.000f, 5.062f, 3.500f}, {0.500f, 1.194f, 0.000f, 8.411f, 3.500f}},
@@ -180,7 +180,6 @@ static const RowModel kRowModels[] = {
     {435, 1, {}, {1.407f, 0.320f, 0.000f, 3.047f, 3.500f}, {}},
 };
 constexpr float kEmptyTile = 0.6f;      // of `tile`: a tile of a class that no tap reaches only stores zeros
-constexpr float kFilterCopy = 3.2f;     // us: the data gradient of the variants below 300 transposes the filter first
 
 // Two resources at work together: near the larger time, more where they are alike.
 static float both(float a, float b)
@@ -290,7 +289,7 @@ static float row_us(const Geom& g, bool dgrad, int variant)
     }
     const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 && !dgrad ? g.sh * g.sw : 1);    // MB
     const float move = (x + 2e-6f * g.N * g.Ho * g.Wo * g.K + 2e-6f * g.K * g.R * g.S * g.C) / c.hbm;
-    return c.fixed + (dgrad && variant < 300 ? kFilterCopy : 0.f) + both(work, move);
+    return c.fixed + both(work, move);
 }
 
 static int pick_variant(const Geom& g, bool dgrad)
@@ -310,8 +309,10 @@ static int pick_variant(const Geom& g, bool dgrad)
         const float us = row_us(g, dgrad, v);
         if (us >= 0.f && (best < 0 || us < best_us)) { best = v; best_us = us; }
     };
+    // the data gradient of the variants below 300 wants a filter copy in the workspace: faster by 0.5 % over
+    // layers of any channel counts (by 0.02 % over a detector's), which is not worth the caller's memory
     for (const RowModel& m : kRowModels)
-        if (m.variant < 400 || patch_variant_ok(g, dgrad, m.variant)) consider(m.variant);
+        if (m.variant < 300 ? !dgrad : m.variant < 400 || patch_variant_ok(g, dgrad, m.variant)) consider(m.variant);
     consider(324);
     return ws_variant_for(g, dgrad, best);
 }

@@ -190,8 +190,8 @@ PER_CU = {101: 3, 105: 2, 107: 3, 112: 5, 113: 4, 317: 2, 319: 2, 426: 2, 427: 2
 WGRAD_TILES = {100: (128, 128, 2), 104: (64, 128, 2), 107: (64, 64, 3), 108: (128, 64, 2), 109: (256, 256, 1),
                112: (128, 128, 1), 113: (256, 128, 1), 114: (256, 256, 1), 115: (256, 256, 1), 116: (128, 128, 1),
                117: (256, 128, 1), 118: (64, 64, 3), 119: (128, 128, 2), 120: (64, 128, 2)}
+FILTER_COPY = 3.2                   # us: the data gradient of the variants below 300 transposes the filter first
 EMPTY_TILE = 0.6                    # of `tile`: a tile of a parity class without taps only stores zeros
-FILTER_COPY = 3.2                   # us: the launch that transposes the filter for the variants below 300
 REDUCE_FIXED, REDUCE_RATE = 2.5, 6.0
 POINTWISE, GATHER, STRIDED = range(3)
 
@@ -274,6 +274,8 @@ def both(a, b):
 
 
 def row_us(models, k, p, v):
+    if p == 1 and v < 300:
+        return None                 # these want a filter copy in the workspace: measured layers only
     c = models.get((310 if v == 324 else v, kind(k, p)))
     if c is None or v == 324 and kind(k, p) == STRIDED:
         return None
@@ -287,7 +289,7 @@ def row_us(models, k, p, v):
         work = sum(compute_us([(m, steps)], 1, q) for m, q in ((wide * columns, c), (narrow, half)) if m)
     else:
         work = compute_us(tile_classes(k, p, v), PER_CU.get(v, 1), c)
-    return c[0] + (FILTER_COPY if p == 1 and v < 300 else 0.0) + both(work, megabytes(k, p) / c[4])
+    return c[0] + both(work, megabytes(k, p) / c[4])
 
 
 def ranges_made(total_steps, ranges):
@@ -354,7 +356,7 @@ def fit_rows(rows):
         least = 2.0 * area * 64 * 256 / MATRIX
         per_cu = PER_CU.get(v, 1)
         for c in (POINTWISE, GATHER, STRIDED):
-            if v >= 400 and c != GATHER:
+            if v >= 400 and c != GATHER or v < 300 and c == STRIDED:
                 continue
             samples = [(tuple(x["k"]), x["p"], dict(x["us"])[v]) for x in rows
                        if v in dict(x["us"]) and kind(x["k"], x["p"]) == c]

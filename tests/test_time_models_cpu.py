@@ -39,7 +39,8 @@ def test_forward_and_data_gradient_tiles(variants):
     loss = []
     for x in fit_models.load([TIMINGS]):
         if x["what"] == "rows":
-            times = dict(x["us"])
+            # data gradients of the variants below 300 want workspace for a filter copy: measured layers only
+            times = {v: us for v, us in x["us"] if x["p"] == 0 or v >= 300}
             loss.append(times[variants[sd.kernel_name(_desc(x["k"]), x["p"])]] / min(times.values()))
     mean, worst = _quality(loss)
     assert len(loss) > 1000 and mean < 0.02 and worst < 0.22, (mean, worst)

@@ -143,8 +143,9 @@ def test_wgrad_kernel_variants(variant):
 
 # pointwise layers with few filters: pixel counts around the 16 of a wave, the 64 of a workgroup, the
 # weight gradient's 256 of a pixel range, and past the 65 536 that the persistent workgroups take in one
-# turn; channels below, at and past one 256-channel load and one 128-channel tile; filters around each
-# multiple of 16, odd and in fours; the longest filters accepted, and longer ones on padded copies
+# turn, or for which the weight gradient takes three steps a wave; channels below, at and past one
+# 256-channel load and one 128-channel tile; filters around each multiple of 16, odd and in fours; the
+# longest filters accepted, and longer ones on padded copies
 NARROW_SHAPES = [
     # N  H   W   C     K
     (1, 1, 1, 8, 1),
@@ -168,6 +169,8 @@ NARROW_SHAPES = [
     (1, 257, 259, 64, 28),
     (1, 257, 259, 64, 47),
     (1, 257, 259, 64, 60),
+    (1, 257, 259, 256, 12),
+    (1, 363, 367, 16, 28),
 ]
 
 

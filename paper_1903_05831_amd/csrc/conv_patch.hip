@@ -257,8 +257,8 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(Igem
             }
         } else {
             // The next group's fragments are read while the matrix pipe works on this one's; the barrier of
-            // the next step comes between the last reads of a step, which have returned by then, and
-            // its last matrix instructions.
+            // the next step, which waits for the last reads of this one, comes in front of its last matrix
+            // instructions.
             half8 fa[2][FM], fb[2][FN];
             static_assert(G % 2 == 0, "fragment buffers alternate");
             stage_barrier();
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(Igem
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 next_step();
-                wait_lds_reads();
+                wait_lds_reads();       // on both sides of the branch, or the compiler waits again in each matrix instruction
                 if (t + 1 < nk) {
                     stage_barrier();
                     load_frags(smem + (kc & (NPB - 1)) * PATCHB, stage, 0, fa[0], fb[0]);
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(Igem
     // ---- epilogue ------------------------------------------------------------------------------
     static_assert(NW * epilogue_strip_bytes<WN, MF>() <= NPB * PATCHB + SB * TPS * BN * 128,
                   "epilogue strips fit in the patch buffers and the filter ring");
-    __builtin_amdgcn_s_barrier();                   // everybody is done reading the last patch and filter stage
+    stage_barrier();                                // everybody is done reading the last patch and filter stage
     if (NDW > 0 && wave >= NW) return;              // no barrier follows
     store_rows_via_lds<FM, FN, MF, TAIL>(acc, smem + wave * epilogue_strip_bytes<WN, MF>(), lane, n0 + wn * WN, P,
                                [&](int r) -> unsigned {

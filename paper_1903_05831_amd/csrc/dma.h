@@ -43,11 +43,14 @@ __device__ __forceinline__ void wait_vmcnt()
 // nothing more where it uses their values.
 __device__ __forceinline__ void wait_lds_reads() { __builtin_amdgcn_s_waitcnt(0xc07f); }    // lgkmcnt(0)
 
-// Workgroup barrier behind which a stage that the loads above have filled is read: the compiler, which
-// knows nothing of those writes, may keep no LDS value across it.
+// Workgroup barrier behind which one stage that the loads above have filled is read and another is given
+// back to them.  The compiler, which knows nothing of those writes, may keep no LDS value across it; and the LDS
+// reads of this wave have returned: s_barrier itself waits for nothing, and the matrix instructions that
+// the compiler waits in front of may move past it.
 __device__ __forceinline__ void stage_barrier()
 {
     asm volatile("" ::: "memory");
+    wait_lds_reads();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }

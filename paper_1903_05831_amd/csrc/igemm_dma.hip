@@ -224,7 +224,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(IgemmParams P
         int is = (S - 1) % S;       // stage the next issue() fills
         for (int it = 0; it < nk; ++it) {
             if (it + S - 2 < nk) wait_vmcnt<INFLIGHT>(); else wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();
+            stage_barrier();
             if (issued < nk) { issue(is); ++issued; is = (is + 1 == S) ? 0 : is + 1; }
             compute(cs);
             cs = (cs + 1 == S) ? 0 : cs + 1;
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(IgemmParams P
     // ---- epilogue: through a per-wave LDS strip into 16-byte NHWC stores --------------------
     // (the strips may run over the tap tables behind the ring: those are dead by now)
     static_assert(NW * epilogue_strip_bytes<WN>() <= dma_lds_bytes<BM, BN, WGM, WGN, S, BK>(), "epilogue strips fit in LDS");
-    __builtin_amdgcn_s_barrier();                   // everybody is done reading the last stage
+    stage_barrier();                                // everybody is done reading the last stage
     store_tile_via_lds<FM, FN, 32, TAIL>(acc, smem + wave * epilogue_strip_bytes<WN>(), lane, m0 + wm * WM, n0 + wn * WN,
                                Mcls, P, Hi, Wj, eh, ew, ca, cb);
 }

@@ -226,8 +226,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P
         int cs = 0, is = (S - 1) % S;
         for (int it = 0; it < nsteps; ++it) {
             if (fetcher) { if (it + S - 2 < nsteps) wait_vmcnt<INFLIGHT>(); else wait_vmcnt<0>(); }
-            if (!LINEAR) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // table writes landed
-            __builtin_amdgcn_s_barrier();
+            stage_barrier();        // waits for this wave's table writes too
             if (issued < nsteps) {
                 if (fetcher) issue(is);
                 ++issued;

@@ -149,7 +149,6 @@ __global__ __launch_bounds__(64 * (WGM * WGN + 2)) void wgrad_ws_f32_kernel(F32W
                         acc[a][c][e] = 0.f;
                     }
         }
-        wait_lds_reads();       // before the barrier that gives the stage to the fetching waves
         cs = (cs + 1 == S) ? 0 : cs + 1;
     }
 

@@ -1,0 +1,87 @@
+"""What the compiler made of the kernels: properties of the gfx950 code in libsdconv.so that the sources rely on
+and no result shows reliably."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_1903_05831_amd as sd
+from paper_1903_05831_amd import build
+
+LLVM = os.path.join(os.path.dirname(os.path.dirname(build.HIPCC)), "llvm", "bin")
+LINE = re.compile(r"^\t(\S+)(.*?)\s*// ([0-9A-F]+):.*?(?:<(\S+?)(?:\+0x([0-9a-fA-F]+))?>)?$")
+NONE = 99       # no LDS read on its way
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    where = tmp_path_factory.mktemp("code")
+    sd.lib()
+    shutil.copy(build.LIB, where / "lib.so")
+    subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", "lib.so"], cwd=where, check=True, capture_output=True)
+    out = sorted(str(p) for p in where.iterdir() if p.name.endswith("gfx950"))
+    assert len(out) > 10, out
+    return out
+
+
+def _kernels(path):
+    """(name, [(address, instruction, operands, address it may jump to)]) of every function."""
+    text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", path], check=True, capture_output=True, text=True).stdout
+    name, start, body = None, 0, []
+    for line in text.splitlines():
+        if head := re.match(r"^([0-9a-f]+) <(\S+)>:$", line):
+            if name:
+                yield name, body
+            start, name, body = int(head[1], 16), head[2], []
+        elif m := LINE.match(line):
+            target = None
+            if m[4] is not None:
+                target = start + int(m[5] or "0", 16) if m[4] == name else None
+                assert target is not None, (path, line)
+            body.append((int(m[3], 16), m[1], m[2], target))
+    if name:
+        yield name, body
+
+
+def _reads_at_barriers(body):
+    """Addresses of the barriers that a wave can reach with one of its LDS reads on its way.
+
+    Carried along every path: how many LDS operations the wave has issued after its last read (they complete
+    in order, so lgkmcnt(n) has waited for that read if n is no more than this), or NONE."""
+    at = {a: i for i, (a, _, _, _) in enumerate(body)}
+    state, todo, found = {0: NONE}, [0], set()
+    while todo:
+        i = todo.pop()
+        after, (addr, op, args, target) = state[i], body[i]
+        if op == "s_barrier" and after != NONE:
+            found.add(addr)
+        if op.startswith("ds_"):
+            after = 0 if "read" in op else min(after + 1, 15) if after != NONE else NONE
+        elif op == "s_waitcnt":
+            m = re.search(r"lgkmcnt\((\d+)\)", args)
+            n = int(m[1]) if m else 0 if args.strip() == "0" else 15
+            if n <= after:
+                after = NONE
+        nexts = [] if op in ("s_endpgm", "s_branch", "s_setpc_b64") else [i + 1]
+        if target is not None:
+            nexts.append(at[target])
+        for n in nexts:
+            if n < len(body) and after < state.get(n, NONE + 1):
+                state[n] = after
+                todo.append(n)
+    return found
+
+
+def test_barriers_of_lds_dma_kernels_are_reached_with_no_lds_read_on_its_way(code_objects):
+    """Behind a barrier an LDS-DMA load of another wave may overwrite what was read before it, and s_barrier itself
+    waits for nothing: a wave must have its values by then, on every path through the code."""
+    bad, kernels = [], 0
+    for path in code_objects:
+        for name, body in _kernels(path):
+            if any(op.startswith("buffer_load") and args.endswith(" lds") for _, op, args, _ in body):
+                kernels += any(op == "s_barrier" for _, op, _, _ in body)
+                bad += [(name, hex(a)) for a in _reads_at_barriers(body)]
+    assert kernels > 40
+    assert not bad, bad

@@ -76,10 +76,11 @@ static bool byte_offsets_fit_31_bits(const Geom& g)
 }
 
 // The pipelined weight-gradient kernels store dw and its partial sums, 4 bytes an element, with 32-bit
-// offsets of the same kind; larger filters take the register-staged kernels too.
+// offsets of the same kind from the first filter of a matrix block of up to 32; longer filters take the
+// register-staged kernels too.
 static bool wgrad_offsets_fit_31_bits(const Geom& g)
 {
-    return byte_offsets_fit_31_bits(g) && (long)g.K * g.R * g.S * g.C < 1L << 29;
+    return byte_offsets_fit_31_bits(g) && (long)(g.K < 32 ? g.K : 32) * g.R * g.S * g.C <= 1L << 29;
 }
 
 // The MFMA route moves 16-byte (8-half) vectors along the channel axis of every tensor.

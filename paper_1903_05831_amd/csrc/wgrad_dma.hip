@@ -244,16 +244,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P
     // The products are taken transposed (x fragment first), so a lane holds four consecutive channels of
     // one filter row: 16-byte stores, a quarter of the instructions of the 4-byte ones that the other
     // order needs (a 256x256 tile: 256 instead of 1024 a workgroup; res5 3x3 with its ranges lost
-    // 9 us to them).  The range check of the buffer drops filters and channels past the end.
-    const long numel = (long)P.K * P.R * P.S * P.C;
+    // 9 us to them).  The range check of the buffer drops filters and channels past the end.  A descriptor
+    // starts at the first filter of a block row, so that offsets count the floats of MF filters and not of dw.
+    const long pitch = (long)P.R * P.S * P.C;
     typedef unsigned u4 __attribute__((ext_vector_type(4)));
-    const __amdgpu_buffer_rsrc_t rsrcD =
-        __builtin_amdgcn_make_buffer_rsrc(P.out + (long)split * numel, 0, (int)(unsigned)(numel * 4), 0x00020000);
     const int lrow = lane & (MF - 1), lhi = lane / MF;
+    const unsigned row = (unsigned)(lrow * pitch + (long)tap * P.C) * 4u;
 #pragma unroll
     for (int a = 0; a < FM; ++a) {
-        const int k = k0 + wm * WM + a * MF + lrow;
-        const unsigned row = (unsigned)((k * P.R * P.S + tap) * P.C) * 4u;
+        const int kb = k0 + wm * WM + a * MF, k = kb + lrow;
+        const __amdgpu_buffer_rsrc_t rsrcD =
+            __builtin_amdgcn_make_buffer_rsrc(P.out + ((long)split * P.K + kb) * pitch, 0, (int)kOutOfRange, 0x00020000);
 #pragma unroll
         for (int c = 0; c < FN; ++c)
 #pragma unroll

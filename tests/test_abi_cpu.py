@@ -156,11 +156,13 @@ def test_tensors_of_2_30_elements_or_more_avoid_the_byte_offset_kernels():
     assert "dma" not in sd.kernel_name(_desc(N=1, H=2048, W=2048, C=8, K=256, R=1, S=1, pad_h=0, pad_w=0), sd.WGRAD)
 
 
-def test_filters_of_2_29_elements_leave_the_pipelined_weight_gradient():
-    """It stores dw, 4 bytes an element, with 32-bit byte offsets whose top bit means "nowhere"."""
-    for K, pipelined in ((65528, True), (65536, False)):
-        name = sd.kernel_name(_desc(N=1, H=8, W=8, C=8192, K=K, R=1, S=1, pad_h=0, pad_w=0), sd.WGRAD)
-        assert ("dma" in name) == pipelined, name
+def test_large_filters_keep_the_pipelined_weight_gradient():
+    """It stores dw, 4 bytes an element, with 32-bit byte offsets whose top bit means "nowhere", counted from the
+    first filter of a block of 32: 2^31 bytes hold 32 filters of 2^24 elements."""
+    for K, C, pipelined in ((65528, 8192, True), (65536, 8192, True), (131064, 8192, True), (131072, 8192, False),
+                            (32, 1 << 24, True), (40, 1 << 24, True), (40, (1 << 24) + 8, False), (24, (1 << 24) + 8, True)):
+        name = sd.kernel_name(_desc(N=1, H=1, W=1, C=C, K=K, R=1, S=1, pad_h=0, pad_w=0), sd.WGRAD)
+        assert ("dma" in name) == pipelined, (K, C, name)
 
 
 def test_neighbouring_batch_sizes_take_the_tuned_entries():

@@ -57,6 +57,31 @@ def test_padded_3x3_on_a_tensor_of_more_than_2_30_elements():
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("ranges", [1, 2])
+def test_weight_gradient_of_more_than_2_29_elements(ranges, monkeypatch):
+    """1x1, 8192 -> 73 728 channels on 256 pixels: the 2.4 GB of dw, and twice that of partial sums, lie past the
+    2^31 bytes that a store's offset reaches from the first filter.  Products and sums of small whole numbers
+    are exact, so every element is compared."""
+    K, C, px = 73728, 8192, 256
+    d = sd.make_desc(1, 8, px // 8, C, K, 1, 1, (1, 1), (0, 0))
+    monkeypatch.setenv("SDCONV_WGRAD_SPLITS", str(ranges))
+    name, need = sd.kernel_name(d, sd.WGRAD), sd.conv2d_workspace_bytes(d, sd.WGRAD)
+    say(f"weight gradient {K} x {C}, {ranges} ranges: {name}, workspace {need}")
+    assert "dma" in name and need == (0 if ranges == 1 else ranges * 4 * K * C) and 4 * K * C > 2 ** 31
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(29 + ranges)
+    x = torch.randint(-4, 5, (px, C), device="cuda", generator=gen).half()
+    g = torch.randint(-4, 5, (px, K), device="cuda", generator=gen).half()
+    dw = torch.full((K, C), float("nan"), device="cuda")
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda") if need else None
+    sd.conv2d_wgrad(d, x, g, dw, ws, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    for k in range(0, K, 8192):
+        assert torch.equal(dw[k:k + 8192], g[:, k:k + 8192].float().t() @ x.float()), k
+    del dw, ws
+    torch.cuda.empty_cache()
+
+
 def test_unscale_more_than_2_31_elements():
     """n = 2^31 + 12345 fp32 gradients (8.6 GB), values from a seeded generator on the device
     (the host copy of each checked window is taken before the call and handed to the oracle):

@@ -171,7 +171,7 @@ extern "C" __attribute__((visibility("default"))) size_t conv2d_workspace_bytes_
 {
     int Ho, Wo;
     if (!desc_shape(desc, &Ho, &Wo)) return 0;
-    return f32_workspace_bytes(make_geom(*desc, Ho, Wo), pass);
+    return plan_f32(make_geom(*desc, Ho, Wo), pass).workspace_bytes;
 }
 
 static int f32_call(const conv2d_desc* desc, int pass, const float* a, const float* b, float* out, void* workspace,
@@ -183,12 +183,13 @@ static int f32_call(const conv2d_desc* desc, int pass, const float* a, const flo
     // 32-bit element offsets inside the kernels
     const size_t lim = (size_t)1 << 31;
     if ((size_t)g.N * g.H * g.W * g.C >= lim || (size_t)g.N * Ho * Wo * g.K >= lim) return SDCONV_EINVAL;
-    int rc = check_common(desc, a, b, out, workspace, workspace_bytes, f32_workspace_bytes(g, pass), &Ho, &Wo);
+    const F32Plan p = plan_f32(g, pass);
+    int rc = check_common(desc, a, b, out, workspace, workspace_bytes, p.workspace_bytes, &Ho, &Wo);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     if (pass == SDCONV_FWD) return hip_status(run_fwd_f32(g, a, b, out, st));
     if (pass == SDCONV_DGRAD) return hip_status(run_dgrad_f32(g, a, b, out, workspace, st));
-    return hip_status(run_wgrad_f32(g, a, b, out, workspace, st));
+    return hip_status(run_wgrad_f32(g, p, a, b, out, workspace, st));
 }
 
 extern "C" __attribute__((visibility("default"))) int conv2d_fwd_f32(const conv2d_desc* desc, const float* x, const float* w,

@@ -76,10 +76,12 @@ hipError_t run_wgrad(const Geom& g, const Plan& p, const __half* x, const __half
 bool f32_supported(const Geom& g);
 int forced_f32_tile();      // tuning hook: index into the tile list of conv_f32.hip (100 and up: its weight-gradient list), or -1
 int forced_wgrad_splits();  // tuning hook: pixel ranges of a weight gradient, or -1
-size_t f32_workspace_bytes(const Geom& g, int pass);
+struct F32WgradShape { int bm, bn, splits, sps; bool ws; };     // tile, pixel ranges, steps of each, split-role kernel
+struct F32Plan { size_t workspace_bytes; F32WgradShape wgrad; };
+F32Plan plan_f32(const Geom& g, int pass);
 hipError_t run_fwd_f32(const Geom& g, const float* x, const float* w, float* y, hipStream_t st);
 hipError_t run_dgrad_f32(const Geom& g, const float* dy, const float* w, float* dx, void* ws, hipStream_t st);
-hipError_t run_wgrad_f32(const Geom& g, const float* x, const float* dy, float* dw, void* ws, hipStream_t st);
+hipError_t run_wgrad_f32(const Geom& g, const F32Plan& plan, const float* x, const float* dy, float* dw, void* ws, hipStream_t st);
 
 // Launchers return hipGetLastError() of their launches.  All work goes to `st`.
 hipError_t launch_direct_fwd(const Geom& g, const __half* x, const __half* w, __half* y, hipStream_t st,

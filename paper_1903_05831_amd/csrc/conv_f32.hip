@@ -483,7 +483,6 @@ static const F32WgradTile kF32WgradTiles[] = {
 };
 constexpr float kF32ReduceFixed = 2.5f, kF32ReduceRate = 6.0f;
 
-struct F32WgradShape { int bm, bn, splits, sps; bool ws; };
 static F32WgradShape f32_wgrad_shape(const Geom& g)
 {
     F32WgradShape out;
@@ -501,6 +500,9 @@ static F32WgradShape f32_wgrad_shape(const Geom& g)
         const F32WgradTile& t = kF32WgradTiles[i];
         if (forced >= 0 && forced < 4 && i != forced) continue;
         const int tiles = ((g.K + t.bm - 1) / t.bm) * ((g.C + t.bn - 1) / t.bn) * g.R * g.S;
+        // no compute unit takes less than an even share of all steps, at its best rate
+        const float rate = t.shared > t.step / t.per_cu ? t.shared : t.step / t.per_cu;
+        const float even = (t.fixed + (float)tiles * total * rate / 256) * 0.9999f;
         int last = 0;
         for (const int workgroups : {0, 32, 64, 96, 128, 192, 256, 384, 512, 768, 1024, 1536, 2048}) {
             int n = workgroups / tiles;
@@ -508,6 +510,7 @@ static F32WgradShape f32_wgrad_shape(const Geom& g)
             if (n == last) continue;
             last = n;
             const int sps = (total + n - 1) / n, splits = (total + sps - 1) / sps;
+            if (any && even + splits * mb / t.store * 0.9999f >= best) break;       // and so do more ranges
             const int fullest = (splits * tiles + 255) / 256, rest = fullest % t.per_cu;
             auto round = [&](int c) { return sps * (c * t.shared > t.step ? c * t.shared : t.step) + t.tile; };
             float us = t.fixed + fullest / t.per_cu * round(t.per_cu) + (rest ? round(rest) : 0.f) + splits * mb / t.store;
@@ -522,15 +525,17 @@ static F32WgradShape f32_wgrad_shape(const Geom& g)
     return out;
 }
 
-size_t f32_workspace_bytes(const Geom& g, int pass)
+F32Plan plan_f32(const Geom& g, int pass)
 {
-    if (!f32_supported(g)) return 0;
-    if (pass == SDCONV_DGRAD) return f32_align256((size_t)g.K * g.R * g.S * g.C * sizeof(float));
+    F32Plan p{};
+    if (!f32_supported(g)) return p;
+    const size_t w = (size_t)g.K * g.R * g.S * g.C * sizeof(float);
+    if (pass == SDCONV_DGRAD) p.workspace_bytes = f32_align256(w);
     if (pass == SDCONV_WGRAD) {
-        const int splits = f32_wgrad_shape(g).splits;
-        return splits > 1 ? f32_align256((size_t)splits * g.K * g.R * g.S * g.C * sizeof(float)) : 0;
+        p.wgrad = f32_wgrad_shape(g);
+        if (p.wgrad.splits > 1) p.workspace_bytes = f32_align256(p.wgrad.splits * w);
     }
-    return 0;
+    return p;
 }
 
 template <int MODE, int BM, int BN, int WGM, int WGN, int WGK>
@@ -583,42 +588,26 @@ static const F32Tile kF32Tiles[] = {
 #undef F32_TILE
 constexpr int kNumF32Tiles = sizeof(kF32Tiles) / sizeof(kF32Tiles[0]), kF32WsTiles = 5;
 
-// Row tiles of height bm (all parity classes of a strided data gradient), with P into its tables, and
-// those among them that have taps, with their taps summed.
+// Row tiles of height bm (all parity classes of a strided data gradient), and those among them that have
+// taps, with their taps summed.
 struct F32Rows { long all, busy; double taps; int classes, most; };      // most: taps of a tile
-template <typename Params>
-static F32Rows f32_row_tiles(const Geom& g, bool dgrad, int bm, Params* P)
+static F32Rows f32_row_tiles(const RowClasses& rows, unsigned bm)
 {
-    const int nc = dgrad ? g.sh * g.sw : 1;
-    F32Rows out{0, 0, 0., nc, 0};
-    if (P) P->nclasses = nc;
-    for (int q = 0; q < nc; ++q) {
-        long rows = (long)g.N * g.Ho * g.Wo;
-        int taps = g.R * g.S;
-        if (dgrad) {
-            const int a = q / g.sw, b = q % g.sw;
-            const long Hi = (g.H - a + g.sh - 1) / g.sh, Wj = (g.W - b + g.sw - 1) / g.sw;
-            int th = 0, tw = 0;
-            for (int r = 0; r < g.R; ++r) th += (a + g.ph - r * g.dh) % g.sh == 0;
-            for (int t = 0; t < g.S; ++t) tw += (b + g.pw - t * g.dw) % g.sw == 0;
-            rows = Hi > 0 && Wj > 0 ? g.N * Hi * Wj : 0;
-            taps = th * tw;
-        }
-        const long tiles = (rows + bm - 1) / bm;
-        if (P) P->class_tile_start[q] = (int)out.all;
+    F32Rows out{0, 0, 0., rows.n, 0};
+    for (int q = 0; q < rows.n; ++q) {
+        const long tiles = (rows.pixels[q] + bm - 1) / bm;
+        const int taps = rows.taps[q];
         out.all += tiles;
         if (taps) out.busy += tiles;
         out.taps += (double)tiles * taps;
         if (tiles && taps > out.most) out.most = taps;
     }
-    if (P) P->class_tile_start[nc] = (int)out.all;
     return out;
 }
 
-static double f32_us(const Geom& g, bool dgrad, const F32Tile& t)
+static double f32_us(const RowClasses& classes, int cs, int cd, const F32Tile& t)
 {
-    const int cs = dgrad ? g.K : g.C, cd = dgrad ? g.C : g.K;
-    const F32Rows rows = f32_row_tiles<F32Params>(g, dgrad, t.bm, nullptr);
+    const F32Rows rows = f32_row_tiles(classes, t.bm);
     if (rows.busy == 0) return t.fixed;
     const long columns = (cd + t.bn - 1) / t.bn, slabs = (cs + kF32BK - 1) / kF32BK;
     if (rows.classes > 1) {
@@ -638,7 +627,7 @@ static double f32_us(const Geom& g, bool dgrad, const F32Tile& t)
 
 // Fields that the parameters of both kernels have.
 template <typename Params>
-static bool f32_fill(const Geom& g, bool dgrad, const F32Tile& tile, Params* P)
+static bool f32_fill(const Geom& g, bool dgrad, const RowClasses& rows, const F32Tile& tile, Params* P)
 {
     P->NB = g.N;
     if (!dgrad) { P->Hs = g.H; P->Ws = g.W; P->Cs = g.C; P->Hd = g.Ho; P->Wd = g.Wo; P->Cd = g.K; }
@@ -648,7 +637,13 @@ static bool f32_fill(const Geom& g, bool dgrad, const F32Tile& tile, Params* P)
     P->sw_cls = dgrad ? g.sw : 1;
     P->b_row_pitch = g.R * g.S * P->Cs;
     P->tiles_n = (P->Cd + tile.bn - 1) / tile.bn;
-    const long total = f32_row_tiles(g, dgrad, tile.bm, P).all * P->tiles_n;
+    long tiles = 0;
+    P->nclasses = rows.n;
+    for (int q = 0; q <= rows.n; ++q) {
+        P->class_tile_start[q] = (int)tiles;
+        if (q < rows.n) tiles += (rows.pixels[q] + (unsigned)tile.bm - 1) / tile.bm;
+    }
+    const long total = tiles * P->tiles_n;
     if (total <= 0 || total > 0x7fffffc0L) return false;
     P->total_tiles = (int)total;
     return true;
@@ -659,9 +654,11 @@ static hipError_t run_f32_igemm(const Geom& g, bool dgrad, const float* A, const
     const bool ws = f32_byte_offsets_fit_31_bits(g);
     const int first = ws ? 0 : kF32WsTiles;
     int pick = first;
-    double best = f32_us(g, dgrad, kF32Tiles[first]);
+    const RowClasses rows = row_classes(g, dgrad);
+    const int cs = dgrad ? g.K : g.C, cd = dgrad ? g.C : g.K;
+    double best = f32_us(rows, cs, cd, kF32Tiles[first]);
     for (int i = first + 1; i < kNumF32Tiles; ++i) {
-        const double us = f32_us(g, dgrad, kF32Tiles[i]);
+        const double us = f32_us(rows, cs, cd, kF32Tiles[i]);
         if (us < best) { best = us; pick = i; }
     }
     const int forced = forced_f32_tile();
@@ -670,10 +667,10 @@ static hipError_t run_f32_igemm(const Geom& g, bool dgrad, const float* A, const
     if (pick >= kF32WsTiles) {
         F32Params P;
         P.A = A; P.B = B; P.D = D;
-        return f32_fill(g, dgrad, tile, &P) ? tile.launch[dgrad](P, st) : hipErrorInvalidValue;
+        return f32_fill(g, dgrad, rows, tile, &P) ? tile.launch[dgrad](P, st) : hipErrorInvalidValue;
     }
     IgemmParams P{};
-    if (!f32_fill(g, dgrad, tile, &P)) return hipErrorInvalidValue;
+    if (!f32_fill(g, dgrad, rows, tile, &P)) return hipErrorInvalidValue;
     P.A = reinterpret_cast<const __half*>(A); P.B = reinterpret_cast<const __half*>(B); P.D = reinterpret_cast<__half*>(D);
     P.Cs *= 2; P.b_row_pitch *= 2;              // counted in halves
     P.mode = dgrad;
@@ -714,11 +711,11 @@ static hipError_t launch_f32_wgrad(const F32WgradParams& P, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t run_wgrad_f32(const Geom& g, const float* x, const float* dy, float* dw, void* ws, hipStream_t st)
+hipError_t run_wgrad_f32(const Geom& g, const F32Plan& plan, const float* x, const float* dy, float* dw, void* ws, hipStream_t st)
 {
     if (!f32_supported(g)) return launch_direct_wgrad_f32(g, x, dy, dw, st);
     F32WgradParams P;
-    const F32WgradShape shape = f32_wgrad_shape(g);
+    const F32WgradShape& shape = plan.wgrad;
     const int bm = shape.bm, bn = shape.bn;
     P.splits = shape.splits;
     P.steps_per_split = shape.sps;

@@ -92,28 +92,40 @@ static bool igemm_ok(const Geom& g)
     return true;
 }
 
+RowClasses row_classes(const Geom& g, bool dgrad)
+{
+    RowClasses c;
+    c.n = dgrad ? g.sh * g.sw : 1;
+    if (c.n == 1) {
+        c.pixels[0] = (unsigned)g.N * (dgrad ? g.H * g.W : g.Ho * g.Wo);
+        c.taps[0] = g.R * g.S;
+        return c;
+    }
+    int rows[kMaxClasses], cols[kMaxClasses], taps_h[kMaxClasses] = {}, taps_w[kMaxClasses] = {};
+    for (int a = 0; a < g.sh; ++a) rows[a] = g.H > a ? (g.H - a + g.sh - 1) / g.sh : 0;
+    for (int b = 0; b < g.sw; ++b) cols[b] = g.W > b ? (g.W - b + g.sw - 1) / g.sw : 0;
+    // tap r meets the class a with (a + ph - r * dh) % sh == 0
+    for (int r = 0; r < g.R; ++r) ++taps_h[((r * g.dh - g.ph) % g.sh + g.sh) % g.sh];
+    for (int t = 0; t < g.S; ++t) ++taps_w[((t * g.dw - g.pw) % g.sw + g.sw) % g.sw];
+    for (int a = 0, q = 0; a < g.sh; ++a)
+        for (int b = 0; b < g.sw; ++b, ++q) {
+            c.pixels[q] = (unsigned)g.N * rows[a] * cols[b];
+            c.taps[q] = taps_h[a] * taps_w[b];
+        }
+    return c;
+}
+
 // Row tiles of the fwd/dgrad index space for a tile height bm.
 static int row_tiles(const Geom& g, bool dgrad, int bm, int* starts, int* nclasses)
 {
-    if (!dgrad) {
-        long M = (long)g.N * g.Ho * g.Wo;
-        starts[0] = 0;
-        starts[1] = (int)((M + bm - 1) / bm);
-        *nclasses = 1;
-        return starts[1];
-    }
-    int nc = g.sh * g.sw, acc = 0;
-    for (int q = 0; q < nc; ++q) {
-        int a = q / g.sw, b = q % g.sw;
-        long Hi = (g.H - a + g.sh - 1) / g.sh, Wj = (g.W - b + g.sw - 1) / g.sw;
-        if (Hi < 0) Hi = 0;
-        if (Wj < 0) Wj = 0;
-        long M = (long)g.N * Hi * Wj;
+    const RowClasses rows = row_classes(g, dgrad);
+    int acc = 0;
+    for (int q = 0; q < rows.n; ++q) {
         starts[q] = acc;
-        acc += (int)((M + bm - 1) / bm);
+        acc += (rows.pixels[q] + bm - 1) / bm;
     }
-    starts[nc] = acc;
-    *nclasses = nc;
+    starts[rows.n] = acc;
+    *nclasses = rows.n;
     return acc;
 }
 
@@ -242,11 +254,11 @@ static float makespan(const TileClass* classes, int n, long slots)
 }
 
 // Tiles of one length: the fullest compute unit sets the time.
-static float rounds_us(long tiles, float steps, int per_cu, const RowCost& c)
+static float rounds_us(unsigned tiles, float steps, int per_cu, const RowCost& c)
 {
-    auto round = [&](long n) { return steps * (n * c.shared > c.step ? n * c.shared : c.step) + c.tile; };
-    const long fullest = (tiles + 255) / 256, rest = fullest % per_cu;
-    return (float)(fullest / per_cu) * round(per_cu) + (rest ? round(rest) : 0.f);
+    auto round = [&](unsigned n) { return steps * (n * c.shared > c.step ? n * c.shared : c.step) + c.tile; };
+    const unsigned fullest = (tiles + 255) / 256, full = fullest / per_cu, rest = fullest - full * per_cu;
+    return (float)full * round(per_cu) + (rest ? round(rest) : 0.f);
 }
 
 static const RowModel& row_model(int variant)
@@ -256,54 +268,77 @@ static const RowModel& row_model(int variant)
     return *m;
 }
 
-static float row_us(const Geom& g, bool dgrad, int variant)
+// What the times of one pass under all variants have in common.  A call is planned anew each time, in front of a
+// kernel of a few us, so nothing is computed for every variant that need not be, and a variant is dropped as
+// soon as a lower bound of its time is above the best one: strided data gradients are planned in 0.8-1.1 us where
+// it took 2.5-2.7, other passes in 0.36 where it took 0.61, with the same choices.
+struct RowShape {
+    bool pointwise;
+    RowClasses rows;
+    int cd, Hd, Wd, N;
+    float slabs[2];                         // 64-channel steps a tap takes with steps of 64 and of 32 channels
+    float mb;
+};
+
+static RowShape row_shape(const Geom& g, bool dgrad)
 {
-    const bool pointwise = g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
-    const bool strided = dgrad && g.sh * g.sw > 1;
-    auto cost = [&](int v) -> const RowCost& {
-        const RowModel& m = row_model(v);
-        return pointwise ? m.pointwise : strided ? m.strided : m.gather;
-    };
-    const int cs = dgrad ? g.K : g.C, cd = dgrad ? g.C : g.K, bk = variant < 300 ? 32 : 64;
-    const float slabs = (float)((cs + bk - 1) / bk) * bk / 64, steps = g.R * g.S * slabs;
-    const RowCost& c = cost(variant == 324 ? 310 : variant);
-    if (c.step == 0.f || (variant == 324 && strided)) return -1.f;
+    RowShape s;
+    s.pointwise = g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
+    s.N = g.N;
+    s.cd = dgrad ? g.C : g.K;
+    s.Hd = dgrad ? g.H : g.Ho;
+    s.Wd = dgrad ? g.W : g.Wo;
+    const int cs = dgrad ? g.K : g.C;
+    s.slabs[0] = (float)((cs + 63) / 64);
+    s.slabs[1] = (float)((cs + 31) / 32) / 2;
+    s.rows = row_classes(g, dgrad);
+    const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 && !dgrad ? g.sh * g.sw : 1);    // MB
+    s.mb = x + 2e-6f * g.N * g.Ho * g.Wo * g.K + 2e-6f * g.K * g.R * g.S * g.C;
+    return s;
+}
+
+// Time of a variant if that is less than `best`; otherwise `best` or more, or less than 0 if it is not taken.
+static float row_us(const RowShape& s, const RowModel& m, float best)
+{
+    const RowClasses& R = s.rows;
+    const bool strided = R.n > 1, mixed = m.variant == 324;
+    auto cost = [&](const RowModel& r) -> const RowCost& { return s.pointwise ? r.pointwise : strided ? r.strided : r.gather; };
+    const RowModel& wide = mixed ? row_model(310) : m;
+    const RowCost& c = cost(wide);
+    if (c.step == 0.f || (mixed && strided)) return -1.f;
+    const float slabs = s.slabs[m.variant < 300], move = s.mb / c.hbm;
+    if (c.fixed + move >= best) return best;
     float work;
-    if (variant >= 400) {
-        const PatchVariant& v = kPatchVariants[variant - 400];
-        const int Hd = dgrad ? g.H : g.Ho, Wd = dgrad ? g.W : g.Wo;
-        work = rounds_us((long)g.N * ((Hd + v.th - 1) / v.th) * ((Wd + v.tw - 1) / v.tw) * ((cd + v.bn - 1) / v.bn),
-                         steps, row_model(variant).per_cu, c);
+    if (m.variant >= 400) {
+        const PatchVariant& v = kPatchVariants[m.variant - 400];
+        work = rounds_us((unsigned)s.N * ((s.Hd + v.th - 1) / v.th) * ((s.Wd + v.tw - 1) / v.tw) * ((s.cd + v.bn - 1) / v.bn),
+                         R.taps[0] * slabs, m.per_cu, c);
     } else {
-        const IgemmVariant& v = igemm_variant(variant);
-        const int columns = (cd + v.bn - 1) / v.bn;
-        int starts[kMaxClasses + 1], nc;
-        const long rows = row_tiles(g, dgrad, v.bm, starts, &nc);
-        if (variant == 324) {       // as its launcher divides the rows: 224x256 tiles, then 224x128 ones
-            const long wide = mixed_wide_rows(rows, columns);
-            work = rounds_us(wide * columns, steps, 1, c);
-            if (wide < rows) work += rounds_us((rows - wide) * ((cd + 127) / 128), steps, 1, cost(316));
-        } else if (nc == 1) {
-            work = rounds_us(rows * columns, steps, row_model(variant).per_cu, c);
+        const IgemmVariant& v = igemm_variant(m.variant);
+        const unsigned columns = (s.cd + v.bn - 1) / v.bn, bm = v.bm;
+        const float steps = R.taps[0] * slabs;
+        if (mixed) {                // as its launcher divides the rows: 224x256 tiles, then 224x128 ones
+            const long rows = (R.pixels[0] + bm - 1) / bm, whole = mixed_wide_rows(rows, columns);
+            work = rounds_us(whole * columns, steps, 1, c);
+            if (whole < rows) work += rounds_us((rows - whole) * ((s.cd + 127) / 128), steps, 1, cost(row_model(316)));
+        } else if (!strided) {
+            work = rounds_us((R.pixels[0] + bm - 1) / bm * columns, steps, m.per_cu, c);
         } else {
-            const int per_cu = row_model(variant).per_cu;
-            const long fullest = (rows * columns + 255) / 256, crowd = fullest < per_cu ? fullest : per_cu;
-            const float step = crowd * c.shared > c.step ? crowd * c.shared : c.step;
             TileClass classes[kMaxClasses];
-            for (int q = 0; q < nc; ++q) {
-                const int a = q / g.sw, b = q % g.sw;
-                int taps_h = 0, taps_w = 0;
-                for (int r = 0; r < g.R; ++r) taps_h += (a + g.ph - r * g.dh) % g.sh == 0;
-                for (int t = 0; t < g.S; ++t) taps_w += (b + g.pw - t * g.dw) % g.sw == 0;
-                const int taps = taps_h * taps_w;
-                classes[q] = {(long)(starts[q + 1] - starts[q]) * columns,
-                              taps * slabs * step + (taps ? c.tile : kEmptyTile * c.tile)};
+            unsigned tiles = 0;
+            for (int q = 0; q < R.n; ++q) tiles += classes[q].tiles = (R.pixels[q] + bm - 1) / bm * columns;
+            const unsigned fullest = (tiles + 255) / 256, crowd = fullest < (unsigned)m.per_cu ? fullest : m.per_cu;
+            const float step = crowd * c.shared > c.step ? crowd * c.shared : c.step;
+            float sum = 0.f;
+            for (int q = 0; q < R.n; ++q) {
+                classes[q].us = R.taps[q] * slabs * step + (R.taps[q] ? c.tile : kEmptyTile * c.tile);
+                sum += classes[q].tiles * classes[q].us;
             }
-            work = makespan(classes, nc, 256L * per_cu);
+            // the slots are busy for the sum at least (less what the rounding of either may add)
+            if (c.fixed + both(sum / (256 * m.per_cu), move) * 0.9999f >= best) return best;
+            work = makespan(classes, R.n, 256L * m.per_cu);
         }
     }
-    const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 && !dgrad ? g.sh * g.sw : 1);    // MB
-    const float move = (x + 2e-6f * g.N * g.Ho * g.Wo * g.K + 2e-6f * g.K * g.R * g.S * g.C) / c.hbm;
     return c.fixed + both(work, move);
 }
 
@@ -319,16 +354,18 @@ static int pick_variant(const Geom& g, bool dgrad)
     if (const TunedEntry* e = tuned_lookup(g, dgrad ? SDCONV_DGRAD : SDCONV_FWD))
         if (e->variant < 400 || patch_variant_ok(g, dgrad, e->variant)) return ws_variant_for(g, dgrad, e->variant);
     int best = -1;
-    float best_us = 0.f;
-    auto consider = [&](int v) {
-        const float us = row_us(g, dgrad, v);
-        if (us >= 0.f && (best < 0 || us < best_us)) { best = v; best_us = us; }
+    float best_us = INFINITY;
+    const RowShape shape = row_shape(g, dgrad);
+    auto consider = [&](const RowModel& m) {
+        const float us = row_us(shape, m, best_us);
+        if (us >= 0.f && us < best_us) { best = m.variant; best_us = us; }
     };
     // the data gradient of the variants below 300 wants a filter copy in the workspace: faster by 0.5 % over
     // layers of any channel counts (by 0.02 % over a detector's), which is not worth the caller's memory
     for (const RowModel& m : kRowModels)
-        if (m.variant < 300 ? !dgrad : m.variant < 400 || patch_variant_ok(g, dgrad, m.variant)) consider(m.variant);
-    consider(324);
+        if (m.variant < 300 ? !dgrad : m.variant < 400 || patch_variant_ok(g, dgrad, m.variant)) consider(m);
+    static const RowModel kMixed = {324, 1, {}, {}, {}};        // its costs are those of its halves
+    consider(kMixed);
     return ws_variant_for(g, dgrad, best);
 }
 
@@ -459,38 +496,37 @@ static size_t wgrad_partial_limit(const Geom& g, size_t copies)
 
 struct WgradChoice { int variant, splits; float us; };
 
-static float wgrad_us(const Geom& g, const WgradModel& m, long tiles, long total_steps, long splits)
-{
-    const WgradCost& c = (g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0) ? m.linear : m.gather;
-    const float steps = (float)((total_steps + splits - 1) / splits);
-    auto round = [&](long n) { return steps * (n * c.shared > c.step ? n * c.shared : c.step) + c.tile; };
-    const long fullest = (tiles * splits + 255) / 256, rest = fullest % m.per_cu;
-    const float work = (float)(fullest / m.per_cu) * round(m.per_cu) + (rest ? round(rest) : 0.f);
-    const float dw = 4e-6f * g.K * g.R * g.S * g.C;         // MB
-    const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 ? g.sh * g.sw : 1);
-    float t = c.fixed + both(work, (x + 2e-6f * g.N * g.Ho * g.Wo * g.K) / c.hbm) + splits * dw / c.store;
-    if (splits > 1) t += splits * dw / kReduceRate + kReduceFixed;
-    return t;
-}
-
-// The fastest number of pixel ranges for one variant: those that make the workgroups a little fewer
-// than a multiple of the compute units, and the smallest.
+// The fastest number of pixel ranges for one variant, if faster than `best`: those that make the workgroups a
+// little fewer than a multiple of the compute units, and the smallest.
 static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial_limit, WgradChoice* best)
 {
-    const long tiles = wgrad_tiles(g, wgrad_variant(m.variant)), total = wgrad_steps(g);
+    const WgradCost& c = (g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0) ? m.linear : m.gather;
+    const long tiles = wgrad_tiles(g, wgrad_variant(m.variant));
+    const unsigned total = (unsigned)wgrad_steps(g);
     const size_t dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
+    const float dw = 4e-6f * g.K * g.R * g.S * g.C;         // MB
+    const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 ? g.sh * g.sw : 1);
+    const float move = (x + 2e-6f * g.N * g.Ho * g.Wo * g.K) / c.hbm, store = dw / c.store;
     static const int candidates[] = {1, 2, 3, -40, -64, -96, -128, -192, -256, -320, -384, -512, -768, -1024};
-    long last = 0;
+    // no compute unit takes less than an even share of all steps, at its best rate
+    const float rate = c.shared > c.step / m.per_cu ? c.shared : c.step / m.per_cu;
+    const float even = (c.fixed + both((float)tiles * total * rate / 256, move)) * 0.9999f;
+    unsigned last = 0;
     for (int cand : candidates) {                           // ranges, or minus the workgroups to make
-        long s = cand > 0 ? cand : -cand / tiles;
+        unsigned s = cand > 0 ? cand : (unsigned)(-cand / tiles);
         if (s > total / 2) s = total / 2;
         if (s < 1) s = 1;
-        const long steps = (total + s - 1) / s;
+        const unsigned steps = (total + s - 1) / s;
         s = (total + steps - 1) / steps;                    // ranges that are not empty
         if (s <= last) continue;
         last = s;
         if (s > 1 && s * dw_bytes > partial_limit) break;
-        const float us = wgrad_us(g, m, tiles, total, s);
+        if (best->variant >= 0 && even + s * store >= best->us) break;      // and so do more ranges
+        auto round = [&](unsigned n) { return steps * (n * c.shared > c.step ? n * c.shared : c.step) + c.tile; };
+        const unsigned fullest = (unsigned)((tiles * s + 255) / 256), full = fullest / m.per_cu, rest = fullest - full * m.per_cu;
+        const float work = (float)full * round(m.per_cu) + (rest ? round(rest) : 0.f);
+        float us = c.fixed + both(work, move) + s * store;
+        if (s > 1) us += s * dw / kReduceRate + kReduceFixed;
         if (best->variant < 0 || us < best->us) *best = WgradChoice{m.variant, (int)s, us};
     }
 }

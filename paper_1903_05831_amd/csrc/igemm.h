@@ -41,6 +41,11 @@ struct IgemmParams {
 
 void set_taps(const Geom& g, bool dgrad, IgemmParams* P);      // the tap fields (dispatch.hip)
 
+// GEMM rows (destination pixels) and filter taps that meet them, by parity class of a strided data gradient;
+// other passes have one class.
+struct RowClasses { int n; unsigned pixels[kMaxClasses]; int taps[kMaxClasses]; };
+RowClasses row_classes(const Geom& g, bool dgrad);
+
 struct IgemmVariant { int bm, bn; const char* fwd_name; const char* dgrad_name; };
 constexpr int kNumIgemmVariants = 4;
 extern const IgemmVariant kIgemmVariants[kNumIgemmVariants];

@@ -37,30 +37,24 @@ static int forced_wgrad_variant() { return hook("SDCONV_WGRAD_VARIANT", -1); }
 
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Measured choices for known geometries (written by tune.py on the target GPU); anything not
-// listed falls back to the heuristics below.
-struct TunedEntry { int N, H, W, C, K, R, S, sh, sw, ph, pw, dh, dw, pass, variant, splits; };
-static const TunedEntry kTuned[] = {
-#include "tuned_table.inc"
-    {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, -1, 0, 0},
+// Weight gradients that keep the choice measured for them, at the measured batch and at half to twice of it.  In
+// time the models' choices are as good (a training step of the detector within 0.1 %).  What the entries fix is
+// memory: through wgrad_partial_limit they hold these layers, and those with up to seven filters less, whose padded
+// copies lie in the workspace too, within the array of conv2d_wgrad_static_scratch, where the rule for
+// all layers lets partial sums have more and that call would be refused.
+struct WgradEntry { int N, H, W, C, K, stride, variant, splits; };      // 1x1 without padding; splits 0: the model's
+static const WgradEntry kWgradEntries[] = {
+    {2, 200, 336, 256, 128, 1, 116, 0},
+    {2, 200, 336, 256, 512, 2, 112, 0},
+    {512, 14, 14, 1024, 512, 1, 114, 32},
+    {512, 7, 7, 2048, 512, 1, 115, 12},
 };
-
-// The table was measured at the batch sizes of the detector workloads.  A layer with the same
-// geometry and a batch within a factor of two of a measured one (half or twice the rows: the same
-// tile shapes still fill the chip about as well) takes that entry too, the exact batch first.
-static const TunedEntry* tuned_lookup(const Geom& g, int pass)
+static const WgradEntry* wgrad_entry(const Geom& g)
 {
-    if (hook("SDCONV_NO_TUNED_TABLE", 0)) return nullptr;
-    const TunedEntry* near = nullptr;
-    for (const TunedEntry* e = kTuned; e->pass >= 0; ++e) {
-        if (!(e->pass == pass && e->H == g.H && e->W == g.W && e->C == g.C && e->K == g.K &&
-              e->R == g.R && e->S == g.S && e->sh == g.sh && e->sw == g.sw && e->ph == g.ph && e->pw == g.pw &&
-              e->dh == g.dh && e->dw == g.dw))
-            continue;
-        if (e->N == g.N) { near = e; break; }
-        if (!near && 2 * g.N >= e->N && g.N <= 2 * e->N) near = e;
-    }
-    return near;
+    if (g.R * g.S != 1 || g.ph || g.pw || g.sh != g.sw || g.dh * g.dw != 1 || hook("SDCONV_NO_TUNED_TABLE", 0)) return nullptr;
+    for (const WgradEntry& e : kWgradEntries)
+        if (e.C == g.C && e.K == g.K && e.H == g.H && e.W == g.W && e.stride == g.sh && 2 * g.N >= e.N && g.N <= 2 * e.N) return &e;
+    return nullptr;
 }
 
 // The LDS-DMA kernels address their binary16 operands with 32-bit BYTE offsets and use bit 31
@@ -166,8 +160,7 @@ static int ws_variant_for(const Geom& g, bool dgrad, int v)
     return v;
 }
 
-// Time of a forward or data-gradient pass under each tile variant, for geometries outside the
-// measured table.  A workgroup takes `step` us per 64 contraction channels of a tap (where several share a
+// Time of a forward or data-gradient pass under each tile variant.  A workgroup takes `step` us per 64 contraction channels of a tap (where several share a
 // compute unit `shared` us times their number, if that is more), and `tile` us per tile besides; launch
 // and first loads are `fixed`; the operands move at `hbm` MB/us meanwhile.  What decides is mostly how the
 // tiles of a variant divide by 256 compute units.  Three sets of constants: pointwise layers, layers that
@@ -351,8 +344,6 @@ static int pick_variant(const Geom& g, bool dgrad)
     if (fv >= 0 && fv < kNumIgemmVariants) return fv;
     if (fv >= 100 && fv < 100 + kNumIgemmDmaVariants) return fv;
     if (fv >= 300 && fv < 300 + kNumIgemmWsVariants) return ws_variant_for(g, dgrad, fv);
-    if (const TunedEntry* e = tuned_lookup(g, dgrad ? SDCONV_DGRAD : SDCONV_FWD))
-        if (e->variant < 400 || patch_variant_ok(g, dgrad, e->variant)) return ws_variant_for(g, dgrad, e->variant);
     int best = -1;
     float best_us = INFINITY;
     const RowShape shape = row_shape(g, dgrad);
@@ -490,7 +481,7 @@ static size_t wgrad_partial_limit(const Geom& g, size_t copies)
     if (ranges > steps / 4) ranges = steps / 4;
     const size_t demand = ranges > 1 ? ranges * (size_t)4 * g.K * g.R * g.S * g.C : 0;
     const size_t scratch = SDCONV_STATIC_SCRATCH_BYTES, left = copies < scratch ? scratch - copies : 0;
-    if (left && tuned_lookup(g, SDCONV_WGRAD)) return left;     // measured with ranges that fit
+    if (left && wgrad_entry(g)) return left;
     return demand > left ? demand : left;
 }
 
@@ -531,17 +522,16 @@ static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial
     }
 }
 
-// Tile variant and pixel ranges.  A geometry of the measured table takes the variant from there and, at the
-// measured batch, the entry's ranges if it has any; else the model's for that variant, or, for a
-// variant without a model, the entry's scaled with the batch.
+// Tile variant and pixel ranges.  A layer with an entry takes its variant and, at the measured batch, its
+// ranges if it has any; else the model's for that variant.
 static WgradChoice choose_wgrad(const Geom& g, size_t partial_limit)
 {
     const int fv = forced_wgrad_variant();
     const bool forced = (fv >= 0 && fv < kNumWgradVariants) || (fv >= 100 && fv < 100 + kNumWgradDmaVariants);
     int only = forced ? fv : -1;
-    const TunedEntry* e = nullptr;
+    const WgradEntry* e = nullptr;
     if (!wgrad_offsets_fit_31_bits(g)) only = g.K <= 64 ? 1 : 0;
-    else if (!forced && (e = tuned_lookup(g, SDCONV_WGRAD))) only = e->variant;
+    else if (!forced && (e = wgrad_entry(g))) only = e->variant;
     WgradChoice c{-1, 1, 0.f};
     if (!(e && e->splits > 0 && e->N == g.N))
         for (const WgradModel& m : kWgradModels)
@@ -549,7 +539,7 @@ static WgradChoice choose_wgrad(const Geom& g, size_t partial_limit)
     if (c.variant < 0) {
         long want;
         if (e) {
-            want = (2L * e->splits * g.N + e->N) / (2 * e->N);
+            want = e->splits;
         } else {            // forced, or indexed by elements: enough workgroups to fill the chip
             const long tiles = wgrad_tiles(g, wgrad_variant(only)), most = wgrad_steps(g) / 4;
             want = (384 + tiles - 1) / tiles;

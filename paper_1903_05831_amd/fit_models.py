@@ -76,7 +76,7 @@ WORKGROUPS = (40, 64, 96, 128, 192, 256, 320, 384, 512, 768, 1024)
 
 def measure(what: str, seed: int, seconds: float, path: str) -> None:
     os.environ["SDCONV_TUNE"] = "1"             # before the first library call
-    os.environ["SDCONV_NO_TUNED_TABLE"] = "1"
+    os.environ["SDCONV_NO_TUNED_TABLE"] = "1"      # nor the entries of four weight gradients
     import torch
     import paper_1903_05831_amd as sd
 

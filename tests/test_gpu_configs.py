@@ -178,13 +178,12 @@ def test_second_shape_set_stratified_samples_plain_and_fused(cfg, li):
 @pytest.mark.parametrize("batch", [1, 4])
 @pytest.mark.parametrize("name", ["res2.0c", "res3.0b", "res3.1b", "res4.1a", "res4.1b", "res4.0p"])
 def test_other_batch_sizes(name, batch):
-    """The tuned table was measured at N = 2; N = 1 and N = 4 take the same entries (tile variant,
-    pixel ranges of the weight gradient scaled with the batch): stratified samples, all passes."""
+    """Half and twice the batch of the benchmark: other tiles, other pixel ranges of the weight gradient:
+    stratified samples, all passes."""
     import dataclasses
     li, l2 = next((i, l) for i, l in enumerate(workloads.CONFIGS[5]) if l.name == name)
     l = dataclasses.replace(l2, N=batch)
     d = sd.desc_of(l)
-    assert sd.kernel_name(d, sd.FWD) == sd.kernel_name(sd.desc_of(l2), sd.FWD)
     say(f"{name} at N={batch}: " + ", ".join(sd.kernel_name(d, p) for p in (sd.FWD, sd.DGRAD, sd.WGRAD)))
     cfg = 70 + batch
     x, w, g = workloads.make_x(l, cfg, li), workloads.make_w(l, cfg, li), workloads.make_g(l, cfg, li)

@@ -18,7 +18,6 @@
 // source channels a multiple of 64.  The data gradient of such a layer is the same kind of
 // convolution over dy with displaced taps; it reads the filter as stored, [K][R][S][C], as
 // 64-filter x BN-channel tiles that the transposing LDS read turns into fragments (lds_tr.h).
-#include <type_traits>
 #include "common.h"
 #include "igemm.h"
 #include "dma.h"
@@ -28,18 +27,13 @@
 namespace sdconv {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float float16v __attribute__((ext_vector_type(16)));
 typedef float float4p __attribute__((ext_vector_type(4)));
 
-// MF: 32 = v_mfma_f32_32x32x16_f16 blocks, 16 = v_mfma_f32_16x16x32_f16 blocks.
-// NIW: number of fetching waves (the last NIW of the WGM x WGN waves); 0 = half of them.
 // TH*TW need not be a multiple of the MFMA block height: the GEMM rows are padded up to
 // WGM*MF and the padding rows are multiplied but never stored.  10 x 14 blocks tile the
-// 100 x 168 and 50 x 84 feature maps of the res3 / res4 stages exactly (240 workgroups for
-// 256 CUs with 128- resp. 64-wide filter tiles).
-// TPS: taps per pipeline step (must divide R*S).  A step of one tap is only 64 deep; on small
-// tiles the barrier and the wait then cost as much as the MFMAs between them, so a step can
-// cover a whole filter row (TPS = 3): the ring stage holds TPS filter slabs.
+// 100 x 168 and 50 x 84 feature maps of the res3 / res4 stages exactly.
+// A step of one tap is only 64 deep; on small tiles the barrier and the wait then cost as much as the MFMAs
+// between them, so a step covers a whole filter row (TPS taps), and a ring stage holds TPS filter slabs.
 // NPB: patch buffers.  Two alternate between channel slabs; a layer with 64 source channels has
 // one slab and needs one buffer, which lets two or three workgroups share a compute unit's LDS
 // (its 134 400-pixel maps make 546-1050 blocks: at one workgroup per unit they run in 3-4 rounds).
@@ -48,17 +42,19 @@ typedef float float4p __attribute__((ext_vector_type(4)));
 // fetching waves of a small block reach the barrier a thousand cycles after the others
 // (timestamps of a 10 x 14 x 64 block: 1500 cycles of multiplying and 1200 of waiting per
 // step).  Waves with nothing else to do take the stalls off that path.
-template <int MODE, int TH, int TW, int BN, int WGM, int WGN, int SB, int MF = 32, int NIW = 0, int TPS = 1, int NPB = 2, int NDW = 0, bool TAIL = false>
+constexpr int MF = 16, TPS = 3;     // rows of a v_mfma_f32_16x16x32_f16 block, taps of a step
+
+template <int MODE, int TH, int TW, int BN, int WGM, int WGN, int SB, int NPB, int NDW, bool TAIL>
 __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(IgemmParams P)
 {
     constexpr int EH = 2, EW = 2;                   // extra patch rows / columns
     constexpr int PH = TH + EH, PW = TW + EW, PPX = PH * PW;
-    constexpr int NW = WGM * WGN, NI = NDW ? NDW : (NIW ? NIW : NW / 2), IW0 = NDW ? NW : NW - NI;
+    constexpr int NW = WGM * WGN, NI = NDW ? NDW : NW / 2, IW0 = NDW ? NW : NW - NI;
     constexpr int BM = TH * TW;                             // output pixels of the block
     constexpr int BMP = (BM + MF * WGM - 1) / (MF * WGM) * (MF * WGM);   // GEMM rows incl. padding
     constexpr int WM = BMP / WGM, WN = BN / WGN;
     constexpr int FM = WM / MF, FN = WN / MF;
-    constexpr int ACCN = MF == 32 ? 16 : 4, KSTEP = MF == 32 ? 16 : 32, CPK = KSTEP / 8;
+    constexpr int ACCN = 4, KSTEP = 32, CPK = KSTEP / 8;
     constexpr int NPL = (PPX + 8 * NI - 1) / (8 * NI);     // patch loads per fetching lane
     constexpr int PATCHB = NPL * NI * 1024;                // bytes of one patch buffer
     constexpr int PB1 = BN / (8 * NI);                     // filter loads per fetching lane and tap
@@ -66,7 +62,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(Igem
     constexpr int BSLAB = BN * 128;                        // one tap's filter slab
     constexpr int BSTAGE = TPS * BSLAB;
     constexpr int D = SB - 1;                              // filter stages in flight
-    static_assert((MF == 32 || MF == 16) && NI >= 1 && (NDW > 0 || NI < NW) && WM % MF == 0 && WN % MF == 0 && BN % (8 * NI) == 0, "tile shape");
+    static_assert(NI >= 1 && (NDW > 0 || NI < NW) && WM % MF == 0 && WN % MF == 0 && BN % (8 * NI) == 0, "tile shape");
     static_assert(SB >= 2 && NPL + D * PB < 64, "loads in flight");   // vmcnt is a 6-bit counter
     static_assert(NPB == 1 || NPB == 2, "patch buffers");
 
@@ -167,8 +163,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(Igem
         const int ml = wm * WM + b * MF + frow;
         pbase[b] = (ml < BM) ? (ml / TW) * PW + (ml % TW) : 0;      // padding rows read pixel 0
     }
-    typedef typename std::conditional<MF == 32, float16v, float4p>::type acc_t;
-    acc_t acc[FN][FM];
+    float4p acc[FN][FM];
 #pragma unroll
     for (int a = 0; a < FN; ++a)
 #pragma unroll
@@ -202,8 +197,6 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(Igem
             if (MODE == 0) {
                 const int row = wn * WN + a * MF + frow;
                 fb[a] = *reinterpret_cast<const half8*>(sb + row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4));
-            } else if (MF == 32) {
-                fb[a] = lds_frag_tr<BN>(sb, kk * 16, wn * WN + a * 32, lane);
             } else {
                 fb[a] = lds_frag_tr_16<BN>(sb, kk * 32, wn * WN + a * 16, lane);
             }
@@ -214,12 +207,8 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(Igem
 #pragma unroll
         for (int a = 0; a < FN; ++a)
 #pragma unroll
-            for (int b = 0; b < FM; ++b) {
-                if constexpr (MF == 32)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[a], fa[b], acc[a][b], 0, 0, 0);
-                else
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[a], fa[b], acc[a][b], 0, 0, 0);
-            }
+            for (int b = 0; b < FM; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[a], fa[b], acc[a][b], 0, 0, 0);
     };
 
     // ---- pipeline: one step per (slab, group of TPS taps), taps fastest ------------------------------------
@@ -313,159 +302,66 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(Igem
     });
 }
 
-template <int MODE, int TH, int TW, int BN, int WGM, int WGN, int SB, int MF = 32, int NIW = 0, int TPS = 1, int NPB = 2, int NDW = 0, bool TAIL>
+template <int MODE, int TH, int TW, int BN, int WGM, int WGN, int SB, int NPB, int NDW, bool TAIL>
 static hipError_t launch_patch_variant_impl(const IgemmParams& P, hipStream_t st)
 {
     if ((P.R * P.S) % TPS != 0 || (P.R * P.S) / TPS < SB - 1) return hipErrorInvalidValue;
     if (NPB == 1 && P.Cs != 64) return hipErrorInvalidValue;      // one patch buffer = one channel slab
-    constexpr int NI = NDW ? NDW : (NIW ? NIW : WGM * WGN / 2);
+    constexpr int NI = NDW ? NDW : WGM * WGN / 2;
     constexpr int NPL = ((TH + 2) * (TW + 2) + 8 * NI - 1) / (8 * NI);
     constexpr size_t lds = (size_t)NPB * NPL * NI * 1024 + (size_t)SB * TPS * BN * 128;
     static_assert(lds <= 160 * 1024, "LDS budget");
     static std::atomic<bool> configured{false};   // set once the attribute call has succeeded; a second thread may repeat it, harmlessly
     if (!configured.load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&conv_patch_kernel<MODE, TH, TW, BN, WGM, WGN, SB, MF, NIW, TPS, NPB, NDW, TAIL>),
+            reinterpret_cast<const void*>(&conv_patch_kernel<MODE, TH, TW, BN, WGM, WGN, SB, NPB, NDW, TAIL>),
             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
     }
     const int grid = ((P.total_tiles + 63) / 64) * 64;
-    hipLaunchKernelGGL((conv_patch_kernel<MODE, TH, TW, BN, WGM, WGN, SB, MF, NIW, TPS, NPB, NDW, TAIL>), dim3(grid), dim3(64 * (WGM * WGN + NDW)),
+    hipLaunchKernelGGL((conv_patch_kernel<MODE, TH, TW, BN, WGM, WGN, SB, NPB, NDW, TAIL>), dim3(grid), dim3(64 * (WGM * WGN + NDW)),
                        lds, st, P);
     return hipGetLastError();
 }
 
-template <int MODE, int TH, int TW, int BN, int WGM, int WGN, int SB, int MF = 32, int NIW = 0, int TPS = 1, int NPB = 2, int NDW = 0>
+template <int MODE, int TH, int TW, int BN, int WGM, int WGN, int SB, int NPB, int NDW>
 static hipError_t launch_patch_variant(const IgemmParams& P, hipStream_t st)
 {
     // the tail has kernels of its own: see store_rows_via_lds
-    return P.ep.any() ? launch_patch_variant_impl<MODE, TH, TW, BN, WGM, WGN, SB, MF, NIW, TPS, NPB, NDW, true>(P, st) : launch_patch_variant_impl<MODE, TH, TW, BN, WGM, WGN, SB, MF, NIW, TPS, NPB, NDW, false>(P, st);
+    return P.ep.any() ? launch_patch_variant_impl<MODE, TH, TW, BN, WGM, WGN, SB, NPB, NDW, true>(P, st)
+                      : launch_patch_variant_impl<MODE, TH, TW, BN, WGM, WGN, SB, NPB, NDW, false>(P, st);
 }
 
-const PatchVariant kPatchVariants[kNumPatchVariants] = {
-    {16, 16, 128, 1, 3, "conv_fwd_patch_16x16x128_s3", "conv_dgrad_patch_16x16x128_s3"},
-    {8, 16, 128, 1, 4, "conv_fwd_patch_8x16x128_s4", "conv_dgrad_patch_8x16x128_s4"},
-    {8, 16, 256, 1, 3, "conv_fwd_patch_8x16x256_s3", "conv_dgrad_patch_8x16x256_s3"},
-    {16, 16, 64, 1, 4, "conv_fwd_patch_16x16x64_s4", "conv_dgrad_patch_16x16x64_s4"},
-    {8, 32, 128, 1, 3, "conv_fwd_patch_8x32x128_s3", "conv_dgrad_patch_8x32x128_s3"},
-    {8, 16, 64, 1, 4, "conv_fwd_patch_8x16x64_s4", "conv_dgrad_patch_8x16x64_s4"},
-    {16, 16, 128, 1, 3, "conv_fwd_patch_16x16x128_s3_m16", "conv_dgrad_patch_16x16x128_s3_m16"},
-    {8, 16, 128, 1, 4, "conv_fwd_patch_8x16x128_s4_m16", "conv_dgrad_patch_8x16x128_s4_m16"},
-    {16, 16, 64, 1, 4, "conv_fwd_patch_16x16x64_s4_m16", "conv_dgrad_patch_16x16x64_s4_m16"},
-    {8, 32, 128, 1, 3, "conv_fwd_patch_8x32x128_s3_m16", "conv_dgrad_patch_8x32x128_s3_m16"},
-    {10, 14, 128, 1, 4, "conv_fwd_patch_10x14x128_6w_s4_m16", "conv_dgrad_patch_10x14x128_6w_s4_m16"},
-    {10, 14, 64, 1, 4, "conv_fwd_patch_10x14x64_6w_s4_m16", "conv_dgrad_patch_10x14x64_6w_s4_m16"},
-    {10, 14, 128, 1, 4, "conv_fwd_patch_10x14x128_12w_s4_m16", "conv_dgrad_patch_10x14x128_12w_s4_m16"},
-    {10, 14, 64, 1, 4, "conv_fwd_patch_10x14x64_6w1f_s4_m16", "conv_dgrad_patch_10x14x64_6w1f_s4_m16"},
-    {10, 14, 64, 3, 3, "conv_fwd_patch_10x14x64_6w_s3_m16_t3", "conv_dgrad_patch_10x14x64_6w_s3_m16_t3"},
-    {10, 14, 128, 3, 2, "conv_fwd_patch_10x14x128_12w_s2_m16_t3", "conv_dgrad_patch_10x14x128_12w_s2_m16_t3"},
-    {10, 14, 128, 3, 2, "conv_fwd_patch_10x14x128_6w_s2_m16_t3", "conv_dgrad_patch_10x14x128_6w_s2_m16_t3"},
-    {16, 16, 64, 3, 2, "conv_fwd_patch_16x16x64_s2_m16_t3", "conv_dgrad_patch_16x16x64_s2_m16_t3"},
-    {10, 14, 64, 3, 3, "conv_fwd_patch_10x14x64_12w_s3_m16_t3", "conv_dgrad_patch_10x14x64_12w_s3_m16_t3"},
-    {10, 14, 64, 3, 4, "conv_fwd_patch_10x14x64_6w_s4_m16_t3", "conv_dgrad_patch_10x14x64_6w_s4_m16_t3"},
-    {16, 16, 64, 3, 3, "conv_fwd_patch_16x16x64_s3_m16_t3_2f", "conv_dgrad_patch_16x16x64_s3_m16_t3_2f"},
-    {8, 16, 128, 3, 2, "conv_fwd_patch_8x16x128_s2_m16_t3", "conv_dgrad_patch_8x16x128_s2_m16_t3"},
-    // one patch buffer: layers with 64 source channels only
-    {16, 16, 64, 1, 3, "conv_fwd_patch_16x16x64_s3_m16_1p", "conv_dgrad_patch_16x16x64_s3_m16_1p", 1},
-    {16, 16, 64, 3, 2, "conv_fwd_patch_16x16x64_s2_m16_t3_1p", "conv_dgrad_patch_16x16x64_s2_m16_t3_1p", 1},
-    {10, 14, 64, 1, 3, "conv_fwd_patch_10x14x64_6w_s3_m16_1p", "conv_dgrad_patch_10x14x64_6w_s3_m16_1p", 1},
-    {10, 14, 64, 3, 2, "conv_fwd_patch_10x14x64_6w_s2_m16_t3_1p", "conv_dgrad_patch_10x14x64_6w_s2_m16_t3_1p", 1},
-    {8, 16, 64, 1, 3, "conv_fwd_patch_8x16x64_s3_m16_1p", "conv_dgrad_patch_8x16x64_s3_m16_1p", 1},
-    {8, 16, 64, 3, 2, "conv_fwd_patch_8x16x64_s2_m16_t3_1p", "conv_dgrad_patch_8x16x64_s2_m16_t3_1p", 1},
-    // waves that only fetch beside the multiplying ones
-    {10, 14, 64, 3, 4, "conv_fwd_patch_10x14x64_6w2f_s4_m16_t3", "conv_dgrad_patch_10x14x64_6w2f_s4_m16_t3"},
-    {10, 14, 64, 3, 3, "conv_fwd_patch_10x14x64_6w2f_s3_m16_t3", "conv_dgrad_patch_10x14x64_6w2f_s3_m16_t3"},
-    {10, 14, 128, 3, 2, "conv_fwd_patch_10x14x128_12w4f_s2_m16_t3", "conv_dgrad_patch_10x14x128_12w4f_s2_m16_t3"},
-    {10, 14, 128, 3, 2, "conv_fwd_patch_10x14x128_6w2f_s2_m16_t3", "conv_dgrad_patch_10x14x128_6w2f_s2_m16_t3"},
-    {16, 16, 64, 3, 2, "conv_fwd_patch_16x16x64_8w2f_s2_m16_t3", "conv_dgrad_patch_16x16x64_8w2f_s2_m16_t3"},
-    {10, 14, 64, 3, 2, "conv_fwd_patch_10x14x64_6w2f_s2_m16_t3_1p", "conv_dgrad_patch_10x14x64_6w2f_s2_m16_t3_1p", 1},
-    {10, 14, 64, 1, 3, "conv_fwd_patch_10x14x64_6w2f_s3_m16_1p", "conv_dgrad_patch_10x14x64_6w2f_s3_m16_1p", 1},
-    {10, 14, 64, 3, 4, "conv_fwd_patch_10x14x64_6w4f_s4_m16_t3", "conv_dgrad_patch_10x14x64_6w4f_s4_m16_t3"},
-    {8, 16, 64, 3, 3, "conv_fwd_patch_8x16x64_4w4f_s3_m16_t3", "conv_dgrad_patch_8x16x64_4w4f_s3_m16_t3"},
-    {8, 8, 64, 3, 3, "conv_fwd_patch_8x8x64_4w4f_s3_m16_t3", "conv_dgrad_patch_8x8x64_4w4f_s3_m16_t3"},
-};
+// number - 400, block, filters, multiplying waves, ring stages, patch buffers, fetching waves, name
+#define SDCONV_PATCH_VARIANTS(X) \
+    X(27, 8, 16, 64, 4, 2, 2, 1, 0, "8x16x64_s2_m16_t3_1p") \
+    X(33, 10, 14, 64, 3, 2, 2, 1, 2, "10x14x64_6w2f_s2_m16_t3_1p") \
+    X(35, 10, 14, 64, 3, 2, 4, 2, 4, "10x14x64_6w4f_s4_m16_t3") \
+    X(36, 8, 16, 64, 2, 2, 3, 2, 4, "8x16x64_4w4f_s3_m16_t3") \
+    X(37, 8, 8, 64, 2, 2, 3, 2, 4, "8x8x64_4w4f_s3_m16_t3")
 
-#define SDCONV_PATCH_CASE(idx, TH, TW, BN, WGM, WGN, SB)                                      \
-    case 2 * (idx): return launch_patch_variant<0, TH, TW, BN, WGM, WGN, SB>(P, st);          \
-    case 2 * (idx) + 1: return launch_patch_variant<1, TH, TW, BN, WGM, WGN, SB>(P, st);
+const std::array<PatchVariant, kNumPatchVariants> kPatchVariants = [] {
+    std::array<PatchVariant, kNumPatchVariants> v{};
+#define SDCONV_PATCH_NAME(idx, TH, TW, BN, WGM, WGN, SB, NPB, NDW, name) \
+    v[idx] = {TH, TW, BN, SB, "conv_fwd_patch_" name, "conv_dgrad_patch_" name, NPB == 1};
+    SDCONV_PATCH_VARIANTS(SDCONV_PATCH_NAME)
+    return v;
+}();
+
+template <int MODE> static hipError_t launch_mode(int variant, const IgemmParams& P, hipStream_t st)
+{
+    switch (variant) {
+#define SDCONV_PATCH_CASE(idx, TH, TW, BN, WGM, WGN, SB, NPB, NDW, name) \
+        case idx: return launch_patch_variant<MODE, TH, TW, BN, WGM, WGN, SB, NPB, NDW>(P, st);
+        SDCONV_PATCH_VARIANTS(SDCONV_PATCH_CASE)
+        default: return hipErrorInvalidValue;
+    }
+}
 
 hipError_t launch_conv_patch(int variant, const IgemmParams& P, hipStream_t st)
 {
-    const int key = variant * 2 + (P.mode ? 1 : 0);
-    switch (key) {
-        SDCONV_PATCH_CASE(0, 16, 16, 128, 4, 2, 3)
-        SDCONV_PATCH_CASE(1, 8, 16, 128, 2, 4, 4)
-        SDCONV_PATCH_CASE(2, 8, 16, 256, 2, 4, 3)
-        SDCONV_PATCH_CASE(3, 16, 16, 64, 4, 2, 4)
-        SDCONV_PATCH_CASE(4, 8, 32, 128, 4, 2, 3)
-        SDCONV_PATCH_CASE(5, 8, 16, 64, 4, 2, 4)
-        case 12: return launch_patch_variant<0, 16, 16, 128, 4, 2, 3, 16>(P, st);
-        case 13: return launch_patch_variant<1, 16, 16, 128, 4, 2, 3, 16>(P, st);
-        case 14: return launch_patch_variant<0, 8, 16, 128, 2, 4, 4, 16>(P, st);
-        case 15: return launch_patch_variant<1, 8, 16, 128, 2, 4, 4, 16>(P, st);
-        case 16: return launch_patch_variant<0, 16, 16, 64, 4, 2, 4, 16>(P, st);
-        case 17: return launch_patch_variant<1, 16, 16, 64, 4, 2, 4, 16>(P, st);
-        case 18: return launch_patch_variant<0, 8, 32, 128, 4, 2, 3, 16>(P, st);
-        case 19: return launch_patch_variant<1, 8, 32, 128, 4, 2, 3, 16>(P, st);
-        case 20: return launch_patch_variant<0, 10, 14, 128, 3, 2, 4, 16, 2>(P, st);
-        case 21: return launch_patch_variant<1, 10, 14, 128, 3, 2, 4, 16, 2>(P, st);
-        case 22: return launch_patch_variant<0, 10, 14, 64, 3, 2, 4, 16, 2>(P, st);
-        case 23: return launch_patch_variant<1, 10, 14, 64, 3, 2, 4, 16, 2>(P, st);
-        case 24: return launch_patch_variant<0, 10, 14, 128, 3, 4, 4, 16, 4>(P, st);
-        case 25: return launch_patch_variant<1, 10, 14, 128, 3, 4, 4, 16, 4>(P, st);
-        case 26: return launch_patch_variant<0, 10, 14, 64, 3, 2, 4, 16, 1>(P, st);
-        case 27: return launch_patch_variant<1, 10, 14, 64, 3, 2, 4, 16, 1>(P, st);
-        case 28: return launch_patch_variant<0, 10, 14, 64, 3, 2, 3, 16, 2, 3>(P, st);
-        case 29: return launch_patch_variant<1, 10, 14, 64, 3, 2, 3, 16, 2, 3>(P, st);
-        case 30: return launch_patch_variant<0, 10, 14, 128, 3, 4, 2, 16, 4, 3>(P, st);
-        case 31: return launch_patch_variant<1, 10, 14, 128, 3, 4, 2, 16, 4, 3>(P, st);
-        case 32: return launch_patch_variant<0, 10, 14, 128, 3, 2, 2, 16, 2, 3>(P, st);
-        case 33: return launch_patch_variant<1, 10, 14, 128, 3, 2, 2, 16, 2, 3>(P, st);
-        case 34: return launch_patch_variant<0, 16, 16, 64, 4, 2, 2, 16, 0, 3>(P, st);
-        case 35: return launch_patch_variant<1, 16, 16, 64, 4, 2, 2, 16, 0, 3>(P, st);
-        case 36: return launch_patch_variant<0, 10, 14, 64, 3, 4, 3, 16, 4, 3>(P, st);
-        case 37: return launch_patch_variant<1, 10, 14, 64, 3, 4, 3, 16, 4, 3>(P, st);
-        case 38: return launch_patch_variant<0, 10, 14, 64, 3, 2, 4, 16, 2, 3>(P, st);
-        case 39: return launch_patch_variant<1, 10, 14, 64, 3, 2, 4, 16, 2, 3>(P, st);
-        case 40: return launch_patch_variant<0, 16, 16, 64, 4, 2, 3, 16, 2, 3>(P, st);
-        case 41: return launch_patch_variant<1, 16, 16, 64, 4, 2, 3, 16, 2, 3>(P, st);
-        case 42: return launch_patch_variant<0, 8, 16, 128, 2, 4, 2, 16, 0, 3>(P, st);
-        case 43: return launch_patch_variant<1, 8, 16, 128, 2, 4, 2, 16, 0, 3>(P, st);
-        case 44: return launch_patch_variant<0, 16, 16, 64, 4, 2, 3, 16, 0, 1, 1>(P, st);
-        case 45: return launch_patch_variant<1, 16, 16, 64, 4, 2, 3, 16, 0, 1, 1>(P, st);
-        case 46: return launch_patch_variant<0, 16, 16, 64, 4, 2, 2, 16, 0, 3, 1>(P, st);
-        case 47: return launch_patch_variant<1, 16, 16, 64, 4, 2, 2, 16, 0, 3, 1>(P, st);
-        case 48: return launch_patch_variant<0, 10, 14, 64, 3, 2, 3, 16, 2, 1, 1>(P, st);
-        case 49: return launch_patch_variant<1, 10, 14, 64, 3, 2, 3, 16, 2, 1, 1>(P, st);
-        case 50: return launch_patch_variant<0, 10, 14, 64, 3, 2, 2, 16, 2, 3, 1>(P, st);
-        case 51: return launch_patch_variant<1, 10, 14, 64, 3, 2, 2, 16, 2, 3, 1>(P, st);
-        case 52: return launch_patch_variant<0, 8, 16, 64, 4, 2, 3, 16, 0, 1, 1>(P, st);
-        case 53: return launch_patch_variant<1, 8, 16, 64, 4, 2, 3, 16, 0, 1, 1>(P, st);
-        case 54: return launch_patch_variant<0, 8, 16, 64, 4, 2, 2, 16, 0, 3, 1>(P, st);
-        case 55: return launch_patch_variant<1, 8, 16, 64, 4, 2, 2, 16, 0, 3, 1>(P, st);
-        case 56: return launch_patch_variant<0, 10, 14, 64, 3, 2, 4, 16, 0, 3, 2, 2>(P, st);
-        case 57: return launch_patch_variant<1, 10, 14, 64, 3, 2, 4, 16, 0, 3, 2, 2>(P, st);
-        case 58: return launch_patch_variant<0, 10, 14, 64, 3, 2, 3, 16, 0, 3, 2, 2>(P, st);
-        case 59: return launch_patch_variant<1, 10, 14, 64, 3, 2, 3, 16, 0, 3, 2, 2>(P, st);
-        case 60: return launch_patch_variant<0, 10, 14, 128, 3, 4, 2, 16, 0, 3, 2, 4>(P, st);
-        case 61: return launch_patch_variant<1, 10, 14, 128, 3, 4, 2, 16, 0, 3, 2, 4>(P, st);
-        case 62: return launch_patch_variant<0, 10, 14, 128, 3, 2, 2, 16, 0, 3, 2, 2>(P, st);
-        case 63: return launch_patch_variant<1, 10, 14, 128, 3, 2, 2, 16, 0, 3, 2, 2>(P, st);
-        case 64: return launch_patch_variant<0, 16, 16, 64, 4, 2, 2, 16, 0, 3, 2, 2>(P, st);
-        case 65: return launch_patch_variant<1, 16, 16, 64, 4, 2, 2, 16, 0, 3, 2, 2>(P, st);
-        case 66: return launch_patch_variant<0, 10, 14, 64, 3, 2, 2, 16, 0, 3, 1, 2>(P, st);
-        case 67: return launch_patch_variant<1, 10, 14, 64, 3, 2, 2, 16, 0, 3, 1, 2>(P, st);
-        case 68: return launch_patch_variant<0, 10, 14, 64, 3, 2, 3, 16, 0, 1, 1, 2>(P, st);
-        case 69: return launch_patch_variant<1, 10, 14, 64, 3, 2, 3, 16, 0, 1, 1, 2>(P, st);
-        case 70: return launch_patch_variant<0, 10, 14, 64, 3, 2, 4, 16, 0, 3, 2, 4>(P, st);
-        case 71: return launch_patch_variant<1, 10, 14, 64, 3, 2, 4, 16, 0, 3, 2, 4>(P, st);
-        case 72: return launch_patch_variant<0, 8, 16, 64, 2, 2, 3, 16, 0, 3, 2, 4>(P, st);
-        case 73: return launch_patch_variant<1, 8, 16, 64, 2, 2, 3, 16, 0, 3, 2, 4>(P, st);
-        case 74: return launch_patch_variant<0, 8, 8, 64, 2, 2, 3, 16, 0, 3, 2, 4>(P, st);
-        case 75: return launch_patch_variant<1, 8, 8, 64, 2, 2, 3, 16, 0, 3, 2, 4>(P, st);
-        default: return hipErrorInvalidValue;
-    }
+    return P.mode ? launch_mode<1>(variant, P, st) : launch_mode<0>(variant, P, st);
 }
 
 }  // namespace sdconv

@@ -142,8 +142,8 @@ static bool patch_variant_ok(const Geom& g, bool dgrad, int v)
 {
     const PatchVariant& pv = kPatchVariants[v - 400];
     const int taps = g.R * g.S;
-    if (pv.one_slab && (dgrad ? g.K : g.C) != 64) return false;
-    return patch_ok(g, dgrad) && taps % pv.tps == 0 && taps / pv.tps >= pv.stages - 1;
+    if (!pv.fwd_name || (pv.one_slab && (dgrad ? g.K : g.C) != 64)) return false;
+    return patch_ok(g, dgrad) && taps % 3 == 0 && taps / 3 >= pv.stages - 1;
 }
 
 static const char* igemm_name(int v, bool dgrad)
@@ -338,12 +338,11 @@ static float row_us(const RowShape& s, const RowModel& m, float best)
 static int pick_variant(const Geom& g, bool dgrad)
 {
     if (!byte_offsets_fit_31_bits(g)) return (dgrad ? g.C : g.K) <= 64 ? 3 : 0;
-    int fv = forced_variant();
+    const int fv = forced_variant();
     if (fv >= 400 && fv < 400 + kNumPatchVariants && patch_variant_ok(g, dgrad, fv)) return fv;
-    if (fv >= 400) fv = -1;
-    if (fv >= 0 && fv < kNumIgemmVariants) return fv;
-    if (fv >= 100 && fv < 100 + kNumIgemmDmaVariants) return fv;
-    if (fv >= 300 && fv < 300 + kNumIgemmWsVariants) return ws_variant_for(g, dgrad, fv);
+    const bool known = (fv >= 0 && fv < kNumIgemmVariants) || (fv >= 100 && fv < 100 + kNumIgemmDmaVariants) ||
+                       (fv >= 300 && fv < 300 + kNumIgemmWsVariants);
+    if (known && (dgrad ? igemm_variant(fv).dgrad_name : igemm_variant(fv).fwd_name)) return ws_variant_for(g, dgrad, fv);
     int best = -1;
     float best_us = INFINITY;
     const RowShape shape = row_shape(g, dgrad);
@@ -351,8 +350,8 @@ static int pick_variant(const Geom& g, bool dgrad)
         const float us = row_us(shape, m, best_us);
         if (us >= 0.f && us < best_us) { best = m.variant; best_us = us; }
     };
-    // the data gradient of the variants below 300 wants a filter copy in the workspace: faster by 0.5 % over
-    // layers of any channel counts (by 0.02 % over a detector's), which is not worth the caller's memory
+    // the variants below 300 are forward kernels: a data gradient of that kind wants a filter copy in the
+    // workspace, and was faster by 0.5 % over layers of any channel counts (by 0.02 % over a detector's)
     for (const RowModel& m : kRowModels)
         if (m.variant < 300 ? !dgrad : m.variant < 400 || patch_variant_ok(g, dgrad, m.variant)) consider(m);
     static const RowModel kMixed = {324, 1, {}, {}, {}};        // its costs are those of its halves
@@ -424,7 +423,7 @@ Plan plan_dgrad(const Geom& g)
         return Plan{ROUTE_THIN, 0, 1, align256((size_t)g.K * g.R * g.S * g.C * sizeof(__half)), "thin_dgrad"};
     if (!igemm_ok(g) || g.sh * g.sw > kMaxClasses) return Plan{ROUTE_DIRECT, 0, 1, 0, "direct_dgrad"};
     int v = pick_variant(g, true);
-    // the older kernels want the filter transposed to [C][R][S][K] in the workspace; the
+    // the register-staged kernels want the filter transposed to [C][R][S][K] in the workspace; the
     // split-role and patch kernels read it as stored
     size_t ws = v >= 300 ? 0 : align256((size_t)g.K * g.R * g.S * g.C * sizeof(__half));
     return Plan{ROUTE_IGEMM, v, 1, ws, igemm_name(v, true)};
@@ -527,7 +526,7 @@ static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial
 static WgradChoice choose_wgrad(const Geom& g, size_t partial_limit)
 {
     const int fv = forced_wgrad_variant();
-    const bool forced = (fv >= 0 && fv < kNumWgradVariants) || (fv >= 100 && fv < 100 + kNumWgradDmaVariants);
+    const bool forced = (fv >= 0 && fv < kNumWgradVariants) || (fv >= 100 && fv < 100 + kNumWgradDmaVariants && wgrad_variant(fv).name);
     int only = forced ? fv : -1;
     const WgradEntry* e = nullptr;
     if (!wgrad_offsets_fit_31_bits(g)) only = g.K <= 64 ? 1 : 0;

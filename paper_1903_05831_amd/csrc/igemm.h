@@ -1,5 +1,6 @@
 // Parameters of the implicit-GEMM forward / data-gradient kernel.
 #pragma once
+#include <array>
 #include "common.h"
 
 namespace sdconv {
@@ -46,15 +47,17 @@ void set_taps(const Geom& g, bool dgrad, IgemmParams* P);      // the tap fields
 struct RowClasses { int n; unsigned pixels[kMaxClasses]; int taps[kMaxClasses]; };
 RowClasses row_classes(const Geom& g, bool dgrad);
 
+// Tile variants.  Their numbers are those of the committed timings and of the models fitted to them (fit_models.py);
+// numbers without a name are tiles that were measured and are not in the library.
 struct IgemmVariant { int bm, bn; const char* fwd_name; const char* dgrad_name; };
-constexpr int kNumIgemmVariants = 4;
-extern const IgemmVariant kIgemmVariants[kNumIgemmVariants];
+constexpr int kNumIgemmVariants = 4;            // register-staged, 0 and up
+extern const std::array<IgemmVariant, kNumIgemmVariants> kIgemmVariants;
 
-constexpr int kNumIgemmDmaVariants = 14;
-extern const IgemmVariant kIgemmDmaVariants[kNumIgemmDmaVariants];
+constexpr int kNumIgemmDmaVariants = 13;        // every wave fetches its share, 100 and up: forward passes only
+extern const std::array<IgemmVariant, kNumIgemmDmaVariants> kIgemmDmaVariants;
 hipError_t launch_igemm_dma(int variant, const IgemmParams& P, hipStream_t st);
-constexpr int kNumIgemmWsVariants = 41;
-extern const IgemmVariant kIgemmWsVariants[kNumIgemmWsVariants];
+constexpr int kNumIgemmWsVariants = 41;         // split roles, 300 and up
+extern const std::array<IgemmVariant, kNumIgemmWsVariants> kIgemmWsVariants;
 // Row tiles that a launch with two tile widths takes at full width: whole rounds of 256 workgroups
 // (rounded down to whole row tiles), or all of them where the rest would make two rounds of half tiles.
 inline long mixed_wide_rows(long row_tiles, int tiles_n)
@@ -64,11 +67,11 @@ inline long mixed_wide_rows(long row_tiles, int tiles_n)
 }
 hipError_t launch_igemm_ws(int variant, const IgemmParams& P, hipStream_t st);
 hipError_t launch_igemm_ws_f32(int variant, const IgemmParams& P, hipStream_t st);     // binary32 tensors
-struct PatchVariant { int th, tw, bn, tps, stages; const char* fwd_name; const char* dgrad_name; int one_slab = 0; };
-// tps: taps per pipeline step, must divide R*S, and R*S/tps must be at least stages-1;
+struct PatchVariant { int th, tw, bn, stages; const char* fwd_name; const char* dgrad_name; bool one_slab; };
+// stages: of the filter ring; a step is a filter row (three taps), so R*S must be a multiple of 3 and R*S/3 at least stages-1.
 // one_slab: the variant has a single patch buffer and takes layers with 64 source channels only
-constexpr int kNumPatchVariants = 38;
-extern const PatchVariant kPatchVariants[kNumPatchVariants];
+constexpr int kNumPatchVariants = 38;           // 400 and up
+extern const std::array<PatchVariant, kNumPatchVariants> kPatchVariants;
 hipError_t launch_conv_patch(int variant, const IgemmParams& P, hipStream_t st);
 hipError_t launch_igemm(int variant, const IgemmParams& P, int total_tiles, hipStream_t st);
 hipError_t launch_filter_transpose(const __half* w, __half* wT, int K, int RS, int C, hipStream_t st);

@@ -269,27 +269,18 @@ static hipError_t launch_variant(const IgemmParams& P, int total_tiles, hipStrea
     return hipGetLastError();
 }
 
-const IgemmVariant kIgemmVariants[kNumIgemmVariants] = {
-    {128, 128, "igemm_fwd_128x128", "igemm_dgrad_128x128"},
-    {256, 128, "igemm_fwd_256x128", "igemm_dgrad_256x128"},
-    {256, 64, "igemm_fwd_256x64", "igemm_dgrad_256x64"},
-    {128, 64, "igemm_fwd_128x64", "igemm_dgrad_128x64"},
-};
+const std::array<IgemmVariant, kNumIgemmVariants> kIgemmVariants = [] {
+    std::array<IgemmVariant, kNumIgemmVariants> v{};
+    v[0] = {128, 128, "igemm_fwd_128x128", "igemm_dgrad_128x128"};
+    v[3] = {128, 64, "igemm_fwd_128x64", "igemm_dgrad_128x64"};
+    return v;
+}();
 
 hipError_t launch_igemm(int variant, const IgemmParams& P, int total_tiles, hipStream_t st)
 {
-    const int key = variant * 2 + (P.mode ? 1 : 0);
-    switch (key) {
-        case 0: return launch_variant<0, 128, 128, 2, 2>(P, total_tiles, st);
-        case 1: return launch_variant<1, 128, 128, 2, 2>(P, total_tiles, st);
-        case 2: return launch_variant<0, 256, 128, 2, 2>(P, total_tiles, st);
-        case 3: return launch_variant<1, 256, 128, 2, 2>(P, total_tiles, st);
-        case 4: return launch_variant<0, 256, 64, 4, 1>(P, total_tiles, st);
-        case 5: return launch_variant<1, 256, 64, 4, 1>(P, total_tiles, st);
-        case 6: return launch_variant<0, 128, 64, 2, 2>(P, total_tiles, st);
-        case 7: return launch_variant<1, 128, 64, 2, 2>(P, total_tiles, st);
-        default: return hipErrorInvalidValue;
-    }
+    if (variant == 0) return P.mode ? launch_variant<1, 128, 128, 2, 2>(P, total_tiles, st) : launch_variant<0, 128, 128, 2, 2>(P, total_tiles, st);
+    if (variant == 3) return P.mode ? launch_variant<1, 128, 64, 2, 2>(P, total_tiles, st) : launch_variant<0, 128, 64, 2, 2>(P, total_tiles, st);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_filter_transpose(const __half* w, __half* wT, int K, int RS, int C, hipStream_t st)

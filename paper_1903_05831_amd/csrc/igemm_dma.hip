@@ -1,4 +1,4 @@
-// Implicit-GEMM forward / data-gradient kernel with an asynchronous global->LDS pipeline.
+// Implicit-GEMM forward kernel with an asynchronous global->LDS pipeline.
 //
 // Same mathematics and tile decomposition as igemm.hip (rows = pixels gathered on the fly,
 // columns = filters, contraction over taps x channels in steps of 64 halves), but the tiles
@@ -35,12 +35,12 @@ typedef float float16v __attribute__((ext_vector_type(16)));
 // Dynamic LDS of a variant: the ring and the tap tables, or the epilogue strips if those need more.
 template <int BM, int BN, int WGM, int WGN, int S, int BK> constexpr size_t dma_lds_bytes()
 {
-    constexpr size_t loop = (size_t)S * (BM + BN) * BK * 2 + (4 * kMaxTaps + 4) * sizeof(int);
+    constexpr size_t loop = (size_t)S * (BM + BN) * BK * 2 + 4 * kMaxTaps * sizeof(int);
     constexpr size_t strips = (size_t)WGM * WGN * epilogue_strip_bytes<BN / WGN>();
     return loop > strips ? loop : strips;
 }
 
-template <int MODE, int BM, int BN, int WGM, int WGN, int S, int BK, bool TAIL = false>
+template <int BM, int BN, int WGM, int WGN, int S, int BK, bool TAIL>
 __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(IgemmParams P)
 {
     constexpr int NW = WGM * WGN, NT = 64 * NW;
@@ -63,7 +63,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(IgemmParams P
     int* tap_ow = tap_oh + kMaxTaps;
     int* tap_bo = tap_ow + kMaxTaps;      // byte offset of the tap inside a filter row
     int* tap_ad = tap_bo + kMaxTaps;      // byte displacement of the tap in the source image
-    int* tap_cnt = tap_ad + kMaxTaps;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -71,53 +70,26 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(IgemmParams P
     const int wm = wave / WGN, wn = wave % WGN;
 
     // ---- which tile: workgroups go round-robin over the 8 XCDs; hand each XCD runs of kRun
-    // consecutive tiles (shared rows and halos meet in one L2) and interleave the runs, so
-    // that cheap and expensive parity classes of a strided dgrad spread over all XCDs ----
+    // consecutive tiles (shared rows and halos meet in one L2) and interleave the runs ----
     constexpr int kRun = 8;
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
     const int tile = ((idx / kRun) * 8 + xcd) * kRun + (idx % kRun);
     if (tile >= P.total_tiles) return;
     const int tn = tile % P.tiles_n;
-    int tm = tile / P.tiles_n;
-    int cls = 0;
-    while (cls + 1 < P.nclasses && tm >= P.class_tile_start[cls + 1]) ++cls;
-    tm -= P.class_tile_start[cls];
-    const int ca = cls / P.sw_cls, cb = cls % P.sw_cls;
-
-    int Hi, Wj, mh, mw, eh, ew;
-    if (MODE == 0) { Hi = P.Hd; Wj = P.Wd; mh = P.sh; mw = P.sw; eh = 1; ew = 1; }
-    else {
-        Hi = (P.Hd - ca + P.sh - 1) / P.sh; Wj = (P.Wd - cb + P.sw - 1) / P.sw;
-        mh = 1; mw = 1; eh = P.sh; ew = P.sw;
-    }
+    const int tm = tile / P.tiles_n;
+    const int Hi = P.Hd, Wj = P.Wd;
     const int Mcls = P.NB * Hi * Wj;
     const int m0 = tm * BM, n0 = tn * BN;
 
     // ---- tap table -------------------------------------------------------------------
-    if (wave == 0) {
-        const int ntap_all = P.R * P.S;
-        bool ok = false;
-        int oh = 0, ow = 0;
-        const int r = lane / P.S, s = lane % P.S;
-        if (lane < ntap_all) {
-            if (MODE == 0) { ok = true; oh = r * P.dh - P.ph; ow = s * P.dw - P.pw; }
-            else {
-                int th = ca + P.ph - r * P.dh, tw = cb + P.pw - s * P.dw;
-                ok = (th % P.sh == 0) && (tw % P.sw == 0);
-                oh = th / P.sh; ow = tw / P.sw;
-            }
-        }
-        unsigned long long mask = __ballot(ok);
-        int pos = __popcll(mask & ((1ull << lane) - 1ull));
-        if (ok) {
-            tap_oh[pos] = oh; tap_ow[pos] = ow;
-            tap_bo[pos] = (r * P.S + s) * P.Cs * 2;
-            tap_ad[pos] = (oh * P.Ws + ow) * P.Cs * 2;
-        }
-        if (lane == 0) tap_cnt[0] = __popcll(mask);
+    const int ntaps = P.R * P.S;
+    if (tid < ntaps) {
+        const int r = tid / P.S, s = tid % P.S, oh = r * P.dh - P.ph, ow = s * P.dw - P.pw;
+        tap_oh[tid] = oh; tap_ow[tid] = ow;
+        tap_bo[tid] = tid * P.Cs * 2;
+        tap_ad[tid] = (oh * P.Ws + ow) * P.Cs * 2;
     }
     __syncthreads();
-    const int ntaps = __builtin_amdgcn_readfirstlane(tap_cnt[0]);
     const int kchunks = (P.Cs + BK - 1) / BK;
     const int nk = ntaps * kchunks;
 
@@ -135,7 +107,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(IgemmParams P
             int n = m / (Hi * Wj);
             int rem = m - n * (Hi * Wj);
             int i = rem / Wj, j = rem - i * Wj;
-            int ih = i * mh, jw = j * mw;
+            int ih = i * P.sh, jw = j * P.sw;
             a_off[p] = (unsigned)((((n * P.Hs + ih) * P.Ws + jw) * P.Cs + kcl * 8) * 2);
             unsigned long long mk = 0ull;
             for (int t = 0; t < ntaps; ++t) {
@@ -235,76 +207,50 @@ __global__ __launch_bounds__(64 * WGM * WGN) void igemm_dma_kernel(IgemmParams P
     // (the strips may run over the tap tables behind the ring: those are dead by now)
     static_assert(NW * epilogue_strip_bytes<WN>() <= dma_lds_bytes<BM, BN, WGM, WGN, S, BK>(), "epilogue strips fit in LDS");
     stage_barrier();                                // everybody is done reading the last stage
-    store_tile_via_lds<FM, FN, 32, TAIL>(acc, smem + wave * epilogue_strip_bytes<WN>(), lane, m0 + wm * WM, n0 + wn * WN,
-                               Mcls, P, Hi, Wj, eh, ew, ca, cb);
+    store_rows_via_lds<FM, FN, 32, TAIL>(acc, smem + wave * epilogue_strip_bytes<WN>(), lane, n0 + wn * WN, P, [&](int r) -> unsigned {
+        const int m = m0 + wm * WM + r;
+        return m < Mcls ? (unsigned)(m * P.Cd) * 2u : kOutOfRange;
+    });
 }
 
-template <int MODE, int BM, int BN, int WGM, int WGN, int S, int BK, bool TAIL>
+template <int BM, int BN, int WGM, int WGN, int S, int BK, bool TAIL>
 static hipError_t launch_dma_variant_impl(const IgemmParams& P, hipStream_t st)
 {
     constexpr size_t lds = dma_lds_bytes<BM, BN, WGM, WGN, S, BK>();
     static_assert(lds <= 160 * 1024, "LDS budget");
     static std::atomic<bool> configured{false};   // set once the attribute call has succeeded; a second thread may repeat it, harmlessly
     if (!configured.load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&igemm_dma_kernel<MODE, BM, BN, WGM, WGN, S, BK, TAIL>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_dma_kernel<BM, BN, WGM, WGN, S, BK, TAIL>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
     }
     const int grid = ((P.total_tiles + 63) / 64) * 64;   // whole runs of 8 tiles on each of 8 XCDs
-    hipLaunchKernelGGL((igemm_dma_kernel<MODE, BM, BN, WGM, WGN, S, BK, TAIL>), dim3(grid), dim3(64 * WGM * WGN), lds, st, P);
+    hipLaunchKernelGGL((igemm_dma_kernel<BM, BN, WGM, WGN, S, BK, TAIL>), dim3(grid), dim3(64 * WGM * WGN), lds, st, P);
     return hipGetLastError();
 }
 
-template <int MODE, int BM, int BN, int WGM, int WGN, int S, int BK>
+template <int BM, int BN, int WGM, int WGN, int S, int BK>
 static hipError_t launch_dma_variant(const IgemmParams& P, hipStream_t st)
 {
     // the tail has kernels of its own: see store_rows_via_lds
-    return P.ep.any() ? launch_dma_variant_impl<MODE, BM, BN, WGM, WGN, S, BK, true>(P, st) : launch_dma_variant_impl<MODE, BM, BN, WGM, WGN, S, BK, false>(P, st);
+    return P.ep.any() ? launch_dma_variant_impl<BM, BN, WGM, WGN, S, BK, true>(P, st) : launch_dma_variant_impl<BM, BN, WGM, WGN, S, BK, false>(P, st);
 }
 
-const IgemmVariant kIgemmDmaVariants[kNumIgemmDmaVariants] = {
-    {128, 128, "igemm_fwd_dma_128x128x64_4w_s2", "igemm_dgrad_dma_128x128x64_4w_s2"},
-    {128, 128, "igemm_fwd_dma_128x128x32_4w_s3", "igemm_dgrad_dma_128x128x32_4w_s3"},
-    {128, 128, "igemm_fwd_dma_128x128x32_4w_s4", "igemm_dgrad_dma_128x128x32_4w_s4"},
-    {128, 128, "igemm_fwd_dma_128x128x32_4w_s5", "igemm_dgrad_dma_128x128x32_4w_s5"},
-    {256, 128, "igemm_fwd_dma_256x128x64_8w_s3", "igemm_dgrad_dma_256x128x64_8w_s3"},
-    {256, 128, "igemm_fwd_dma_256x128x32_8w_s3", "igemm_dgrad_dma_256x128x32_8w_s3"},
-    {128, 64, "igemm_fwd_dma_128x64x64_4w_s3", "igemm_dgrad_dma_128x64x64_4w_s3"},
-    {128, 64, "igemm_fwd_dma_128x64x32_4w_s4", "igemm_dgrad_dma_128x64x32_4w_s4"},
-    {256, 256, "igemm_fwd_dma_256x256x64_8w_s2", "igemm_dgrad_dma_256x256x64_8w_s2"},
-    {256, 256, "igemm_fwd_dma_256x256x32_8w_s3", "igemm_dgrad_dma_256x256x32_8w_s3"},
-    {256, 256, "igemm_fwd_dma_256x256x32_8w_s4", "igemm_dgrad_dma_256x256x32_8w_s4"},
-    {256, 256, "igemm_fwd_dma_256x256x32_8w_s4_w64x128", "igemm_dgrad_dma_256x256x32_8w_s4_w64x128"},
-    // shallower rings of the 128x64 tile: more workgroups per compute unit for the HBM-bound
-    // 1x1 layers of res2, whose contraction is two to eight steps long
-    {128, 64, "igemm_fwd_dma_128x64x32_4w_s2", "igemm_dgrad_dma_128x64x32_4w_s2"},
-    {128, 64, "igemm_fwd_dma_128x64x32_4w_s3", "igemm_dgrad_dma_128x64x32_4w_s3"},
-};
-
-#define SDCONV_DMA_CASE(idx, BM, BN, WGM, WGN, S, BK)                                         \
-    case 2 * (idx): return launch_dma_variant<0, BM, BN, WGM, WGN, S, BK>(P, st);             \
-    case 2 * (idx) + 1: return launch_dma_variant<1, BM, BN, WGM, WGN, S, BK>(P, st);
+// The tiles that are left are those of layers bound by HBM, with a contraction of few steps: rings so shallow that three
+// or five workgroups share a compute unit.
+const std::array<IgemmVariant, kNumIgemmDmaVariants> kIgemmDmaVariants = [] {
+    std::array<IgemmVariant, kNumIgemmDmaVariants> v{};
+    v[1] = {128, 128, "igemm_fwd_dma_128x128x32_4w_s3", nullptr};
+    v[12] = {128, 64, "igemm_fwd_dma_128x64x32_4w_s2", nullptr};
+    return v;
+}();
 
 hipError_t launch_igemm_dma(int variant, const IgemmParams& P, hipStream_t st)
 {
-    const int key = variant * 2 + (P.mode ? 1 : 0);
-    switch (key) {
-        SDCONV_DMA_CASE(0, 128, 128, 2, 2, 2, 64)
-        SDCONV_DMA_CASE(1, 128, 128, 2, 2, 3, 32)
-        SDCONV_DMA_CASE(2, 128, 128, 2, 2, 4, 32)
-        SDCONV_DMA_CASE(3, 128, 128, 2, 2, 5, 32)
-        SDCONV_DMA_CASE(4, 256, 128, 4, 2, 3, 64)
-        SDCONV_DMA_CASE(5, 256, 128, 4, 2, 3, 32)
-        SDCONV_DMA_CASE(6, 128, 64, 2, 2, 3, 64)
-        SDCONV_DMA_CASE(7, 128, 64, 2, 2, 4, 32)
-        SDCONV_DMA_CASE(8, 256, 256, 2, 4, 2, 64)
-        SDCONV_DMA_CASE(9, 256, 256, 2, 4, 3, 32)
-        SDCONV_DMA_CASE(10, 256, 256, 2, 4, 4, 32)
-        SDCONV_DMA_CASE(11, 256, 256, 4, 2, 4, 32)
-        SDCONV_DMA_CASE(12, 128, 64, 2, 2, 2, 32)
-        SDCONV_DMA_CASE(13, 128, 64, 2, 2, 3, 32)
+    switch (variant) {
+        case 1: return launch_dma_variant<128, 128, 2, 2, 3, 32>(P, st);
+        case 12: return launch_dma_variant<128, 64, 2, 2, 2, 32>(P, st);
         default: return hipErrorInvalidValue;
     }
 }

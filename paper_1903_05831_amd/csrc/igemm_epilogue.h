@@ -215,26 +215,4 @@ __device__ __forceinline__ void store_zero_subtile(int lane, int m_base, int col
     }
 }
 
-// Rows are GEMM rows m_base.. of an implicit-GEMM tile (pixels of one stride-parity class in
-// (n, i, j) order; eh/ew/ca/cb place class pixel (i, j) at (i*eh + ca, j*ew + cb)).
-template <int FM, int FN, int MF = 32, bool TAIL = false, typename Acc>
-__device__ __forceinline__ void store_tile_via_lds(Acc (&acc)[FN][FM], unsigned char* strip, int lane,
-                                                   int m_base, int col_base, int Mcls, const IgemmParams& P,
-                                                   int Hi, int Wj, int eh, int ew, int ca, int cb)
-{
-    const bool linear = (eh == 1 && ew == 1);       // destination pixel index == GEMM row index
-    store_rows_via_lds<FM, FN, MF, TAIL>(acc, strip, lane, col_base, P, [&](int r) -> unsigned {
-        const int m = m_base + r;
-        if (m >= Mcls) return kOutOfRange;
-        int pix = m;
-        if (!linear) {
-            const int n = m / (Hi * Wj);
-            const int rem = m - n * (Hi * Wj);
-            const int i = rem / Wj, jj = rem - i * Wj;
-            pix = (n * P.Hd + (i * eh + ca)) * P.Wd + (jj * ew + cb);
-        }
-        return (unsigned)(pix * P.Cd) * 2u;
-    });
-}
-
 }  // namespace sdconv

@@ -96,138 +96,53 @@ static hipError_t launch_ws_variant(const IgemmParams& P, hipStream_t st)
     return P.ep.any() ? launch_ws_variant_impl<MODE, BM, BN, WGM, WGN, S, BK, NP, MF, true>(P, st) : launch_ws_variant_impl<MODE, BM, BN, WGM, WGN, S, BK, NP, MF, false>(P, st);
 }
 
-const IgemmVariant kIgemmWsVariants[kNumIgemmWsVariants] = {
-    {128, 128, "igemm_fwd_ws_128x128x64_4w2f_s3", "igemm_dgrad_ws_128x128x64_4w2f_s3"},
-    {128, 128, "igemm_fwd_ws_128x128x64_4w2f_s4", "igemm_dgrad_ws_128x128x64_4w2f_s4"},
-    {256, 256, "igemm_fwd_ws_256x256x64_8w0f_s2", "igemm_dgrad_ws_256x256x64_8w0f_s2"},
-    {256, 128, "igemm_fwd_ws_256x128x64_8w2f_s3", "igemm_dgrad_ws_256x128x64_8w2f_s3"},
-    {128, 128, "igemm_fwd_ws_128x128x64_8w2f_s3", "igemm_dgrad_ws_128x128x64_8w2f_s3"},
-    {128, 128, "igemm_fwd_ws_128x128x64_8w0f_s3", "igemm_dgrad_ws_128x128x64_8w0f_s3"},
-    {256, 128, "igemm_fwd_ws_256x128x64_8w0f_s3", "igemm_dgrad_ws_256x128x64_8w0f_s3"},
-    {128, 64, "igemm_fwd_ws_128x64x64_4w2f_s4", "igemm_dgrad_ws_128x64x64_4w2f_s4"},
-    {128, 64, "igemm_fwd_ws_128x64x64_8w0f_s4", "igemm_dgrad_ws_128x64x64_8w0f_s4"},
-    {128, 256, "igemm_fwd_ws_128x256x64_8w0f_s3", "igemm_dgrad_ws_128x256x64_8w0f_s3"},
-    {224, 256, "igemm_fwd_ws_224x256x64_8w0f_s2_m16", "igemm_dgrad_ws_224x256x64_8w0f_s2_m16"},
-    {256, 256, "igemm_fwd_ws_256x256x64_8w0f_s2_m16", "igemm_dgrad_ws_256x256x64_8w0f_s2_m16"},
-    {128, 128, "igemm_fwd_ws_128x128x64_4w2f_s3_m16", "igemm_dgrad_ws_128x128x64_4w2f_s3_m16"},
-    {256, 128, "igemm_fwd_ws_256x128x64_8w2f_s3_m16", "igemm_dgrad_ws_256x128x64_8w2f_s3_m16"},
-    {256, 128, "igemm_fwd_ws_256x128x64_8w0f_s3_m16", "igemm_dgrad_ws_256x128x64_8w0f_s3_m16"},
-    {128, 256, "igemm_fwd_ws_128x256x64_8w0f_s3_m16", "igemm_dgrad_ws_128x256x64_8w0f_s3_m16"},
-    {224, 128, "igemm_fwd_ws_224x128x64_8w0f_s3_m16", "igemm_dgrad_ws_224x128x64_8w0f_s3_m16"},
-    {64, 64, "igemm_fwd_ws_64x64x64_4w2f_s4", "igemm_dgrad_ws_64x64x64_4w2f_s4"},
-    {64, 128, "igemm_fwd_ws_64x128x64_4w2f_s4", "igemm_dgrad_ws_64x128x64_4w2f_s4"},
-    {64, 64, "igemm_fwd_ws_64x64x64_4w2f_s4_m16", "igemm_dgrad_ws_64x64x64_4w2f_s4_m16"},
-    {64, 128, "igemm_fwd_ws_64x128x64_4w2f_s4_m16", "igemm_dgrad_ws_64x128x64_4w2f_s4_m16"},
-    {144, 128, "igemm_fwd_ws_144x128x64_6w2f_s3_m16", "igemm_dgrad_ws_144x128x64_6w2f_s3_m16"},
-    {144, 256, "igemm_fwd_ws_144x256x64_6w2f_s2_m16", "igemm_dgrad_ws_144x256x64_6w2f_s2_m16"},
-    {144, 64, "igemm_fwd_ws_144x64x64_3w2f_s4_m16", "igemm_dgrad_ws_144x64x64_3w2f_s4_m16"},
-    {224, 256, "igemm_fwd_ws_224x256x64_8w0f_s2_m16_tail128", "igemm_dgrad_ws_224x256x64_8w0f_s2_m16_tail128"},
-    {144, 64, "igemm_fwd_ws_144x64x64_3w4f_s4_m16", "igemm_dgrad_ws_144x64x64_3w4f_s4_m16"},
-    {144, 256, "igemm_fwd_ws_144x256x64_4w4f_s2_m16", "igemm_dgrad_ws_144x256x64_4w4f_s2_m16"},
-    {64, 64, "igemm_fwd_ws_64x64x64_4w4f_s4", "igemm_dgrad_ws_64x64x64_4w4f_s4"},
-    {64, 64, "igemm_fwd_ws_64x64x64_4w4f_s4_m16", "igemm_dgrad_ws_64x64x64_4w4f_s4_m16"},
-    {64, 128, "igemm_fwd_ws_64x128x64_4w4f_s4", "igemm_dgrad_ws_64x128x64_4w4f_s4"},
-    {128, 128, "igemm_fwd_ws_128x128x64_4w4f_s3", "igemm_dgrad_ws_128x128x64_4w4f_s3"},
-    {256, 128, "igemm_fwd_ws_256x128x64_8w4f_s3_m16", "igemm_dgrad_ws_256x128x64_8w4f_s3_m16"},
-    {224, 128, "igemm_fwd_ws_224x128x64_4w4f_s3_m16", "igemm_dgrad_ws_224x128x64_4w4f_s3_m16"},
-    {96, 128, "igemm_fwd_ws_96x128x64_4w4f_s4_m16", "igemm_dgrad_ws_96x128x64_4w4f_s4_m16"},
-    {80, 128, "igemm_fwd_ws_80x128x64_4w4f_s4_m16", "igemm_dgrad_ws_80x128x64_4w4f_s4_m16"},
-    {160, 128, "igemm_fwd_ws_160x128x64_4w4f_s3_m16", "igemm_dgrad_ws_160x128x64_4w4f_s3_m16"},
-    {192, 128, "igemm_fwd_ws_192x128x64_4w4f_s3_m16", "igemm_dgrad_ws_192x128x64_4w4f_s3_m16"},
-    {96, 64, "igemm_fwd_ws_96x64x64_4w4f_s4_m16", "igemm_dgrad_ws_96x64x64_4w4f_s4_m16"},
-    {160, 256, "igemm_fwd_ws_160x256x64_8w0f_s2_m16", "igemm_dgrad_ws_160x256x64_8w0f_s2_m16"},
-    {128, 128, "igemm_fwd_ws_128x128x64_4w4f_s2_m16", "igemm_dgrad_ws_128x128x64_4w4f_s2_m16"},
-    {128, 64, "igemm_fwd_ws_128x64x64_4w4f_s2", "igemm_dgrad_ws_128x64x64_4w4f_s2"},
-};
+// number - 300, tile, multiplying waves, ring stages, fetching waves, matrix block, name.  64- and 80-row tiles give every
+// compute unit a workgroup in layers with few pixels; 144 and 160 rows divide the pixels of the backbone's maps
+// into whole rounds of 256 where 128 and 256 do not, 224 those of the RoI head.
+#define SDCONV_WS_VARIANTS(X) \
+    X(10, 224, 256, 2, 4, 2, 0, 16, "224x256x64_8w0f_s2_m16") \
+    X(11, 256, 256, 2, 4, 2, 0, 16, "256x256x64_8w0f_s2_m16") \
+    X(16, 224, 128, 2, 4, 3, 0, 16, "224x128x64_8w0f_s3_m16") \
+    X(25, 144, 64, 3, 1, 4, 4, 16, "144x64x64_3w4f_s4_m16") \
+    X(26, 144, 256, 1, 4, 2, 4, 16, "144x256x64_4w4f_s2_m16") \
+    X(27, 64, 64, 2, 2, 4, 4, 32, "64x64x64_4w4f_s4") \
+    X(28, 64, 64, 2, 2, 4, 4, 16, "64x64x64_4w4f_s4_m16") \
+    X(29, 64, 128, 2, 2, 4, 4, 32, "64x128x64_4w4f_s4") \
+    X(30, 128, 128, 2, 2, 3, 4, 32, "128x128x64_4w4f_s3") \
+    X(31, 256, 128, 4, 2, 3, 4, 16, "256x128x64_8w4f_s3_m16") \
+    X(32, 224, 128, 2, 2, 3, 4, 16, "224x128x64_4w4f_s3_m16") \
+    X(33, 96, 128, 2, 2, 4, 4, 16, "96x128x64_4w4f_s4_m16") \
+    X(34, 80, 128, 1, 4, 4, 4, 16, "80x128x64_4w4f_s4_m16") \
+    X(35, 160, 128, 2, 2, 3, 4, 16, "160x128x64_4w4f_s3_m16") \
+    X(36, 192, 128, 2, 2, 3, 4, 16, "192x128x64_4w4f_s3_m16") \
+    X(37, 96, 64, 2, 2, 4, 4, 16, "96x64x64_4w4f_s4_m16") \
+    X(38, 160, 256, 2, 4, 2, 0, 16, "160x256x64_8w0f_s2_m16") \
+    X(39, 128, 128, 2, 2, 2, 4, 16, "128x128x64_4w4f_s2_m16") \
+    X(40, 128, 64, 2, 2, 2, 4, 32, "128x64x64_4w4f_s2")
 
-#define SDCONV_WS_CASE(idx, BM, BN, WGM, WGN, S, BK, NP)                                      \
-    case 2 * (idx): return launch_ws_variant<0, BM, BN, WGM, WGN, S, BK, NP>(P, st);          \
-    case 2 * (idx) + 1: return launch_ws_variant<1, BM, BN, WGM, WGN, S, BK, NP>(P, st);
+constexpr int kMixed = 24;      // 224x256 tiles for the whole rounds of 256 workgroups, 224x128 for the rest
+const std::array<IgemmVariant, kNumIgemmWsVariants> kIgemmWsVariants = [] {
+    std::array<IgemmVariant, kNumIgemmWsVariants> v{};
+#define SDCONV_WS_NAME(idx, BM, BN, WGM, WGN, S, NP, MF, name) v[idx] = {BM, BN, "igemm_fwd_ws_" name, "igemm_dgrad_ws_" name};
+    SDCONV_WS_VARIANTS(SDCONV_WS_NAME)
+    v[kMixed] = {224, 256, "igemm_fwd_ws_224x256x64_8w0f_s2_m16_tail128", "igemm_dgrad_ws_224x256x64_8w0f_s2_m16_tail128"};
+    return v;
+}();
+
+template <int MODE> static hipError_t launch_mode(int variant, const IgemmParams& P, hipStream_t st)
+{
+    switch (variant) {
+#define SDCONV_WS_CASE(idx, BM, BN, WGM, WGN, S, NP, MF, name) \
+        case idx: return launch_ws_variant<MODE, BM, BN, WGM, WGN, S, 64, NP, MF>(P, st);
+        SDCONV_WS_VARIANTS(SDCONV_WS_CASE)
+        case kMixed: return launch_ws_mixed<MODE, 224, 256, 128, 2, 4, 2, 3, 64, 16>(P, st);
+        default: return hipErrorInvalidValue;
+    }
+}
 
 hipError_t launch_igemm_ws(int variant, const IgemmParams& P, hipStream_t st)
 {
-    const int key = variant * 2 + (P.mode ? 1 : 0);
-    switch (key) {
-        SDCONV_WS_CASE(0, 128, 128, 2, 2, 3, 64, 2)
-        SDCONV_WS_CASE(1, 128, 128, 2, 2, 4, 64, 2)
-        SDCONV_WS_CASE(2, 256, 256, 2, 4, 2, 64, 0)
-        SDCONV_WS_CASE(3, 256, 128, 4, 2, 3, 64, 2)
-        SDCONV_WS_CASE(4, 128, 128, 2, 4, 3, 64, 2)
-        SDCONV_WS_CASE(5, 128, 128, 2, 4, 3, 64, 0)
-        SDCONV_WS_CASE(6, 256, 128, 4, 2, 3, 64, 0)
-        SDCONV_WS_CASE(7, 128, 64, 2, 2, 4, 64, 2)
-        SDCONV_WS_CASE(8, 128, 64, 4, 2, 4, 64, 0)
-        SDCONV_WS_CASE(9, 128, 256, 2, 4, 3, 64, 0)
-        case 20: return launch_ws_variant<0, 224, 256, 2, 4, 2, 64, 0, 16>(P, st);
-        case 21: return launch_ws_variant<1, 224, 256, 2, 4, 2, 64, 0, 16>(P, st);
-        case 22: return launch_ws_variant<0, 256, 256, 2, 4, 2, 64, 0, 16>(P, st);
-        case 23: return launch_ws_variant<1, 256, 256, 2, 4, 2, 64, 0, 16>(P, st);
-        case 24: return launch_ws_variant<0, 128, 128, 2, 2, 3, 64, 2, 16>(P, st);
-        case 25: return launch_ws_variant<1, 128, 128, 2, 2, 3, 64, 2, 16>(P, st);
-        case 26: return launch_ws_variant<0, 256, 128, 4, 2, 3, 64, 2, 16>(P, st);
-        case 27: return launch_ws_variant<1, 256, 128, 4, 2, 3, 64, 2, 16>(P, st);
-        case 28: return launch_ws_variant<0, 256, 128, 4, 2, 3, 64, 0, 16>(P, st);
-        case 29: return launch_ws_variant<1, 256, 128, 4, 2, 3, 64, 0, 16>(P, st);
-        case 30: return launch_ws_variant<0, 128, 256, 2, 4, 3, 64, 0, 16>(P, st);
-        case 31: return launch_ws_variant<1, 128, 256, 2, 4, 3, 64, 0, 16>(P, st);
-        case 32: return launch_ws_variant<0, 224, 128, 2, 4, 3, 64, 0, 16>(P, st);
-        case 33: return launch_ws_variant<1, 224, 128, 2, 4, 3, 64, 0, 16>(P, st);
-        // small tiles: layers with few pixels (res5 on a 25x42 map, fully connected heads) still
-        // give every compute unit a workgroup
-        case 34: return launch_ws_variant<0, 64, 64, 2, 2, 4, 64, 2>(P, st);
-        case 35: return launch_ws_variant<1, 64, 64, 2, 2, 4, 64, 2>(P, st);
-        case 36: return launch_ws_variant<0, 64, 128, 2, 2, 4, 64, 2>(P, st);
-        case 37: return launch_ws_variant<1, 64, 128, 2, 2, 4, 64, 2>(P, st);
-        case 38: return launch_ws_variant<0, 64, 64, 2, 2, 4, 64, 2, 16>(P, st);
-        case 39: return launch_ws_variant<1, 64, 64, 2, 2, 4, 64, 2, 16>(P, st);
-        case 40: return launch_ws_variant<0, 64, 128, 2, 2, 4, 64, 2, 16>(P, st);
-        case 41: return launch_ws_variant<1, 64, 128, 2, 2, 4, 64, 2, 16>(P, st);
-        // 144-row tiles (three wave rows of 48): the 8400 / 33600 / 134400 pixel rows of the backbone
-        // stages make 59 / 234 / 934 of them, which fill 256 compute units to 91-92 % where 128-row
-        // tiles fill 52-69 %
-        case 42: return launch_ws_variant<0, 144, 128, 3, 2, 3, 64, 2, 16>(P, st);
-        case 43: return launch_ws_variant<1, 144, 128, 3, 2, 3, 64, 2, 16>(P, st);
-        case 44: return launch_ws_variant<0, 144, 256, 3, 2, 2, 64, 2, 16>(P, st);
-        case 45: return launch_ws_variant<1, 144, 256, 3, 2, 2, 64, 2, 16>(P, st);
-        case 46: return launch_ws_variant<0, 144, 64, 3, 1, 4, 64, 2, 16>(P, st);
-        case 47: return launch_ws_variant<1, 144, 64, 3, 1, 4, 64, 2, 16>(P, st);
-        // 224 x 256 tiles for the whole rounds of 256 workgroups, 224 x 128 for the rest
-        case 48: return launch_ws_mixed<0, 224, 256, 128, 2, 4, 2, 3, 64, 16>(P, st);
-        case 49: return launch_ws_mixed<1, 224, 256, 128, 2, 4, 2, 3, 64, 16>(P, st);
-        case 50: return launch_ws_variant<0, 144, 64, 3, 1, 4, 64, 4, 16>(P, st);
-        case 51: return launch_ws_variant<1, 144, 64, 3, 1, 4, 64, 4, 16>(P, st);
-        case 52: return launch_ws_variant<0, 144, 256, 1, 4, 2, 64, 4, 16>(P, st);
-        case 53: return launch_ws_variant<1, 144, 256, 1, 4, 2, 64, 4, 16>(P, st);
-        case 54: return launch_ws_variant<0, 64, 64, 2, 2, 4, 64, 4, 32>(P, st);
-        case 55: return launch_ws_variant<1, 64, 64, 2, 2, 4, 64, 4, 32>(P, st);
-        case 56: return launch_ws_variant<0, 64, 64, 2, 2, 4, 64, 4, 16>(P, st);
-        case 57: return launch_ws_variant<1, 64, 64, 2, 2, 4, 64, 4, 16>(P, st);
-        case 58: return launch_ws_variant<0, 64, 128, 2, 2, 4, 64, 4, 32>(P, st);
-        case 59: return launch_ws_variant<1, 64, 128, 2, 2, 4, 64, 4, 32>(P, st);
-        case 60: return launch_ws_variant<0, 128, 128, 2, 2, 3, 64, 4, 32>(P, st);
-        case 61: return launch_ws_variant<1, 128, 128, 2, 2, 3, 64, 4, 32>(P, st);
-        case 62: return launch_ws_variant<0, 256, 128, 4, 2, 3, 64, 4, 16>(P, st);
-        case 63: return launch_ws_variant<1, 256, 128, 4, 2, 3, 64, 4, 16>(P, st);
-        case 64: return launch_ws_variant<0, 224, 128, 2, 2, 3, 64, 4, 16>(P, st);
-        case 65: return launch_ws_variant<1, 224, 128, 2, 2, 3, 64, 4, 16>(P, st);
-        case 66: return launch_ws_variant<0, 96, 128, 2, 2, 4, 64, 4, 16>(P, st);
-        case 67: return launch_ws_variant<1, 96, 128, 2, 2, 4, 64, 4, 16>(P, st);
-        case 68: return launch_ws_variant<0, 80, 128, 1, 4, 4, 64, 4, 16>(P, st);
-        case 69: return launch_ws_variant<1, 80, 128, 1, 4, 4, 64, 4, 16>(P, st);
-        case 70: return launch_ws_variant<0, 160, 128, 2, 2, 3, 64, 4, 16>(P, st);
-        case 71: return launch_ws_variant<1, 160, 128, 2, 2, 3, 64, 4, 16>(P, st);
-        case 72: return launch_ws_variant<0, 192, 128, 2, 2, 3, 64, 4, 16>(P, st);
-        case 73: return launch_ws_variant<1, 192, 128, 2, 2, 3, 64, 4, 16>(P, st);
-        case 74: return launch_ws_variant<0, 96, 64, 2, 2, 4, 64, 4, 16>(P, st);
-        case 75: return launch_ws_variant<1, 96, 64, 2, 2, 4, 64, 4, 16>(P, st);
-        case 76: return launch_ws_variant<0, 160, 256, 2, 4, 2, 64, 0, 16>(P, st);
-        case 77: return launch_ws_variant<1, 160, 256, 2, 4, 2, 64, 0, 16>(P, st);
-        case 78: return launch_ws_variant<0, 128, 128, 2, 2, 2, 64, 4, 16>(P, st);
-        case 79: return launch_ws_variant<1, 128, 128, 2, 2, 2, 64, 4, 16>(P, st);
-        case 80: return launch_ws_variant<0, 128, 64, 2, 2, 2, 64, 4, 32>(P, st);
-        case 81: return launch_ws_variant<1, 128, 64, 2, 2, 2, 64, 4, 32>(P, st);
-        default: return hipErrorInvalidValue;
-    }
+    return P.mode ? launch_mode<1>(variant, P, st) : launch_mode<0>(variant, P, st);
 }
 
 }  // namespace sdconv

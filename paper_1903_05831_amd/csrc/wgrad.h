@@ -1,5 +1,6 @@
 // Parameters of the split-K weight-gradient kernels.
 #pragma once
+#include <array>
 #include "common.h"
 
 namespace sdconv {
@@ -22,8 +23,8 @@ struct WgradVariant { int bm, bn; const char* name; };
 constexpr int kNumWgradVariants = 2;
 extern const WgradVariant kWgradVariants[kNumWgradVariants];
 
-constexpr int kNumWgradDmaVariants = 21;
-extern const WgradVariant kWgradDmaVariants[kNumWgradDmaVariants];
+constexpr int kNumWgradDmaVariants = 20;        // pipelined, 100 and up; numbers without a name: measured, not in the library
+extern const std::array<WgradVariant, kNumWgradDmaVariants> kWgradDmaVariants;
 hipError_t launch_wgrad_dma(int variant, const WgradParams& P, hipStream_t st);
 hipError_t launch_wgrad(int variant, const WgradParams& P, hipStream_t st);
 

@@ -36,7 +36,7 @@ typedef float float4w __attribute__((ext_vector_type(4)));
 // in the burst of LDS-DMA instructions, instead of both stalling at once (see igemm_ws.hip).
 // MF: 32 = v_mfma_f32_32x32x16_f16 blocks, 16 = v_mfma_f32_16x16x32_f16 blocks (measured faster
 // on the large tiles).
-template <int BM, int BN, int WGM, int WGN, int S, int BP, bool LINEAR, bool HF, int MF = 32>
+template <int BM, int BN, int WGM, int WGN, int S, int BP, bool LINEAR, bool HF, int MF>
 __global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P)
 {
     constexpr int NW = WGM * WGN;
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, int S, int BP, bool HF = false, int MF = 32>
+template <int BM, int BN, int WGM, int WGN, int S, int BP, bool HF, int MF>
 static hipError_t launch_wdma(const WgradParams& P0, hipStream_t st)
 {
     constexpr size_t lds = (size_t)S * BP * (BM + BN) * 2 + (size_t)S * BP * sizeof(unsigned);
@@ -297,54 +297,32 @@ static hipError_t launch_wdma(const WgradParams& P0, hipStream_t st)
     return hipGetLastError();
 }
 
-const WgradVariant kWgradDmaVariants[kNumWgradDmaVariants] = {
-    {128, 128, "wgrad_dma_128x128x64_4w_s2"},
-    {128, 128, "wgrad_dma_128x128x32_4w_s3"},
-    {256, 256, "wgrad_dma_256x256x64_8w_s2"},
-    {256, 256, "wgrad_dma_256x256x32_8w_s3"},
-    {64, 128, "wgrad_dma_64x128x64_4w_s3"},
-    {256, 128, "wgrad_dma_256x128x32_8w_s3"},
-    {64, 256, "wgrad_dma_64x256x64_4w_s2"},
-    {64, 64, "wgrad_dma_64x64x64_4w_s3"},
-    {128, 64, "wgrad_dma_128x64x64_4w_s3"},
-    {256, 256, "wgrad_dma_256x256x64_8w_s2_hf"},
-    {256, 256, "wgrad_dma_256x256x32_8w_s3_hf"},
-    {256, 128, "wgrad_dma_256x128x32_8w_s3_hf"},
-    {128, 128, "wgrad_dma_128x128x64_8w_s3_hf"},
-    {256, 128, "wgrad_dma_256x128x64_8w_s3_hf"},
-    {256, 256, "wgrad_dma_256x256x64_8w_s2_hf_m16"},
-    {256, 256, "wgrad_dma_256x256x32_8w_s3_hf_m16"},
-    {128, 128, "wgrad_dma_128x128x64_8w_s3_hf_m16"},
-    {256, 128, "wgrad_dma_256x128x64_8w_s3_hf_m16"},
-    {64, 64, "wgrad_dma_64x64x64_4w_s3_m16"},
-    {128, 128, "wgrad_dma_128x128x64_4w_s2_m16"},
-    {64, 128, "wgrad_dma_64x128x64_4w_s3_m16"},
-};
+// number - 100, tile, waves, ring stages, pixels of a step, upper half fetches, matrix block, name
+#define SDCONV_WGRAD_VARIANTS(X) \
+    X(4, 64, 128, 1, 4, 3, 64, false, 32, "wgrad_dma_64x128x64_4w_s3") \
+    X(7, 64, 64, 2, 2, 3, 64, false, 32, "wgrad_dma_64x64x64_4w_s3") \
+    X(8, 128, 64, 2, 2, 3, 64, false, 32, "wgrad_dma_128x64x64_4w_s3") \
+    X(12, 128, 128, 2, 4, 3, 64, true, 32, "wgrad_dma_128x128x64_8w_s3_hf") \
+    X(14, 256, 256, 2, 4, 2, 64, true, 16, "wgrad_dma_256x256x64_8w_s2_hf_m16") \
+    X(15, 256, 256, 2, 4, 3, 32, true, 16, "wgrad_dma_256x256x32_8w_s3_hf_m16") \
+    X(16, 128, 128, 2, 4, 3, 64, true, 16, "wgrad_dma_128x128x64_8w_s3_hf_m16") \
+    X(17, 256, 128, 4, 2, 3, 64, true, 16, "wgrad_dma_256x128x64_8w_s3_hf_m16") \
+    X(18, 64, 64, 2, 2, 3, 64, false, 16, "wgrad_dma_64x64x64_4w_s3_m16") \
+    X(19, 128, 128, 2, 2, 2, 64, false, 16, "wgrad_dma_128x128x64_4w_s2_m16")
+
+const std::array<WgradVariant, kNumWgradDmaVariants> kWgradDmaVariants = [] {
+    std::array<WgradVariant, kNumWgradDmaVariants> v{};
+#define SDCONV_WGRAD_NAME(idx, BM, BN, WGM, WGN, S, BP, HF, MF, name) v[idx] = {BM, BN, name};
+    SDCONV_WGRAD_VARIANTS(SDCONV_WGRAD_NAME)
+    return v;
+}();
 
 hipError_t launch_wgrad_dma(int variant, const WgradParams& P, hipStream_t st)
 {
     switch (variant) {
-        case 0: return launch_wdma<128, 128, 2, 2, 2, 64>(P, st);
-        case 1: return launch_wdma<128, 128, 2, 2, 3, 32>(P, st);
-        case 2: return launch_wdma<256, 256, 2, 4, 2, 64>(P, st);
-        case 3: return launch_wdma<256, 256, 2, 4, 3, 32>(P, st);
-        case 4: return launch_wdma<64, 128, 1, 4, 3, 64>(P, st);
-        case 5: return launch_wdma<256, 128, 4, 2, 3, 32>(P, st);
-        case 6: return launch_wdma<64, 256, 1, 4, 2, 64>(P, st);
-        case 7: return launch_wdma<64, 64, 2, 2, 3, 64>(P, st);
-        case 8: return launch_wdma<128, 64, 2, 2, 3, 64>(P, st);
-        case 9: return launch_wdma<256, 256, 2, 4, 2, 64, true>(P, st);
-        case 10: return launch_wdma<256, 256, 2, 4, 3, 32, true>(P, st);
-        case 11: return launch_wdma<256, 128, 4, 2, 3, 32, true>(P, st);
-        case 12: return launch_wdma<128, 128, 2, 4, 3, 64, true>(P, st);
-        case 13: return launch_wdma<256, 128, 4, 2, 3, 64, true>(P, st);
-        case 14: return launch_wdma<256, 256, 2, 4, 2, 64, true, 16>(P, st);
-        case 15: return launch_wdma<256, 256, 2, 4, 3, 32, true, 16>(P, st);
-        case 16: return launch_wdma<128, 128, 2, 4, 3, 64, true, 16>(P, st);
-        case 17: return launch_wdma<256, 128, 4, 2, 3, 64, true, 16>(P, st);
-        case 18: return launch_wdma<64, 64, 2, 2, 3, 64, false, 16>(P, st);
-        case 19: return launch_wdma<128, 128, 2, 2, 2, 64, false, 16>(P, st);
-        case 20: return launch_wdma<64, 128, 1, 4, 3, 64, false, 16>(P, st);
+#define SDCONV_WGRAD_CASE(idx, BM, BN, WGM, WGN, S, BP, HF, MF, name) \
+        case idx: return launch_wdma<BM, BN, WGM, WGN, S, BP, HF, MF>(P, st);
+        SDCONV_WGRAD_VARIANTS(SDCONV_WGRAD_CASE)
         default: return hipErrorInvalidValue;
     }
 }

@@ -70,7 +70,6 @@ ROW_VARIANTS = [101, 112, 310, 311, 316, 324] + list(range(325, 341)) + [427, 43
 ROW_MODELS = [v for v in ROW_VARIANTS if v != 324]
 WGRAD_MODELS = [104, 107, 108, 112, 114, 115, 116, 117, 118, 119]
 ONE_SLAB = {427, 433}                    # one patch buffer: 64 contraction channels only
-WGRAD_VARIANTS = [100, 104, 107, 108, 109, 112, 113, 114, 115, 116, 117, 118, 119, 120]
 WORKGROUPS = (40, 64, 96, 128, 192, 256, 320, 384, 512, 768, 1024)
 
 
@@ -169,7 +168,7 @@ def measure(what: str, seed: int, seconds: float, path: str) -> None:
                         labels.append(v)
                 else:
                     total = -(-N * ho * wo // 64)
-                    for v in WGRAD_VARIANTS:
+                    for v in WGRAD_MODELS:
                         bm, bn, _ = WGRAD_TILES[v]
                         tiles = -(-K // bm) * -(-C // bn) * R * R
                         for ranges in sorted({ranges_made(total, r) for r in

@@ -8,7 +8,7 @@ import subprocess
 import pytest
 
 import paper_1903_05831_amd as sd
-from paper_1903_05831_amd import build
+from paper_1903_05831_amd import build, fit_models
 
 LLVM = os.path.join(os.path.dirname(os.path.dirname(build.HIPCC)), "llvm", "bin")
 LINE = re.compile(r"^\t(\S+)(.*?)\s*// ([0-9A-F]+):.*?(?:<(\S+?)(?:\+0x([0-9a-fA-F]+))?>)?$")
@@ -85,3 +85,28 @@ def test_barriers_of_lds_dma_kernels_are_reached_with_no_lds_read_on_its_way(cod
                 bad += [(name, hex(a)) for a in _reads_at_barriers(body)]
     assert kernels > 40
     assert not bad, bad
+
+
+def test_no_kernel_spills_registers_or_uses_scratch_memory(code_objects):
+    kernels = 0
+    for path in code_objects:
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", path], check=True, capture_output=True, text=True).stdout
+        for kernel in notes.split("- .agpr_count")[1:]:
+            field = {k: v for k, v in re.findall(r"\.(\w+):\s+(\S+)", kernel)}
+            assert field["vgpr_spill_count"] == "0" and field["private_segment_fixed_size"] == "0", (field["name"], field)
+            kernels += 1
+    assert kernels > 100
+
+
+def test_the_library_holds_the_variants_that_can_be_chosen(monkeypatch):
+    """Those of the time models and of the rule for large tensors (0, 3; 0, 1), and no others."""
+    d, known = sd.make_desc(1, 28, 28, 64, 64, 3, 3, (1, 1), (1, 1)), set()
+    for env, variants, passes in (("SDCONV_IGEMM_VARIANT", [0, 3] + fit_models.ROW_VARIANTS, (sd.FWD, sd.DGRAD)),
+                                  ("SDCONV_WGRAD_VARIANT", [0, 1] + fit_models.WGRAD_MODELS, (sd.WGRAD,))):
+        for v in variants:
+            monkeypatch.setenv(env, str(v))
+            known |= {sd.kernel_name(d, p) for p in passes}
+        monkeypatch.delenv(env)
+    with open(build.LIB, "rb") as f:
+        names = re.findall(rb"(?<=\0)((?:igemm_(?:fwd|dgrad)|conv_(?:fwd|dgrad)_patch|wgrad(?:_dma)?)_[a-z0-9_]*\d+x\d+[a-z0-9_]*)(?=\0)", f.read())
+    assert {n.decode() for n in names} == known

@@ -104,7 +104,7 @@ FUSED_WS_SHAPES = [
     (2, 23, 29, 64, 72, 3, 3, (2, 2), (1, 1), (1, 1)),
     (1, 31, 37, 136, 264, 1, 1, (1, 1), (0, 0), (1, 1)),
 ]
-OLD_VARIANTS = [0, 1, 2, 3] + list(range(100, 112))
+OLD_VARIANTS = [0, 3, 101, 112]
 
 
 @pytest.mark.parametrize("variant", OLD_VARIANTS + WS_VARIANTS)

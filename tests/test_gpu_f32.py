@@ -27,7 +27,7 @@ FRO_TOL_F32 = 2e-5
 F32_TILES = 11          # tiles of the forward / data-gradient kernels
 
 
-def _compare(got, ref, what, nterms, term_rms):
+def _compare(got, ref, what, nterms, term_rms, fro_tol=FRO_TOL_F32):
     g, r = got.astype(np.float64).ravel(), ref.ravel()
     assert np.all(np.isfinite(g)), f"{what}: non-finite output"
     err = np.abs(g - r)
@@ -36,12 +36,12 @@ def _compare(got, ref, what, nterms, term_rms):
     rn = np.linalg.norm(r)
     fro = np.linalg.norm(g - r) / (rn if rn > 0 else 1.0)
     say(f"    {what}: max err/bound {float(np.max(err / bound)):.3f}, max err / (2^-23 n t) "
-        f"{float(err.max() / (2.0 ** -23 * nterms * term_rms)):.3f}, Frobenius {fro:.2e} (bar {FRO_TOL_F32:.0e})")
+        f"{float(err.max() / (2.0 ** -23 * nterms * term_rms)):.3f}, Frobenius {fro:.2e} (bar {fro_tol:.1e})")
     assert err[worst] <= bound[worst], f"{what}: element {worst} gpu={g[worst]!r} ref={r[worst]!r}"
-    assert fro <= FRO_TOL_F32, f"{what}: Frobenius"
+    assert fro <= fro_tol, f"{what}: Frobenius"
 
 
-def _check(d, x, w, g, tag, sample=None, seed=0, layer=None):
+def _check(d, x, w, g, tag, sample=None, seed=0, layer=None, fro_tol=FRO_TOL_F32):
     od = oracle_desc(d)
     ho, wo = sd.conv2d_out_shape(d)
     st = torch.cuda.current_stream().cuda_stream
@@ -62,11 +62,11 @@ def _check(d, x, w, g, tag, sample=None, seed=0, layer=None):
         assert out.all_written(), f"{what}: some output elements were never written"
         got = out.numpy()
         if sample is None:
-            _compare(got, ofn(od, an, bn), what, nterms, term_rms)
+            _compare(got, ofn(od, an, bn), what, nterms, term_rms, fro_tol)
         else:
             idx = (workloads.stratified_indices(layer, pid, seed) if layer is not None
                    else workloads.sample_indices(got.size, sample, seed + pid))
-            _compare(got.ravel()[idx], ofn(od, an, bn, idx=idx), what + f" ({idx.size} samples)", nterms, term_rms)
+            _compare(got.ravel()[idx], ofn(od, an, bn, idx=idx), what + f" ({idx.size} samples)", nterms, term_rms, fro_tol)
 
 
 def _rand32(N, H, W, C, K, R, S, stride, pad, dil, seed):
@@ -99,12 +99,16 @@ def test_f32_small_shapes_full_tensor(case):
     _check(d, x, w, g, f"f32{case}")
 
 
-# a tile's rows and columns with remainders, a contraction that ends inside a step, classes without taps
+# a tile's rows and columns with remainders, a contraction that ends inside a step, classes without taps, more than 32
+# taps, with a short last slab or in classes of 9 to 16, strides and dilations without a common factor
 TILE_SHAPES = [
     (1, 13, 17, 36, 164, 3, 3, (1, 1), (1, 1), (1, 1)),
     (2, 15, 14, 132, 68, 3, 3, (2, 2), (1, 1), (1, 1)),
     (1, 20, 25, 64, 100, 1, 1, (2, 2), (0, 0), (1, 1)),
     (1, 1, 2, 4, 4, 1, 1, (1, 1), (0, 0), (1, 1)),
+    (1, 17, 19, 36, 64, 7, 7, (1, 1), (3, 3), (1, 1)),
+    (1, 17, 19, 64, 36, 7, 7, (2, 2), (3, 3), (1, 1)),
+    (1, 20, 23, 64, 64, 3, 5, (3, 2), (1, 2), (2, 3)),
 ]
 
 
@@ -126,6 +130,28 @@ def test_f32_weight_gradient_tiles(tile, ranges, monkeypatch):
         say(f"f32 weight-gradient tile {tile} ranges {ranges} case {case}")
         d, x, w, g = _rand32(*case, seed=sum(case[:7]) + tile + ranges)
         _check(d, x, w, g, f"f32wgrad{tile}x{ranges}{case}")
+
+
+def _folded_bar(products):
+    """Twice the error, relative in the 2-norm, that sums of random terms have when every 64 products (32 additions of two)
+    are added to a sum of their own.  The i-th addition of a chain rounds a value of size sqrt(i) with an error of 2^-24
+    x 0.41 (rms over the mantissas), so a chain of n additions is off by 2^-24 x 0.41 x sqrt(n / 2) of its result: the
+    64 products and the products / 64 sums each contribute that.  One chain would have products / 2 additions: 2.3 to 2.7
+    times this bar for the contractions below."""
+    return 2 * 2.0 ** -24 * 0.41 * np.sqrt(32 / 2 + products / 64 / 2)
+
+
+@pytest.mark.parametrize("tile", list(range(3)) + list(range(100, 104)))
+def test_f32_sums_are_folded(tile, monkeypatch):
+    """Long contractions in one range: 3x3 over 512 channels and filters (4608 products), and, for the weight
+    gradient, 16 384 pixels.  (The 64x32 and 32x32 tiles divide the products among their waves besides.)"""
+    monkeypatch.setenv("SDCONV_F32_TILE", str(tile))
+    monkeypatch.setenv("SDCONV_WGRAD_SPLITS", "1")
+    case, products = (((1, 24, 40, 512, 512, 3, 3, (1, 1), (1, 1), (1, 1)), 9 * 512) if tile < 100 else
+                      ((1, 128, 128, 64, 64, 1, 1, (1, 1), (0, 0), (1, 1)), 128 * 128))
+    say(f"f32 folded sums tile {tile} case {case}")
+    d, x, w, g = _rand32(*case, seed=77 + tile)
+    _check(d, x, w, g, f"f32fold{tile}", sample=4000, seed=5, fro_tol=_folded_bar(products))
 
 
 def _distinct_backbone_and_head_shapes():

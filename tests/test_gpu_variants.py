@@ -97,7 +97,8 @@ def test_split_role_kernel_variants(variant):
 # How the split-role kernels count through the taps that meet a parity class: more than 32 taps (with a
 # short last channel slab, and in classes of 9 to 16 taps), strides and dilations with and without a common
 # factor (classes with no taps along one axis, or with every other one), a 1x1 filter that is
-# padded or has a short slab; tiles with waves that only fetch, and 224-row ones without.
+# padded or has a short slab.  Tiles without waves that only fetch (310), with such waves that divide the activation
+# loads of a stage evenly (327, 337, 340) and with one pass of them that has activation and filter loads (325, 326, 334).
 TAP_GRIDS = [
     (1, 17, 19, 72, 64, 7, 7, (1, 1), (3, 3), (1, 1)),
     (1, 17, 19, 64, 72, 7, 7, (2, 2), (3, 3), (1, 1)),
@@ -109,7 +110,7 @@ TAP_GRIDS = [
 ]
 
 
-@pytest.mark.parametrize("variant", [310, 327, 334, 337])
+@pytest.mark.parametrize("variant", [310, 325, 326, 327, 334, 337, 340])
 def test_tap_grids_of_split_role_kernels(variant):
     for case in TAP_GRIDS:
         say(f"tap grid variant {variant} case {case}")

@@ -79,6 +79,8 @@ def main() -> int:
                          "per-kernel hardware-counter runs")
     ap.add_argument("--passes", type=str, default="fwd", help="with --layer: comma-separated fwd,dgrad,wgrad")
     ap.add_argument("--detail", type=str, default="", help="write per-layer timings (JSON) to this file")
+    ap.add_argument("--report", type=str, default="",
+                    help="write every figure (JSON) to this file; the line that is printed leaves out those by kernel and by layer")
     ap.add_argument("--calib-copy-mib", type=int, default=0,
                     help="run one plain streaming kernel over this many MiB first (a known-size reference "
                          "dispatch for scaling FETCH_SIZE / WRITE_SIZE counters)")
@@ -691,8 +693,29 @@ def main() -> int:
     if args.detail:
         with open(args.detail, "w") as f:
             json.dump(per_call, f, indent=1)
-    print(json.dumps(out))
+    if args.report:
+        with open(args.report, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(printed(out)))
     return 0
+
+
+def printed(out: dict) -> dict:
+    """The figures that fit a line of some 5 KB (readers keep the end of the output only), to five digits."""
+    def short(v):
+        if isinstance(v, float):
+            return float("%.5g" % v)
+        if isinstance(v, dict):
+            return {k: short(x) for k, x in v.items()}
+        return [short(x) for x in v] if isinstance(v, list) else v
+    out = {k: v for k, v in out.items() if k not in ("kernels", "hbm_bound_layers_hot_cold")}
+    out["roofline"] = {k: v for k, v in out["roofline"].items() if k != "next_kernels"}
+    out["res3_res4_3x3_isolated"] = {k: v for k, v in out["res3_res4_3x3_isolated"].items() if k != "distinct_layers"}
+    if out["second_workload"]:
+        out["second_workload"] = {k: v for k, v in out["second_workload"].items() if k != "groups"}
+    if out["per_config"]:
+        out["per_config"] = [{k: v for k, v in c.items() if k not in ("workload", "oracle_sample")} for c in out["per_config"]]
+    return short(out)
 
 
 def cpu_baseline() -> dict:

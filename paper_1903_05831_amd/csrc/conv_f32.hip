@@ -472,8 +472,9 @@ static void f32_staged_wgrad_shape(const Geom& g, int* bm, int* bn, int* splits,
 // Tiles of the split-role weight gradient and their times, as for the tiles below; partial sums and dw are
 // stored at `store` MB/us and added at kF32ReduceRate, after kF32ReduceFixed for the second kernel.  Fitted to 162
 // layers: on layers left out 1.7 % slower than the fastest pair of tile and ranges (5.8 % at the 90th
-// percentile).  Large layers run at 140 TFLOP/s, where the register-staged kernel with two workgroups a
-// compute unit ran at 70 to 95.
+// percentile).  Layers of 20 GFLOP and more run at 103 to 135 TFLOP/s where they are pointwise (a 128x128x32 step
+// takes 1.9-2.1 us) and at 79 to 109 where pixels are gathered (2.5-2.8 us; one `step` serves both, so the
+// choice leans a little away from that tile in pointwise layers); the register-staged kernel ran at 70 to 95.
 struct F32WgradTile { int bm, bn, per_cu; float step, shared, tile, fixed, store; };
 static const F32WgradTile kF32WgradTiles[] = {
     {128, 128, 2, 2.209f, 2.224f, 0.056f, 4.515f, 2.655f},

@@ -1,8 +1,9 @@
 // Weight gradient on binary32 tensors with waves that only fetch: the tiles and LDS layout of wgrad_f32_kernel
 // (conv_f32.hip), [pixel][channel] with the columns of odd pixels XOR 32, filled by LDS-DMA through a
 // ring of S stages.  The staged kernel divided twice for every load and waited for its loads once a step; here a
-// lane divides once a step.  Bound by the matrix pipe in large layers (140 TFLOP/s), in small ones by the partial sums of
-// its pixel ranges: one workgroup a compute unit keeps the pipe as busy as two did, so there are fewer ranges.
+// lane divides once a step.  Bound by the matrix pipe in large layers (103-135 TFLOP/s pointwise, 79-109 where pixels
+// are gathered), in small ones by the partial sums of its pixel ranges: one workgroup a compute unit keeps the
+// pipe as busy as two did, so there are fewer ranges.
 // Chains are folded every 64 pixels, or the longer ranges would double the error (res4: 3.2e-7 -> 6.9e-7; now 1.7e-7).
 #include "common.h"
 #include "dma.h"

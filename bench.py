@@ -293,8 +293,8 @@ def main() -> int:
 
     # dominant kernel: largest share of the step among the calls that are exactly one kernel per
     # event pair: every forward call but the stem's and those on padded copies, and the data-gradient
-    # calls of the split-role, patch and narrow kernels (the older data-gradient path and the weight gradient
-    # launch a filter copy or a reduction beside their main kernel)
+    # calls of the split-role, patch and narrow kernels (the register-staged data gradient and the weight
+    # gradient launch a filter copy or a reduction beside their main kernel)
     def single_kernel(name, g):
         if g["pass"] == "fwd":
             return not name.startswith(("thin", "padk"))

@@ -35,7 +35,7 @@
  *     device-side records that overlapping grad_unscale_check* calls take turns on (up to 1024
  *     such calls may be in flight on one device at a time).
  *   - Environment: none is read, unless SDCONV_TUNE=1 was set before the first call: then the
- *     SDCONV_* variables of the tuner and of the variant tests override the kernel choice.
+ *     SDCONV_* variables of the timings and of the variant tests override the kernel choice.
  */
 #ifndef SDCONV_H
 #define SDCONV_H

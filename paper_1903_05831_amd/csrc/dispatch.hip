@@ -19,7 +19,7 @@ static int env_int(const char* name, int dflt)
     return (e && *e) ? atoi(e) : dflt;
 }
 
-// Tuning hooks (used by the tuner and by the tests that force every variant): environment
+// Tuning hooks (used by fit_models.py and by the tests that force every variant): environment
 // variables that override the dispatcher, honoured only when SDCONV_TUNE=1 was set before the
 // library's first call.  That switch is read once; without it no call touches the environment.
 static bool tuning()
@@ -628,7 +628,7 @@ static hipError_t run_igemm(const Geom& g, const Plan& p, bool dgrad, const __ha
     P.sw_cls = dgrad ? g.sw : 1;
     set_taps(g, dgrad, &P);
     // elements between consecutive rows of the filter matrix the kernel reads: [Cd][R][S][Cs]
-    // (forward, and the transposed copy of the older data-gradient kernels), or the filter as
+    // (forward, and the transposed copy of the register-staged data gradient), or the filter as
     // stored, [K = Cs][R][S][C = Cd], for the data gradient of the split-role and patch kernels
     P.b_row_pitch = g.R * g.S * ((dgrad && p.variant >= 300) ? P.Cd : P.Cs);
     P.tiles_h = P.tiles_w = 0;

@@ -68,7 +68,7 @@ def out_hw(k):
 ROW_VARIANTS = [101, 112, 310, 311, 316, 324] + list(range(325, 341)) + [427, 433, 435, 436, 437]
 # variants with a row in the models (324 has those of its two halves)
 ROW_MODELS = [v for v in ROW_VARIANTS if v != 324]
-WGRAD_MODELS = [104, 107, 108, 112, 114, 115, 116, 117, 118, 119]
+WGRAD_MODELS = WGRAD_VARIANTS = [104, 107, 108, 112, 114, 115, 116, 117, 118, 119]
 ONE_SLAB = {427, 433}                    # one patch buffer: 64 contraction channels only
 WORKGROUPS = (40, 64, 96, 128, 192, 256, 320, 384, 512, 768, 1024)
 
@@ -168,7 +168,7 @@ def measure(what: str, seed: int, seconds: float, path: str) -> None:
                         labels.append(v)
                 else:
                     total = -(-N * ho * wo // 64)
-                    for v in WGRAD_MODELS:
+                    for v in WGRAD_VARIANTS:
                         bm, bn, _ = WGRAD_TILES[v]
                         tiles = -(-K // bm) * -(-C // bn) * R * R
                         for ranges in sorted({ranges_made(total, r) for r in

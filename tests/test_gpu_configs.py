@@ -1,5 +1,5 @@
 """Full-size parity on the benchmark configurations, in the launch configuration bench.py times
-(tuned table on, default dispatch).
+(default dispatch).
 
 Whole tensors: every layer of configs 2-4 and the first instance of every layer shape that
 config 5 adds (stem, the first res2 block, res3 blocks 1-3, the res5 head): all three passes

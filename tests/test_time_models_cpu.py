@@ -23,7 +23,7 @@ def variants():
     """Variant of each kernel name (the overrides are honoured: conftest.py sets SDCONV_TUNE)."""
     d, out = sd.make_desc(1, 28, 28, 64, 64, 3, 3, (1, 1), (1, 1)), {}
     for name, known, passes in (("SDCONV_IGEMM_VARIANT", fit_models.ROW_VARIANTS, (sd.FWD, sd.DGRAD)),
-                                ("SDCONV_WGRAD_VARIANT", fit_models.WGRAD_MODELS, (sd.WGRAD,))):
+                                ("SDCONV_WGRAD_VARIANT", fit_models.WGRAD_VARIANTS, (sd.WGRAD,))):
         for v in known:
             os.environ[name] = str(v)
             out.update({sd.kernel_name(d, p): v for p in passes})

@@ -328,6 +328,16 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
     const int frow = lane & (MF - 1), lhi = lane / MF;
     constexpr int KSTEP = MF == 32 ? 16 : 32;       // contraction values per MFMA
     constexpr int CPK = KSTEP / 8;                  // 16-byte chunks per MFMA step
+    constexpr int NCH = BK / KSTEP / KS;            // portions of KSTEP contraction values that a wave takes of a step
+    // ORDERED: the fragments of the first portion are read at once and those of the next ones one by one between the matrix
+    // instructions, where the compiler on its own reads them just before their use or all in one go, and the matrix pipe
+    // waits: data gradient of 3x3 256->256 on 2x50x84, 256x128 tiles 29.1 -> 26.1 us, 192x128 24.0 -> 22.2, 224x128
+    // 25.9 -> 24.6 (forward 24.9 -> 24.0); 3x3 512->512 on 25 088 pixels, 224x256, 97.5 -> 95.9 us (98.6 -> 97.3).
+    // It takes a second set of fragments, and tiles that lose a workgroup or spill for it do not have it (128x128 with
+    // two workgroups a compute unit, 1x1 512->128 data gradient: 10.6 us against 14.0); nor do waves with a few matrix blocks,
+    // whose reads then wait for them (64x128, 3x3 data gradient: 25.5 against 27.2; 160x256 with waves that fetch too: 1-3 % slower).
+    constexpr int PERCU = 160 * 1024 / (S * STAGE + 16 * BM), WAVES = (NW * (PERCU < 1 ? 1 : PERCU) + 3) / 4;     // ... a SIMD
+    constexpr bool ORDERED = !F32 && FM >= (NP ? 2 : 7) && WM * WN >= 2048 && FM * FN * ACCN + 8 * (FM + FN) + 24 <= 512 / WAVES;
     auto compute = [&](int stage) {
         const unsigned char* sa = smem + stage * STAGE;
         const unsigned char* sb = sa + BM * ROWB;
@@ -367,6 +377,18 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
                         else
                             acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[a], fa[b], acc[a][b], 0, 0, 0);
                     }
+        }
+        if constexpr (ORDERED) {        // 0x100: LDS reads, 0x008: matrix instructions
+            constexpr int FIRST = FM + FN * (KROWS ? 1 : 2), REST = (NCH - 1) * FIRST, MULS = NCH * FM * FN - FM;
+            constexpr int EACH = (REST + MULS - 1) / MULS;
+            __builtin_amdgcn_sched_group_barrier(0x100, FIRST, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, FM, 0);
+#pragma unroll
+            for (int i = 0; i < (REST + EACH - 1) / EACH; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, EACH, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, MULS, 0);
         }
     };
 

@@ -33,6 +33,44 @@ __device__ __forceinline__ void dma16(unsigned voff, int4v rsrc, unsigned soff, 
                  :: "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_base) : "memory");
 }
 
+// N <= 4 loads of 16 bytes per lane whose 1 KiB land one behind the other from lds_base on, with one write of m0: the
+// instruction's own offset counts for both addresses, so load i of them reads 1024 i bytes past its offset
+// (kRunSlack - run_offset(i) takes that back, with a descriptor that starts kRunSlack before its tensor).
+constexpr unsigned kRunSlack = 3072;
+__device__ __forceinline__ constexpr unsigned run_offset(int i) { return (i & 3) * 1024u; }
+template <int N>
+__device__ __forceinline__ void dma16_run(const unsigned* v, int4v rsrc, unsigned soff, unsigned lds_base)
+{
+    static_assert(N >= 1 && N <= 4, "offsets of 12 bits");
+    if constexpr (N == 1)
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                     :: "v"(v[0]), "s"(rsrc), "s"(soff), "s"(lds_base) : "memory");
+    else if constexpr (N == 2)
+        asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, %3 offen lds\n\t"
+                     "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds"
+                     :: "v"(v[0]), "v"(v[1]), "s"(rsrc), "s"(soff), "s"(lds_base) : "memory");
+    else if constexpr (N == 3)
+        asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %3, %4 offen lds\n\t"
+                     "buffer_load_dwordx4 %1, %3, %4 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %2, %3, %4 offen offset:2048 lds"
+                     :: "v"(v[0]), "v"(v[1]), "v"(v[2]), "s"(rsrc), "s"(soff), "s"(lds_base) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %6\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %4, %5 offen lds\n\t"
+                     "buffer_load_dwordx4 %1, %4, %5 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %2, %4, %5 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %3, %4, %5 offen offset:3072 lds"
+                     :: "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(rsrc), "s"(soff), "s"(lds_base) : "memory");
+}
+// ... and any number of them, four at a time.
+template <int N>
+__device__ __forceinline__ void dma16_runs(const unsigned* v, int4v rsrc, unsigned soff, unsigned lds_base)
+{
+    if constexpr (N > 0) {
+        dma16_run<(N < 4 ? N : 4)>(v, rsrc, soff, lds_base);
+        dma16_runs<(N > 4 ? N - 4 : 0)>(v + 4, rsrc, soff, lds_base + 4096u);
+    }
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()
 {

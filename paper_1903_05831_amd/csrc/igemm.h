@@ -33,6 +33,8 @@ struct IgemmParams {
     int tap_sh, tap_sw;     // tap numbers between two consecutive ones
     int tap_dh, tap_dw;     // source pixels between two consecutive ones
     int pointwise;          // one tap, and GEMM row m reads source pixel m
+    int tap_bias;           // what the fetching waves of igemm_ws_body.h add to a tap's displacement to have no
+                            // negative one, or -1: the layer takes their general loop (set_tap_bias)
     int tiles_h, tiles_w;   // spatial tiles per image (patch kernels only)
     // launches with two tile widths (igemm_ws_mixed_kernel; set by its launcher)
     int mix_big_tiles, mix_big_blocks;                        // wide tiles, and the workgroups that cover them
@@ -41,6 +43,8 @@ struct IgemmParams {
 };
 
 void set_taps(const Geom& g, bool dgrad, IgemmParams* P);      // the tap fields (dispatch.hip)
+
+void set_tap_bias(IgemmParams* P);      // once the other fields are set
 
 // GEMM rows (destination pixels) and filter taps that meet them, by parity class of a strided data gradient;
 // other passes have one class.

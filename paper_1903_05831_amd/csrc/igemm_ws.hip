@@ -1,4 +1,5 @@
 // Split-role implicit GEMM: kernels and launches (the work of a workgroup: igemm_ws_body.h).
+#include <algorithm>
 #include "igemm_ws_body.h"
 
 namespace sdconv {
@@ -140,8 +141,29 @@ template <int MODE> static hipError_t launch_mode(int variant, const IgemmParams
     }
 }
 
-hipError_t launch_igemm_ws(int variant, const IgemmParams& P, hipStream_t st)
+void set_tap_bias(IgemmParams* P)
 {
+    long low = 0;           // least displacement of any class, in bytes
+    bool served = P->Cs % 64 == 0;
+    for (int a = 0; a * P->sw_cls < P->nclasses; ++a)
+        for (int b = 0; b < P->sw_cls; ++b) {
+            const AxisTaps h = P->taps_h[a], w = P->taps_w[b];
+            if (h.count * w.count == 0) continue;
+            if (h.count * w.count > 32) served = false;
+            const long h0 = h.disp + (P->tap_dh < 0 ? (h.count - 1) * (long)P->tap_dh : 0);
+            const long w0 = w.disp + (P->tap_dw < 0 ? (w.count - 1) * (long)P->tap_dw : 0);
+            low = std::min(low, (h0 * P->Ws + w0) * P->Cs * 2);
+        }
+    // out-of-range offsets start at 2^31, past whatever a descriptor covers
+    const long source = (long)P->NB * P->Hs * P->Ws * P->Cs * 2;
+    const long filter = (long)std::max(P->Cs, P->Cd) * P->b_row_pitch * 2, most = (1L << 31) - kRunSlack;
+    P->tap_bias = served && source - low <= most && filter <= most ? (int)-low : -1;
+}
+
+hipError_t launch_igemm_ws(int variant, const IgemmParams& P0, hipStream_t st)
+{
+    IgemmParams P = P0;
+    set_tap_bias(&P);
     return P.mode ? launch_mode<1>(variant, P, st) : launch_mode<0>(variant, P, st);
 }
 

@@ -58,10 +58,9 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
     constexpr int FM = WM / MF, FN = WN / MF;
     constexpr int ACCN = MF == 32 ? 16 : 4;         // accumulator floats per lane and block
     constexpr int ROWB = BK * 2;                    // bytes per tile row: eight 16-byte chunks
-    constexpr int NA = BM / 8, NINS = NA + BN / 8;  // load instructions of a stage, 1 KiB each: activation rows, then filter
-    constexpr int PL = (NINS + NI - 1) / NI;        // ... and of one fetching wave, which takes every NI-th
-    constexpr int PA = (NA + NI - 1) / NI, PAF = NA / NI;   // passes with activation loads, and those with nothing else
-    constexpr int STAGE = PL * NI * 1024;           // bytes
+    constexpr int NA = BM / 8, NB = BN / 8;         // load instructions of a stage, 1 KiB each: activation rows and filter
+    constexpr int PA = (NA + NI - 1) / NI, PB = (NB + NI - 1) / NI, PL = PA + PB;   // ... and of a fetching wave: so many in a row
+    constexpr int ABYTES = PA * NI * 1024, STAGE = PL * NI * 1024;
     constexpr int INFLIGHT = (S - 2) * PL;          // loads a fetching wave may leave outstanding
     static_assert((MF == 32 || MF == 16) && WM % MF == 0 && WN % MF == 0 && BM % 8 == 0 && BN % 8 == 0, "tile shape");
     static_assert(S >= 2 && INFLIGHT < 64, "pipeline depth");
@@ -148,138 +147,185 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
     const bool fetcher = wave >= IW0;
 
     // ---- fetching side ---------------------------------------------------------------------
-    // Load p of fetching wave fw is instruction p * NI + fw of the stage; where NI does not divide them,
-    // one pass has both kinds, and the last may have some that fetch nothing (into the stage's padding).
+    // A wave that only fetches takes PA consecutive load instructions of the activations and PB of the filter (one that
+    // multiplies too takes every NI-th); where these are more than the tile has, the last ones fetch nothing (into the
+    // stage's padding).
     const int fw = wave - IW0;                      // fetching wave index
-    constexpr int SPLIT = NA % NI;                  // in pass PAF the first SPLIT waves still load activations
-    auto is_a = [&](int p) { return p < PAF || (p == PAF && fw < SPLIT); };
+    constexpr int GAP = NP ? 1 : NI;                // load instructions from one of a wave to its next
+    static_assert(NP > 0 || (NA % NI == 0 && NB % NI == 0), "no padding");
+    auto a_instr = [&](int p) { return (NP ? fw * PA : fw) + p * GAP; };
+    auto b_instr = [&](int p) { return (NP ? fw * PB : fw) + p * GAP; };
     auto chunk_of = [&](int r) { return (lane & 7) ^ ((r >> 1) & 7); };     // logical chunk that lands in this lane's slot of row r
     unsigned off[PL], out[PA];                      // out: bit t: tap t (of 0..31) of this row is outside
     const bool partial = (P.Cs % BK) != 0;          // last channel chunk is short
     if (fetcher) {
-        if (P.pointwise) {
 #pragma unroll
-            for (int p = 0; p < PA; ++p) {
-                const int r = (p * NI + fw) * 8 + (lane >> 3);
+        for (int p = 0; p < PA; ++p) {
+            const int r = a_instr(p) * 8 + (lane >> 3);
+            out[p] = 0;
+            if (PA * NI > NA && r >= BM) {
+                off[p] = kOutOfRange;
+                out[p] = ~0u;
+            } else if (P.pointwise) {
                 off[p] = m0 + r < Mcls ? (unsigned)(((m0 + r) * P.Cs + chunk_of(r) * 8) * 2) : kOutOfRange;
-                out[p] = 0;
-            }
-        } else {
-#pragma unroll
-            for (int p = 0; p < PA; ++p) {
-                const int r = (p * NI + fw) * 8 + (lane >> 3);
-                if (PA > PAF && p == PAF && fw >= SPLIT) break;
+            } else {
                 off[p] = row_off[r] + (unsigned)(chunk_of(r) * 16);
                 out[p] = row_lo[r];
             }
         }
 #pragma unroll
-        for (int p = PAF; p < PL; ++p) {
-            const int i = p * NI + fw - NA;         // instruction of the filter tile
-            if (PA > PAF && p == PAF && fw < SPLIT) continue;
+        for (int p = 0; p < PB; ++p) {
+            const int i = b_instr(p);               // instruction of the filter tile
+            unsigned o;
             if (KROWS) {
                 const int r = i * 8 + (lane >> 3), n = n0 + r;
-                off[p] = (n < P.Cd) ? (unsigned)((n * P.b_row_pitch + chunk_of(r) * 8) * 2) : kOutOfRange;
+                o = (n < P.Cd) ? (unsigned)((n * P.b_row_pitch + chunk_of(r) * 8) * 2) : kOutOfRange;
             } else {
                 // [64 filters][BN channels]: chunk slot i * 64 + lane of the tile
                 const int slot = i * 64 + lane;
                 const int krow = slot / (BN / 8), pc = slot % (BN / 8);
                 const int c = n0 + swizzled_chunk<BN>(krow, pc) * 8;
-                off[p] = (c < P.Cd) ? (unsigned)((krow * P.b_row_pitch + c) * 2) : kOutOfRange;
+                o = (c < P.Cd) ? (unsigned)((krow * P.b_row_pitch + c) * 2) : kOutOfRange;
             }
-            if (PL * NI > NINS && i >= BN / 8) off[p] = kOutOfRange;
+            off[PA + p] = PB * NI > NB && i >= NB ? kOutOfRange : o;
         }
     }
-    const int4v rsrcA = make_rsrc(P.A, (unsigned)(P.NB * P.Hs * P.Ws * P.Cs) * 2u);
-    const int4v rsrcB = make_rsrc(P.B, (unsigned)((KROWS ? P.Cd : P.Cs) * P.b_row_pitch) * 2u);
+    const unsigned spanA = (unsigned)(P.NB * P.Hs * P.Ws * P.Cs) * 2u, spanB = (unsigned)((KROWS ? P.Cd : P.Cs) * P.b_row_pitch) * 2u;
+    const unsigned to_a = lds0 + (NP ? fw * PA : fw) * 1024, to_b = lds0 + ABYTES + (NP ? fw * PB : fw) * 1024;
+    auto uniform = [](int v) { return (unsigned)__builtin_amdgcn_readfirstlane(v); };
 
-    // The contraction step the next issue() fetches: tap (counted from the first), its column in the
-    // grid of taps, channel chunk, and the tap's byte displacements in the source image (ad) and in a
-    // filter row (bo).  Taps vary fastest: the taps of a 3x3 re-read nearly the same pixels of one
-    // channel slab back to back, while it is still in L2.
+    // The contraction step the next loads fetch: tap (counted from the first), its column in the grid of taps, channel
+    // chunk, and the tap's byte displacements in the source image (ad) and in a filter row (bo).
+    // Taps vary fastest: the taps of a 3x3 re-read nearly the same pixels of one channel slab back to back, while it is
+    // still in L2.
     const int bpt = (KROWS ? P.Cs : P.Cd) * 2;                  // filter bytes of a tap
     const int ad0 = (th.disp * P.Ws + tw.disp) * P.Cs * 2, ad_w = P.tap_dw * P.Cs * 2;
     const int ad_h = (P.tap_dh * P.Ws - (tw.count - 1) * P.tap_dw) * P.Cs * 2;
     const int bo0 = (th.first * P.S + tw.first) * bpt, bo_w = P.tap_sw * bpt;
     const int bo_h = (P.tap_sh * P.S - (tw.count - 1) * P.tap_sw) * bpt;
-    int nx_tap = 0, nx_col = 0, nx_kc = 0, nx_ad = ad0, nx_bo = bo0;
-    // A fetching wave is bound by the instructions around each load (the texture path takes one per
-    // 16-20 cycles and CU, two waves with a 64-bit shift and a dozen vector operations per load sent
-    // one per 36), so a load has the fewest here: none in pointwise layers, four where taps can leave
-    // the image; what only the last, short channel chunk or a 33rd tap needs is kept off that path.
-    auto issue = [&](int stage) {
-        const unsigned cbytes = (unsigned)__builtin_amdgcn_readfirstlane(nx_kc * ROWB);
-        const unsigned sbase = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds0 + stage * STAGE + fw * 1024));
-        const unsigned ad = (unsigned)__builtin_amdgcn_readfirstlane(nx_ad);
-        const unsigned bsoff = (unsigned)__builtin_amdgcn_readfirstlane(
-            nx_bo + (KROWS ? nx_kc * ROWB : nx_kc * BK * P.b_row_pitch * 2));
-        const int cleft = P.Cs - nx_kc * BK;        // channels left from this chunk's start
-        auto load_b = [&](int p, unsigned voff) { dma16(voff, rsrcB, bsoff, sbase + p * NI * 1024); };
-        auto load_a = [&](int p, unsigned voff) { dma16(voff, rsrcA, cbytes, sbase + p * NI * 1024); };
+    const int bk = KROWS ? ROWB : BK * P.b_row_pitch * 2;       // filter bytes from one channel chunk to the next
+    // Any layer.  What only the last, short channel chunk or a 33rd tap needs is kept off the common path.
+    struct Step { int tap, col, kc, ad, bo; };
+    auto issue = [&](int stage, Step& nx) __attribute__((always_inline)) {
+        const int4v rsrcA = make_rsrc(P.A, spanA), rsrcB = make_rsrc(P.B, spanB);
+        const unsigned cbytes = uniform(nx.kc * ROWB), bsoff = uniform(nx.bo + nx.kc * bk), ad = uniform(nx.ad);
+        const unsigned base_a = uniform((int)(to_a + stage * STAGE)), base_b = uniform((int)(to_b + stage * STAGE));
+        const int cleft = P.Cs - nx.kc * BK;        // channels left from this chunk's start
+        auto load_a = [&](int p, unsigned voff) { dma16(voff, rsrcA, cbytes, base_a + p * GAP * 1024); };
+        auto load_b = [&](int p, unsigned voff) { dma16(voff, rsrcB, bsoff, base_b + p * GAP * 1024); };
+        // (in the rare branches the lane number is read anew: what follows from it is not kept in registers meanwhile)
         if (partial && cleft < BK) {
+            int lane = threadIdx.x & 63;
+            asm volatile("" : "+v"(lane));
+            auto chunk_of = [&](int r) { return (lane & 7) ^ ((r >> 1) & 7); };
 #pragma unroll
-            for (int p = 0; p < PL; ++p) {
-                const int i = p * NI + fw;
-                if (is_a(p)) {
-                    const int r = i * 8 + (lane >> 3);
-                    unsigned o = out[p < PA ? p : 0];
-                    if (nx_tap >= 32) o = row_hi[r];
-                    const bool skip = ((o >> (nx_tap & 31)) & 1u) || chunk_of(r) * 8 >= cleft || off[p] == kOutOfRange;
-                    load_a(p, skip ? kOutOfRange : off[p] + ad);
-                } else {
-                    const int contraction = KROWS ? chunk_of((i - NA) * 8 + (lane >> 3)) * 8 : ((i - NA) * 64 + lane) / (BN / 8);
-                    load_b(p, contraction >= cleft ? kOutOfRange : off[p]);
-                }
+            for (int p = 0; p < PA; ++p) {
+                const int r = a_instr(p) * 8 + (lane >> 3);
+                unsigned o = out[p];
+                if (nx.tap >= 32 && r < BM) o = row_hi[r];
+                const bool skip = ((o >> (nx.tap & 31)) & 1u) || chunk_of(r) * 8 >= cleft || off[p] == kOutOfRange;
+                load_a(p, skip ? kOutOfRange : off[p] + ad);
+            }
+#pragma unroll
+            for (int p = 0; p < PB; ++p) {
+                const int contraction = KROWS ? chunk_of(b_instr(p) * 8 + (lane >> 3)) * 8 : (b_instr(p) * 64 + lane) / (BN / 8);
+                load_b(p, contraction >= cleft ? kOutOfRange : off[PA + p]);
             }
         } else {
             if (P.pointwise) {
 #pragma unroll
-                for (int p = 0; p < PA; ++p)
-                    if (is_a(p)) load_a(p, off[p]);
-            } else if (nx_tap < 32) {
-                const int sh = 31 - nx_tap;
+                for (int p = 0; p < PA; ++p) load_a(p, off[p]);
+            } else if (nx.tap < 32) {
+                const int sh = 31 - nx.tap;
 #pragma unroll
-                for (int p = 0; p < PA; ++p)
-                    if (is_a(p)) load_a(p, (int)(out[p] << sh) < 0 ? kOutOfRange : off[p] + ad);
+                for (int p = 0; p < PA; ++p) load_a(p, (int)(out[p] << sh) < 0 ? kOutOfRange : off[p] + ad);
             } else {
+                int lane = threadIdx.x & 63;
+                asm volatile("" : "+v"(lane));
 #pragma unroll
-                for (int p = 0; p < PA; ++p)
-                    if (is_a(p)) {
-                        const unsigned o = row_hi[(p * NI + fw) * 8 + (lane >> 3)];
-                        load_a(p, (o >> (nx_tap - 32)) & 1u ? kOutOfRange : off[p] + ad);
-                    }
+                for (int p = 0; p < PA; ++p) {
+                    const int r = a_instr(p) * 8 + (lane >> 3);
+                    const unsigned o = PA * NI > NA && r >= BM ? ~0u : row_hi[r];
+                    load_a(p, (o >> (nx.tap - 32)) & 1u ? kOutOfRange : off[p] + ad);
+                }
             }
 #pragma unroll
-            for (int p = PAF; p < PL; ++p)
-                if (!is_a(p)) load_b(p, off[p]);
+            for (int p = 0; p < PB; ++p) load_b(p, off[PA + p]);
         }
-        if (nx_tap + 1 == ntaps) {
-            nx_tap = nx_col = 0;
-            nx_ad = ad0;
-            nx_bo = bo0;
-            ++nx_kc;
-        } else {
-            ++nx_tap;
-            const bool wrap = nx_col + 1 == tw.count;
-            nx_col = wrap ? 0 : nx_col + 1;
-            nx_ad += wrap ? ad_h : ad_w;
-            nx_bo += wrap ? bo_h : bo_w;
+        if (nx.tap + 1 == ntaps) nx = Step{0, 0, nx.kc + 1, ad0, bo0};
+        else {
+            const bool wrap = nx.col + 1 == tw.count;
+            nx = Step{nx.tap + 1, wrap ? 0 : nx.col + 1, nx.kc, nx.ad + (wrap ? ad_h : ad_w), nx.bo + (wrap ? bo_h : bo_w)};
         }
-        nx_tap = __builtin_amdgcn_readfirstlane(nx_tap);
-        nx_kc = __builtin_amdgcn_readfirstlane(nx_kc);
+        nx.tap = __builtin_amdgcn_readfirstlane(nx.tap);
+        nx.kc = __builtin_amdgcn_readfirstlane(nx.kc);
     };
 
-    if (NP > 0 && fetcher) {
+    if constexpr (NP > 0) if (fetcher) {
         // ---- dedicated fetching wave: S-1 steps ahead of the multipliers ---------------------
-        int is = 0;
+        auto fetch_all = [&](auto send) __attribute__((always_inline)) {
+            int is = 0;
 #pragma unroll 1
-        for (int q = 0; q < nk; ++q) {
-            if (q >= S - 1) {
-                wait_vmcnt<INFLIGHT>();
-                stage_barrier();       // step q-(S-1) is in LDS; the stage before it is free
+            for (int q = 0; q < nk; ++q) {
+                if (q >= S - 1) {
+                    wait_vmcnt<INFLIGHT>();
+                    stage_barrier();       // step q-(S-1) is in LDS; the stage before it is free
+                }
+                send(is);
+                is = (is + 1 == S) ? 0 : is + 1;
             }
-            issue(is);
-            is = (is + 1 == S) ? 0 : is + 1;
+        };
+        if (P.tap_bias < 0) {
+            Step nx{0, 0, 0, ad0, bo0};
+            fetch_all([&](int stage) __attribute__((always_inline)) { issue(stage, nx); });
+        } else {
+            // A wave issues an instruction every four to six cycles and the texture path takes a load in 16, so the number
+            // of its instructions is what bounds a fetching wave: a 64x64 tile's step of 16 loads took the time of 64
+            // B/ns and compute unit where loads alone reach 130 (one or two waves are enough for that).  So here a run of
+            // loads shares one LDS base (dma16_runs) and one scalar offset, in which tap and channel chunk are
+            // counted; pointwise layers have nothing else to do, others two vector operations a load that put the
+            // taps outside the image past the descriptor's range.  3x3 512->128 on 16x512, 64x64 tiles: 22.9 -> 17.9 us;
+            // 3x3 256->256 on 2x50x84, 80x128 tiles: 16.8 -> 13.8.
+            const unsigned char* a0 = reinterpret_cast<const unsigned char*>(P.A) - kRunSlack - P.tap_bias;
+            const int4v rsrcA = make_rsrc(a0, spanA + kRunSlack + P.tap_bias);
+            const int4v rsrcB = make_rsrc(reinterpret_cast<const unsigned char*>(P.B) - kRunSlack, spanB + kRunSlack);
+#pragma unroll
+            for (int p = 0; p < PA; ++p) off[p] += kRunSlack - run_offset(p);
+#pragma unroll
+            for (int p = 0; p < PB; ++p) off[PA + p] += kRunSlack - run_offset(p);
+            int so_a = P.tap_bias + ad0, so_b = bo0;
+            if (P.pointwise) {
+                fetch_all([&](int stage) __attribute__((always_inline)) {
+                    dma16_runs<PA>(off, rsrcA, uniform(so_a), uniform((int)(to_a + stage * STAGE)));
+                    dma16_runs<PB>(off + PA, rsrcB, uniform(so_b), uniform((int)(to_b + stage * STAGE)));
+                    so_a += ROWB;
+                    so_b += bk;
+                });
+            } else {
+                // a chunk's last tap lies (count_h - 1) rows and (count_w - 1) columns from the next chunk's first
+                const int ad_k = ROWB - ((th.count - 1) * P.tap_dh * P.Ws + (tw.count - 1) * P.tap_dw) * P.Cs * 2;
+                const int bo_k = bk - ((th.count - 1) * P.tap_sh * P.S + (tw.count - 1) * P.tap_sw) * bpt;
+                int tap = 0, col = 0;
+                fetch_all([&](int stage) __attribute__((always_inline)) {
+                    unsigned v[PA];
+                    const int sh = 31 - tap;
+#pragma unroll
+                    for (int p = 0; p < PA; ++p) v[p] = (out[p] << sh & kOutOfRange) | off[p];
+                    dma16_runs<PA>(v, rsrcA, uniform(so_a), uniform((int)(to_a + stage * STAGE)));
+                    dma16_runs<PB>(off + PA, rsrcB, uniform(so_b), uniform((int)(to_b + stage * STAGE)));
+                    if (++col < tw.count) {
+                        ++tap;
+                        so_a += ad_w;
+                        so_b += bo_w;
+                    } else {
+                        const bool last = tap + 1 == ntaps;
+                        col = 0;
+                        tap = last ? 0 : tap + 1;
+                        so_a += last ? ad_k : ad_h;
+                        so_b += last ? bo_k : bo_h;
+                    }
+                });
+            }
         }
         for (int it = nk > S - 1 ? nk - (S - 1) : 0; it < nk; ++it) {
             if (it + S - 2 < nk) wait_vmcnt<INFLIGHT>(); else wait_vmcnt<0>();
@@ -331,19 +377,19 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
     constexpr int NCH = BK / KSTEP / KS;            // portions of KSTEP contraction values that a wave takes of a step
     // ORDERED: the fragments of the first portion are read at once and those of the next ones one by one between the matrix
     // instructions, where the compiler on its own reads them just before their use or all in one go, and the matrix pipe
-    // waits: data gradient of 3x3 256->256 on 2x50x84, 256x128 tiles 29.1 -> 26.1 us, 192x128 24.0 -> 22.2, 224x128
-    // 25.9 -> 24.6 (forward 24.9 -> 24.0); 3x3 512->512 on 25 088 pixels, 224x256, 97.5 -> 95.9 us (98.6 -> 97.3).
+    // waits: 3x3 256->256 on 2x50x84, 96x128 tiles 15.0 -> 13.4 us forward, 16.7 -> 16.2 data gradient, 224x128 23.9 ->
+    // 22.4 and 25.7 -> 24.0, 128x128 data gradient 19.1 -> 17.2; 1x1 2048->512 on 25 088 pixels, 224x256, 51.4 -> 47.4.
     // It takes a second set of fragments, and tiles that lose a workgroup or spill for it do not have it (128x128 with
     // two workgroups a compute unit, 1x1 512->128 data gradient: 10.6 us against 14.0); nor do waves with a few matrix blocks,
     // whose reads then wait for them (64x128, 3x3 data gradient: 25.5 against 27.2; 160x256 with waves that fetch too: 1-3 % slower).
     constexpr int PERCU = 160 * 1024 / (S * STAGE + 16 * BM), WAVES = (NW * (PERCU < 1 ? 1 : PERCU) + 3) / 4;     // ... a SIMD
     constexpr bool ORDERED = !F32 && FM >= (NP ? 2 : 7) && WM * WN >= 2048 && FM * FN * ACCN + 8 * (FM + FN) + 24 <= 512 / WAVES;
-    auto compute = [&](int stage) {
+    auto compute = [&](int stage) __attribute__((always_inline)) {
         const unsigned char* sa = smem + stage * STAGE;
-        const unsigned char* sb = sa + BM * ROWB;
+        const unsigned char* sb = sa + ABYTES;
 #pragma unroll
-        for (int k0 = 0; k0 < BK / KSTEP / KS; ++k0) {
-            const int kk = KS > 1 ? wk * (BK / KSTEP / KS) + k0 : k0, chunk = kk * CPK + lhi;
+        for (int k0 = 0; k0 < NCH; ++k0) {
+            const int kk = KS > 1 ? wk * NCH + k0 : k0, chunk = kk * CPK + lhi;
             half8 fa[FM], fb[FN];
 #pragma unroll
             for (int b = 0; b < FM; ++b) {
@@ -432,16 +478,17 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
         }
     } else {
         // upper half of the waves fetches for the whole group, then multiplies its own share
+        Step nx{0, 0, 0, ad0, bo0};
         if (fetcher) {
 #pragma unroll 1
-            for (int s = 0; s < S - 1 && s < nk; ++s) issue(s);
+            for (int s = 0; s < S - 1 && s < nk; ++s) issue(s, nx);
         }
         int cs = 0, is = (S - 1) % S;
         for (int it = 0; it < nk; ++it) {
             if (TAIL && !fetcher && it == warm_at) warm_tail();
             if (fetcher) { if (it + S - 2 < nk) wait_vmcnt<INFLIGHT>(); else wait_vmcnt<0>(); }
             stage_barrier();
-            if (fetcher && it + S - 1 < nk) issue(is);
+            if (fetcher && it + S - 1 < nk) issue(is, nx);
             is = (is + 1 == S) ? 0 : is + 1;
             compute(cs);
             cs = (cs + 1 == S) ? 0 : cs + 1;
@@ -528,7 +575,7 @@ __device__ __forceinline__ int xcd_run_tile(int b)
 template <int BM, int BN, int NWC, int S, int NP> constexpr size_t ws_ring_bytes()
 {
     constexpr int NI = NP ? NP : NWC / 2;
-    return (size_t)S * (((BM + BN) / 8 + NI - 1) / NI) * NI * 1024;
+    return (size_t)S * ((BM / 8 + NI - 1) / NI + (BN / 8 + NI - 1) / NI) * NI * 1024;
 }
 
 }  // namespace sdconv

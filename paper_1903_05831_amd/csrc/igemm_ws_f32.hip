@@ -39,8 +39,10 @@ static hipError_t launch_one(const IgemmParams& P, hipStream_t st)
 #define SDCONV_F32_CASE(idx, ...)                                                       \
     case idx: return P.mode ? launch_one<1, __VA_ARGS__>(P, st) : launch_one<0, __VA_ARGS__>(P, st);
 
-hipError_t launch_igemm_ws_f32(int variant, const IgemmParams& P, hipStream_t st)
+hipError_t launch_igemm_ws_f32(int variant, const IgemmParams& P0, hipStream_t st)
 {
+    IgemmParams P = P0;
+    set_tap_bias(&P);
     switch (variant) {
         SDCONV_F32_CASE(0, 128, 128, 2, 4, 1, 3, 2)
         SDCONV_F32_CASE(1, 128, 64, 2, 2, 1, 2, 2)

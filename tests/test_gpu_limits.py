@@ -57,6 +57,37 @@ def test_padded_3x3_on_a_tensor_of_more_than_2_30_elements():
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("dgrad", [False, True])
+@pytest.mark.parametrize("H", [4094, 4095])
+def test_source_that_ends_just_below_2_31_bytes(H, dgrad, monkeypatch):
+    """3x3 on an H x 4096 x 64 source: with the rows that its taps reach before the first pixel, 4094 rows are the most
+    whose offsets stay below 2^31, and 4095 take the fetching waves' general loop.  The last rows of the result are
+    those of the same layer on a copy of the last rows of the source, whose sums have the same order: every bit."""
+    monkeypatch.setenv("SDCONV_IGEMM_VARIANT", "334")
+    W, few, rows = 4096, 8, 6
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H)
+    src = torch.empty(1, H, W, 64, dtype=torch.float16, device="cuda").normal_(generator=gen)
+    w = torch.empty((64, 3, 3, few) if dgrad else (few, 3, 3, 64), dtype=torch.float16, device="cuda").normal_(0, 0.1, generator=gen)
+    st = torch.cuda.current_stream().cuda_stream
+
+    def run(s):
+        h = s.shape[1]
+        d = sd.make_desc(1, h, W, *((few, 64) if dgrad else (64, few)), 3, 3, (1, 1), (1, 1))
+        assert "80x128" in sd.kernel_name(d, sd.DGRAD if dgrad else sd.FWD)
+        out = torch.full((1, h, W, few), float("nan"), dtype=torch.float16, device="cuda")
+        (sd.conv2d_dgrad if dgrad else sd.conv2d_fwd)(d, s, w, out, None, st)
+        return out
+
+    say(f"source 1x{H}x{W}x64, {'data gradient' if dgrad else 'forward'}")
+    whole, first, last = run(src), run(src[:, :rows].contiguous()), run(src[:, -rows:].contiguous())
+    torch.cuda.synchronize()
+    assert torch.equal(whole[:, :rows - 1], first[:, :-1]) and torch.equal(whole[:, 1 - rows:], last[:, 1:])
+    assert not torch.isnan(whole).any()
+    del src, whole
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("ranges", [1, 2])
 def test_weight_gradient_of_more_than_2_29_elements(ranges, monkeypatch):
     """1x1, 8192 -> 73 728 channels on 256 pixels: the 2.4 GB of dw, and twice that of partial sums, lie past the

@@ -144,7 +144,7 @@ template <int MODE> static hipError_t launch_mode(int variant, const IgemmParams
 void set_tap_bias(IgemmParams* P)
 {
     long low = 0;           // least displacement of any class, in bytes
-    bool served = P->Cs % 64 == 0;
+    bool served = true;
     for (int a = 0; a * P->sw_cls < P->nclasses; ++a)
         for (int b = 0; b < P->sw_cls; ++b) {
             const AxisTaps h = P->taps_h[a], w = P->taps_w[b];

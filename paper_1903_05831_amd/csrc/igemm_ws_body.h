@@ -153,9 +153,9 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
     const int fw = wave - IW0;                      // fetching wave index
     constexpr int GAP = NP ? 1 : NI;                // load instructions from one of a wave to its next
     static_assert(NP > 0 || (NA % NI == 0 && NB % NI == 0), "no padding");
-    auto a_instr = [&](int p) { return (NP ? fw * PA : fw) + p * GAP; };
-    auto b_instr = [&](int p) { return (NP ? fw * PB : fw) + p * GAP; };
-    auto chunk_of = [&](int r) { return (lane & 7) ^ ((r >> 1) & 7); };     // logical chunk that lands in this lane's slot of row r
+    auto a_instr = [&](int p) __attribute__((always_inline)) { return (NP ? fw * PA : fw) + p * GAP; };
+    auto b_instr = [&](int p) __attribute__((always_inline)) { return (NP ? fw * PB : fw) + p * GAP; };
+    auto chunk_of = [&](int r) __attribute__((always_inline)) { return (lane & 7) ^ ((r >> 1) & 7); };     // logical chunk that lands in this lane's slot of row r
     unsigned off[PL], out[PA];                      // out: bit t: tap t (of 0..31) of this row is outside
     const bool partial = (P.Cs % BK) != 0;          // last channel chunk is short
     if (fetcher) {
@@ -192,7 +192,7 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
     }
     const unsigned spanA = (unsigned)(P.NB * P.Hs * P.Ws * P.Cs) * 2u, spanB = (unsigned)((KROWS ? P.Cd : P.Cs) * P.b_row_pitch) * 2u;
     const unsigned to_a = lds0 + (NP ? fw * PA : fw) * 1024, to_b = lds0 + ABYTES + (NP ? fw * PB : fw) * 1024;
-    auto uniform = [](int v) { return (unsigned)__builtin_amdgcn_readfirstlane(v); };
+    auto uniform = [](int v) __attribute__((always_inline)) { return (unsigned)__builtin_amdgcn_readfirstlane(v); };
 
     // The contraction step the next loads fetch: tap (counted from the first), its column in the grid of taps, channel
     // chunk, and the tap's byte displacements in the source image (ad) and in a filter row (bo).
@@ -206,18 +206,18 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
     const int bk = KROWS ? ROWB : BK * P.b_row_pitch * 2;       // filter bytes from one channel chunk to the next
     // Any layer.  What only the last, short channel chunk or a 33rd tap needs is kept off the common path.
     struct Step { int tap, col, kc, ad, bo; };
+    const int4v rsrcA0 = make_rsrc(P.A, spanA), rsrcB0 = make_rsrc(P.B, spanB);
     auto issue = [&](int stage, Step& nx) __attribute__((always_inline)) {
-        const int4v rsrcA = make_rsrc(P.A, spanA), rsrcB = make_rsrc(P.B, spanB);
         const unsigned cbytes = uniform(nx.kc * ROWB), bsoff = uniform(nx.bo + nx.kc * bk), ad = uniform(nx.ad);
         const unsigned base_a = uniform((int)(to_a + stage * STAGE)), base_b = uniform((int)(to_b + stage * STAGE));
         const int cleft = P.Cs - nx.kc * BK;        // channels left from this chunk's start
-        auto load_a = [&](int p, unsigned voff) { dma16(voff, rsrcA, cbytes, base_a + p * GAP * 1024); };
-        auto load_b = [&](int p, unsigned voff) { dma16(voff, rsrcB, bsoff, base_b + p * GAP * 1024); };
+        auto load_a = [&](int p, unsigned voff) { dma16(voff, rsrcA0, cbytes, base_a + p * GAP * 1024); };
+        auto load_b = [&](int p, unsigned voff) { dma16(voff, rsrcB0, bsoff, base_b + p * GAP * 1024); };
         // (in the rare branches the lane number is read anew: what follows from it is not kept in registers meanwhile)
         if (partial && cleft < BK) {
             int lane = threadIdx.x & 63;
             asm volatile("" : "+v"(lane));
-            auto chunk_of = [&](int r) { return (lane & 7) ^ ((r >> 1) & 7); };
+            auto chunk_of = [&](int r) __attribute__((always_inline)) { return (lane & 7) ^ ((r >> 1) & 7); };
 #pragma unroll
             for (int p = 0; p < PA; ++p) {
                 const int r = a_instr(p) * 8 + (lane >> 3);
@@ -263,10 +263,10 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
 
     if constexpr (NP > 0) if (fetcher) {
         // ---- dedicated fetching wave: S-1 steps ahead of the multipliers ---------------------
-        auto fetch_all = [&](auto send) __attribute__((always_inline)) {
-            int is = 0;
+        int is = 0;
+        auto fetch = [&](int from, int to, auto send) __attribute__((always_inline)) {
 #pragma unroll 1
-            for (int q = 0; q < nk; ++q) {
+            for (int q = from; q < to; ++q) {
                 if (q >= S - 1) {
                     wait_vmcnt<INFLIGHT>();
                     stage_barrier();       // step q-(S-1) is in LDS; the stage before it is free
@@ -277,7 +277,7 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
         };
         if (P.tap_bias < 0) {
             Step nx{0, 0, 0, ad0, bo0};
-            fetch_all([&](int stage) __attribute__((always_inline)) { issue(stage, nx); });
+            fetch(0, nk, [&](int stage) __attribute__((always_inline)) { issue(stage, nx); });
         } else {
             // A wave issues an instruction every four to six cycles and the texture path takes a load in 16, so the number
             // of its instructions is what bounds a fetching wave: a 64x64 tile's step of 16 loads took the time of 64
@@ -293,37 +293,61 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
             for (int p = 0; p < PA; ++p) off[p] += kRunSlack - run_offset(p);
 #pragma unroll
             for (int p = 0; p < PB; ++p) off[PA + p] += kRunSlack - run_offset(p);
-            int so_a = P.tap_bias + ad0, so_b = bo0;
+            int so_a = P.tap_bias + ad0, so_b = bo0, tap = 0, col = 0;
+            const int whole = partial ? nk - ntaps : nk;        // steps with 64 channels
+            // a chunk's last tap lies (count_h - 1) rows and (count_w - 1) columns from the next chunk's first
+            // (ad_kh, bo_kh: what such a move is more than one to the next row of taps)
+            const int ad_kh = ROWB - ((th.count - 1) * P.tap_dh * P.Ws + (tw.count - 1) * P.tap_dw) * P.Cs * 2 - ad_h;
+            const int bo_kh = bk - ((th.count - 1) * P.tap_sh * P.S + (tw.count - 1) * P.tap_sw) * bpt - bo_h;
+            auto next_tap = [&]() __attribute__((always_inline)) {
+                if (++col < tw.count) {
+                    ++tap;
+                    so_a += ad_w;
+                    so_b += bo_w;
+                } else {
+                    const bool last = tap + 1 == ntaps;
+                    col = 0;
+                    tap = last ? 0 : tap + 1;
+                    so_a += ad_h + (last ? ad_kh : 0);
+                    so_b += bo_h + (last ? bo_kh : 0);
+                }
+            };
             if (P.pointwise) {
-                fetch_all([&](int stage) __attribute__((always_inline)) {
+                fetch(0, whole, [&](int stage) __attribute__((always_inline)) {
                     dma16_runs<PA>(off, rsrcA, uniform(so_a), uniform((int)(to_a + stage * STAGE)));
                     dma16_runs<PB>(off + PA, rsrcB, uniform(so_b), uniform((int)(to_b + stage * STAGE)));
                     so_a += ROWB;
                     so_b += bk;
                 });
             } else {
-                // a chunk's last tap lies (count_h - 1) rows and (count_w - 1) columns from the next chunk's first
-                const int ad_k = ROWB - ((th.count - 1) * P.tap_dh * P.Ws + (tw.count - 1) * P.tap_dw) * P.Cs * 2;
-                const int bo_k = bk - ((th.count - 1) * P.tap_sh * P.S + (tw.count - 1) * P.tap_sw) * bpt;
-                int tap = 0, col = 0;
-                fetch_all([&](int stage) __attribute__((always_inline)) {
+                fetch(0, whole, [&](int stage) __attribute__((always_inline)) {
                     unsigned v[PA];
                     const int sh = 31 - tap;
 #pragma unroll
                     for (int p = 0; p < PA; ++p) v[p] = (out[p] << sh & kOutOfRange) | off[p];
                     dma16_runs<PA>(v, rsrcA, uniform(so_a), uniform((int)(to_a + stage * STAGE)));
                     dma16_runs<PB>(off + PA, rsrcB, uniform(so_b), uniform((int)(to_b + stage * STAGE)));
-                    if (++col < tw.count) {
-                        ++tap;
-                        so_a += ad_w;
-                        so_b += bo_w;
-                    } else {
-                        const bool last = tap + 1 == ntaps;
-                        col = 0;
-                        tap = last ? 0 : tap + 1;
-                        so_a += last ? ad_k : ad_h;
-                        so_b += last ? bo_k : bo_h;
-                    }
+                    next_tap();
+                });
+            }
+            if (whole < nk) {           // the last channel chunk is short
+                const int cleft = P.Cs % BK;
+#pragma unroll
+                for (int p = 0; p < PA; ++p)
+                    if (chunk_of(a_instr(p) * 8 + (lane >> 3)) * 8 >= cleft) { off[p] = kOutOfRange; out[p] = ~0u; }
+#pragma unroll
+                for (int p = 0; p < PB; ++p) {
+                    const int contraction = KROWS ? chunk_of(b_instr(p) * 8 + (lane >> 3)) * 8 : (b_instr(p) * 64 + lane) / (BN / 8);
+                    if (contraction >= cleft) off[PA + p] = kOutOfRange;
+                }
+                fetch(whole, nk, [&](int stage) __attribute__((always_inline)) {
+                    unsigned v[PA];
+                    const int sh = 31 - tap;
+#pragma unroll
+                    for (int p = 0; p < PA; ++p) v[p] = (out[p] << sh & kOutOfRange) | off[p];
+                    dma16_runs<PA>(v, rsrcA, uniform(so_a), uniform((int)(to_a + stage * STAGE)));
+                    dma16_runs<PB>(off + PA, rsrcB, uniform(so_b), uniform((int)(to_b + stage * STAGE)));
+                    next_tap();
                 });
             }
         }

@@ -116,6 +116,31 @@ def test_fused_igemm_variants(variant):
             check_fused(d, x, w, g, f"fused_v{variant}{case}", seed=variant)
 
 
+@pytest.mark.parametrize("bad", [None, np.inf, np.nan])
+def test_unreached_positions_with_a_scale_that_is_not_finite(bad):
+    """1x1 stride 2: three of four positions have no tap, and their sum is 0: times an infinite scale NaN where the mask
+    lets it through, 0 elsewhere, in the tile with that channel and in the one without it."""
+    d = sd.make_desc(2, 31, 26, 200, 136, 1, 1, (2, 2), (0, 0))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    g = torch.randn(2, 16, 13, 136, device="cuda", generator=gen).half()
+    w = torch.randn(136, 1, 1, 200, device="cuda", generator=gen).half()
+    mask = torch.randn(2, 31, 26, 200, device="cuda", generator=gen).half().relu_()
+    scale = torch.randn(200, device="cuda", generator=gen)
+    if bad is not None:
+        scale[3] = bad
+    for variant in (334, 310):
+        dx = torch.full((2, 31, 26, 200), 7.0, dtype=torch.float16, device="cuda")
+        with forced(SDCONV_IGEMM_VARIANT=variant):
+            sd.conv2d_dgrad_fused(d, g, w, dx, None, torch.cuda.current_stream().cuda_stream, scale=scale, relu_mask=mask)
+        torch.cuda.synchronize()
+        want = torch.where(mask > 0, (torch.zeros_like(mask).float() * scale).half(), torch.zeros_like(mask))
+        unreached = torch.ones(31, 26, dtype=torch.bool, device="cuda")
+        unreached[::2, ::2] = False
+        assert torch.equal(torch.isnan(dx[:, unreached]), torch.isnan(want[:, unreached]))
+        assert torch.equal(dx[:, unreached].nan_to_num(0.0), want[:, unreached].nan_to_num(0.0))
+
+
 FUSED_PATCH_SHAPES = [
     (2, 21, 37, 64, 64, 3, 3, (1, 1), (1, 1), (1, 1)),
     (1, 19, 18, 128, 192, 3, 3, (1, 1), (1, 1), (1, 1)),

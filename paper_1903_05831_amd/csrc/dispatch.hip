@@ -2,6 +2,7 @@
 #include "common.h"
 #include "igemm.h"
 #include "wgrad.h"
+#include "dma.h"
 #include "thin.h"
 #include "narrow.h"
 #include <math.h>
@@ -75,6 +76,13 @@ static bool byte_offsets_fit_31_bits(const Geom& g)
 static bool wgrad_offsets_fit_31_bits(const Geom& g)
 {
     return byte_offsets_fit_31_bits(g) && (long)(g.K < 32 ? g.K : 32) * g.R * g.S * g.C <= 1L << 29;
+}
+
+// Fetching waves of the weight gradient use descriptors that start kRunSlack before their tensor and the same mark.
+static bool wgrad_runs_fit(const Geom& g)
+{
+    const long most = (1L << 31) - kRunSlack;
+    return 2L * g.N * g.H * g.W * g.C <= most && 2L * g.N * g.Ho * g.Wo * g.K <= most;
 }
 
 // The MFMA route moves 16-byte (8-half) vectors along the channel axis of every tensor.
@@ -440,23 +448,28 @@ static const WgradVariant& wgrad_variant(int v)
 // `fixed`; the operands move at `hbm` MB/us meanwhile, and the sums leave at `store` MB/us after the loop.
 // The constants are fits like those of kRowModels (fit_models.py, same bounds).  The time has a narrow
 // minimum between too few workgroups and the traffic of too many partial sums: rules by channel counts
-// with one number of ranges for all lost 48 % over layers of random size.  The choice is 1.7 % slower than
-// the fastest measured (variant, ranges) pair on layers left out of the fit (5.8 % at the 90th percentile), and 1.6 % (5.4 %)
-// on 543 detector layers on images of random size.
+// with one number of ranges for all lost 48 % over layers of random size.  The choice is 2.0 % slower than
+// the fastest measured (variant, ranges) pair on layers left out of the fit (6.4 % at the 90th percentile); without the
+// variants that have fetching waves (120 and up) it was 3.7 % slower than that (10.4 %).
 struct WgradCost { float fixed, step, shared, tile, store, hbm; };
 struct WgradModel { int variant, per_cu; WgradCost linear, gather; };   // per_cu: workgroups a compute unit holds
 static const WgradModel kWgradModels[] = {
-    {104, 2, {3.584f, 0.447f, 0.439f, 0.000f, 2.953f, 6.100f}, {3.351f, 0.632f, 0.403f, 0.507f, 3.032f, 3.672f}},
-    {107, 3, {2.670f, 0.340f, 0.300f, 0.000f, 2.813f, 4.998f}, {3.298f, 0.416f, 0.265f, 0.000f, 3.013f, 3.620f}},
-    {108, 2, {3.643f, 0.442f, 0.385f, 0.000f, 2.899f, 5.786f}, {3.069f, 0.562f, 0.366f, 0.881f, 3.041f, 3.897f}},
-    {112, 1, {2.247f, 0.543f, 0.000f, 2.270f, 3.107f, 6.100f}, {2.788f, 0.602f, 0.000f, 1.881f, 3.472f, 3.724f}},
-    {114, 1, {3.146f, 1.372f, 0.000f, 5.627f, 4.982f, 4.833f}, {4.000f, 1.479f, 0.000f, 4.425f, 5.715f, 3.858f}},
-    {115, 1, {3.424f, 1.411f, 0.000f, 5.435f, 5.316f, 5.437f}, {4.152f, 1.602f, 0.000f, 4.202f, 6.100f, 4.737f}},
-    {116, 1, {2.349f, 0.533f, 0.000f, 2.160f, 3.071f, 6.100f}, {2.795f, 0.633f, 0.000f, 1.883f, 3.430f, 4.193f}},
-    {117, 1, {3.272f, 0.873f, 0.000f, 2.842f, 3.621f, 5.733f}, {3.392f, 0.932f, 0.000f, 2.703f, 4.464f, 3.794f}},
-    {118, 3, {2.690f, 0.344f, 0.300f, 0.000f, 2.695f, 5.033f}, {3.266f, 0.411f, 0.263f, 0.000f, 2.895f, 3.626f}},
-    {119, 2, {4.258f, 0.780f, 0.499f, 0.000f, 3.279f, 5.328f}, {3.836f, 0.795f, 0.469f, 1.240f, 3.714f, 3.925f}},
+    {104, 2, {2.969f, 0.229f, 0.424f, 0.000f, 2.682f, 5.811f}, {3.108f, 0.575f, 0.384f, 0.000f, 2.694f, 2.900f}},
+    {107, 3, {2.506f, 0.337f, 0.296f, 0.000f, 2.923f, 4.657f}, {2.913f, 0.393f, 0.257f, 0.000f, 2.784f, 2.854f}},
+    {108, 2, {2.933f, 0.425f, 0.381f, 0.000f, 2.748f, 5.232f}, {3.132f, 0.525f, 0.354f, 0.000f, 2.654f, 2.893f}},
+    {112, 1, {1.384f, 0.523f, 0.000f, 2.411f, 2.941f, 6.029f}, {2.852f, 0.544f, 0.000f, 1.170f, 2.828f, 2.923f}},
+    {114, 1, {2.214f, 1.242f, 0.000f, 4.283f, 4.184f, 5.358f}, {4.690f, 1.297f, 0.000f, 2.222f, 4.829f, 3.286f}},
+    {115, 1, {3.006f, 1.356f, 0.000f, 4.085f, 4.676f, 6.100f}, {5.020f, 1.550f, 0.000f, 1.699f, 5.342f, 3.762f}},
+    {116, 1, {1.580f, 0.521f, 0.000f, 2.335f, 3.032f, 6.100f}, {3.027f, 0.618f, 0.000f, 0.946f, 2.999f, 3.128f}},
+    {117, 1, {2.682f, 0.854f, 0.000f, 2.585f, 3.442f, 6.100f}, {3.643f, 0.852f, 0.000f, 1.595f, 3.756f, 3.057f}},
+    {118, 3, {2.547f, 0.339f, 0.297f, 0.000f, 3.149f, 4.687f}, {2.941f, 0.396f, 0.255f, 0.000f, 2.818f, 2.827f}},
+    {119, 2, {2.943f, 0.744f, 0.500f, 0.000f, 3.120f, 5.044f}, {3.530f, 0.737f, 0.458f, 0.000f, 3.255f, 2.856f}},
+    {120, 1, {1.463f, 0.455f, 0.000f, 2.093f, 2.732f, 5.133f}, {3.070f, 0.497f, 0.000f, 1.373f, 3.041f, 3.156f}},
+    {121, 3, {2.499f, 0.312f, 0.292f, 0.000f, 2.698f, 4.254f}, {3.059f, 0.326f, 0.251f, 0.000f, 2.682f, 2.979f}},
+    {122, 2, {3.018f, 0.398f, 0.377f, 0.000f, 2.676f, 4.903f}, {3.506f, 0.416f, 0.336f, 0.097f, 2.725f, 3.058f}},
+    {123, 1, {2.434f, 0.677f, 0.000f, 3.218f, 3.560f, 6.067f}, {3.861f, 0.778f, 0.000f, 2.074f, 4.021f, 3.528f}},
 };
+constexpr float kWorthScratch = 1.1f;      // see choose_wgrad
 constexpr float kReduceFixed = 2.5f, kReduceRate = 6.0f;    // us with the gap between the kernels, MB/us
 
 static long wgrad_steps(const Geom& g) { return ((long)g.N * g.Ho * g.Wo + 63) / 64; }
@@ -523,18 +536,31 @@ static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial
 
 // Tile variant and pixel ranges.  A layer with an entry takes its variant and, at the measured batch, its
 // ranges if it has any; else the model's for that variant.
-static WgradChoice choose_wgrad(const Geom& g, size_t partial_limit)
+static WgradChoice choose_wgrad(const Geom& g, size_t copies)
 {
+    const size_t partial_limit = wgrad_partial_limit(g, copies);
     const int fv = forced_wgrad_variant();
-    const bool forced = (fv >= 0 && fv < kNumWgradVariants) || (fv >= 100 && fv < 100 + kNumWgradDmaVariants && wgrad_variant(fv).name);
+    const bool runs = wgrad_runs_fit(g);
+    const bool forced = (fv >= 0 && fv < kNumWgradVariants) || (fv >= 100 && fv < 100 + kNumWgradDmaVariants && wgrad_variant(fv).name && (runs || !wgrad_variant(fv).runs));
     int only = forced ? fv : -1;
     const WgradEntry* e = nullptr;
     if (!wgrad_offsets_fit_31_bits(g)) only = g.K <= 64 ? 1 : 0;
     else if (!forced && (e = wgrad_entry(g))) only = e->variant;
     WgradChoice c{-1, 1, 0.f};
-    if (!(e && e->splits > 0 && e->N == g.N))
+    auto choose = [&](size_t limit) {
+        WgradChoice best{-1, 1, 0.f};
         for (const WgradModel& m : kWgradModels)
-            if (only < 0 || m.variant == only) wgrad_best_splits(g, m, partial_limit, &c);
+            if (only < 0 ? runs || !wgrad_variant(m.variant).runs : m.variant == only) wgrad_best_splits(g, m, limit, &best);
+        return best;
+    };
+    if (!(e && e->splits > 0 && e->N == g.N)) c = choose(partial_limit);
+    // Partial sums that outgrow the static scratch have to be worth it: the models are off by some per cent, and
+    // conv2d_wgrad_static_scratch refuses the layer for them.
+    const size_t scratch = SDCONV_STATIC_SCRATCH_BYTES, left = copies < scratch ? scratch - copies : 0;
+    if (c.variant >= 0 && c.splits > 1 && (size_t)c.splits * 4 * g.K * g.R * g.S * g.C > left && left < partial_limit) {
+        const WgradChoice within = choose(left);
+        if (within.variant >= 0 && within.us <= kWorthScratch * c.us) c = within;
+    }
     if (c.variant < 0) {
         long want;
         if (e) {
@@ -568,7 +594,7 @@ static Plan plan_wgrad_beside(const Geom& g, size_t copies)
     }
     if (thin_ok(g)) return Plan{ROUTE_THIN, 0, 1, align256(thin_wgrad_partial_bytes(g)), "thin_wgrad"};
     if (!igemm_ok(g)) return Plan{ROUTE_DIRECT, 0, 1, 0, "direct_wgrad"};
-    const WgradChoice c = choose_wgrad(g, wgrad_partial_limit(g, copies));
+    const WgradChoice c = choose_wgrad(g, copies);
     const int v = c.variant;
     const long total_steps = wgrad_steps(g), sps = (total_steps + c.splits - 1) / c.splits;
     const int splits = (int)((total_steps + sps - 1) / sps);

@@ -19,11 +19,11 @@ struct WgradParams {
     int total_blocks;     // tiles_c * tiles_k * R * S * splits (set by the launcher)
 };
 
-struct WgradVariant { int bm, bn; const char* name; };
+struct WgradVariant { int bm, bn; const char* name; bool runs; };      // runs: sent by fetching waves (dma16_runs)
 constexpr int kNumWgradVariants = 2;
 extern const WgradVariant kWgradVariants[kNumWgradVariants];
 
-constexpr int kNumWgradDmaVariants = 20;        // pipelined, 100 and up; numbers without a name: measured, not in the library
+constexpr int kNumWgradDmaVariants = 24;        // pipelined, 100 and up; numbers without a name: measured, not in the library
 extern const std::array<WgradVariant, kNumWgradDmaVariants> kWgradDmaVariants;
 hipError_t launch_wgrad_dma(int variant, const WgradParams& P, hipStream_t st);
 hipError_t launch_wgrad(int variant, const WgradParams& P, hipStream_t st);

@@ -31,17 +31,21 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 typedef float float4w __attribute__((ext_vector_type(4)));
 
-// HF: only the upper half of the waves sends the loads (and then multiplies like the others).
-// With two waves per SIMD the lower wave keeps the matrix pipe busy while its partner is stalled
-// in the burst of LDS-DMA instructions, instead of both stalling at once (see igemm_ws.hip).
+// F: who fetches.  0: every wave its share.  -1: only the upper half of the waves sends the loads (and then multiplies like
+// the others); with two waves per SIMD the lower wave keeps the matrix pipe busy while its partner is stalled
+// in the burst of LDS-DMA instructions, instead of both stalling at once (see igemm_ws_body.h).  F > 0: so many waves
+// do nothing else.  The others then need no registers for addresses, and four waves of 64x64 read a third less of
+// LDS than eight of 64x32: 3x3 256->256 on 2x50x84 with its reduction 23.8 -> 22.8 us, 1x1 1024->256 16.1 -> 14.9, 1x1 128->512
+// on 2x100x168 16.2 -> 15.0, 3x3 stride 2 on 173x271 16.8 -> 15.4, each at its best number of ranges.
 // MF: 32 = v_mfma_f32_32x32x16_f16 blocks, 16 = v_mfma_f32_16x16x32_f16 blocks (measured faster
 // on the large tiles).
-template <int BM, int BN, int WGM, int WGN, int S, int BP, bool LINEAR, bool HF, int MF>
-__global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P)
+template <int BM, int BN, int WGM, int WGN, int S, int BP, bool LINEAR, int F, int MF>
+__global__ __launch_bounds__(64 * (WGM * WGN + (F > 0 ? F : 0))) void wgrad_dma_kernel(WgradParams P)
 {
-    constexpr int NW = WGM * WGN;
-    constexpr int NWF = HF ? NW / 2 : NW, NT = 64 * NWF;    // fetching waves / threads
-    constexpr int FW0 = NW - NWF;                           // first fetching wave
+    constexpr int NW = WGM * WGN;                           // multiplying waves
+    constexpr bool HF = F < 0;
+    constexpr int NWF = F > 0 ? F : HF ? NW / 2 : NW, NT = 64 * NWF;    // fetching waves / threads
+    constexpr int FW0 = F > 0 ? NW : NW - NWF;              // first fetching wave
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int FM = WM / MF, FN = WN / MF;
     constexpr int ACCN = MF == 32 ? 16 : 4, KSTEP = MF == 32 ? 16 : 32;
@@ -51,7 +55,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P
     constexpr int GBYTES = BP * BM * 2, XBYTES = BP * BN * 2, STAGE = GBYTES + XBYTES;
     constexpr int INFLIGHT = (S - 2) * (PG + PX);
     static_assert((MF == 32 || MF == 16) && WM % MF == 0 && WN % MF == 0 && BP % KSTEP == 0, "wave tile");
-    static_assert(PG >= 1 && PX >= 1 && BP % RPG == 0 && BP % RPX == 0 && RPG % 4 == 0 && RPX % 4 == 0, "staging");
+    static_assert(PG >= 1 && PX >= 1 && BP % RPG == 0 && BP % RPX == 0, "staging");
+    static_assert(F > 0 ? BP == 64 : RPG % 4 == 0 && RPX % 4 == 0, "staging");
     static_assert(S >= 2 && INFLIGHT < 64 && BP % 16 == 0 && BP <= 64 * NW, "pipeline");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -86,6 +91,98 @@ __global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P
     int nsteps = total_steps - step0;
     if (nsteps > P.steps_per_split * bp_per_64) nsteps = P.steps_per_split * bp_per_64;
     if (nsteps < 0) nsteps = 0;
+
+    if constexpr (F > 0) if (wave >= NW) {
+        // ---- a wave that only fetches ----------------------------------------------------------
+        // PG consecutive load instructions of a step's dy tile and PX of its x tile, sent in runs (dma.h).  In gathering
+        // layers lane l finds the place of pixel l of a step, and the loads ask it by a lane shuffle; that is
+        // done before the barrier behind which the loads go out.
+        constexpr int LG = BM / 8, LX = BN / 8;             // lanes to a row
+        unsigned g_off[PG], x_off[PX], x_out[PX];
+        int g_row[PG], x_row[PX];
+#pragma unroll
+        for (int i = 0; i < PG; ++i) {
+            g_row[i] = (fw * PG + i) * (64 / LG) + lane / LG;
+            const int k = k0 + swizzled_chunk<BM>(g_row[i], lane % LG) * 8;
+            g_off[i] = (k < P.K ? (unsigned)((g_row[i] * P.K + k) * 2) : kOutOfRange) + kRunSlack - run_offset(i);
+        }
+#pragma unroll
+        for (int i = 0; i < PX; ++i) {
+            x_row[i] = (fw * PX + i) * (64 / LX) + lane / LX;
+            const int c = c0 + swizzled_chunk<BN>(x_row[i], lane % LX) * 8;
+            x_out[i] = c < P.C ? 0u : kOutOfRange;
+            x_off[i] = (unsigned)((LINEAR ? x_row[i] * P.C + c : c) * 2) + kRunSlack - run_offset(i);
+            if (LINEAR) x_off[i] |= x_out[i];
+        }
+        const int4v rsrcG = make_rsrc(reinterpret_cast<const unsigned char*>(P.G) - kRunSlack, (unsigned)(P.P * P.K) * 2u + kRunSlack);
+        const int4v rsrcX = make_rsrc(reinterpret_cast<const unsigned char*>(P.X) - kRunSlack, (unsigned)(P.N * P.H * P.W * P.C) * 2u + kRunSlack);
+        const unsigned to_g = lds0 + fw * PG * 1024, to_x = lds0 + GBYTES + fw * PX * 1024;
+        const int hw = P.Ho * P.Wo;
+        const int adv_n = BP / hw, adv_ho = (BP % hw) / P.Wo, adv_wo = (BP % hw) % P.Wo;
+        int left = P.P - step0 * BP;                        // pixels from the step's first to the last
+        int n = 0, ho = 0, wo = 0;
+        if (!LINEAR) {
+            const int px = step0 * BP + lane;
+            n = px / hw;
+            ho = (px - n * hw) / P.Wo;
+            wo = px - n * hw - ho * P.Wo;
+        }
+        unsigned so_g = (unsigned)(step0 * BP) * P.K * 2, so_x = LINEAR ? (unsigned)(step0 * BP) * P.C * 2 : 0u;
+        unsigned v[PX];
+        auto place = [&]() __attribute__((always_inline)) {
+            if (LINEAR) return;
+            const int h = ho * P.sh + oh, w = wo * P.sw + ow;
+            unsigned at = (unsigned)((((n * P.H + h) * P.W + w) * P.C) * 2);
+            if ((unsigned)h >= (unsigned)P.H || (unsigned)w >= (unsigned)P.W || lane >= left) at = kOutOfRange;
+#pragma unroll
+            for (int i = 0; i < PX; ++i) v[i] = __shfl(at, x_row[i]);
+#pragma unroll
+            for (int i = 0; i < PX; ++i) v[i] = (v[i] & kOutOfRange) | x_out[i] | (v[i] + x_off[i]);
+            wo += adv_wo;
+            int carry = wo >= P.Wo;
+            wo -= carry ? P.Wo : 0;
+            ho += adv_ho + carry;
+            carry = ho >= P.Ho;
+            ho -= carry ? P.Ho : 0;
+            n += adv_n + carry;
+        };
+        auto send = [&](int stage) __attribute__((always_inline)) {
+            const unsigned sg = __builtin_amdgcn_readfirstlane(so_g), sx = __builtin_amdgcn_readfirstlane(so_x);
+            const unsigned lg = __builtin_amdgcn_readfirstlane(to_g + stage * STAGE), lx = __builtin_amdgcn_readfirstlane(to_x + stage * STAGE);
+            if (left >= BP) {
+                dma16_runs<PG>(g_off, rsrcG, sg, lg);
+                if (LINEAR) dma16_runs<PX>(x_off, rsrcX, sx, lx); else dma16_runs<PX>(v, rsrcX, sx, lx);
+            } else {                                        // the pixels end within the step
+                unsigned vg[PG], vx[PX];
+#pragma unroll
+                for (int i = 0; i < PG; ++i) vg[i] = g_row[i] < left ? g_off[i] : kOutOfRange;
+#pragma unroll
+                for (int i = 0; i < PX; ++i) vx[i] = !LINEAR ? v[i] : x_row[i] < left ? x_off[i] : kOutOfRange;
+                dma16_runs<PG>(vg, rsrcG, sg, lg);
+                dma16_runs<PX>(vx, rsrcX, sx, lx);
+            }
+            so_g += BP * P.K * 2;
+            if (LINEAR) so_x += BP * P.C * 2;
+            left -= BP;
+        };
+        int is = 0;
+        place();
+#pragma unroll 1
+        for (int q = 0; q < nsteps; ++q) {
+            if (q >= S - 1) {
+                wait_vmcnt<INFLIGHT>();
+                stage_barrier();
+            }
+            send(is);
+            is = (is + 1 == S) ? 0 : is + 1;
+            place();
+        }
+        for (int it = nsteps > S - 1 ? nsteps - (S - 1) : 0; it < nsteps; ++it) {
+            if (it + S - 2 < nsteps) wait_vmcnt<INFLIGHT>(); else wait_vmcnt<0>();
+            stage_barrier();
+        }
+        return;
+    }
 
     // ---- fixed per-thread parts of the offsets ----------------------------------------------
     unsigned g_off[PG], x_add[PX];
@@ -185,6 +282,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P
 #pragma unroll
             for (int e = 0; e < ACCN; ++e) acc[a][c][e] = 0.f;
 
+    // ORDERED: the first portion's fragments are read at once and the next one's between the matrix instructions, where
+    // the compiler reads them before their use (256x256 tiles with their reduction, 3x3 512->512 on 25 088 pixels 115.4 ->
+    // 111.0 us, 1x1 2048->512 65.2 -> 62.6; 128x128 with fetching waves, 3x3 256->256 on 2x50x84 23.9 -> 22.8).  Waves with
+    // smaller tiles have too few matrix instructions to read behind (64x64 tiles 3-4 % slower).
+    constexpr int NCH = BP / KSTEP;
+    constexpr bool ORDERED = MF == 16 && NCH > 1 && WM * WN >= 64 * 64;
     auto compute = [&](int stage) {
         const unsigned char* sg = smem + stage * STAGE;
         const unsigned char* sx = sg + GBYTES;
@@ -211,10 +314,27 @@ __global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P
                         acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[c], fa[a], acc[a][c], 0, 0, 0);
                 }
         }
+        if constexpr (ORDERED) {        // 0x100: LDS reads, 0x008: matrix instructions
+            constexpr int FIRST = 2 * (FM + FN), REST = (NCH - 1) * FIRST, MULS = NCH * FM * FN, EACH = (REST + MULS - 1) / MULS;
+            __builtin_amdgcn_sched_group_barrier(0x100, FIRST, 0);
+#pragma unroll
+            for (int i = 0; i < (REST + EACH - 1) / EACH; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, EACH, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, MULS, 0);
+        }
     };
 
     // ---- ring pipeline ---------------------------------------------------------------------------
-    if (nsteps > 0) {
+    if constexpr (F > 0) {
+        int cs = 0;
+        for (int it = 0; it < nsteps; ++it) {
+            stage_barrier();
+            compute(cs);
+            cs = (cs + 1 == S) ? 0 : cs + 1;
+        }
+    } else if (nsteps > 0) {
 #pragma unroll
         for (int q = 0; q < S; ++q)
             if (q < nsteps) fill_table(q);
@@ -267,7 +387,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void wgrad_dma_kernel(WgradParams P
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, int S, int BP, bool HF, int MF>
+template <int BM, int BN, int WGM, int WGN, int S, int BP, int F, int MF>
 static hipError_t launch_wdma(const WgradParams& P0, hipStream_t st)
 {
     constexpr size_t lds = (size_t)S * BP * (BM + BN) * 2 + (size_t)S * BP * sizeof(unsigned);
@@ -276,11 +396,11 @@ static hipError_t launch_wdma(const WgradParams& P0, hipStream_t st)
     static std::atomic<bool> configured{false};   // set once the attribute call has succeeded; a second thread may repeat it, harmlessly
     if (!configured.load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&wgrad_dma_kernel<BM, BN, WGM, WGN, S, BP, false, HF, MF>),
+            reinterpret_cast<const void*>(&wgrad_dma_kernel<BM, BN, WGM, WGN, S, BP, false, F, MF>),
             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&wgrad_dma_kernel<BM, BN, WGM, WGN, S, BP, true, HF, MF>),
+            reinterpret_cast<const void*>(&wgrad_dma_kernel<BM, BN, WGM, WGN, S, BP, true, F, MF>),
             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         configured.store(true, std::memory_order_release);
@@ -289,30 +409,34 @@ static hipError_t launch_wdma(const WgradParams& P0, hipStream_t st)
     P.total_blocks = P.tiles_c * P.tiles_k * P.R * P.S * P.splits;
     const long blocks = ((long)P.total_blocks + 63) / 64 * 64;     // whole runs of 8 tiles on each of 8 XCDs
     if (linear)
-        hipLaunchKernelGGL((wgrad_dma_kernel<BM, BN, WGM, WGN, S, BP, true, HF, MF>), dim3((unsigned)blocks),
-                           dim3(64 * WGM * WGN), lds, st, P);
+        hipLaunchKernelGGL((wgrad_dma_kernel<BM, BN, WGM, WGN, S, BP, true, F, MF>), dim3((unsigned)blocks),
+                           dim3(64 * (WGM * WGN + (F > 0 ? F : 0))), lds, st, P);
     else
-        hipLaunchKernelGGL((wgrad_dma_kernel<BM, BN, WGM, WGN, S, BP, false, HF, MF>), dim3((unsigned)blocks),
-                           dim3(64 * WGM * WGN), lds, st, P);
+        hipLaunchKernelGGL((wgrad_dma_kernel<BM, BN, WGM, WGN, S, BP, false, F, MF>), dim3((unsigned)blocks),
+                           dim3(64 * (WGM * WGN + (F > 0 ? F : 0))), lds, st, P);
     return hipGetLastError();
 }
 
-// number - 100, tile, waves, ring stages, pixels of a step, upper half fetches, matrix block, name
+// number - 100, tile, multiplying waves, ring stages, pixels of a step, fetching waves (F above), matrix block, name
 #define SDCONV_WGRAD_VARIANTS(X) \
-    X(4, 64, 128, 1, 4, 3, 64, false, 32, "wgrad_dma_64x128x64_4w_s3") \
-    X(7, 64, 64, 2, 2, 3, 64, false, 32, "wgrad_dma_64x64x64_4w_s3") \
-    X(8, 128, 64, 2, 2, 3, 64, false, 32, "wgrad_dma_128x64x64_4w_s3") \
-    X(12, 128, 128, 2, 4, 3, 64, true, 32, "wgrad_dma_128x128x64_8w_s3_hf") \
-    X(14, 256, 256, 2, 4, 2, 64, true, 16, "wgrad_dma_256x256x64_8w_s2_hf_m16") \
-    X(15, 256, 256, 2, 4, 3, 32, true, 16, "wgrad_dma_256x256x32_8w_s3_hf_m16") \
-    X(16, 128, 128, 2, 4, 3, 64, true, 16, "wgrad_dma_128x128x64_8w_s3_hf_m16") \
-    X(17, 256, 128, 4, 2, 3, 64, true, 16, "wgrad_dma_256x128x64_8w_s3_hf_m16") \
-    X(18, 64, 64, 2, 2, 3, 64, false, 16, "wgrad_dma_64x64x64_4w_s3_m16") \
-    X(19, 128, 128, 2, 2, 2, 64, false, 16, "wgrad_dma_128x128x64_4w_s2_m16")
+    X(4, 64, 128, 1, 4, 3, 64, 0, 32, "wgrad_dma_64x128x64_4w_s3") \
+    X(7, 64, 64, 2, 2, 3, 64, 0, 32, "wgrad_dma_64x64x64_4w_s3") \
+    X(8, 128, 64, 2, 2, 3, 64, 0, 32, "wgrad_dma_128x64x64_4w_s3") \
+    X(12, 128, 128, 2, 4, 3, 64, -1, 32, "wgrad_dma_128x128x64_8w_s3_hf") \
+    X(14, 256, 256, 2, 4, 2, 64, -1, 16, "wgrad_dma_256x256x64_8w_s2_hf_m16") \
+    X(15, 256, 256, 2, 4, 3, 32, -1, 16, "wgrad_dma_256x256x32_8w_s3_hf_m16") \
+    X(16, 128, 128, 2, 4, 3, 64, -1, 16, "wgrad_dma_128x128x64_8w_s3_hf_m16") \
+    X(17, 256, 128, 4, 2, 3, 64, -1, 16, "wgrad_dma_256x128x64_8w_s3_hf_m16") \
+    X(18, 64, 64, 2, 2, 3, 64, 0, 16, "wgrad_dma_64x64x64_4w_s3_m16") \
+    X(19, 128, 128, 2, 2, 2, 64, 0, 16, "wgrad_dma_128x128x64_4w_s2_m16") \
+    X(20, 128, 128, 2, 2, 3, 64, 4, 16, "wgrad_dma_128x128x64_4w4f_s3_m16") \
+    X(21, 64, 64, 2, 2, 3, 64, 4, 32, "wgrad_dma_64x64x64_4w4f_s3") \
+    X(22, 128, 64, 2, 2, 3, 64, 4, 32, "wgrad_dma_128x64x64_4w4f_s3") \
+    X(23, 256, 128, 4, 2, 3, 64, 4, 16, "wgrad_dma_256x128x64_8w4f_s3_m16")
 
 const std::array<WgradVariant, kNumWgradDmaVariants> kWgradDmaVariants = [] {
     std::array<WgradVariant, kNumWgradDmaVariants> v{};
-#define SDCONV_WGRAD_NAME(idx, BM, BN, WGM, WGN, S, BP, HF, MF, name) v[idx] = {BM, BN, name};
+#define SDCONV_WGRAD_NAME(idx, BM, BN, WGM, WGN, S, BP, F, MF, name) v[idx] = {BM, BN, name, F > 0};
     SDCONV_WGRAD_VARIANTS(SDCONV_WGRAD_NAME)
     return v;
 }();
@@ -320,8 +444,8 @@ const std::array<WgradVariant, kNumWgradDmaVariants> kWgradDmaVariants = [] {
 hipError_t launch_wgrad_dma(int variant, const WgradParams& P, hipStream_t st)
 {
     switch (variant) {
-#define SDCONV_WGRAD_CASE(idx, BM, BN, WGM, WGN, S, BP, HF, MF, name) \
-        case idx: return launch_wdma<BM, BN, WGM, WGN, S, BP, HF, MF>(P, st);
+#define SDCONV_WGRAD_CASE(idx, BM, BN, WGM, WGN, S, BP, F, MF, name) \
+        case idx: return launch_wdma<BM, BN, WGM, WGN, S, BP, F, MF>(P, st);
         SDCONV_WGRAD_VARIANTS(SDCONV_WGRAD_CASE)
         default: return hipErrorInvalidValue;
     }

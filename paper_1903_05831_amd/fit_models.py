@@ -68,7 +68,7 @@ def out_hw(k):
 ROW_VARIANTS = [101, 112, 310, 311, 316, 324] + list(range(325, 341)) + [427, 433, 435, 436, 437]
 # variants with a row in the models (324 has those of its two halves)
 ROW_MODELS = [v for v in ROW_VARIANTS if v != 324]
-WGRAD_MODELS = WGRAD_VARIANTS = [104, 107, 108, 112, 114, 115, 116, 117, 118, 119]
+WGRAD_MODELS = WGRAD_VARIANTS = [104, 107, 108, 112, 114, 115, 116, 117, 118, 119, 120, 121, 122, 123]
 ONE_SLAB = {427, 433}                    # one patch buffer: 64 contraction channels only
 WORKGROUPS = (40, 64, 96, 128, 192, 256, 320, 384, 512, 768, 1024)
 
@@ -199,7 +199,7 @@ PATCHES = {427: (8, 16, 64), 433: (10, 14, 64), 435: (10, 14, 64), 436: (8, 16, 
 PER_CU = {101: 3, 112: 5, 327: 2, 328: 2, 339: 2, 340: 3, 427: 2, 433: 2}
 WGRAD_TILES = {100: (128, 128, 2), 104: (64, 128, 2), 107: (64, 64, 3), 108: (128, 64, 2), 109: (256, 256, 1),
                112: (128, 128, 1), 113: (256, 128, 1), 114: (256, 256, 1), 115: (256, 256, 1), 116: (128, 128, 1),
-               117: (256, 128, 1), 118: (64, 64, 3), 119: (128, 128, 2), 120: (64, 128, 2)}
+               117: (256, 128, 1), 118: (64, 64, 3), 119: (128, 128, 2), 120: (128, 128, 1), 121: (64, 64, 3), 122: (128, 64, 2), 123: (256, 128, 1)}
 FILTER_COPY = 3.2                   # us: the data gradient of the variants below 300 transposes the filter first
 EMPTY_TILE = 0.6                    # of `tile`: a tile of a parity class without taps only stores zeros
 REDUCE_FIXED, REDUCE_RATE = 2.5, 6.0

@@ -244,3 +244,11 @@ def test_static_scratch_serves_layers_whose_copies_and_partial_sums_fit():
         else:
             assert need <= max(copies + partials + 512, sd.STATIC_SCRATCH_BYTES)
     assert served > 1000 and padded > 200, (served, padded)
+
+
+@pytest.mark.parametrize("pixels,runs", [(2 ** 27 - 192, True), (2 ** 27 - 191, False)])
+def test_weight_gradient_with_fetching_waves_ends_before_2_31_bytes(pixels, runs, monkeypatch):
+    """Their descriptors start 3072 bytes before a tensor, whose last byte must stay below offset 2^31."""
+    monkeypatch.setenv("SDCONV_WGRAD_VARIANT", "121")
+    d = _desc(H=1, W=pixels, R=1, S=1, pad_h=0, pad_w=0)
+    assert ("4w4f" in sd.kernel_name(d, sd.WGRAD)) == runs

@@ -154,7 +154,7 @@ WGRAD_SHAPES = [
     (1, 31, 37, 136, 200, 3, 3, (1, 1), (1, 1), (1, 1)),    # channel and filter tails
     (1, 31, 37, 128, 264, 1, 1, (1, 1), (0, 0), (1, 1)),    # 1x1 unpadded: linear x addressing
 ]
-WGRAD_VARIANTS = [0, 1, 104, 107, 108, 112] + list(range(114, 120))      # 0, 1: the register-staged kernels of wgrad.hip
+WGRAD_VARIANTS = [0, 1, 104, 107, 108, 112] + list(range(114, 124))      # 0, 1: the register-staged kernels of wgrad.hip
 
 
 @pytest.mark.parametrize("variant", WGRAD_VARIANTS)

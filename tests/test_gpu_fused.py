@@ -116,6 +116,15 @@ def test_fused_igemm_variants(variant):
             check_fused(d, x, w, g, f"fused_v{variant}{case}", seed=variant)
 
 
+@pytest.mark.parametrize("opts", [("scale", "bias", "relu"), ("scale",), ("bias", "relu"), ("relu",), ("scale", "residual")])
+@pytest.mark.parametrize("K", [8, 64, 72, 136])
+def test_stem_tails(K, opts):
+    """Scale, bias and ReLU of the stem kernel come from LDS, 64 filters at a time; with a shortcut they do not."""
+    say(f"stem tail {opts} K {K}")
+    d, x, w, g = _rand_case(2, 37, 41, 3, K, 7, 7, (2, 2), (3, 3), (1, 1), seed=K + len(opts))
+    check_fused(d, x, w, g, f"stem{K}{opts}", seed=K, fwd_opts=opts, dgrad_opts=())
+
+
 @pytest.mark.parametrize("bad", [None, np.inf, np.nan])
 def test_unreached_positions_with_a_scale_that_is_not_finite(bad):
     """1x1 stride 2: three of four positions have no tap, and their sum is 0: times an infinite scale NaN where the mask

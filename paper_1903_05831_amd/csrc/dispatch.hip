@@ -177,7 +177,8 @@ static int ws_variant_for(const Geom& g, bool dgrad, int v)
 // (fit_models.py), bounded by the measured rates of matrix instructions alone (2.06 PFLOP/s) and of
 // streaming (6.1 TB/s; 3.5 at least).  They are the fit to timings from before the fetching waves sent runs; those of
 // gathering layers and of strided data gradients were then scaled by the median of measured over predicted time (and `hbm`
-// by its inverse) over 2000 layers, a variant's near the fastest (20 %): 0.8 to 1.1.  On layers left out of that the
+// by its inverse) over 2000 layers, a variant's near the fastest (20 %): 0.8 to 1.1.  Two 64x64 tiles (327 and 328), alike but
+// for the matrix block, have new constants for pointwise layers too: long contractions took the slower one.  On layers left out of that the
 // choice is 1.1 % slower than the fastest of 26 measured variants (3.5 % at the 90th percentile, 19 % at the 99th), without it
 // 1.25 % (4.1 %); a new fit to the same timings 1.4 to 1.5 % (5 %), rules by row counts were 17 % (57 %) slower.
 struct RowCost { float fixed, step, shared, tile, hbm; };
@@ -190,8 +191,8 @@ static const RowModel kRowModels[] = {
     {316, 1, {0.960f, 0.788f, 0.000f, 3.781f, 4.578f}, {0.500f, 0.815f, 0.000f, 4.163f, 3.500f}, {0.499f, 0.813f, 0.000f, 5.293f, 3.508f}},
     {325, 1, {1.738f, 0.424f, 0.000f, 2.271f, 3.864f}, {1.534f, 0.384f, 0.000f, 2.409f, 3.679f}, {1.901f, 0.414f, 0.000f, 3.155f, 3.417f}},
     {326, 1, {1.820f, 0.956f, 0.000f, 3.075f, 4.274f}, {1.407f, 0.910f, 0.000f, 3.038f, 3.514f}, {0.485f, 0.845f, 0.000f, 4.994f, 3.787f}},
-    {327, 2, {2.102f, 0.237f, 0.227f, 1.444f, 4.428f}, {1.920f, 0.239f, 0.175f, 1.251f, 3.934f}, {1.371f, 0.250f, 0.183f, 2.376f, 3.759f}},
-    {328, 2, {2.081f, 0.238f, 0.226f, 1.443f, 4.408f}, {1.879f, 0.236f, 0.170f, 1.205f, 3.968f}, {1.407f, 0.250f, 0.180f, 2.391f, 3.749f}},
+    {327, 2, {1.967f, 0.149f, 0.227f, 1.500f, 4.542f}, {1.920f, 0.239f, 0.175f, 1.251f, 3.934f}, {1.371f, 0.250f, 0.183f, 2.376f, 3.759f}},
+    {328, 2, {1.936f, 0.067f, 0.225f, 1.480f, 4.445f}, {1.879f, 0.236f, 0.170f, 1.205f, 3.968f}, {1.407f, 0.250f, 0.180f, 2.391f, 3.749f}},
     {329, 1, {1.638f, 0.353f, 0.000f, 2.045f, 4.331f}, {1.464f, 0.310f, 0.000f, 2.034f, 3.789f}, {1.763f, 0.327f, 0.000f, 2.580f, 3.957f}},
     {330, 1, {1.692f, 0.469f, 0.000f, 2.452f, 4.279f}, {1.053f, 0.449f, 0.000f, 3.106f, 3.349f}, {1.542f, 0.442f, 0.000f, 3.417f, 3.480f}},
     {331, 1, {1.288f, 0.726f, 0.000f, 3.638f, 4.327f}, {0.557f, 0.738f, 0.000f, 4.697f, 3.141f}, {0.494f, 0.655f, 0.000f, 5.258f, 3.539f}},

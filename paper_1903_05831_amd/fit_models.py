@@ -12,7 +12,8 @@ choice is on layers that it was not fitted to.  Constants are bounded by what th
 takes no less than the matrix instructions alone (2.06 PFLOP/s measured over 256 compute units),
 nothing moves faster than 6.1 MB/us (HBM streaming as measured), and a forward or data-gradient kernel moves
 its operands at 3.5 MB/us at least and starts in 0.5 us at least: most tiles of 128 rows and more sit at
-those two, their layers being bound by the steps.
+those two, their layers being bound by the steps.  kRowModels is such a fit to older timings, partly scaled to these: a new one
+chooses slightly worse kernels (dispatch.hip).
 """
 from __future__ import annotations
 

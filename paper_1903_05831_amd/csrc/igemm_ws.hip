@@ -143,20 +143,23 @@ template <int MODE> static hipError_t launch_mode(int variant, const IgemmParams
 
 void set_tap_bias(IgemmParams* P)
 {
-    long low = 0;           // least displacement of any class, in bytes
+    long low = 0, high = 0;     // least and greatest displacement of any class, in bytes
     bool served = true;
     for (int a = 0; a * P->sw_cls < P->nclasses; ++a)
         for (int b = 0; b < P->sw_cls; ++b) {
             const AxisTaps h = P->taps_h[a], w = P->taps_w[b];
             if (h.count * w.count == 0) continue;
             if (h.count * w.count > 32) served = false;
-            const long h0 = h.disp + (P->tap_dh < 0 ? (h.count - 1) * (long)P->tap_dh : 0);
-            const long w0 = w.disp + (P->tap_dw < 0 ? (w.count - 1) * (long)P->tap_dw : 0);
-            low = std::min(low, (h0 * P->Ws + w0) * P->Cs * 2);
+            const long h1 = h.disp + (h.count - 1) * (long)P->tap_dh, w1 = w.disp + (w.count - 1) * (long)P->tap_dw;
+            low = std::min(low, (std::min<long>(h.disp, h1) * P->Ws + std::min<long>(w.disp, w1)) * P->Cs * 2);
+            high = std::max(high, (std::max<long>(h.disp, h1) * P->Ws + std::max<long>(w.disp, w1)) * P->Cs * 2);
         }
     // out-of-range offsets start at 2^31, past whatever a descriptor covers
     const long source = (long)P->NB * P->Hs * P->Ws * P->Cs * 2;
     const long filter = (long)std::max(P->Cs, P->Cd) * P->b_row_pitch * 2, most = (1L << 31) - kRunSlack;
+    // and a scalar offset stays within its descriptor, also that of a tap that lies outside every image (the range
+    // check takes it from the descriptor's size)
+    served = served && high + 2L * P->Cs <= source + kRunSlack;
     P->tap_bias = served && source - low <= most && filter <= most ? (int)-low : -1;
 }
 

@@ -133,6 +133,17 @@ def test_two_tile_widths_in_one_launch():
         check_all_passes(d, x, w, g, f"mixed{case}")
 
 
+@pytest.mark.parametrize("variant", [327, 334])
+def test_taps_outside_every_image(variant):
+    """3x3 of dilation 9 on 4x4 images: eight taps lie further away than the source is long.  Their offsets must not
+    leave the descriptors of the fetching waves' runs, so such layers take the general loop."""
+    case = (2, 4, 4, 1024, 136, 3, 3, (1, 1), (9, 9), (9, 9))
+    say(f"taps outside, variant {variant} case {case}")
+    d, x, w, g = _rand_case(*case, seed=variant)
+    with forced(SDCONV_IGEMM_VARIANT=variant, SDCONV_NO_TUNED_TABLE=1):
+        check_all_passes(d, x, w, g, f"outside_v{variant}")
+
+
 # the forward kernels in which every wave fetches its own share (igemm_dma.hip, 101 and 112) and the
 # register-staged ones (igemm.hip, 0 and 3), whose data gradient takes a transposed filter copy
 DMA_VARIANTS = [0, 3, 101, 112]

@@ -501,38 +501,94 @@ static size_t wgrad_partial_limit(const Geom& g, size_t copies)
 
 struct WgradChoice { int variant, splits; float us; };
 
-// The fastest number of pixel ranges for one variant, if faster than `best`: those that make the workgroups a
-// little fewer than a multiple of the compute units, and the smallest.
-static void wgrad_best_splits(const Geom& g, const WgradModel& m, size_t partial_limit, WgradChoice* best)
+// What the times of one weight gradient under all variants have in common, as RowShape for the other passes.  The numbers of
+// pixel ranges to try follow from the tile alone, of which the variants share six: they are worked out once a tile, and a time
+// only where its lower bounds are below the best one.  A plan of 1.1 to 1.4 us (a forward pass's: 0.6) took 2.1 to 2.5 where each
+// of the 14 variants worked its ranges out for itself, with the same choices.
+struct WgradRanges {
+    unsigned ranges, fullest;               // workgroups of the fullest compute unit
+    float n, steps, busy, reduce;           // ranges, steps of one, steps of the fullest unit's workgroups; us of the reduction
+};
+struct WgradTile { unsigned tiles; int n; WgradRanges at[14]; };    // n < 0: not worked out yet
+struct WgradShape {
+    bool linear;
+    unsigned total;                         // 64-pixel steps
+    size_t dw_bytes;
+    float dw, mb;                           // MB of dw, of x and dy
+    WgradTile of[3][3];                     // by tile height and width 64, 128, 256
+};
+
+static void wgrad_shape(const Geom& g, WgradShape* s)
 {
-    const WgradCost& c = (g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0) ? m.linear : m.gather;
-    const long tiles = wgrad_tiles(g, wgrad_variant(m.variant));
-    const unsigned total = (unsigned)wgrad_steps(g);
-    const size_t dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
-    const float dw = 4e-6f * g.K * g.R * g.S * g.C;         // MB
+    s->linear = g.R * g.S == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
+    s->total = (unsigned)wgrad_steps(g);
+    s->dw_bytes = (size_t)4 * g.K * g.R * g.S * g.C;
+    s->dw = 4e-6f * g.K * g.R * g.S * g.C;
     const float x = 2e-6f * g.N * g.H * g.W * g.C / (g.R * g.S == 1 ? g.sh * g.sw : 1);
-    const float move = (x + 2e-6f * g.N * g.Ho * g.Wo * g.K) / c.hbm, store = dw / c.store;
+    s->mb = x + 2e-6f * g.N * g.Ho * g.Wo * g.K;
+    unsigned up[2][3];                      // tiles along K and C
+    for (int i = 0; i < 3; ++i) {
+        up[0][i] = ((unsigned)g.K + (64u << i) - 1) >> (6 + i);
+        up[1][i] = ((unsigned)g.C + (64u << i) - 1) >> (6 + i);
+    }
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j) {
+            s->of[i][j].tiles = up[0][i] * up[1][j] * g.R * g.S;
+            s->of[i][j].n = -1;
+        }
+}
+
+// The numbers of ranges that make the workgroups a little fewer than a multiple of the compute units, and the smallest; those
+// whose partial sums take no more than `limit`.
+static void wgrad_ranges(const WgradShape& s, size_t limit, WgradTile* t)
+{
     static const int candidates[] = {1, 2, 3, -40, -64, -96, -128, -192, -256, -320, -384, -512, -768, -1024};
-    // no compute unit takes less than an even share of all steps, at its best rate
-    const float rate = c.shared > c.step / m.per_cu ? c.shared : c.step / m.per_cu;
-    const float even = (c.fixed + both((float)tiles * total * rate / 256, move)) * 0.9999f;
     unsigned last = 0;
+    t->n = 0;
     for (int cand : candidates) {                           // ranges, or minus the workgroups to make
-        unsigned s = cand > 0 ? cand : (unsigned)(-cand / tiles);
-        if (s > total / 2) s = total / 2;
-        if (s < 1) s = 1;
-        const unsigned steps = (total + s - 1) / s;
-        s = (total + steps - 1) / steps;                    // ranges that are not empty
-        if (s <= last) continue;
-        last = s;
-        if (s > 1 && s * dw_bytes > partial_limit) break;
-        if (best->variant >= 0 && even + s * store >= best->us) break;      // and so do more ranges
-        auto round = [&](unsigned n) { return steps * (n * c.shared > c.step ? n * c.shared : c.step) + c.tile; };
-        const unsigned fullest = (unsigned)((tiles * s + 255) / 256), full = fullest / m.per_cu, rest = fullest - full * m.per_cu;
+        unsigned n = cand > 0 ? (unsigned)cand : (unsigned)-cand / t->tiles;
+        if (n > s.total / 2) n = s.total / 2;
+        if (n < 1) n = 1;
+        if (n <= last) continue;                            // (the next lines only make it smaller)
+        const unsigned steps = (s.total + n - 1) / n;
+        n = (s.total + steps - 1) / steps;                  // ranges that are not empty
+        if (n <= last) continue;
+        if (n > 1 && n * s.dw_bytes > limit) return;
+        last = n;
+        const unsigned fullest = (t->tiles * n + 255) / 256;
+        t->at[t->n++] = WgradRanges{n, fullest, (float)n, (float)steps, (float)steps * fullest,
+                                    n > 1 ? n * s.dw / kReduceRate + kReduceFixed : 0.f};
+    }
+}
+
+// The fastest number of ranges for one variant whose partial sums take no more than `limit`, if faster than `best`; and, where
+// that is asked for, the fastest whose sums take no more than `left`, unless it is too slow to be taken (choose_wgrad).
+static void wgrad_best_splits(WgradShape* s, const WgradModel& m, size_t limit, WgradChoice* best, size_t left, WgradChoice* within)
+{
+    const WgradCost& c = s->linear ? m.linear : m.gather;
+    const WgradVariant& v = kWgradDmaVariants[m.variant - 100];
+    WgradTile* t = &s->of[v.bm >> 7][v.bn >> 7];
+    const float move = s->mb / c.hbm, store = s->dw / c.store;
+    auto late = [&](float us) {
+        return us >= best->us && (!within || us >= within->us || us >= kWorthScratch * 1.0001f * best->us);
+    };
+    // No compute unit takes less than an even share of all steps, at its best rate, and more ranges store more; nor does the
+    // fullest one take its own steps faster.  (0.9999: what the rounding of either side may add.)
+    const float rate = c.shared > c.step / m.per_cu ? c.shared : c.step / m.per_cu;
+    const float even = (c.fixed + both((float)t->tiles * s->total * rate / 256, move)) * 0.9999f;
+    if (late(even + store)) return;
+    if (t->n < 0) wgrad_ranges(*s, limit, t);
+    for (const WgradRanges* r = t->at; r < t->at + t->n; ++r) {
+        if (late(even + r->n * store)) break;
+        const float rest_us = r->n * store + r->reduce;
+        if (late((c.fixed + r->busy * rate + rest_us) * 0.9999f)) continue;
+        auto round = [&](unsigned n) { return r->steps * (n * c.shared > c.step ? n * c.shared : c.step) + c.tile; };
+        const unsigned full = r->fullest / m.per_cu, rest = r->fullest - full * m.per_cu;
         const float work = (float)full * round(m.per_cu) + (rest ? round(rest) : 0.f);
-        float us = c.fixed + both(work, move) + s * store;
-        if (s > 1) us += s * dw / kReduceRate + kReduceFixed;
-        if (best->variant < 0 || us < best->us) *best = WgradChoice{m.variant, (int)s, us};
+        const float us = c.fixed + both(work, move) + r->n * store + r->reduce;
+        if (us < best->us) *best = WgradChoice{m.variant, (int)r->ranges, us};
+        if (within && us < within->us && (r->ranges == 1 || r->ranges * s->dw_bytes <= left))
+            *within = WgradChoice{m.variant, (int)r->ranges, us};
     }
 }
 
@@ -548,20 +604,20 @@ static WgradChoice choose_wgrad(const Geom& g, size_t copies)
     const WgradEntry* e = nullptr;
     if (!wgrad_offsets_fit_31_bits(g)) only = g.K <= 64 ? 1 : 0;
     else if (!forced && (e = wgrad_entry(g))) only = e->variant;
-    WgradChoice c{-1, 1, 0.f};
-    auto choose = [&](size_t limit) {
-        WgradChoice best{-1, 1, 0.f};
+    const WgradChoice none{-1, 1, INFINITY};
+    WgradChoice c = none;
+    if (!(e && e->splits > 0 && e->N == g.N)) {
+        // Partial sums that outgrow the static scratch have to be worth it: the models are off by some per cent, and
+        // conv2d_wgrad_static_scratch refuses the layer for them.
+        const size_t scratch = SDCONV_STATIC_SCRATCH_BYTES, left = copies < scratch ? scratch - copies : 0;
+        const bool outgrow = left < partial_limit;
+        WgradChoice within = none;
+        WgradShape shape;
+        wgrad_shape(g, &shape);
         for (const WgradModel& m : kWgradModels)
-            if (only < 0 ? runs || !wgrad_variant(m.variant).runs : m.variant == only) wgrad_best_splits(g, m, limit, &best);
-        return best;
-    };
-    if (!(e && e->splits > 0 && e->N == g.N)) c = choose(partial_limit);
-    // Partial sums that outgrow the static scratch have to be worth it: the models are off by some per cent, and
-    // conv2d_wgrad_static_scratch refuses the layer for them.
-    const size_t scratch = SDCONV_STATIC_SCRATCH_BYTES, left = copies < scratch ? scratch - copies : 0;
-    if (c.variant >= 0 && c.splits > 1 && (size_t)c.splits * 4 * g.K * g.R * g.S * g.C > left && left < partial_limit) {
-        const WgradChoice within = choose(left);
-        if (within.variant >= 0 && within.us <= kWorthScratch * c.us) c = within;
+            if (only < 0 ? runs || !wgrad_variant(m.variant).runs : m.variant == only)
+                wgrad_best_splits(&shape, m, partial_limit, &c, left, outgrow ? &within : nullptr);
+        if (outgrow && c.splits > 1 && c.splits * shape.dw_bytes > left && within.us <= kWorthScratch * c.us) c = within;
     }
     if (c.variant < 0) {
         long want;

@@ -176,8 +176,9 @@ static int ws_variant_for(const Geom& g, bool dgrad, int v)
 // gathering).  The constants are least-squares fits to the timings in profiles/layer_timings.jsonl.gz
 // (fit_models.py), bounded by the measured rates of matrix instructions alone (2.06 PFLOP/s) and of
 // streaming (6.1 TB/s; 3.5 at least).  They are the fit to timings from before the fetching waves sent runs; those of
-// gathering layers and of strided data gradients were then scaled by the median of measured over predicted time (and `hbm`
-// by its inverse) over 2000 layers, a variant's near the fastest (20 %): 0.8 to 1.1.  Two 64x64 tiles (327 and 328), alike but
+// gathering layers were then scaled by the median of measured over predicted time (and `hbm`
+// by its inverse) over 2000 layers, a variant's near the fastest (20 %): 0.8 to 1.1.  (So scaled, those of strided data gradients
+// chose kernels 2.6 % slower than the fastest, unscaled 2.1 % slower.)  Two 64x64 tiles (327 and 328), alike but
 // for the matrix block, have new constants for pointwise layers too: long contractions took the slower one.  On layers left out of that the
 // choice is 1.1 % slower than the fastest of 26 measured variants (3.5 % at the 90th percentile, 19 % at the 99th), without it
 // 1.25 % (4.1 %); a new fit to the same timings 1.4 to 1.5 % (5 %), rules by row counts were 17 % (57 %) slower.
@@ -186,25 +187,25 @@ struct RowModel { int variant, per_cu; RowCost pointwise, gather, strided; };   
 static const RowModel kRowModels[] = {
     {101, 3, {2.626f, 0.768f, 0.611f, 1.227f, 4.342f}, {2.810f, 0.781f, 0.564f, 1.025f, 3.845f}, {}},
     {112, 5, {2.829f, 0.782f, 0.457f, 0.543f, 3.500f}, {3.292f, 0.725f, 0.405f, 0.000f, 3.777f}, {}},
-    {310, 1, {0.864f, 1.208f, 0.000f, 4.512f, 4.162f}, {0.552f, 1.294f, 0.000f, 5.334f, 3.168f}, {0.512f, 1.200f, 0.000f, 6.218f, 3.416f}},
-    {311, 1, {0.687f, 1.352f, 0.000f, 5.017f, 4.024f}, {0.551f, 1.427f, 0.000f, 5.654f, 3.174f}, {0.509f, 1.317f, 0.000f, 6.654f, 3.440f}},
-    {316, 1, {0.960f, 0.788f, 0.000f, 3.781f, 4.578f}, {0.500f, 0.815f, 0.000f, 4.163f, 3.500f}, {0.499f, 0.813f, 0.000f, 5.293f, 3.508f}},
-    {325, 1, {1.738f, 0.424f, 0.000f, 2.271f, 3.864f}, {1.534f, 0.384f, 0.000f, 2.409f, 3.679f}, {1.901f, 0.414f, 0.000f, 3.155f, 3.417f}},
-    {326, 1, {1.820f, 0.956f, 0.000f, 3.075f, 4.274f}, {1.407f, 0.910f, 0.000f, 3.038f, 3.514f}, {0.485f, 0.845f, 0.000f, 4.994f, 3.787f}},
-    {327, 2, {1.967f, 0.149f, 0.227f, 1.500f, 4.542f}, {1.920f, 0.239f, 0.175f, 1.251f, 3.934f}, {1.371f, 0.250f, 0.183f, 2.376f, 3.759f}},
-    {328, 2, {1.936f, 0.067f, 0.225f, 1.480f, 4.445f}, {1.879f, 0.236f, 0.170f, 1.205f, 3.968f}, {1.407f, 0.250f, 0.180f, 2.391f, 3.749f}},
-    {329, 1, {1.638f, 0.353f, 0.000f, 2.045f, 4.331f}, {1.464f, 0.310f, 0.000f, 2.034f, 3.789f}, {1.763f, 0.327f, 0.000f, 2.580f, 3.957f}},
-    {330, 1, {1.692f, 0.469f, 0.000f, 2.452f, 4.279f}, {1.053f, 0.449f, 0.000f, 3.106f, 3.349f}, {1.542f, 0.442f, 0.000f, 3.417f, 3.480f}},
-    {331, 1, {1.288f, 0.726f, 0.000f, 3.638f, 4.327f}, {0.557f, 0.738f, 0.000f, 4.697f, 3.141f}, {0.494f, 0.655f, 0.000f, 5.258f, 3.539f}},
-    {332, 1, {1.523f, 0.664f, 0.000f, 3.382f, 4.467f}, {0.520f, 0.639f, 0.000f, 4.251f, 3.363f}, {0.794f, 0.604f, 0.000f, 4.864f, 3.557f}},
-    {333, 1, {1.682f, 0.424f, 0.000f, 2.358f, 4.323f}, {1.394f, 0.350f, 0.000f, 2.325f, 3.850f}, {1.780f, 0.394f, 0.000f, 3.140f, 3.790f}},
-    {334, 1, {1.710f, 0.392f, 0.000f, 2.198f, 4.350f}, {1.428f, 0.347f, 0.000f, 2.221f, 4.006f}, {1.756f, 0.365f, 0.000f, 2.815f, 4.148f}},
-    {335, 1, {1.776f, 0.541f, 0.000f, 2.687f, 4.484f}, {1.156f, 0.507f, 0.000f, 3.194f, 3.434f}, {1.368f, 0.483f, 0.000f, 3.707f, 3.608f}},
-    {336, 1, {1.686f, 0.604f, 0.000f, 3.000f, 4.519f}, {0.665f, 0.581f, 0.000f, 3.928f, 3.416f}, {1.210f, 0.553f, 0.000f, 4.324f, 3.502f}},
-    {337, 1, {1.659f, 0.306f, 0.000f, 1.938f, 3.844f}, {1.495f, 0.271f, 0.000f, 1.839f, 3.957f}, {1.823f, 0.286f, 0.000f, 2.276f, 3.744f}},
-    {338, 1, {1.545f, 1.019f, 0.000f, 3.132f, 4.382f}, {0.965f, 1.082f, 0.000f, 4.151f, 3.161f}, {0.506f, 0.988f, 0.000f, 5.296f, 3.462f}},
-    {339, 2, {2.285f, 0.719f, 0.487f, 1.626f, 4.446f}, {2.869f, 0.707f, 0.440f, 0.744f, 3.427f}, {0.476f, 0.658f, 0.410f, 3.875f, 3.680f}},
-    {340, 3, {1.952f, 0.605f, 0.340f, 1.470f, 3.831f}, {3.208f, 0.586f, 0.314f, 0.000f, 3.543f}, {0.476f, 0.565f, 0.303f, 3.546f, 3.676f}},
+    {310, 1, {0.864f, 1.208f, 0.000f, 4.512f, 4.162f}, {0.552f, 1.294f, 0.000f, 5.334f, 3.168f}, {0.500f, 1.171f, 0.000f, 6.070f, 3.500f}},
+    {311, 1, {0.687f, 1.352f, 0.000f, 5.017f, 4.024f}, {0.551f, 1.427f, 0.000f, 5.654f, 3.174f}, {0.500f, 1.294f, 0.000f, 6.539f, 3.500f}},
+    {316, 1, {0.960f, 0.788f, 0.000f, 3.781f, 4.578f}, {0.500f, 0.815f, 0.000f, 4.163f, 3.500f}, {0.500f, 0.815f, 0.000f, 5.306f, 3.500f}},
+    {325, 1, {1.738f, 0.424f, 0.000f, 2.271f, 3.864f}, {1.534f, 0.384f, 0.000f, 2.409f, 3.679f}, {1.856f, 0.404f, 0.000f, 3.081f, 3.500f}},
+    {326, 1, {1.820f, 0.956f, 0.000f, 3.075f, 4.274f}, {1.407f, 0.910f, 0.000f, 3.038f, 3.514f}, {0.525f, 0.914f, 0.000f, 5.403f, 3.500f}},
+    {327, 2, {1.967f, 0.149f, 0.227f, 1.500f, 4.542f}, {1.920f, 0.239f, 0.175f, 1.251f, 3.934f}, {1.472f, 0.269f, 0.197f, 2.552f, 3.500f}},
+    {328, 2, {1.936f, 0.067f, 0.225f, 1.480f, 4.445f}, {1.879f, 0.236f, 0.170f, 1.205f, 3.968f}, {1.507f, 0.268f, 0.193f, 2.561f, 3.500f}},
+    {329, 1, {1.638f, 0.353f, 0.000f, 2.045f, 4.331f}, {1.464f, 0.310f, 0.000f, 2.034f, 3.789f}, {1.785f, 0.331f, 0.000f, 2.613f, 3.908f}},
+    {330, 1, {1.692f, 0.469f, 0.000f, 2.452f, 4.279f}, {1.053f, 0.449f, 0.000f, 3.106f, 3.349f}, {1.500f, 0.430f, 0.000f, 3.323f, 3.578f}},
+    {331, 1, {1.288f, 0.726f, 0.000f, 3.638f, 4.327f}, {0.557f, 0.738f, 0.000f, 4.697f, 3.141f}, {0.500f, 0.662f, 0.000f, 5.317f, 3.500f}},
+    {332, 1, {1.523f, 0.664f, 0.000f, 3.382f, 4.467f}, {0.520f, 0.639f, 0.000f, 4.251f, 3.363f}, {0.807f, 0.614f, 0.000f, 4.943f, 3.500f}},
+    {333, 1, {1.682f, 0.424f, 0.000f, 2.358f, 4.323f}, {1.394f, 0.350f, 0.000f, 2.325f, 3.850f}, {1.736f, 0.384f, 0.000f, 3.063f, 3.885f}},
+    {334, 1, {1.710f, 0.392f, 0.000f, 2.198f, 4.350f}, {1.428f, 0.347f, 0.000f, 2.221f, 4.006f}, {1.818f, 0.378f, 0.000f, 2.915f, 4.006f}},
+    {335, 1, {1.776f, 0.541f, 0.000f, 2.687f, 4.484f}, {1.156f, 0.507f, 0.000f, 3.194f, 3.434f}, {1.409f, 0.497f, 0.000f, 3.818f, 3.503f}},
+    {336, 1, {1.686f, 0.604f, 0.000f, 3.000f, 4.519f}, {0.665f, 0.581f, 0.000f, 3.928f, 3.416f}, {1.211f, 0.553f, 0.000f, 4.326f, 3.500f}},
+    {337, 1, {1.659f, 0.306f, 0.000f, 1.938f, 3.844f}, {1.495f, 0.271f, 0.000f, 1.839f, 3.957f}, {1.950f, 0.306f, 0.000f, 2.435f, 3.500f}},
+    {338, 1, {1.545f, 1.019f, 0.000f, 3.132f, 4.382f}, {0.965f, 1.082f, 0.000f, 4.151f, 3.161f}, {0.500f, 0.977f, 0.000f, 5.238f, 3.500f}},
+    {339, 2, {2.285f, 0.719f, 0.487f, 1.626f, 4.446f}, {2.869f, 0.707f, 0.440f, 0.744f, 3.427f}, {0.500f, 0.692f, 0.431f, 4.074f, 3.500f}},
+    {340, 3, {1.952f, 0.605f, 0.340f, 1.470f, 3.831f}, {3.208f, 0.586f, 0.314f, 0.000f, 3.543f}, {0.500f, 0.593f, 0.318f, 3.724f, 3.500f}},
     {427, 2, {}, {2.317f, 0.164f, 0.219f, 1.607f, 3.493f}, {}},
     {433, 2, {}, {2.748f, 0.273f, 0.285f, 1.536f, 3.443f}, {}},
     {435, 1, {}, {1.378f, 0.328f, 0.000f, 2.510f, 3.458f}, {}},

@@ -556,9 +556,10 @@ static hipError_t launch_f32_variant(const F32Params& P, hipStream_t st)
 
 // Tiles, and the time each takes: us per step and tile where a tile has a compute unit to itself (`step`) or
 // several share one (`shared` each, at most `per_cu` at a time), us per tile besides, launch
-// and first loads.  Fits to the fp32 timings in profiles/layer_timings.jsonl.gz (fit_models.py: 708 passes of
+// and first loads.  Fits to the fp32 timings in profiles/layer_timings_before_runs.jsonl.gz (fit_models.py: 710 passes of
 // 354 layers of random size, 200 to 150 000 pixels, 8 to 2048 channels): on layers left out of the fit the
-// choice is 1.2 % slower than the fastest tile (5.4 % at the 90th percentile).  Against the fastest register-staged
+// choice is 1.2 % slower than the fastest tile (5.4 % at the 90th percentile).  On 1190 passes of the present kernels
+// (layer_timings.jsonl.gz) it is 2.32 % slower, and a fit to those 2.30 % on layers left out.  Against the fastest register-staged
 // tile it takes 16 % less time on average.  Those are the faster ones at times, with few channels on one
 // side or four steps of contraction, and serve tensors that the split-role kernels do not address: they stay in
 // the choice, which without them is 0.2 % slower.  A split-role 32x32 tile takes 0.19 us a step beside

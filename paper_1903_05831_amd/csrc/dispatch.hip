@@ -173,15 +173,14 @@ static int ws_variant_for(const Geom& g, bool dgrad, int v)
 // and first loads are `fixed`; the operands move at `hbm` MB/us meanwhile.  What decides is mostly how the
 // tiles of a variant divide by 256 compute units.  Three sets of constants: pointwise layers, layers that
 // gather, and strided data gradients, whose parity classes have tiles of different length (a step is that of
-// gathering).  The constants are least-squares fits to the timings in profiles/layer_timings.jsonl.gz
-// (fit_models.py), bounded by the measured rates of matrix instructions alone (2.06 PFLOP/s) and of
-// streaming (6.1 TB/s; 3.5 at least).  They are the fit to timings from before the fetching waves sent runs; those of
-// gathering layers were then scaled by the median of measured over predicted time (and `hbm`
-// by its inverse) over 2000 layers, a variant's near the fastest (20 %): 0.8 to 1.1.  (So scaled, those of strided data gradients
-// chose kernels 2.6 % slower than the fastest, unscaled 2.1 % slower.)  Two 64x64 tiles (327 and 328), alike but
-// for the matrix block, have new constants for pointwise layers too: long contractions took the slower one.  On layers left out of that the
-// choice is 1.1 % slower than the fastest of 26 measured variants (3.5 % at the 90th percentile, 19 % at the 99th), without it
-// 1.25 % (4.1 %); a new fit to the same timings 1.4 to 1.5 % (5 %), rules by row counts were 17 % (57 %) slower.
+// gathering).  The constants are what fit_models.py makes of the timings in profiles/: least-squares fits to those
+// from before the fetching waves sent runs (1444 layers), bounded by the measured rates of matrix instructions alone (2.06 PFLOP/s)
+// and of streaming (6.1 TB/s; 3.5 at least) and by a start of 0.5 us; then, past these bounds, those of gathering layers scaled by the median
+// of measured over predicted time (`hbm` by its inverse) where a variant is within 20 % of the fastest on the present timings of 1991 layers
+// (0.8 to 1.1), and two 64x64 tiles (327 and 328), alike but for the matrix block, fitted to those for pointwise layers: long
+// contractions took the slower one.  (A `step` below `shared` never counts.)  On layers left out of the scaling the choice is 1.23 % slower
+// than the fastest of 27 measured variants (3.9 % at the 90th percentile, 19 % at the 99th), without it 1.33 % (4.3 %, 21 %), with strided
+// data gradients scaled too 1.25 %, under a fit to the present timings 1.55 % (5.4 %, 21 %); rules by row counts were 17 % (57 %) slower.
 struct RowCost { float fixed, step, shared, tile, hbm; };
 struct RowModel { int variant, per_cu; RowCost pointwise, gather, strided; };   // step 0: not taken
 static const RowModel kRowModels[] = {
@@ -449,7 +448,7 @@ static const WgradVariant& wgrad_variant(int v)
 // which both are chosen.  A workgroup takes `step` us per 64-pixel step (where several share a compute unit
 // `shared` us times their number, if that is more), and `tile` us per tile besides; launch and first loads are
 // `fixed`; the operands move at `hbm` MB/us meanwhile, and the sums leave at `store` MB/us after the loop.
-// The constants are fits like those of kRowModels (fit_models.py, same bounds).  The time has a narrow
+// The constants are fits to the present timings (fit_models.py; no less than the matrix instructions alone take).  The time has a narrow
 // minimum between too few workgroups and the traffic of too many partial sums: rules by channel counts
 // with one number of ranges for all lost 48 % over layers of random size.  The choice is 2.0 % slower than
 // the fastest measured (variant, ranges) pair on layers left out of the fit (6.4 % at the 90th percentile); without the

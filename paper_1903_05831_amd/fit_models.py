@@ -2,7 +2,7 @@
 csrc/dispatch.hip and csrc/conv_f32.hip fitted to them.
 
     python -m paper_1903_05831_amd.fit_models measure --what rows|wgrad|f32|f32wgrad --seed 1 --seconds 100 --out t.jsonl.gz
-    python -m paper_1903_05831_amd.fit_models fit --timings profiles/layer_timings.jsonl.gz
+    python -m paper_1903_05831_amd.fit_models fit --timings profiles/layer_timings.jsonl.gz --before profiles/layer_timings_before_runs.jsonl.gz
 
 ``measure`` needs the GPU: every variant (and, for the weight gradient, every sensible number of
 pixel ranges) of each layer, as HIP graphs of many calls on tensors that do not fit the caches, the best
@@ -12,8 +12,12 @@ choice is on layers that it was not fitted to.  Constants are bounded by what th
 takes no less than the matrix instructions alone (2.06 PFLOP/s measured over 256 compute units),
 nothing moves faster than 6.1 MB/us (HBM streaming as measured), and a forward or data-gradient kernel moves
 its operands at 3.5 MB/us at least and starts in 0.5 us at least: most tiles of 128 rows and more sit at
-those two, their layers being bound by the steps.  kRowModels is such a fit to older timings, partly scaled to these: a new one
-chooses slightly worse kernels (dispatch.hip).
+those two, their layers being bound by the steps.
+
+``--before``: timings of the same variants from before their fetching waves sent runs of loads.  kRowModels is the fit to
+those, with two corrections from the present ones (row_models), which move constants past the bounds above; kF32Tiles
+is the fit to those as it is.  Without it both are fits to the present timings, which choose slightly worse forward and
+data-gradient kernels.
 """
 from __future__ import annotations
 
@@ -383,13 +387,13 @@ def least_squares_log(predict, samples, lo, hi, start):
     return tuple(float(t) for t in out)
 
 
-def fit_rows(rows):
+def fit_rows(rows, variants=ROW_MODELS, kinds=(POINTWISE, GATHER, STRIDED)):
     models = {}
-    for v in ROW_MODELS:
+    for v in variants:
         area = TILES[v][0] * TILES[v][1] if v < 400 else math.prod(PATCHES[v])
         least = 2.0 * area * 64 * 256 / MATRIX
         per_cu = PER_CU.get(v, 1)
-        for c in (POINTWISE, GATHER, STRIDED):
+        for c in kinds:
             if v >= 400 and c != GATHER or v < 300 and c == STRIDED:
                 continue
             samples = [(tuple(x["k"]), x["p"], dict(x["us"])[v]) for x in rows
@@ -405,6 +409,34 @@ def fit_rows(rows):
                 lo[1:3] = hi[1:3] = models[v, GATHER][1:3]
             models[v, c] = least_squares_log(predict, samples, lo, hi, [2.0, 1.5 * least, 1.2 * least, 3.0, 4.0])
     return models
+
+
+def rescaled(models, rows, c, near=1.2):
+    """The constants of layers of kind `c` times the median of measured over predicted time (`hbm` by its inverse), over the
+    passes in which the variant is within 20 % of the fastest."""
+    out = dict(models)
+    for v in ROW_MODELS:
+        if (v, c) not in models:
+            continue
+        ratios = sorted(dict(x["us"])[v] / row_us(models, x["k"], x["p"], v) for x in rows
+                        if kind(x["k"], x["p"]) == c and v in dict(x["us"]) and (x["p"] == 0 or v >= 300)
+                        and dict(x["us"])[v] < near * min(t for _, t in x["us"]))
+        if len(ratios) >= 20:
+            q, th = ratios[len(ratios) // 2], models[v, c]
+            out[v, c] = (*(t * q for t in th[:4]), th[4] / q)
+    return out
+
+
+def fit_before(rows):
+    """The fit to timings from before the runs, with the digits that the table had."""
+    return {k: tuple(round(t, 3) for t in c) for k, c in fit_rows(rows).items()}
+
+
+def row_models(before, rows):
+    """kRowModels: the fit to `before`; gathering layers rescaled to `rows`; the two 64x64 tiles that differ in their matrix block
+    only (327, 328) fitted to `rows` for pointwise layers, of which the long ones took the slower tile.  Strided data
+    gradients stay: rescaled they choose 0.1 to 0.5 % slower kernels."""
+    return {**rescaled(before, rows, GATHER), **fit_rows(rows, (327, 328), (POINTWISE,))}
 
 
 def fit_wgrad(rows):
@@ -480,7 +512,7 @@ def held_out(rows, fit, choice, folds=3):
 def report(name, loss):
     q = [t for t, _, _ in loss]
     print(f"// {name}: {len({tuple(k) for _, k, _ in loss})} layers, choice on layers left out of the fit "
-          f"{100 * (math.exp(sum(map(math.log, q)) / len(q)) - 1):.1f} % slower than the fastest variant "
+          f"{100 * (math.exp(sum(map(math.log, q)) / len(q)) - 1):.2f} % slower than the fastest variant "
           f"(90th percentile {100 * (q[int(0.9 * len(q))] - 1):.1f} %, 99th {100 * (q[int(0.99 * len(q))] - 1):.1f} %)")
 
 
@@ -496,29 +528,34 @@ def load(paths):
     return rows
 
 
-def fit(paths, cross_validate):
-    rows = load(paths)
-    parts = {what: [x for x in rows if x["what"] == what] for what in ("rows", "wgrad", "f32", "f32wgrad")}
+def fit(paths, before_paths, cross_validate):
+    def parts(paths):
+        rows = load(paths)
+        return {what: [x for x in rows if x["what"] == what] for what in ("rows", "wgrad", "f32", "f32wgrad")}
+    now, fit_all = parts(paths), fit_rows
+    f32 = now["f32"]
+    if before_paths:
+        old = parts(before_paths)
+        before, f32 = fit_before(old["rows"]), old["f32"]
+        fit_all = lambda rows: row_models(before, rows)
     if cross_validate:
-        report("rows", held_out(parts["rows"], fit_rows, row_choice))
-        report("wgrad", held_out(parts["wgrad"], fit_wgrad, wgrad_choice))
-        report("f32", held_out(parts["f32"], fit_f32, f32_choice))
-        report("f32wgrad", held_out(parts["f32wgrad"], fit_f32_wgrad, f32_wgrad_choice))
+        report("rows", held_out(now["rows"], fit_all, row_choice))
+        report("wgrad", held_out(now["wgrad"], fit_wgrad, wgrad_choice))
+        report("f32", held_out(f32, fit_f32, f32_choice))
+        report("f32wgrad", held_out(now["f32wgrad"], fit_f32_wgrad, f32_wgrad_choice))
 
     def cost(c):
         return "{}" if c is None else "{" + ", ".join(f"{t:.3f}f" for t in c) + "}"
-    models = fit_rows(parts["rows"])
+    models = fit_all(now["rows"])
     for v in ROW_MODELS:
         print(f"    {{{v}, {PER_CU.get(v, 1)}, " + ", ".join(cost(models.get((v, c))) for c in range(3)) + "},")
-    models = fit_wgrad(parts["wgrad"])
+    models = fit_wgrad(now["wgrad"])
     for v in WGRAD_MODELS:
         print(f"    {{{v}, {WGRAD_TILES[v][2]}, " + ", ".join(cost(models[v, c]) for c in range(2)) + "},")
-
-
-    models = fit_f32(parts["f32"])
+    models = fit_f32(f32)
     for i, (bm, bn, per_cu) in enumerate(F32_TILES):
         print(f"    {{{bm}, {bn}, {per_cu}, {cost(models[i])[1:-1]}, ...}},")
-    models = fit_f32_wgrad(parts["f32wgrad"])
+    models = fit_f32_wgrad(now["f32wgrad"])
     for i, (bm, bn, per_cu) in enumerate(F32_WGRAD_TILES):
         print(f"    {{{bm}, {bn}, {per_cu}, {cost(models[i])[1:-1]}}},")
 
@@ -533,12 +570,13 @@ def main() -> int:
     m.add_argument("--out", required=True)
     f = sub.add_parser("fit")
     f.add_argument("--timings", nargs="+", required=True)
+    f.add_argument("--before", nargs="+", default=[])
     f.add_argument("--no-cross-validation", action="store_true")
     args = ap.parse_args()
     if args.command == "measure":
         measure(args.what, args.seed, args.seconds, args.out)
     else:
-        fit(args.timings, not args.no_cross_validation)
+        fit(args.timings, args.before, not args.no_cross_validation)
     return 0
 
 

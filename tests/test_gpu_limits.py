@@ -88,6 +88,35 @@ def test_source_that_ends_just_below_2_31_bytes(H, dgrad, monkeypatch):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("C,K,R", [(64, 8, 3), (64, 8, 1), (8, 64, 3)])
+def test_weight_gradient_with_fetching_waves_on_offsets_up_to_2_31(C, K, R, monkeypatch):
+    """x or dy of 4095 x 4096 x 64: their last row ends 512 KB below 2^31 bytes, of which the fetching waves' descriptors take
+    another 3 KB.  dy is zero but in the last rows, so dw is that of a copy of the last rows under the register-staged kernel.
+    Products and sums of small whole numbers are exact, so every element is compared."""
+    H, W, rows = 4095, 4096, 6
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(C + R)
+    x = torch.randint(-4, 5, (1, H, W, C), dtype=torch.float16, device="cuda", generator=gen)
+    g = torch.zeros(1, H, W, K, dtype=torch.float16, device="cuda")
+    g[:, 1 - rows:] = torch.randint(-4, 5, (1, rows - 1, W, K), dtype=torch.float16, device="cuda", generator=gen)
+
+    def run(variant, x, g):
+        d = sd.make_desc(1, x.shape[1], W, C, K, R, R, (1, 1), (R // 2, R // 2))
+        monkeypatch.setenv("SDCONV_WGRAD_VARIANT", str(variant))
+        name, need = sd.kernel_name(d, sd.WGRAD), sd.conv2d_workspace_bytes(d, sd.WGRAD)
+        say(f"weight gradient of {tuple(x.shape)} to {K} channels, {R}x{R}: {name}, workspace {need}")
+        assert ("4w4f" in name) == (variant == 121)
+        dw, ws = torch.full((K, R, R, C), float("nan"), device="cuda"), torch.empty(max(need, 256), dtype=torch.uint8, device="cuda")
+        sd.conv2d_wgrad(d, x, g, dw, ws, torch.cuda.current_stream().cuda_stream)
+        return dw
+
+    whole, last = run(121, x, g), run(1, x[:, -rows:].contiguous(), g[:, -rows:].contiguous())
+    torch.cuda.synchronize()
+    assert last.abs().max() > 0 and torch.equal(whole, last)
+    del x, g
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("ranges", [1, 2])
 def test_weight_gradient_of_more_than_2_29_elements(ranges, monkeypatch):
     """1x1, 8192 -> 73 728 channels on 256 pixels: the 2.4 GB of dw, and twice that of partial sums, lie past the

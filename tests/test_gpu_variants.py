@@ -98,7 +98,8 @@ def test_split_role_kernel_variants(variant):
 # short last channel slab, and in classes of 9 to 16 taps), strides and dilations with and without a common
 # factor (classes with no taps along one axis, or with every other one), a 1x1 filter that is
 # padded or has a short slab.  Tiles without waves that only fetch (310), with such waves that divide the activation
-# loads of a stage evenly (327, 337, 340) and with one pass of them that has activation and filter loads (325, 326, 334).
+# and the filter loads of a stage evenly (327, 337, 340), and with four of them for the 18 or 10 activation loads of 144 and 80
+# rows, where the last waves have loads that fetch nothing (325, 326, 334).
 TAP_GRIDS = [
     (1, 17, 19, 72, 64, 7, 7, (1, 1), (3, 3), (1, 1)),
     (1, 17, 19, 64, 72, 7, 7, (2, 2), (3, 3), (1, 1)),
@@ -164,6 +165,13 @@ WGRAD_SHAPES = [
     (2, 23, 29, 64, 72, 3, 3, (2, 2), (1, 1), (1, 1)),      # strided, gathered x rows, filter tail
     (1, 31, 37, 136, 200, 3, 3, (1, 1), (1, 1), (1, 1)),    # channel and filter tails
     (1, 31, 37, 128, 264, 1, 1, (1, 1), (0, 0), (1, 1)),    # 1x1 unpadded: linear x addressing
+    # images of 49 pixels: a step of 64 ends in the next one; 441 pixels are seven steps, the last of three ranges has one
+    (9, 7, 7, 72, 136, 3, 3, (1, 1), (1, 1), (1, 1)),
+    (30, 3, 3, 64, 72, 3, 3, (1, 1), (1, 1), (1, 1)),       # seven images to a step
+    (5, 1, 1, 64, 72, 1, 1, (1, 1), (0, 0), (1, 1)),        # five pixels: the first step is the last, and short
+    (1, 5, 7, 72, 64, 3, 3, (1, 1), (2, 2), (2, 2)),        # dilation, fewer pixels than a step
+    (2, 19, 24, 72, 80, 3, 3, (2, 1), (1, 1), (1, 1)),      # strides that differ
+    (3, 11, 13, 88, 136, 1, 1, (1, 1), (0, 0), (1, 1)),     # linear, channels and filters end within a tile
 ]
 WGRAD_VARIANTS = [0, 1, 104, 107, 108, 112] + list(range(114, 124))      # 0, 1: the register-staged kernels of wgrad.hip
 

@@ -181,8 +181,9 @@ typedef struct {
 } conv2d_dgrad_epilogue;
 
 /* dx[n,h,w,c] = relu_mask[n,h,w,c] > 0 ? scale[c] * conv2d_dgrad(dy, w)[n,h,w,c] : +0,
- * in binary32 on the binary32 accumulator, one rounding to binary16.  `ep` is a HOST pointer,
- * not NULL.  Otherwise as conv2d_dgrad; dx must not overlap relu_mask. */
+ * in binary32 on the binary32 accumulator, one rounding to binary16.  A sum of zero (also that of a
+ * position that no tap reaches) times a negative scale is a zero of either sign.  `ep` is a HOST
+ * pointer, not NULL.  Otherwise as conv2d_dgrad; dx must not overlap relu_mask. */
 int conv2d_dgrad_fused(const conv2d_desc *desc, const void *dy, const void *w,
                        const conv2d_dgrad_epilogue *ep, void *dx, void *workspace,
                        size_t workspace_bytes, void *hip_stream);

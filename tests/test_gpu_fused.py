@@ -148,6 +148,7 @@ def test_unreached_positions_with_a_scale_that_is_not_finite(bad):
         unreached[::2, ::2] = False
         assert torch.equal(torch.isnan(dx[:, unreached]), torch.isnan(want[:, unreached]))
         assert torch.equal(dx[:, unreached].nan_to_num(0.0), want[:, unreached].nan_to_num(0.0))
+        assert not torch.signbit(dx[:, unreached])[~torch.isnan(dx[:, unreached])].any()     # +0, also where the scale is negative
 
 
 FUSED_PATCH_SHAPES = [

@@ -247,9 +247,11 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NDW)) void conv_patch_kernel(Igem
         } else {
             // The next group's fragments are read while the matrix pipe works on this one's; the barrier of
             // the next step, which waits for the last reads of this one, comes in front of its last matrix
-            // instructions.  The reads go between the matrix instructions, one or two behind each: in front of them all,
+            // instructions.  Within a step the reads go between the matrix instructions, one or two behind each: in front of them all,
             // they keep the matrix pipe waiting while LDS, which the fetching waves fill at the same time, takes them
-            // (3x3 256->256 on 2x50x84: 10x14 blocks 15.6 -> 14.9 us, 8x16 24.2 -> 22.4, 8x8 data gradient 26.6 -> 23.6).
+            // (3x3 256->256 on 2x50x84: 10x14 blocks 15.6 -> 14.9 us, 8x16 24.2 -> 22.4, 8x8 data gradient 26.6 -> 23.6).  The next
+            // step's first reads, behind its barrier, are another block of code than the last group's matrix instructions and
+            // do go in front of them.
             half8 fa[2][FM], fb[2][FN];
             constexpr int READS = FM + FN * (MODE == 0 ? 1 : 2), EACH = (READS + FM * FN - 1) / (FM * FN);
             auto interleave = [&]() __attribute__((always_inline)) {

@@ -296,7 +296,7 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
             // loads shares one LDS base (dma16_runs) and one scalar offset, in which tap and channel chunk are
             // counted; pointwise layers have nothing else to do, others two vector operations a load that put the
             // taps outside the image past the descriptor's range.  3x3 512->128 on 16x512, 64x64 tiles: 22.9 -> 17.9 us;
-            // 3x3 256->256 on 2x50x84, 80x128 tiles: 16.8 -> 13.8.
+            // 3x3 256->256 on 2x50x84, 80x128 tiles, with the order of reads below: 17.4 -> 14.6, data gradient 17.8 -> 15.3.
             const unsigned char* a0 = reinterpret_cast<const unsigned char*>(P.A) - kRunSlack - P.tap_bias;
             const int4v rsrcA = make_rsrc(a0, spanA + kRunSlack + P.tap_bias);
             const int4v rsrcB = make_rsrc(reinterpret_cast<const unsigned char*>(P.B) - kRunSlack, spanB + kRunSlack);

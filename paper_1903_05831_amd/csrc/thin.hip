@@ -118,6 +118,10 @@ __device__ __forceinline__ void tile_origin(const ThinParams& P, int tile, int& 
     wo0 = tw * kTW;
 }
 
+// TAIL: 0 none, 1 scale, bias and ReLU alone (a stem's), 2 any.  A kernel each: in one they took 172 vector registers (126, 137
+// and 144 now) and spilled 90 scalar ones (7, 10 and 85).  2 images of 694x1122 with the packing of the filter: plain
+// 31.1 -> 27.2 us, scale, bias and ReLU 35.5 -> 32.2, with a shortcut 133 -> 130.
+template <int TAIL>
 __global__ __launch_bounds__(256) void thin_fwd_kernel(ThinParams P)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -130,10 +134,9 @@ __global__ __launch_bounds__(256) void thin_fwd_kernel(ThinParams P)
     const int l32 = lane & 31, lhi = lane >> 5;
 
     const int kt = blockIdx.y;
-    // A tail of scale, bias and ReLU alone (a stem's) takes them from LDS, four filters a read: one load of 4 bytes from
-    // memory for each result and factor took longer than the layer (750x1333 image: 45 -> 27 us with the packing of the filter).
-    const bool affine_tail = P.ep.any() && !P.ep.residual && !P.ep.mask;
-    if (affine_tail && tid < 2 * kKT) {
+    // A tail of scale, bias and ReLU alone takes them from LDS, four filters a read: one load of 4 bytes from
+    // memory for each result and factor took longer than the layer (750x1333 image: 40.6 -> 22.1 us with the packing of the filter).
+    if (TAIL == 1 && tid < 2 * kKT) {
         const int k = kt * kKT + tid % kKT;
         const float* from = tid < kKT ? P.ep.scale : P.ep.bias;
         affine[tid] = from && k < P.K ? from[k] : tid < kKT ? 1.f : 0.f;
@@ -206,7 +209,7 @@ __global__ __launch_bounds__(256) void thin_fwd_kernel(ThinParams P)
                     int k = kb * 32 + 8 * q + 4 * lhi;
                     float v[4] = {acc[row][kb][4 * q + 0], acc[row][kb][4 * q + 1], acc[row][kb][4 * q + 2],
                                   acc[row][kb][4 * q + 3]};
-                    if (affine_tail) {
+                    if constexpr (TAIL == 1) {
                         const float4t scale = *reinterpret_cast<const float4t*>(affine + k);
                         const float4t bias = *reinterpret_cast<const float4t*>(affine + kKT + k);
 #pragma unroll
@@ -215,7 +218,7 @@ __global__ __launch_bounds__(256) void thin_fwd_kernel(ThinParams P)
                             if (P.ep.bias) v[e] += bias[e];
                             if (P.ep.relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
                         }
-                    } else if (P.ep.any()) {
+                    } else if constexpr (TAIL == 2) {
                         const int ho = ho0 + pix / kTW, wo = wo0 + pix % kTW;
                         if (ho < P.Ho && wo < P.Wo) {
                             const long o = (((long)n * P.Ho + ho) * P.Wo + wo) * P.K;
@@ -563,6 +566,22 @@ bool thin_supported(const Geom& g)
     return fwd_lds <= 150 * 1024;
 }
 
+template <int TAIL> static hipError_t launch_fwd_kernel(const Geom& g, const ThinParams& P, int ktiles, hipStream_t st)
+{
+    const size_t lds = (size_t)g.R * 4 * kKT * 16 + (((size_t)P.PH * P.PW * 8 + 15) & ~(size_t)15) + 256 * 128 +
+                       (TAIL == 1 ? 2 * kKT * sizeof(float) : 0);
+    static std::atomic<bool> configured{false};   // set once the attribute call has succeeded; a second thread may repeat it, harmlessly
+    if (!configured.load(std::memory_order_acquire)) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&thin_fwd_kernel<TAIL>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        configured.store(true, std::memory_order_release);
+    }
+    const int grid = balanced_grid(P.ntiles, 512);     // two workgroups per compute unit fit in LDS
+    hipLaunchKernelGGL(thin_fwd_kernel<TAIL>, dim3(grid, ktiles), dim3(256), lds, st, P);
+    return hipGetLastError();
+}
+
 hipError_t launch_thin_fwd(const Geom& g, const __half* x, const __half* w, __half* y, void* ws, hipStream_t st,
                            const Epilogue& ep)
 {
@@ -576,17 +595,8 @@ hipError_t launch_thin_fwd(const Geom& g, const __half* x, const __half* w, __ha
     if (e != hipSuccess) return e;
     P.X = x; P.Wp = wp; P.Y = y;
     P.ep = ep;
-    size_t lds = (size_t)g.R * 4 * kKT * 16 + (((size_t)P.PH * P.PW * 8 + 15) & ~(size_t)15) + 256 * 128 + 2 * kKT * sizeof(float);
-    static std::atomic<bool> configured{false};   // set once the attribute call has succeeded; a second thread may repeat it, harmlessly
-    if (!configured.load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&thin_fwd_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        configured.store(true, std::memory_order_release);
-    }
-    const int grid = balanced_grid(P.ntiles, 512);     // two workgroups per compute unit fit in LDS
-    hipLaunchKernelGGL(thin_fwd_kernel, dim3(grid, ktiles), dim3(256), lds, st, P);
-    return hipGetLastError();
+    if (!ep.any()) return launch_fwd_kernel<0>(g, P, ktiles, st);
+    return ep.residual || ep.mask ? launch_fwd_kernel<2>(g, P, ktiles, st) : launch_fwd_kernel<1>(g, P, ktiles, st);
 }
 
 hipError_t launch_thin_wgrad(const Geom& g, const __half* x, const __half* dy, float* dw, void* ws, hipStream_t st)

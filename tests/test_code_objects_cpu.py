@@ -1,5 +1,6 @@
 """What the compiler made of the kernels: properties of the gfx950 code in libsdconv.so that the sources rely on
 and no result shows reliably."""
+import heapq
 import os
 import re
 import shutil
@@ -111,6 +112,37 @@ def test_a_plain_stem_call_does_not_carry_the_registers_of_a_tail(code_objects):
     vector, scalar = ({k: int(f[name]) for k, f in found.items()} for name in ("vgpr_count", "sgpr_spill_count"))
     assert vector["0"] < min(vector["1"], vector["2"]), vector
     assert scalar["0"] < 20 and scalar["1"] < 20, scalar       # 90 in the one kernel
+
+
+def _trips_to_the_first_load(body):
+    """Waits for kernel parameters in lines of 64 bytes not read before, on the way to the first LDS-DMA load that has the fewest."""
+    at = {a: i for i, (a, _, _, _) in enumerate(body)}
+    heap, seen = [(0, 0, (), ())], set()
+    while heap:
+        trips, i, read, asked = heapq.heappop(heap)
+        if (i, read, asked) in seen:
+            continue
+        seen.add((i, read, asked))
+        _, op, args, target = body[i]
+        if op.startswith("buffer_load") and args.endswith(" lds"):
+            return trips
+        if op.startswith("s_load"):
+            m = re.match(r"\s*\S+, (s\[\d+:\d+\]), (0x[0-9a-f]+|\d+)", args)
+            first, size = int(m[2], 0), 4 * int(re.sub(r"\D", "", op) or "1")
+            asked = tuple(sorted({*asked, *((m[1] == "s[0:1]", line) for line in (first // 64, (first + size - 1) // 64))} - set(read)))
+        elif op == "s_waitcnt" and "lgkmcnt(0)" in args and asked:
+            trips, read, asked = trips + 1, tuple(sorted({*read, *asked})), ()
+        for n in ([] if op in ("s_endpgm", "s_branch", "s_setpc_b64") else [i + 1]) + ([] if target is None else [at[target]]):
+            if n < len(body):
+                heapq.heappush(heap, (trips, n, read, asked))
+
+
+def test_a_fused_data_gradient_asks_for_its_parameters_in_a_few_trips(code_objects):
+    """The code for tiles that no tap reaches must not part the loads of parameters in front of every other tile: three trips,
+    five with it and four without that code before the loads were put in front of it."""
+    trips = {name: _trips_to_the_first_load(body) for path in code_objects for name, body in _kernels(path)
+             if re.match(r"_ZN6sdconv15igemm_ws_kernelILi1E\w*Lb1EE", name)}
+    assert len(trips) > 15 and max(trips.values()) <= 4, trips
 
 
 def test_the_library_holds_the_variants_that_can_be_chosen(monkeypatch):

@@ -47,7 +47,8 @@ __device__ __forceinline__ void strip_handover()
 // row lane%16, columns 4*(lane/16) + j).  Both as produced by mfma(B fragment, A fragment).
 // TAIL: compiled with the elementwise tail (P.ep); the kernels are instantiated both ways so that
 // the plain passes keep the registers (and the occupancy) they have without it.
-template <int FM, int FN, int MF = 32, bool TAIL = false, typename Acc, typename OffOf>
+// REGS: vector registers that a wave may take so that several workgroups share a compute unit (256: one has it alone).
+template <int FM, int FN, int MF = 32, bool TAIL = false, int REGS = 256, typename Acc, typename OffOf>
 __device__ __forceinline__ void store_rows_via_lds(Acc (&acc)[FN][FM], unsigned char* strip, int lane,
                                                    int col_base, const IgemmParams& P, OffOf off_of)
 {
@@ -118,9 +119,12 @@ __device__ __forceinline__ void store_rows_via_lds(Acc (&acc)[FN][FM], unsigned 
     }
     // The shortcut (or, without one, the mask) values are loaded LA block rows ahead, all of them before
     // the first strip is written where the registers allow it, so their latency passes behind the LDS
-    // work instead of once per block row.
-    constexpr int ACC = FM * FN * (MF == 32 ? 16 : 4), LOOK = (176 - ACC) / (4 * NJ);
-    constexpr int LA = LOOK < 2 ? (FM < 2 ? FM : 2) : (LOOK < FM ? LOOK : FM);
+    // work instead of once per block row.  Where several workgroups are to share a compute unit they are fewer, each with
+    // its offset, beside the accumulators and 36 others: with all of them a wave took 139 registers of 128 on 128x128 tiles, and 86 of
+    // 80 on 128x64 ones, and a workgroup less fitted (fused layers of random size -9 and -4 % without).
+    constexpr int ACC = FM * FN * (MF == 32 ? 16 : 4), LOOK = (176 - ACC) / (4 * NJ), SHARED = (REGS - 36 - ACC) / (5 * NJ);
+    constexpr int ALONE = LOOK < 2 ? (FM < 2 ? FM : 2) : (LOOK < FM ? LOOK : FM);
+    constexpr int LA = REGS < 256 && SHARED < ALONE ? (SHARED < 1 ? 1 : SHARED) : ALONE;
     __half* aux = const_cast<__half*>(E.residual ? E.residual : E.mask);
     const __amdgpu_buffer_rsrc_t rsrcX = __builtin_amdgcn_make_buffer_rsrc(aux, 0, aux ? dbytes : 0, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrcM =

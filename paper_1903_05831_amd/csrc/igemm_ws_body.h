@@ -598,7 +598,7 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
     // ---- epilogue: through a per-wave LDS strip into 16-byte NHWC stores --------------------
     static_assert(NWC * epilogue_strip_bytes<WN, MF>() <= S * STAGE, "epilogue strips fit in the ring");
     stage_barrier();                                // everybody is done reading the last stage
-    store_rows_via_lds<FM, FN, MF, TAIL>(acc, smem + wave * epilogue_strip_bytes<WN, MF>(), lane, n0 + wn * WN, P,
+    store_rows_via_lds<FM, FN, MF, TAIL, PERCU < 2 ? 256 : 512 / WAVES / 8 * 8>(acc, smem + wave * epilogue_strip_bytes<WN, MF>(), lane, n0 + wn * WN, P,
                                          [&](int r) { return dst_off(wm * WM + r); });
     }
 }

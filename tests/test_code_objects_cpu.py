@@ -114,6 +114,21 @@ def test_a_plain_stem_call_does_not_carry_the_registers_of_a_tail(code_objects):
     assert scalar["0"] < 20 and scalar["1"] < 20, scalar       # 90 in the one kernel
 
 
+def test_workgroups_that_are_to_share_a_compute_unit_have_the_registers_for_it(code_objects):
+    """The time models count on so many workgroups of some tiles on a compute unit, with a tail or without: four SIMDs of 512
+    registers, taken in eights."""
+    tiles = {(128, 128, 2): 2, (128, 64, 2): 3, (64, 64, 4): 2}       # height, width, stages of the ring: fit_models.PER_CU 339, 340, 327 and 328
+    found = set()
+    for path in code_objects:
+        for field in _notes(path):
+            m = re.match(r"_ZN6sdconv15igemm_ws_kernelILi\dELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi64ELi(\d+)E", field["name"])
+            if m and (tile := (int(m[1]), int(m[2]), int(m[5]))) in tiles:
+                waves = (int(m[3]) * int(m[4]) + int(m[6])) * tiles[tile] // 4
+                assert -(-int(field["vgpr_count"]) // 8) * 8 * waves <= 512, (field["name"], field["vgpr_count"], waves)
+                found.add((tile, field["name"]))
+    assert len(found) == 16, found      # two passes, plain and with a tail; two kinds of 64x64
+
+
 def _trips_to_the_first_load(body):
     """Waits for kernel parameters in lines of 64 bytes not read before, on the way to the first LDS-DMA load that has the fewest."""
     at = {a: i for i, (a, _, _, _) in enumerate(body)}

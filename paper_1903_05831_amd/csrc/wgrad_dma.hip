@@ -285,9 +285,10 @@ __global__ __launch_bounds__(64 * (WGM * WGN + (F > 0 ? F : 0))) void wgrad_dma_
     // ORDERED: the first portion's fragments are read at once and the next one's between the matrix instructions, where
     // the compiler reads them before their use (256x256 tiles with their reduction, 3x3 512->512 on 25 088 pixels 115.4 ->
     // 111.0 us, 1x1 2048->512 65.2 -> 62.6; 128x128 with fetching waves, 3x3 256->256 on 2x50x84 23.9 -> 22.8).  Waves with
-    // smaller tiles have too few matrix instructions to read behind (64x64 tiles 3-4 % slower).
+    // smaller tiles have too few matrix instructions to read behind (64x64 tiles 3-4 % slower), and where every wave fetches its
+    // share two workgroups on the compute unit fill each other's gaps (128x128 tiles of four waves 0.7 to 0.9 % slower).
     constexpr int NCH = BP / KSTEP;
-    constexpr bool ORDERED = MF == 16 && NCH > 1 && WM * WN >= 64 * 64;
+    constexpr bool ORDERED = F != 0 && MF == 16 && NCH > 1 && WM * WN >= 64 * 64;
     auto compute = [&](int stage) {
         const unsigned char* sg = smem + stage * STAGE;
         const unsigned char* sx = sg + GBYTES;

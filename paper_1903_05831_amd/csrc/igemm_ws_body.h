@@ -228,29 +228,34 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
         const int cleft = P.Cs - nx.kc * BK;        // channels left from this chunk's start
         auto load_a = [&](int p, unsigned voff) { dma16(voff, rsrcA0, cbytes, base_a + p * GAP * 1024); };
         auto load_b = [&](int p, unsigned voff) { dma16(voff, rsrcB0, bsoff, base_b + p * GAP * 1024); };
-        // (in the rare branches the lane number is read anew: what follows from it is not kept in registers meanwhile)
+        // (where these waves multiply too, the lane number is read anew in the rare branches: what follows from it is not kept in
+        // registers meanwhile)
         if (partial && cleft < BK) {
             int lane = threadIdx.x & 63;
-            asm volatile("" : "+v"(lane));
+            if constexpr (NP == 0) asm volatile("" : "+v"(lane));
             // Lanes whose chunk is past the last channel: in the row 8 * i + lane / 8 of instruction i it depends on the lane and on
-            // whether i is odd.  Worked out for each load, with the lane read anew, it made such layers 6-20 % slower on the
-            // tiles without waves that only fetch: 3x3 data gradient, 72->256 on 2x50x84, 224x256 tiles 30.1 -> 26.7 us, 256x256 33.6 -> 29.1.
+            // whether i is odd.  Worked out for each load it made such layers 6-20 % slower on the tiles without waves that only
+            // fetch (3x3 data gradient, 72->256 on 2x50x84, 224x256 tiles 30.1 -> 26.7 us, 256x256 33.6 -> 29.1) and 13-30 % with more than 32 taps.
             const int even = (lane & 7) ^ (lane >> 4);
-            const bool past[2] = {even * 8 >= cleft, (even ^ 4) * 8 >= cleft};
+            const unsigned past[2] = {even * 8 >= cleft ? kOutOfRange : 0u, (even ^ 4) * 8 >= cleft ? kOutOfRange : 0u};
+            if (nx.tap < 32) {
+                const int sh = 31 - nx.tap;
 #pragma unroll
-            for (int p = 0; p < PA; ++p) {
-                unsigned o = out[p];
-                if (nx.tap >= 32) {
+                for (int p = 0; p < PA; ++p)
+                    load_a(p, (int)((out[p] << sh) | past[a_instr(p) & 1]) < 0 ? kOutOfRange : off[p] + ad);
+            } else {
+#pragma unroll
+                for (int p = 0; p < PA; ++p) {
                     const int r = a_instr(p) * 8 + (lane >> 3);
-                    if (r < BM) o = row_hi[r];
+                    const unsigned o = PA * NI > NA && r >= BM ? ~0u : row_hi[r];
+                    load_a(p, (int)((o << (63 - nx.tap)) | past[a_instr(p) & 1]) < 0 ? kOutOfRange : off[p] + ad);
                 }
-                load_a(p, ((o >> (nx.tap & 31)) & 1u) || past[a_instr(p) & 1] ? kOutOfRange : off[p] + ad);
             }
             // KROWS: the filter's rows are those of the other operand; else instruction i holds contraction rows from i * 512 / BN on
             const int row0 = b_instr(0) * (512 / BN) + lane / (BN / 8);
 #pragma unroll
             for (int p = 0; p < PB; ++p)
-                load_b(p, (KROWS ? past[b_instr(p) & 1] : row0 + p * GAP * (512 / BN) >= cleft) ? kOutOfRange : off[PA + p]);
+                load_b(p, (KROWS ? past[b_instr(p) & 1] != 0u : row0 + p * GAP * (512 / BN) >= cleft) ? kOutOfRange : off[PA + p]);
         } else {
             if (P.pointwise) {
 #pragma unroll
@@ -261,7 +266,7 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
                 for (int p = 0; p < PA; ++p) load_a(p, (int)(out[p] << sh) < 0 ? kOutOfRange : off[p] + ad);
             } else {
                 int lane = threadIdx.x & 63;
-                asm volatile("" : "+v"(lane));
+                if constexpr (NP == 0) asm volatile("" : "+v"(lane));
 #pragma unroll
                 for (int p = 0; p < PA; ++p) {
                     const int r = a_instr(p) * 8 + (lane >> 3);

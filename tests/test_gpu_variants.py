@@ -124,19 +124,20 @@ def test_tap_grids_of_split_role_kernels(variant):
 
 
 @pytest.mark.parametrize("dgrad", [False, True])
-@pytest.mark.parametrize("variant", [310, 311, 316, 338])
-def test_a_short_last_channel_chunk_takes_no_longer_than_a_whole_one(variant, dgrad):
-    """Tiles whose multiplying waves fetch too: 72 and 128 contraction channels are two chunks of a tap each, the short one with
-    less to move.  1.02 to 1.06 times the time, 1.12 to 1.22 where its lanes were told apart load by load."""
+@pytest.mark.parametrize("variant,R,short,whole", [(v, 3, 72, 128) for v in (310, 311, 316, 338)] + [(v, 7, 40, 64) for v in (328, 334, 337)])
+def test_a_short_last_channel_chunk_takes_no_longer_than_a_whole_one(variant, R, short, whole, dgrad):
+    """Tiles whose multiplying waves fetch too, and more than 32 taps on tiles with waves that only fetch: as many chunks, the short one
+    with less to move: 0.99 to 1.02 and 0.96 to 1.10 times the time, 1.13 to 1.22 and 1.29 to 1.59 where its lanes were told apart
+    load by load."""
     stream, graphs, best = torch.cuda.Stream(), [], [1e9, 1e9]
-    for cs in (72, 128):
+    for cs in (short, whole):
         C, K = (256, cs) if dgrad else (cs, 256)
-        d = sd.make_desc(2, 50, 84, C, K, 3, 3, (1, 1), (1, 1))
+        d = sd.make_desc(2, 50, 84, C, K, R, R, (1, 1), (R // 2, R // 2))
         src = torch.randn(2, 50, 84, cs, device="cuda").half()
-        w = torch.randn(K, 3, 3, C, device="cuda").mul_(0.05).half()
+        w = torch.randn(K, R, R, C, device="cuda").mul_(0.05).half()
         out = torch.empty(2, 50, 84, 256, dtype=torch.float16, device="cuda")
         with forced(SDCONV_IGEMM_VARIANT=variant):
-            assert "8w0f" in sd.kernel_name(d, sd.DGRAD if dgrad else sd.FWD)
+            assert ("8w0f" if R == 3 else "4w4f") in sd.kernel_name(d, sd.DGRAD if dgrad else sd.FWD)
             call = sd.conv2d_dgrad if dgrad else sd.conv2d_fwd
             stream.wait_stream(torch.cuda.current_stream())
             call(d, src, w, out, None, stream.cuda_stream)
@@ -155,7 +156,8 @@ def test_a_short_last_channel_chunk_takes_no_longer_than_a_whole_one(variant, dg
                 b.record()
             stream.synchronize()
             best[i] = min(best[i], a.elapsed_time(b))
-    assert best[0] < 1.09 * best[1], best
+    say(f"variant {variant} {R}x{R} {'data gradient' if dgrad else 'forward'}: {short} / {whole} channels {best[0] / best[1]:.3f}")
+    assert best[0] < (1.09 if R == 3 else 1.2) * best[1], best
 
 
 def test_two_tile_widths_in_one_launch():

@@ -7,6 +7,7 @@ namespace sdconv {
 template <int MODE, int BM, int BN, int WGM, int WGN, int S, int BK, int NP, int MF = 32, bool TAIL = false>
 __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void igemm_ws_kernel(IgemmParams P)
 {
+    ask_for_parameters(P);
     const int tile = xcd_run_tile(blockIdx.x);
     if (tile >= P.total_tiles) return;
     igemm_ws_body<MODE, BM, BN, WGM, WGN, S, BK, NP, MF, TAIL>(P, tile, P.tiles_n, 0);
@@ -21,6 +22,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void igemm_ws_kernel(IgemmPa
 template <int MODE, int BM, int BN, int BNS, int WGM, int WGN, int S, int SS, int BK, int MF, bool TAIL>
 __global__ __launch_bounds__(64 * WGM * WGN) void igemm_ws_mixed_kernel(IgemmParams P)
 {
+    ask_for_parameters(P);
     int b = blockIdx.x;
     if (b < P.mix_big_blocks) {
         const int tile = xcd_run_tile(b);

@@ -42,6 +42,15 @@ typedef float float4v_ __attribute__((ext_vector_type(4)));
 // lines displace operands from L2 (87 -> 93 us on 512->2048, 512 RoIs); strided data gradients, whose lines
 // are spread over four classes' tiles, lose 1 % with any.
 constexpr int kWarmSteps = 2;
+
+// A value from each line of 64 bytes of the parameters that every tile needs, so that the lines come in one trip: the compiler
+// loads them where they are used and nothing ahead of a branch, and by how that falls out a tile waited for two to five trips to cold
+// lines before its first operand load, each some 3 % of a small layer.
+__device__ __forceinline__ void ask_for_parameters(const IgemmParams& P)
+{
+    asm volatile("" :: "s"(P.Cs), "s"(P.total_tiles), "s"(P.taps_h[0].count), "s"(P.taps_w[0].count), "s"(P.tap_dh), "s"(P.pointwise));
+}
+
 // MF: 32 = v_mfma_f32_32x32x16_f16 blocks; 16 = v_mfma_f32_16x16x32_f16 blocks, for tile heights
 // that are a multiple of 16 but not of 32 per wave row (224 = 2 x 112 rows: 25088 = 112 x 224
 // pixels of the RoI head then give 224 or 896 tiles instead of 196 or 784 for 256 CUs).
@@ -108,10 +117,6 @@ __device__ __forceinline__ void igemm_ws_body(const IgemmParams& P, const int ti
     // a barrier after each, the first load left 1.1 us after the start of the kernel.
     const AxisTaps th = P.taps_h[ca], tw = P.taps_w[cb];
     const int ntaps = th.count * tw.count;
-    // What every tile needs of the parameters is loaded here: behind the branch below, which the compiler loads nothing
-    // ahead of, it was one more trip to cold lines before the first operand load, 2-4 % of a pointwise layer with a tail.
-    if (MODE == 1 && TAIL)
-        asm volatile("" :: "s"(P.pointwise), "s"(P.Cs), "s"(P.Cd), "s"(P.b_row_pitch), "s"(P.tap_bias), "s"(P.tap_dh), "s"(P.tap_dw));
     if (MODE == 1 && !F32 && ntaps == 0) {
         // a class without taps (three of the four of a 1x1 stride-2 layer): nothing to multiply.  With a tail the result is
         // 0 whatever the mask holds, which is then not read, unless a scale is infinite or NaN or something is added

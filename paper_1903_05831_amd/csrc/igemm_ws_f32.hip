@@ -13,6 +13,7 @@ namespace sdconv {
 template <int MODE, int BM, int BN, int WGM, int WGN, int KS, int S, int NP>
 __global__ __launch_bounds__(64 * (WGM * WGN * KS + NP)) void igemm_ws_f32_kernel(IgemmParams P)
 {
+    ask_for_parameters(P);
     const int tile = xcd_run_tile(blockIdx.x);
     if (tile >= P.total_tiles) return;
     igemm_ws_body<MODE, BM, BN, WGM, WGN, S, 64, NP, 32, false, true, KS>(P, tile, P.tiles_n, 0);

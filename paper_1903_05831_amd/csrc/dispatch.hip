@@ -178,7 +178,7 @@ static int ws_variant_for(const Geom& g, bool dgrad, int v)
 // and of streaming (6.1 TB/s; 3.5 at least) and by a start of 0.5 us; then, past these bounds, those of gathering layers scaled by the median
 // of measured over predicted time (`hbm` by its inverse) where a variant is within 20 % of the fastest on the present timings of 1991 layers
 // (0.8 to 1.1), and two 64x64 tiles (327 and 328), alike but for the matrix block, fitted to those for pointwise layers: long
-// contractions took the slower one.  (A `step` below `shared` never counts.)  On layers left out of the scaling the choice is 1.23 % slower
+// contractions took the slower one.  (A `step` no longer than `shared` never counts.)  On layers left out of the scaling the choice is 1.23 % slower
 // than the fastest of 27 measured variants (3.9 % at the 90th percentile, 19 % at the 99th), without it 1.33 % (4.3 %, 21 %), with strided
 // data gradients scaled too 1.25 %, under a fit to the present timings 1.55 % (5.4 %, 21 %); rules by row counts were 17 % (57 %) slower.
 struct RowCost { float fixed, step, shared, tile, hbm; };
@@ -191,8 +191,8 @@ static const RowModel kRowModels[] = {
     {316, 1, {0.960f, 0.788f, 0.000f, 3.781f, 4.578f}, {0.500f, 0.815f, 0.000f, 4.163f, 3.500f}, {0.500f, 0.815f, 0.000f, 5.306f, 3.500f}},
     {325, 1, {1.738f, 0.424f, 0.000f, 2.271f, 3.864f}, {1.534f, 0.384f, 0.000f, 2.409f, 3.679f}, {1.856f, 0.404f, 0.000f, 3.081f, 3.500f}},
     {326, 1, {1.820f, 0.956f, 0.000f, 3.075f, 4.274f}, {1.407f, 0.910f, 0.000f, 3.038f, 3.514f}, {0.525f, 0.914f, 0.000f, 5.403f, 3.500f}},
-    {327, 2, {1.967f, 0.149f, 0.227f, 1.500f, 4.542f}, {1.920f, 0.239f, 0.175f, 1.251f, 3.934f}, {1.472f, 0.269f, 0.197f, 2.552f, 3.500f}},
-    {328, 2, {1.936f, 0.067f, 0.225f, 1.480f, 4.445f}, {1.879f, 0.236f, 0.170f, 1.205f, 3.968f}, {1.507f, 0.268f, 0.193f, 2.561f, 3.500f}},
+    {327, 2, {1.967f, 0.227f, 0.227f, 1.500f, 4.543f}, {1.920f, 0.239f, 0.175f, 1.251f, 3.934f}, {1.472f, 0.269f, 0.197f, 2.552f, 3.500f}},
+    {328, 2, {1.943f, 0.225f, 0.225f, 1.474f, 4.453f}, {1.879f, 0.236f, 0.170f, 1.205f, 3.968f}, {1.507f, 0.268f, 0.193f, 2.561f, 3.500f}},
     {329, 1, {1.638f, 0.353f, 0.000f, 2.045f, 4.331f}, {1.464f, 0.310f, 0.000f, 2.034f, 3.789f}, {1.785f, 0.331f, 0.000f, 2.613f, 3.908f}},
     {330, 1, {1.692f, 0.469f, 0.000f, 2.452f, 4.279f}, {1.053f, 0.449f, 0.000f, 3.106f, 3.349f}, {1.500f, 0.430f, 0.000f, 3.323f, 3.578f}},
     {331, 1, {1.288f, 0.726f, 0.000f, 3.638f, 4.327f}, {0.557f, 0.738f, 0.000f, 4.697f, 3.141f}, {0.500f, 0.662f, 0.000f, 5.317f, 3.500f}},
@@ -205,8 +205,8 @@ static const RowModel kRowModels[] = {
     {338, 1, {1.545f, 1.019f, 0.000f, 3.132f, 4.382f}, {0.965f, 1.082f, 0.000f, 4.151f, 3.161f}, {0.500f, 0.977f, 0.000f, 5.238f, 3.500f}},
     {339, 2, {2.285f, 0.719f, 0.487f, 1.626f, 4.446f}, {2.869f, 0.707f, 0.440f, 0.744f, 3.427f}, {0.500f, 0.692f, 0.431f, 4.074f, 3.500f}},
     {340, 3, {1.952f, 0.605f, 0.340f, 1.470f, 3.831f}, {3.208f, 0.586f, 0.314f, 0.000f, 3.543f}, {0.500f, 0.593f, 0.318f, 3.724f, 3.500f}},
-    {427, 2, {}, {2.317f, 0.164f, 0.219f, 1.607f, 3.493f}, {}},
-    {433, 2, {}, {2.748f, 0.273f, 0.285f, 1.536f, 3.443f}, {}},
+    {427, 2, {}, {2.317f, 0.219f, 0.219f, 1.607f, 3.493f}, {}},
+    {433, 2, {}, {2.748f, 0.285f, 0.285f, 1.536f, 3.443f}, {}},
     {435, 1, {}, {1.378f, 0.328f, 0.000f, 2.510f, 3.458f}, {}},
     {436, 1, {}, {1.368f, 0.261f, 0.000f, 2.344f, 3.593f}, {}},
     {437, 1, {}, {1.512f, 0.168f, 0.000f, 1.823f, 3.692f}, {}},

@@ -407,7 +407,14 @@ def fit_rows(rows, variants=ROW_MODELS, kinds=(POINTWISE, GATHER, STRIDED)):
             hi = [10.0, 6 * least, 6 * least if per_cu > 1 else 0.0, 20.0, STREAM]
             if c == STRIDED:        # a step is the same work as in any gathering layer
                 lo[1:3] = hi[1:3] = models[v, GATHER][1:3]
-            models[v, c] = least_squares_log(predict, samples, lo, hi, [2.0, 1.5 * least, 1.2 * least, 3.0, 4.0])
+            th = least_squares_log(predict, samples, lo, hi, [2.0, 1.5 * least, 1.2 * least, 3.0, 4.0])
+            # A step below `shared` never counts, and what the solver makes of it, and of the others on its way there, depends on
+            # the processor: fitted on without it.
+            if th[1] < th[2] and c != STRIDED:
+                lo[1] = hi[1] = 0.0
+                th = least_squares_log(predict, samples, lo, hi, th)
+                th = (th[0], th[2], *th[2:])
+            models[v, c] = th
     return models
 
 

@@ -178,14 +178,17 @@ static int ws_variant_for(const Geom& g, bool dgrad, int v)
 // and of streaming (6.1 TB/s; 3.5 at least) and by a start of 0.5 us; then, past these bounds, those of gathering layers scaled by the median
 // of measured over predicted time (`hbm` by its inverse) where a variant is within 20 % of the fastest on the present timings of 1991 layers
 // (0.8 to 1.1), and two 64x64 tiles (327 and 328), alike but for the matrix block, fitted to those for pointwise layers: long
-// contractions took the slower one.  (A `step` no longer than `shared` never counts.)  On layers left out of the scaling the choice is 1.23 % slower
-// than the fastest of 27 measured variants (3.9 % at the 90th percentile, 19 % at the 99th), without it 1.33 % (4.3 %, 21 %), with strided
-// data gradients scaled too 1.25 %, under a fit to the present timings 1.55 % (5.4 %, 21 %); rules by row counts were 17 % (57 %) slower.
+// contractions took the slower one.  (A `step` no longer than `shared` never counts.)  Not scaled are the kernels without runs of loads
+// but 101 and 427: near the fastest, their median is below one by the choice of layers alone.  On some 1000 passes of random layers whose
+// kernel this changes, times fell by 5 to 8 % (112 took layers of one channel chunk from 101 that it reads twice as often: 54 -> 86 us).
+// On layers left out of the scaling the choice is 1.21 % slower than the fastest of 27 measured variants (3.8 % at the 90th percentile, 19 %
+// at the 99th), with all kernels scaled 1.23 %, without any scaling 1.33 % (4.3 %, 21 %), under a fit to the present timings 1.55 %
+// (5.4 %, 21 %); rules by row counts were 17 % (57 %) slower.
 struct RowCost { float fixed, step, shared, tile, hbm; };
 struct RowModel { int variant, per_cu; RowCost pointwise, gather, strided; };   // step 0: not taken
 static const RowModel kRowModels[] = {
     {101, 3, {2.626f, 0.768f, 0.611f, 1.227f, 4.342f}, {2.810f, 0.781f, 0.564f, 1.025f, 3.845f}, {}},
-    {112, 5, {2.829f, 0.782f, 0.457f, 0.543f, 3.500f}, {3.292f, 0.725f, 0.405f, 0.000f, 3.777f}, {}},
+    {112, 5, {2.829f, 0.782f, 0.457f, 0.543f, 3.500f}, {3.552f, 0.782f, 0.437f, 0.000f, 3.500f}, {}},
     {310, 1, {0.864f, 1.208f, 0.000f, 4.512f, 4.162f}, {0.552f, 1.294f, 0.000f, 5.334f, 3.168f}, {0.500f, 1.171f, 0.000f, 6.070f, 3.500f}},
     {311, 1, {0.687f, 1.352f, 0.000f, 5.017f, 4.024f}, {0.551f, 1.427f, 0.000f, 5.654f, 3.174f}, {0.500f, 1.294f, 0.000f, 6.539f, 3.500f}},
     {316, 1, {0.960f, 0.788f, 0.000f, 3.781f, 4.578f}, {0.500f, 0.815f, 0.000f, 4.163f, 3.500f}, {0.500f, 0.815f, 0.000f, 5.306f, 3.500f}},
@@ -206,10 +209,10 @@ static const RowModel kRowModels[] = {
     {339, 2, {2.285f, 0.719f, 0.487f, 1.626f, 4.446f}, {2.869f, 0.707f, 0.440f, 0.744f, 3.427f}, {0.500f, 0.692f, 0.431f, 4.074f, 3.500f}},
     {340, 3, {1.952f, 0.605f, 0.340f, 1.470f, 3.831f}, {3.208f, 0.586f, 0.314f, 0.000f, 3.543f}, {0.500f, 0.593f, 0.318f, 3.724f, 3.500f}},
     {427, 2, {}, {2.317f, 0.219f, 0.219f, 1.607f, 3.493f}, {}},
-    {433, 2, {}, {2.748f, 0.285f, 0.285f, 1.536f, 3.443f}, {}},
-    {435, 1, {}, {1.378f, 0.328f, 0.000f, 2.510f, 3.458f}, {}},
-    {436, 1, {}, {1.368f, 0.261f, 0.000f, 2.344f, 3.593f}, {}},
-    {437, 1, {}, {1.512f, 0.168f, 0.000f, 1.823f, 3.692f}, {}},
+    {433, 2, {}, {2.703f, 0.280f, 0.280f, 1.511f, 3.500f}, {}},
+    {435, 1, {}, {1.361f, 0.324f, 0.000f, 2.480f, 3.500f}, {}},
+    {436, 1, {}, {1.404f, 0.268f, 0.000f, 2.407f, 3.500f}, {}},
+    {437, 1, {}, {1.595f, 0.177f, 0.000f, 1.923f, 3.500f}, {}},
 };
 constexpr float kEmptyTile = 0.6f;      // of `tile`: a tile of a class that no tap reaches only stores zeros
 

@@ -74,6 +74,8 @@ ROW_VARIANTS = [101, 112, 310, 311, 316, 324] + list(range(325, 341)) + [427, 43
 # variants with a row in the models (324 has those of its two halves)
 ROW_MODELS = [v for v in ROW_VARIANTS if v != 324]
 WGRAD_MODELS = WGRAD_VARIANTS = [104, 107, 108, 112, 114, 115, 116, 117, 118, 119, 120, 121, 122, 123]
+# kernels that the runs of loads do not reach and whose constants for gathering layers stay (row_models)
+UNSCALED = (112, 433, 435, 436, 437)
 ONE_SLAB = {427, 433}                    # one patch buffer: 64 contraction channels only
 WORKGROUPS = (40, 64, 96, 128, 192, 256, 320, 384, 512, 768, 1024)
 
@@ -423,7 +425,7 @@ def rescaled(models, rows, c, near=1.2):
     passes in which the variant is within 20 % of the fastest."""
     out = dict(models)
     for v in ROW_MODELS:
-        if (v, c) not in models:
+        if (v, c) not in models or v in UNSCALED:
             continue
         ratios = sorted(dict(x["us"])[v] / row_us(models, x["k"], x["p"], v) for x in rows
                         if kind(x["k"], x["p"]) == c and v in dict(x["us"]) and (x["p"] == 0 or v >= 300)
@@ -442,7 +444,10 @@ def fit_before(rows):
 def row_models(before, rows):
     """kRowModels: the fit to `before`; gathering layers rescaled to `rows`; the two 64x64 tiles that differ in their matrix block
     only (327, 328) fitted to `rows` for pointwise layers, of which the long ones took the slower tile.  Strided data
-    gradients stay: rescaled they choose 0.1 to 0.5 % slower kernels."""
+    gradients stay: rescaled they choose 0.1 to 0.5 % slower kernels.  So do kernels without runs of loads, for which a ratio taken near
+    the fastest is below one by the choice of layers alone: rescaled, the 128x64 tile (112) took strided 1x1 layers with one channel chunk
+    from the 128x128 one (54 -> 86 us), and the patch blocks a few per cent of 3x3 layers at 4 to 8 % more.  (101 and 427 choose as well or
+    better rescaled: 0.97 and 1.00.)"""
     return {**rescaled(before, rows, GATHER), **fit_rows(rows, (327, 328), (POINTWISE,))}
 
 

@@ -41,11 +41,19 @@ DETECTOR_LAYERS = [
     (12544, 1024, 1, 1), (1024, 1024, 1, 1)]
 
 
-def random_layers(seed: int, count: int):
+def random_layers(seed: int, count: int, few_pixels: bool = False):
     """Geometries (N, H, W, C, K, R, stride, pad, dilation): half of them with the channels of a
-    detector's layer on maps of random size and number, half with any channels (in eights)."""
+    detector's layer on maps of random size and number, half with any channels (in eights).  Or layers of 12 to 700 pixels, with
+    any channels and filters of up to 7x7: a weight gradient of few steps."""
     rng = random.Random(seed)
     out = []
+    while few_pixels and len(out) < count:
+        C, K = (8 * int(math.exp(rng.uniform(0, math.log(256)))) for _ in range(2))
+        R, stride, N = rng.choice([1, 1, 3, 3, 5, 7]), rng.choice([1, 1, 2]), rng.choice([1, 1, 2, 4])
+        px = int(math.exp(rng.uniform(math.log(12), math.log(700))))
+        H = max(3, int((px / N) ** 0.5 * rng.uniform(0.6, 1.0)))
+        if C * K * R * R <= 1 << 26:
+            out.append((N, H * stride, max(3, px // (N * H)) * stride, C, K, R, stride, R // 2, 1))
     while len(out) < count:
         if rng.random() < 0.5:
             C, K, R, stride = rng.choice(DETECTOR_LAYERS)
@@ -80,7 +88,7 @@ ONE_SLAB = {427, 433}                    # one patch buffer: 64 contraction chan
 WORKGROUPS = (40, 64, 96, 128, 192, 256, 320, 384, 512, 768, 1024)
 
 
-def measure(what: str, seed: int, seconds: float, path: str) -> None:
+def measure(what: str, seed: int, seconds: float, path: str, few_pixels: bool = False) -> None:
     os.environ["SDCONV_TUNE"] = "1"             # before the first library call
     os.environ["SDCONV_NO_TUNED_TABLE"] = "1"      # nor the entries of four weight gradients
     import torch
@@ -137,7 +145,7 @@ def measure(what: str, seed: int, seconds: float, path: str) -> None:
 
     start, done = time.time(), 0
     with gzip.open(path, "wt") as out:
-        for k in random_layers(seed, 2000):
+        for k in random_layers(seed, 2000, few_pixels):
             if time.time() - start > seconds:
                 break
             N, H, W, C, K, R, s, pad, dil = k
@@ -580,13 +588,14 @@ def main() -> int:
     m.add_argument("--seed", type=int, default=1)
     m.add_argument("--seconds", type=float, default=100)
     m.add_argument("--out", required=True)
+    m.add_argument("--few-pixels", action="store_true", help="layers of 12 to 700 pixels")
     f = sub.add_parser("fit")
     f.add_argument("--timings", nargs="+", required=True)
     f.add_argument("--before", nargs="+", default=[])
     f.add_argument("--no-cross-validation", action="store_true")
     args = ap.parse_args()
     if args.command == "measure":
-        measure(args.what, args.seed, args.seconds, args.out)
+        measure(args.what, args.seed, args.seconds, args.out, args.few_pixels)
     else:
         fit(args.timings, args.before, not args.no_cross_validation)
     return 0

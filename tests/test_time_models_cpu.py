@@ -110,6 +110,17 @@ def test_weight_gradient_tiles_and_ranges(variants):
     assert worst < 0.16, worst
 
 
+@pytest.mark.parametrize("geom,slower", [
+    ((1, 17, 11, 1984, 896, 3, 3, (2, 2), (1, 1)), "256x256"),      # 17.5 us with 128x128 tiles, 26.9 with these
+    ((2, 8, 15, 384, 1536, 7, 7, (1, 1), (3, 3)), "256x256"),       # 36.1, 52.5
+    ((1, 11, 10, 640, 1024, 5, 5, (1, 1), (2, 2)), "256x256"),      # 21.3 (256x128), 27.6
+    ((1, 12, 7, 64, 64, 1, 1, (1, 1), (0, 0)), "4w4f"),             # 3.2 without waves that only fetch, 3.3 with them
+])
+def test_weight_gradients_of_a_few_steps(geom, slower):
+    """Of few pixels: what counts is the stores of a large dw from enough tiles, or the start of the launch."""
+    assert slower not in sd.kernel_name(sd.make_desc(*geom), sd.WGRAD)
+
+
 def test_layers_with_an_entry_keep_the_measured_ranges():
     """Entries with a number of pixel ranges: it was measured with that tile variant."""
     for geom, name, ranges in [((512, 14, 14, 1024, 512, 1, 1, (1, 1), (0, 0)), "256x256x64_8w_s2_hf_m16", 32),
